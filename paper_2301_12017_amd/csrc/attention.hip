@@ -1,93 +1,270 @@
 // FP16 attention between the QKV projection and the attention output (Sec. 4.2 keeps the attention
-// in FP16 and takes its kernel from elsewhere; this is a plain stand-in so that a whole encoder
-// layer can be timed): softmax(q.k / sqrt(64)) V per sequence and head, no mask, fp32 arithmetic.
-// One workgroup per (sequence, head, block of 4 or 16 queries): the keys and values of the head go to
-// LDS once, then each of the four waves takes one query at a time: a lane scores keys lane,
-// lane + 64, ..., the wave reduces maximum and sum, and lane d accumulates output feature d.
+// in FP16 and takes its kernel from elsewhere): softmax(q.k / sqrt(64)) V per sequence and head, no
+// mask, on the FP16 matrix instruction with FP32 accumulation.
+//
+// A wave owns 32 queries and walks the keys in blocks of 32 with a running maximum.  It computes the
+// scores TRANSPOSED (keys as rows: K Q^T), so that a lane holds sixteen scores of ONE query: the
+// softmax needs a single exchange between the two halves of the wave, and the weights are already
+// the B operand of the second product O^T = V^T P^T.  That product sums over keys in the order the
+// first one leaves them in (eight per half: 0..3 and 8..11, or 4..7 and 12..15 of every sixteen); V
+// is read from LDS in the same order with the transposing load.
+//
+// The weights stay at FP32 accuracy: p = hi + lo, two FP16 numbers (22 bits; the matrix instruction
+// takes subnormal halves), so the second product costs two matrix instructions per operand of V.
+//
+// Bound by the vector ALU between the products (per score: scale, v_exp at a quarter of the rate, sum,
+// split into two halves), not by memory: 24 x 512 tokens, 16 heads: 55 us, where the kernel it replaced
+// (one query at a time per wave, v_dot2 scores and an FMA per key and feature) took 1896 us and the bytes
+// 19 us; 128 x 128 tokens, 12 heads: 24 us (275 us); 1 x 128: 3.9 us (7.7 us), the launch floor.
 #include "common.hpp"
 
 namespace w4a4 {
 namespace {
 
-constexpr int kHead = 64;             // features per head
-constexpr int kAttnWaves = 4;
-constexpr int kKeyPitch = kHead / 2 + 1;   // key rows in 32-bit words, padded: lanes read different rows
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+typedef float float16_t __attribute__((ext_vector_type(16)));
+typedef short short4_t __attribute__((__vector_size__(8)));
+typedef __attribute__((address_space(3))) short4_t lds_short4;
 
-__device__ __forceinline__ float wave_sum_f(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+constexpr int kHead = 64;             // features per head
+constexpr int kAttnThreads = 256;
+constexpr int kRowHalves = 72;        // LDS pitch of a key / value row: 144 bytes, rows start in different banks
+constexpr float kScoreScale = 0.125f * 1.44269504f;   // 1 / sqrt(64), base 2
+
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ uint32_t pack_halves(float a, float b) {      // round to nearest even
+    const float2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, half2_t));
 }
 
-__global__ __launch_bounds__(kAttnWaves *kWave) void attention_f16_kernel(const __half *qkv, __half *ctx, int seq,
-                                                                            int heads, int qblock) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    uint32_t *k_lds = reinterpret_cast<uint32_t *>(smem);                       // [seq][kKeyPitch] half2
-    const int k_words = (seq * kKeyPitch + 3) & ~3;                              // keeps the value rows 16-byte aligned
-    __half *v_lds = reinterpret_cast<__half *>(k_lds + k_words);                 // [seq][64]
-    float *p_lds = reinterpret_cast<float *>(v_lds + (size_t)seq * kHead);       // [waves][seq]
+// op over the two lanes l, l + 32 of a wave, in both of them
+template <typename Op>
+__device__ __forceinline__ float both_halves(float x, Op op) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    return op(__builtin_bit_cast(float, (unsigned)sw[0]), __builtin_bit_cast(float, (unsigned)sw[1]));
+}
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int qblocks = (seq + qblock - 1) / qblock;
-    const int qb = blockIdx.x % qblocks, head = (blockIdx.x / qblocks) % heads, b = blockIdx.x / (qblocks * heads);
-    const int h = heads * kHead;
+// State of a wave's 32 queries: lane l belongs to query l % 32 and holds features 32 f + 8 (i / 4) + 4 (l / 32) + i % 4.
+struct QueryBlock {
+    half8_t q[4];                     // B operands: features 16 s + 8 (l / 32) ..+7 of the lane's query
+    float16_t o[2];
+    float m, l;                       // running maximum of the raw scores; the lane's half of the sum
+};
+
+// One block of 32 keys: rows 0..31 of the LDS tiles ks / vs, of which the first `valid` are keys.
+__device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, const _Float16 *vs, int lane, int valid) {
+    const int row = lane & 31, hl = lane >> 5;
+    float16_t s = {};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const half8_t k = *reinterpret_cast<const half8_t *>(ks + row * kRowHalves + 16 * t + 8 * hl);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_f16(k, Q.q[t], s, 0, 0, 0);
+    }
+    if (valid < 32) {                 // wave-uniform: the last block of a sequence
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (8 * (i / 4) + 4 * hl + i % 4 >= valid) s[i] = -INFINITY;
+    }
+    float mx = max3(s[0], s[1], s[2]);
+#pragma unroll
+    for (int i = 3; i < 15; i += 2) mx = max3(mx, s[i], s[i + 1]);
+    mx = both_halves(fmaxf(mx, s[15]), [](float x, float y) { return fmaxf(x, y); });
+    if (__any(mx > Q.m)) {            // wave-uniform, seldom taken after the first blocks
+        const float m = fmaxf(Q.m, mx);
+        const float a = __builtin_amdgcn_exp2f((Q.m - m) * kScoreScale);
+        Q.m = m;
+        Q.l *= a;
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) Q.o[f][i] *= a;
+    }
+    const float shift = -Q.m * kScoreScale;
+    uint32_t hi[8], lo[8];
+    float sum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i], kScoreScale, shift));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i + 1], kScoreScale, shift));
+        sum += p0 + p1;
+        hi[i] = pack_halves(p0, p1);
+        float r0, r1;                 // p - hi, exact
+        asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hi[i]), "v"(p0));
+        asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hi[i]), "v"(p1));
+        lo[i] = pack_halves(r0, r1);
+    }
+    Q.l += sum;
+    // the lane's address in a transposing load: row (lane % 16) / 4 of four, columns 4 (lane % 4) of sixteen
+    const _Float16 *vrow = vs + (4 * hl + ((lane & 15) >> 2)) * kRowHalves + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        struct B2 { uint32_t w[4]; };
+        const half8_t ph = __builtin_bit_cast(half8_t, (B2{{hi[4 * t], hi[4 * t + 1], hi[4 * t + 2], hi[4 * t + 3]}}));
+        const half8_t pl = __builtin_bit_cast(half8_t, (B2{{lo[4 * t], lo[4 * t + 1], lo[4 * t + 2], lo[4 * t + 3]}}));
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            struct S2 { short4_t a, b; } v;
+            v.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(vrow + (16 * t) * kRowHalves + 32 * f));
+            v.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(vrow + (16 * t + 8) * kRowHalves + 32 * f));
+            const half8_t vf = __builtin_bit_cast(half8_t, v);
+            Q.o[f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, ph, Q.o[f], 0, 0, 0);
+            Q.o[f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pl, Q.o[f], 0, 0, 0);
+        }
+    }
+}
+
+// One workgroup of four waves per block of queries of one (sequence, head).  SPLIT == 1: a wave per 32 queries, 128
+// queries, keys and values staged 64 rows at a time and shared by the four.  SPLIT == 4: 32 queries, the waves take a
+// quarter of every 128 staged keys each and add up their parts through LDS: for launches that would leave CUs idle.
+template <int SPLIT>
+__global__ __launch_bounds__(kAttnThreads, 3) void attention_mfma_kernel(const __half *qkv, __half *ctx, int seq, int heads,
+                                                                      int pairs, int qblocks) {
+    constexpr int TILE = SPLIT == 4 ? 128 : 64, CH = TILE / 32;
+    extern __shared__ __attribute__((aligned(16))) _Float16 smem[];           // [buffers][keys, values][TILE][kRowHalves]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hl = lane >> 5;
+    // the query blocks of a (sequence, head) run on one XCD: they share its keys and values in that L2
+    const int loc = blockIdx.x >> 3, pair = (loc / qblocks) * 8 + (blockIdx.x & 7), qb = loc % qblocks;
+    if (pair >= pairs) return;
+    const int b = pair / heads, head = pair % heads, h = heads * kHead;
     const long ld = 3L * h;
-    const __half *base = qkv + (long)b * seq * ld + head * kHead;
+    const _Float16 *base = reinterpret_cast<const _Float16 *>(qkv) + (long)b * seq * ld + head * kHead;
+    const int q0 = SPLIT == 4 ? qb * 32 : qb * 128 + wave * 32;
+    const int qi = q0 + (lane & 31);
 
-    // keys and values of this head: 8 halves per thread and step
-    for (int i = tid; i < seq * (kHead / 8); i += kAttnWaves * kWave) {
-        const int row = i / (kHead / 8), c = i % (kHead / 8);
-        const uint4 kk = *reinterpret_cast<const uint4 *>(base + row * ld + h + c * 8);
-        const uint4 vv = *reinterpret_cast<const uint4 *>(base + row * ld + 2 * h + c * 8);
-        uint32_t *kd = k_lds + row * kKeyPitch + c * 4;
-        kd[0] = kk.x; kd[1] = kk.y; kd[2] = kk.z; kd[3] = kk.w;
-        *reinterpret_cast<uint4 *>(v_lds + row * kHead + c * 8) = vv;
-    }
-    __syncthreads();
-
-    float *p = p_lds + wave * seq;
-    for (int qi = wave; qi < qblock; qi += kAttnWaves) {
-        const int i = qb * qblock + qi;
-        if (i >= seq) break;                                    // uniform per wave; no barrier below
-        // the query, the same 64 values in every lane
-        uint32_t q2[kHead / 2];
-        const uint4 *qp = reinterpret_cast<const uint4 *>(base + i * ld);
+    uint4 kreg[CH], vreg[CH];
+    const int srow = tid >> 3, scol = (tid & 7) * 8;
+    auto fetch = [&](int tile) {
 #pragma unroll
-        for (int c = 0; c < kHead / 8; ++c) {
-            const uint4 t = qp[c];
-            q2[4 * c] = t.x; q2[4 * c + 1] = t.y; q2[4 * c + 2] = t.z; q2[4 * c + 3] = t.w;
-        }
-        // scores of keys lane, lane + 64, ...
-        float m = -INFINITY;
-        for (int k = lane; k < seq; k += kWave) {
-            const uint32_t *kr = k_lds + k * kKeyPitch;
-            float s = 0.0f;
-#pragma unroll
-            for (int w = 0; w < kHead / 2; ++w) {
-                typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-                const uint32_t kw = kr[w];
-                s = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, q2[w]), __builtin_bit_cast(h2, kw), s, false);   // fp32 sum of exact products
+        for (int j = 0; j < CH; ++j) {
+            const int r = tile * TILE + srow + 32 * j;
+            kreg[j] = vreg[j] = uint4{0, 0, 0, 0};
+            if (r < seq) {
+                kreg[j] = *reinterpret_cast<const uint4 *>(base + r * ld + h + scol);
+                vreg[j] = *reinterpret_cast<const uint4 *>(base + r * ld + 2 * h + scol);
             }
-            s *= 0.125f;                                        // 1 / sqrt(64)
-            p[k] = s;
-            m = fmaxf(m, s);
         }
-        m = wave_max(m);
-        float sum = 0.0f;
-        for (int k = lane; k < seq; k += kWave) {
-            const float e = expf(p[k] - m);
-            p[k] = e;
-            sum += e;
+    };
+    auto put = [&](int buf) {
+        _Float16 *d = smem + buf * 2 * TILE * kRowHalves + srow * kRowHalves + scol;
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            *reinterpret_cast<uint4 *>(d + 32 * j * kRowHalves) = kreg[j];
+            *reinterpret_cast<uint4 *>(d + (TILE + 32 * j) * kRowHalves) = vreg[j];
         }
-        sum = wave_sum_f(sum);
-        __builtin_amdgcn_wave_barrier();                        // the wave's LDS writes are in order; keep the compiler from moving the reads up
-        // output feature `lane`
-        float acc = 0.0f;
-#pragma unroll 8
-        for (int k = 0; k < seq; ++k) acc = fmaf(p[k], __half2float(v_lds[k * kHead + lane]), acc);
-        ctx[((long)b * seq + i) * h + head * kHead + lane] = __float2half(acc / sum);
-        __builtin_amdgcn_wave_barrier();                        // p is reused by the wave's next query
+    };
+
+    QueryBlock Q;
+    fetch(0);
+    {
+        const _Float16 *qp = base + (qi < seq ? qi : seq - 1) * ld + 8 * hl;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) Q.q[t] = *reinterpret_cast<const half8_t *>(qp + 16 * t);
     }
+    Q.o[0] = float16_t{};
+    Q.o[1] = float16_t{};
+    Q.m = -INFINITY;
+    Q.l = 0.0f;
+    put(0);
+    const int tiles = (seq + TILE - 1) / TILE;
+    if (tiles > 1) fetch(1);
+    __syncthreads();
+    for (int t = 0; t < tiles; ++t) {
+        const _Float16 *ks = smem + (t & 1) * 2 * TILE * kRowHalves, *vs = ks + TILE * kRowHalves;
+        if (SPLIT == 4) {
+            const int left = seq - t * TILE - wave * 32;
+            if (left > 0) attend32(Q, ks + wave * 32 * kRowHalves, vs + wave * 32 * kRowHalves, lane, left);
+        } else if (q0 < seq) {
+            attend32(Q, ks, vs, lane, seq - t * TILE);
+            if (t * TILE + 32 < seq) attend32(Q, ks + 32 * kRowHalves, vs + 32 * kRowHalves, lane, seq - t * TILE - 32);
+        }
+        if (t + 1 < tiles) {
+            put((t + 1) & 1);
+            if (t + 2 < tiles) fetch(t + 2);
+            __syncthreads();
+        }
+    }
+
+    __half *dst = ctx + ((long)b * seq + qi) * h + head * kHead;
+    float l = both_halves(Q.l, [](float x, float y) { return x + y; });
+    // Two blocks of four features of a lane and of its partner in the other half make eight consecutive ones each:
+    // features 8 blk..+7 for the lower half, 8 (blk + 1)..+7 for the upper one, sixteen bytes per lane.
+    auto store16 = [&](const float (&x)[4], const float (&y)[4], int blk) {
+        const uint32_t x0 = pack_halves(x[0], x[1]), x1 = pack_halves(x[2], x[3]);
+        const uint32_t y0 = pack_halves(y[0], y[1]), y1 = pack_halves(y[2], y[3]);
+        const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+        if (qi < seq) *reinterpret_cast<uint4 *>(dst + 8 * (blk + hl)) = uint4{(uint32_t)s0[0], (uint32_t)s1[0], (uint32_t)s0[1], (uint32_t)s1[1]};
+    };
+    if (SPLIT == 1) {
+        if (q0 >= seq) return;
+        const float inv = 1.0f / l;
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int g = 0; g < 4; g += 2) {
+                float x[4], y[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { x[i] = Q.o[f][4 * g + i] * inv; y[i] = Q.o[f][4 * g + 4 + i] * inv; }
+                store16(x, y, 4 * f + g);
+            }
+        return;
+    }
+    // the four waves' parts of the same queries: maxima first, then the rescaled sums and outputs
+    float *part = reinterpret_cast<float *>(smem);                            // [4 waves][32 registers][64 lanes]
+    float *ml = part + 4 * 32 * 64;                                           // [4 waves][32 queries]: maxima, then sums
+    __syncthreads();
+    if (hl == 0) ml[wave * 32 + lane] = Q.m;
+    __syncthreads();
+    float m = ml[lane & 31];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) m = fmaxf(m, ml[w * 32 + (lane & 31)]);
+    const float a = __builtin_amdgcn_exp2f((Q.m - m) * kScoreScale);          // 0 for a wave without keys
+    if (hl == 0) ml[128 + wave * 32 + lane] = l * a;
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) part[(wave * 32 + 16 * f + i) * 64 + lane] = Q.o[f][i] * a;
+    __syncthreads();
+    l = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) l += ml[128 + w * 32 + (lane & 31)];
+    const float inv = 1.0f / l;
+    float x[4], y[4];                                                         // wave w finishes registers 8 w .. 8 w + 7
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float u = 0.0f, v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            u += part[(w * 32 + 8 * wave + i) * 64 + lane];
+            v += part[(w * 32 + 8 * wave + 4 + i) * 64 + lane];
+        }
+        x[i] = u * inv;
+        y[i] = v * inv;
+    }
+    store16(x, y, 2 * wave);
+}
+
+constexpr size_t tile_bytes(int tile) { return (size_t)2 * tile * kRowHalves * sizeof(_Float16); }
+
+template <int SPLIT>
+int launch_attention(const void *qkv, void *ctx, int batch, int seq, int heads, hipStream_t st) {
+    constexpr int TILE = SPLIT == 4 ? 128 : 64, QB = SPLIT == 4 ? 32 : 128;
+    const int pairs = batch * heads, qblocks = (seq + QB - 1) / QB;
+    size_t lds = tile_bytes(TILE) * (seq > TILE ? 2 : 1);
+    const size_t combine = (size_t)(4 * 32 * 64 + 256) * sizeof(float);
+    if (SPLIT == 4 && lds < combine) lds = combine;
+    static KernelState ks;
+    if (prepare_kernel(reinterpret_cast<const void *>(attention_mfma_kernel<SPLIT>), lds, ks) < 0) return W4A4_ERR_HIP;
+    hipLaunchKernelGGL((attention_mfma_kernel<SPLIT>), dim3((unsigned)((pairs + 7) / 8 * 8 * qblocks)), dim3(kAttnThreads), lds, st,
+                       static_cast<const __half *>(qkv), static_cast<__half *>(ctx), seq, heads, pairs, qblocks);
+    return launch_status();
 }
 
 }  // namespace
@@ -101,15 +278,10 @@ extern "C" int w4a4_attention_f16(const void *QKV_f16, int batch, int seq, int h
     if (!QKV_f16 || !ctx_f16) return W4A4_ERR_INVALID_ARG;
     if (seq > 512 || heads > 1024) return W4A4_ERR_UNSUPPORTED_SHAPE;
     if (!aligned16(QKV_f16) || !aligned16(ctx_f16)) return W4A4_ERR_UNSUPPORTED_SHAPE;
-    // sixteen queries share one copy of the head's keys and values; with few sequences and heads four do, so that
-    // the launch still covers the chip
-    const int qblock = (long)batch * heads * ((seq + 15) / 16) >= 512 ? 16 : 4;
-    const long blocks = (long)batch * heads * ((seq + qblock - 1) / qblock);
-    if (blocks > 0x7fffffffL || (long)batch * seq * 3 * heads * kHead >= 0x7fffffffL) return W4A4_ERR_UNSUPPORTED_SHAPE;
-    const size_t lds = (size_t)((seq * kKeyPitch + 3) & ~3) * 4 + (size_t)seq * kHead * 2 + (size_t)kAttnWaves * seq * 4;
-    static KernelState ks;
-    if (prepare_kernel(reinterpret_cast<const void *>(attention_f16_kernel), lds, ks) < 0) return W4A4_ERR_HIP;
-    hipLaunchKernelGGL(attention_f16_kernel, dim3((unsigned)blocks), dim3(kAttnWaves * kWave), lds, as_stream(stream),
-                       static_cast<const __half *>(QKV_f16), static_cast<__half *>(ctx_f16), seq, heads, qblock);
-    return hipGetLastError() == hipSuccess ? W4A4_OK : W4A4_ERR_HIP;
+    if ((long)batch * seq * 3 * heads * kHead >= 0x7fffffffL) return W4A4_ERR_UNSUPPORTED_SHAPE;
+    // 128 queries per workgroup share each staged tile; below 192 such workgroups most CUs idle and 32 queries per
+    // workgroup, keys split over its waves, are faster.  us at 128 | 32 queries, twelve heads: 1 x 128 tokens (12 workgroups
+    // of 128) 5.5 | 3.9, 5 x 93 (60) 5.1 | 4.1, 16 x 128 (192) 6.3 | 6.9, 4 x 512 (192) 16.1 | 15.1, 64 x 128 (768) 13.9 | 19.3.
+    if ((long)batch * heads * ((seq + 127) / 128) >= 192) return launch_attention<1>(QKV_f16, ctx_f16, batch, seq, heads, as_stream(stream));
+    return launch_attention<4>(QKV_f16, ctx_f16, batch, seq, heads, as_stream(stream));
 }

@@ -28,6 +28,21 @@ def test_attention_against_the_oracle(B, orc, batch, seq, heads):
     np.testing.assert_allclose(got, want, rtol=2e-3, atol=2e-3 * np.sqrt((want ** 2).mean()))
 
 
+@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries; a wave per block
+@pytest.mark.parametrize("seq", [1, 31, 32, 33, 64, 65, 127, 128, 129, 255, 257, 511, 512])
+def test_attention_at_the_edges_of_its_tiles(B, orc, batch, heads, seq):
+    rng = np.random.default_rng(seq)
+    QKV = (rng.standard_normal((batch * seq, 3 * heads * 64)) * 1.5).astype(np.float16)
+    got = host(B.attention(dev(QKV), batch, seq, heads)).reshape(batch, seq, heads, 64).astype(np.float64)
+    last = batch - 1                                             # the first and the last (sequence, head) of the launch
+    for b, h in ((0, 0), (last, heads - 1)):
+        one = np.ascontiguousarray(QKV.reshape(batch, seq, 3, heads, 64)[b, :, :, h]).reshape(seq, 192)
+        want = orc.attention(one, 1, seq, 1)
+        # one rounding to fp16; sums of `seq` fp32 terms (2^-24 each) of at most max|v|
+        bound = 2.0 ** -11 * np.abs(want) + (seq + 64) * 2.0 ** -24 * np.abs(one[:, 128:].astype(np.float64)).max()
+        assert np.all(np.abs(got[b, :, h] - want) <= bound)
+
+
 def test_attention_of_peaked_scores_does_not_overflow(B, orc):
     batch, seq, heads = 1, 64, 2
     rng = np.random.default_rng(3)
