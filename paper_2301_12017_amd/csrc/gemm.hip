@@ -1,6 +1,7 @@
 // Dispatch and C entry points of the GEMM side of libw4a4: schedule table, argument
 // validation, w4a4_linear / w4a4_gemm_i32 / w4a4_workspace_bytes.
 #include "gemm_common.hpp"
+#include "layer.hpp"
 
 namespace w4a4 {
 
@@ -488,11 +489,12 @@ extern "C" int w4a4_gemm_i32(const w4a4_act *A, const w4a4_weight *W, int32_t *a
 }
 
 // w4a4_linear behind its argument checks.  `exchange` is the area the fused requantize exchanges row maxima
-// through (fused_workspace_bytes(M) bytes, cleared here by a fill kernel); `rows_f32` receives the fp32 rows
-// of a requantize that cannot be fused.  Whichever the layer does not need may be NULL.
+// through (fused_workspace_bytes(M) bytes, cleared here by a fill kernel together with the code sums, unless a kernel
+// before it on the stream has done so: `cleared`); `rows_f32` receives the fp32 rows of a requantize that cannot be
+// fused.  Whichever the layer does not need may be NULL.
 static int linear_impl(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, void *out, float *out_scale,
                        float *out_zero, int32_t *out_gsum, int ng, int fused, uint32_t *exchange, void *rows_f32,
-                       hipStream_t st) {
+                       hipStream_t st, bool cleared = false) {
     GemmArgs g;
     fill_args(g, A, W, ng);
     g.bias = static_cast<const __half *>(ep->bias_f16);
@@ -530,8 +532,9 @@ static int linear_impl(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilo
         // everything that can refuse the launch is checked before the outputs are touched
         const int rc = resolve_schedule(g, false, out_kind, &schedule);
         if (rc) return rc;
-        hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + n2 + 255) / 256)), dim3(256), 0, st, exchange, words,
-                           reinterpret_cast<uint32_t *>(out_gsum), (int)n2);
+        if (!cleared)
+            hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + n2 + 255) / 256)), dim3(256), 0, st, exchange, words,
+                               reinterpret_cast<uint32_t *>(out_gsum), (int)n2);
         return run_gemm(g, A->mode, false, out_kind, schedule, st);
     }
     // Requantize: the per-token range needs the whole output row, which no single tile
@@ -546,9 +549,9 @@ static int linear_impl(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilo
                              ep->requant_layout);
 }
 
-extern "C" int w4a4_linear(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, void *out,
-                           float *out_scale, float *out_zero, int32_t *out_gsum, void *workspace,
-                           size_t workspace_bytes, void *stream) {
+static int linear_checked(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, void *out, float *out_scale,
+                          float *out_zero, int32_t *out_gsum, void *workspace, size_t workspace_bytes, void *stream,
+                          bool cleared) {
     int ng = 0, rng = 0;
     int rc = check_layer(A, W, ep, out, out_scale, out_zero, &ng, &rng);
     if (rc) return rc;
@@ -561,7 +564,32 @@ extern "C" int w4a4_linear(const w4a4_act *A, const w4a4_weight *W, const w4a4_e
     const size_t need = !ep->requant ? 0 : fused ? fused_workspace_bytes(A->M) : (size_t)A->M * (size_t)W->N * sizeof(float);
     if (need && (!workspace || workspace_bytes < need || !aligned16(workspace))) return W4A4_ERR_WORKSPACE;
     return linear_impl(A, W, ep, out, out_scale, out_zero, out_gsum, ng, fused, static_cast<uint32_t *>(workspace),
-                       workspace, as_stream(stream));
+                       workspace, as_stream(stream), cleared);
+}
+
+extern "C" int w4a4_linear(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, void *out,
+                           float *out_scale, float *out_zero, int32_t *out_gsum, void *workspace,
+                           size_t workspace_bytes, void *stream) {
+    return linear_checked(A, W, ep, out, out_scale, out_zero, out_gsum, workspace, workspace_bytes, stream, false);
+}
+
+// The same behind a kernel that has cleared linear_clear_ranges() on the stream (one launch less per requantizing layer).
+int w4a4::linear_cleared(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, void *out, float *out_scale,
+                         int32_t *out_gsum, void *workspace, size_t workspace_bytes, void *stream) {
+    return linear_checked(A, W, ep, out, out_scale, nullptr, out_gsum, workspace, workspace_bytes, stream, true);
+}
+ClearRanges w4a4::linear_clear_ranges(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, int32_t *out_gsum,
+                                      void *workspace) {
+    ClearRanges r = {nullptr, nullptr, 0, 0};
+    const int fused = fused_requant_kind(A, W, ep, out_gsum != nullptr);
+    if (!fused || A->M <= 0) return r;
+    r.p0 = static_cast<uint32_t *>(workspace);
+    r.n0 = (int)(fused_workspace_bytes(A->M) / sizeof(uint32_t));
+    if (fused == 2 && ep->requant_layout == W4A4_LAYOUT_MFMA) {
+        r.p1 = reinterpret_cast<uint32_t *>(out_gsum);
+        r.n1 = A->M * (W->N / (ep->requant_group == 0 ? W->N : ep->requant_group));
+    }
+    return r;
 }
 
 // ---- w4a4_linear for callers that cannot allocate -----------------------------------------------------------

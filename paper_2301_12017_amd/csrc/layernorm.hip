@@ -11,32 +11,17 @@
 // round to nearest even) from its fp32 value, and optionally stored as fp16 for the residual
 // stream.  HBM-bound: 2 (+2) bytes in and 0.5 (+2) bytes out per element.
 //
-// One wavefront owns one token: 16-byte loads, the row stays in registers (K <= 4096: eight
-// chunks of eight elements per lane), sums and ranges are reduced with wave shuffles, codes
-// leave as one dword per lane and step (FP6 operand layout: the four lanes of a quad hold one
-// operand of 32 codes, of which three store eight bytes each).
-#include "common.hpp"
+// A token is owned by 32 lanes where its row splits into up to four whole sixteen-byte chunks for each
+// of them (K = 256, 512, 768, 1024: no lane idles, two tokens per wave), else by a wavefront (K <= 4096: up
+// to eight chunks per lane).  Every load of a row, the affine parameters' included, is issued before the
+// first use; sums and ranges are reduced through the cross-lane operand modes, not the LDS.  Codes leave as
+// one dword per lane and chunk (FP6 operand layout: the four lanes of a quad hold one operand of 32 codes,
+// of which three store eight bytes each).
+#include "layer.hpp"
 
 namespace w4a4 {
 
-constexpr int kLnRowsPerBlock = 4;
-
-struct LnArgs {
-    const __half *X, *R; long ldx;       // [M, ldx] each; R may be NULL
-    const __half *gamma, *beta;          // [K]
-    float eps;
-    __half *Y;                           // [M, K] or NULL
-    uint8_t *q; float *s, *z;            // [M, K/2], [M], [M]
-    int32_t *gsum; int ng, cpg;          // [M, ng] code sums of runs of cpg chunks (NULL = not wanted)
-    int32_t *psum;                       // [M] odd-position code sums (MFMA operand layout)
-    int M, K;
-};
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
+constexpr int kLnWaves = 4;              // waves per workgroup
 
 __device__ __forceinline__ void halves8(const uint4 &raw, float (&v)[8]) {
     const __half2 *h = reinterpret_cast<const __half2 *>(&raw);
@@ -67,51 +52,63 @@ __device__ __forceinline__ void fp6_store_chunk(uint8_t *q, int K, long row, int
 }
 
 // LAYOUT: 0 canonical nibbles, 1 the MFMA operand layout of activations, 2 the FP6 operand layout (both: symmetric codes only)
-template <int MODE, int ITERS, int LAYOUT>
-__global__ __launch_bounds__(kLnRowsPerBlock *kWave) void layernorm_quantize_kernel(LnArgs a) {
-    const int lane = threadIdx.x % kWave;
-    const long row = (long)blockIdx.x * kLnRowsPerBlock + threadIdx.x / kWave;
+// CODES: what is quantized (LnCodes).  LPR lanes own a row, CPL chunks each; with LPR == 32 the row fits exactly.
+template <int MODE, int LAYOUT, int CODES, int LPR, int CPL>
+__global__ __launch_bounds__(kLnWaves *kWave) void layernorm_quantize_kernel(LnArgs a) {
+    constexpr bool EXACT = LPR == 32, EARLY = CPL <= 4;         // EARLY: registers for the affine parameters from the start
+    const int lane = threadIdx.x % kWave, l = lane % LPR;
+    const long row = ((long)blockIdx.x * kLnWaves + threadIdx.x / kWave) * (kWave / LPR) + lane / LPR;
     const int K = a.K, nchunks = K / 8;
-    if (row >= a.M) {                                           // whole wave leaves; no block barrier below
-        if constexpr (LAYOUT == 2) {                            // the layout stores whole 64-token panels: zero rows behind M
-            if (row < (((long)a.M + 63) & ~63L)) {
+    for (int i = blockIdx.x * kLnWaves * kWave + threadIdx.x; i < a.n0 + a.n1; i += gridDim.x * kLnWaves * kWave) {
+        if (i < a.n0) a.zero0[i] = 0u;                          // counters of a later kernel on the stream
+        else a.zero1[i - a.n0] = 0u;
+    }
+    const bool live = row < a.M;
+    const __half *xr = a.X + (live ? row : (long)a.M - 1) * a.ldx;
+    const __half *rr = a.R ? a.R + (live ? row : (long)a.M - 1) * a.ldx : nullptr;
+
+    uint4 x4[CPL], r4[CPL], g4[CPL], b4[CPL];
 #pragma unroll
-                for (int it = 0; it < ITERS; ++it)
-                    if (lane + it * kWave < nchunks) fp6_store_chunk(a.q, K, row, lane + it * kWave, 0u, 0u, 0u, 0u);
+    for (int it = 0; it < CPL; ++it) {
+        const int c = l + it * LPR;
+        x4[it] = r4[it] = uint4{0, 0, 0, 0};
+        if (EXACT || c < nchunks) {
+            x4[it] = *reinterpret_cast<const uint4 *>(xr + c * 8);
+            if (rr) r4[it] = *reinterpret_cast<const uint4 *>(rr + c * 8);
+        }
+    }
+    if (EARLY) {
+#pragma unroll
+        for (int it = 0; it < CPL; ++it) {
+            const int c = l + it * LPR;
+            if (EXACT || c < nchunks) {
+                g4[it] = *reinterpret_cast<const uint4 *>(a.gamma + c * 8);
+                b4[it] = *reinterpret_cast<const uint4 *>(a.beta + c * 8);
             }
         }
-        return;
     }
-    const __half *xr = a.X + row * a.ldx;
-    const __half *rr = a.R ? a.R + row * a.ldx : nullptr;
 
     // ---- v = x + r, in registers ------------------------------------------------------------------
-    float v[ITERS][8];
+    float v[CPL][8];
     float sum = 0.0f;
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        const int c = lane + it * kWave;
-        if (c < nchunks) {
-            halves8(*reinterpret_cast<const uint4 *>(xr + c * 8), v[it]);
-            if (rr) {
-                float t[8];
-                halves8(*reinterpret_cast<const uint4 *>(rr + c * 8), t);
+    for (int it = 0; it < CPL; ++it) {
+        halves8(x4[it], v[it]);
+        if (rr) {
+            float t[8];
+            halves8(r4[it], t);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[it][e] = v[it][e] + t[e];
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sum += v[it][e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[it][e] = 0.0f;
+            for (int e = 0; e < 8; ++e) v[it][e] = v[it][e] + t[e];
         }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum += v[it][e];
     }
     const float inv_k = 1.0f / (float)K;
-    const float mean = wave_sum(sum) * inv_k;
+    const float mean = lanes_reduce<LPR>(sum, [](float p, float q) { return p + q; }) * inv_k;
     float sq = 0.0f;
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        if (lane + it * kWave < nchunks) {
+    for (int it = 0; it < CPL; ++it) {
+        if (EXACT || l + it * LPR < nchunks) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 v[it][e] = v[it][e] - mean;
@@ -120,39 +117,60 @@ __global__ __launch_bounds__(kLnRowsPerBlock *kWave) void layernorm_quantize_ker
             }
         }
     }
-    const float var = wave_sum(sq) * inv_k;
+    const float var = lanes_reduce<LPR>(sq, [](float p, float q) { return p + q; }) * inv_k;
     const float rstd = 1.0f / sqrtf(var + a.eps);
 
     // ---- y = (v - mean) * rstd * gamma + beta; fp16 copy; range of the row ---------------------------
     float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        const int c = lane + it * kWave;
-        if (c < nchunks) {
+    for (int it = 0; it < CPL; ++it) {
+        const int c = l + it * LPR;
+        if (EXACT || c < nchunks) {
+            if (!EARLY) {
+                g4[it] = *reinterpret_cast<const uint4 *>(a.gamma + c * 8);
+                b4[it] = *reinterpret_cast<const uint4 *>(a.beta + c * 8);
+            }
             float g[8], b[8];
-            halves8(*reinterpret_cast<const uint4 *>(a.gamma + c * 8), g);
-            halves8(*reinterpret_cast<const uint4 *>(a.beta + c * 8), b);
+            halves8(g4[it], g);
+            halves8(b4[it], b);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float y = v[it][e] * rstd;
                 y = y * g[e];
-                y = y + b[e];
-                v[it][e] = y;
-                if (MODE == W4A4_SYM) hi = fmaxf(hi, fabsf(y));
-                else { hi = fmaxf(hi, y); lo = fminf(lo, y); }
+                v[it][e] = y + b[e];
             }
-            if (a.Y) {
+            if (a.Y || CODES == LN_CODES_F16) {
                 __half2 h[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) h[i] = __floats2half2_rn(v[it][2 * i], v[it][2 * i + 1]);
+                const uint4 h4 = *reinterpret_cast<const uint4 *>(h);
                 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
                 // written once, read by a later kernel: keep it out of the way of the rows still being read
-                __builtin_nontemporal_store(*reinterpret_cast<const u4 *>(h), reinterpret_cast<u4 *>(a.Y + row * (long)K + c * 8));
+                if (a.Y && live)
+                    __builtin_nontemporal_store(u4{h4.x, h4.y, h4.z, h4.w}, reinterpret_cast<u4 *>(a.Y + row * (long)K + c * 8));
+                if (CODES == LN_CODES_F16) halves8(h4, v[it]);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (MODE == W4A4_SYM) hi = fmaxf(hi, fabsf(v[it][e]));
+                else { hi = fmaxf(hi, v[it][e]); lo = fminf(lo, v[it][e]); }
             }
         }
     }
-    const Range r = MODE == W4A4_SYM ? range_sym(wave_max(hi)) : range_asym(wave_min(lo), wave_max(hi));
-    if (lane == 0) {
+    if constexpr (CODES == LN_CODES_NONE) return;
+    if (!live) {
+        if constexpr (LAYOUT == 2) {                            // the layout stores whole 64-token panels: zero rows behind M
+            if (row < (((long)a.M + 63) & ~63L)) {
+#pragma unroll
+                for (int it = 0; it < CPL; ++it)
+                    if (EXACT || l + it * LPR < nchunks) fp6_store_chunk(a.q, K, row, l + it * LPR, 0u, 0u, 0u, 0u);
+            }
+        }
+    }
+    hi = lanes_reduce<LPR>(hi, [](float p, float q) { return fmaxf(p, q); });
+    if (MODE == W4A4_ASYM) lo = lanes_reduce<LPR>(lo, [](float p, float q) { return fminf(p, q); });
+    const Range r = MODE == W4A4_SYM ? range_sym(hi) : range_asym(lo, hi);
+    if (l == 0 && live) {
         a.s[row] = r.S;
         if (MODE == W4A4_ASYM) a.z[row] = r.lo;
     }
@@ -166,8 +184,8 @@ __global__ __launch_bounds__(kLnRowsPerBlock *kWave) void layernorm_quantize_ker
         // exponent and mantissa bits of t's FP6 E2M3 encoding: a field is that byte without its two zero bits
         typedef short v2s __attribute__((ext_vector_type(2)));
 #pragma unroll
-        for (int it = 0; it < ITERS; ++it) {
-            const int c = lane + it * kWave;
+        for (int it = 0; it < CPL; ++it) {
+            const int c = l + it * LPR;
             uint32_t f24[2];
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
@@ -184,18 +202,18 @@ __global__ __launch_bounds__(kLnRowsPerBlock *kWave) void layernorm_quantize_ker
             }
             const uint32_t lo = f24[0] | (f24[1] << 24), hi = f24[1] >> 8;            // 48 bits
             const uint32_t nlo = dpp_fetch<0xF9>(lo), nhi = dpp_fetch<0xF9>(hi);      // quad permute [1,2,3,3]: the next lane's
-            if (c < nchunks) fp6_store_chunk(a.q, K, row, c, lo, hi, nlo, nhi);
+            if (live && (EXACT || c < nchunks)) fp6_store_chunk(a.q, K, row, c, lo, hi, nlo, nhi);
         }
         return;
     }
     constexpr float kMagic = MODE == W4A4_SYM ? 12582920.0f : 12582912.0f;
     constexpr uint32_t kFlip = MODE == W4A4_ASYM ? 0u : LAYOUT == 0 ? 0x88888888u : 0x80808080u;
     uint32_t *qr = reinterpret_cast<uint32_t *>(a.q + row * (long)(K / 2));
-    int part = 0, total = 0;
+    int part = 0, total = 0, open = 0;
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        const int c = lane + it * kWave;
-        const bool in = c < nchunks;
+    for (int it = 0; it < CPL; ++it) {
+        const int c = l + it * LPR;
+        const bool in = live && (EXACT || c < nchunks);
         uint32_t packed = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -212,36 +230,59 @@ __global__ __launch_bounds__(kLnRowsPerBlock *kWave) void layernorm_quantize_ker
         if (LAYOUT != 0 && in) part += (int)__builtin_amdgcn_sad_u8(odd, 0u, 0u) - 32;
         if (in) qr[c] = packed ^ kFlip;                         // (a plain store: the next GEMM reads the codes from cache)
         total += s8;
-        if (a.gsum && a.ng > 1) {                               // groups of cpg lanes, all inside this `it`
-            for (int o = 1; o < a.cpg; o <<= 1) s8 += __shfl_xor(s8, o, kWave);
-            if ((lane & (a.cpg - 1)) == 0 && in) a.gsum[row * (long)a.ng + c / a.cpg] = s8;
+        if (a.gsum && a.ng > 1) {                               // groups of cpg chunks: cpg lanes of one `it`, or whole rows of lanes of cpg / LPR
+            for (int o = 1; o < a.cpg && o < LPR; o <<= 1) s8 += __shfl_xor(s8, o, kWave);
+            open += s8;
+            if (a.cpg <= LPR ? (l & (a.cpg - 1)) == 0 : (l == 0 && ((it + 1) * LPR) % a.cpg == 0)) {
+                if (in) a.gsum[row * (long)a.ng + c / a.cpg] = a.cpg <= LPR ? s8 : open;
+                open = 0;
+            }
         }
     }
     if (a.gsum && a.ng == 1) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, kWave);
-        if (lane == 0) a.gsum[row] = total;
+        total = lanes_reduce<LPR>(total, [](int p, int q) { return p + q; });
+        if (l == 0 && live) a.gsum[row] = total;
     }
     if (LAYOUT != 0) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, kWave);
-        if (lane == 0) a.psum[row] = part;
+        part = lanes_reduce<LPR>(part, [](int p, int q) { return p + q; });
+        if (l == 0 && live) a.psum[row] = part;
     }
 }
 
-template <int MODE, int LAYOUT>
+template <int MODE, int LAYOUT, int CODES>
 static int launch_ln(const LnArgs &a, hipStream_t st) {
-    const int iters = (a.K / 8 + kWave - 1) / kWave;
-    const long rows = LAYOUT == 2 ? (((long)a.M + 63) & ~63L) : a.M;     // (FP6: the zero rows that fill the last panel too)
-    dim3 grid((unsigned)((rows + kLnRowsPerBlock - 1) / kLnRowsPerBlock)), block(kLnRowsPerBlock * kWave);
-#define W4A4_LN(I) hipLaunchKernelGGL((layernorm_quantize_kernel<MODE, I, LAYOUT>), grid, block, 0, st, a)
-    if (iters <= 1) W4A4_LN(1);
-    else if (iters <= 2) W4A4_LN(2);
-    else if (iters <= 4) W4A4_LN(4);
-    else if (iters <= 8) W4A4_LN(8);
+    const long rows = LAYOUT == 2 && CODES != LN_CODES_NONE ? (((long)a.M + 63) & ~63L) : a.M;     // (FP6: the zero rows that fill the last panel too)
+    const int chunks = a.K / 8;
+#define W4A4_LN(L, C)                                                                                                \
+    hipLaunchKernelGGL((layernorm_quantize_kernel<MODE, LAYOUT, CODES, L, C>),                                         \
+                       dim3((unsigned)((rows + kLnWaves * (kWave / L) - 1) / (kLnWaves * (kWave / L)))), dim3(kLnWaves *kWave), 0, st, a)
+    if (chunks % 32 == 0 && chunks <= 128) {
+        switch (chunks / 32) {
+            case 1: W4A4_LN(32, 1); break;
+            case 2: W4A4_LN(32, 2); break;
+            case 3: W4A4_LN(32, 3); break;
+            default: W4A4_LN(32, 4); break;
+        }
+    }
+    else if (chunks <= 64) W4A4_LN(64, 1);
+    else if (chunks <= 128) W4A4_LN(64, 2);
+    else if (chunks <= 256) W4A4_LN(64, 4);
+    else if (chunks <= 512) W4A4_LN(64, 8);
     else return W4A4_ERR_UNSUPPORTED_SHAPE;
 #undef W4A4_LN
     return launch_status();
+}
+
+int layernorm_rows(const LnArgs &a, int layout, int codes, hipStream_t st) {
+    if (codes == LN_CODES_NONE) return launch_ln<W4A4_SYM, 0, LN_CODES_NONE>(a, st);
+    if (codes == LN_CODES_F16) {
+        if (layout == W4A4_LAYOUT_MFMA) return launch_ln<W4A4_SYM, 1, LN_CODES_F16>(a, st);
+        if (layout == W4A4_LAYOUT_FP6) return launch_ln<W4A4_SYM, 2, LN_CODES_F16>(a, st);
+        return launch_ln<W4A4_SYM, 0, LN_CODES_F16>(a, st);
+    }
+    if (layout == W4A4_LAYOUT_MFMA) return launch_ln<W4A4_SYM, 1, LN_CODES_F32>(a, st);
+    if (layout == W4A4_LAYOUT_FP6) return launch_ln<W4A4_SYM, 2, LN_CODES_F32>(a, st);
+    return launch_ln<W4A4_SYM, 0, LN_CODES_F32>(a, st);
 }
 
 }  // namespace w4a4
@@ -280,8 +321,7 @@ extern "C" int w4a4_layernorm_quantize(const void *X_f16, const void *R_f16, int
     a.eps = eps; a.Y = static_cast<__half *>(Y_f16);
     a.q = q; a.s = scale; a.z = zero; a.gsum = gsum; a.ng = ng; a.cpg = cpg; a.psum = osum;
     a.M = M; a.K = K;
-    hipStream_t st = as_stream(stream);
-    if (layout == W4A4_LAYOUT_MFMA) return launch_ln<W4A4_SYM, 1>(a, st);
-    if (layout == W4A4_LAYOUT_FP6) return launch_ln<W4A4_SYM, 2>(a, st);
-    return mode == W4A4_SYM ? launch_ln<W4A4_SYM, 0>(a, st) : launch_ln<W4A4_ASYM, 0>(a, st);
+    a.zero0 = a.zero1 = nullptr; a.n0 = a.n1 = 0;
+    if (mode == W4A4_ASYM) return launch_ln<W4A4_ASYM, 0, LN_CODES_F32>(a, as_stream(stream));
+    return layernorm_rows(a, layout, LN_CODES_F32, as_stream(stream));
 }

@@ -10,7 +10,7 @@
 #include <tuple>
 #include <vector>
 
-#include "common.hpp"
+#include "layer.hpp"
 
 namespace w4a4 {
 namespace {
@@ -149,7 +149,7 @@ size_t unfused_bytes(int M, const w4a4_part &f1, const w4a4_part &f2) {
 // ---- whole encoder layer ------------------------------------------------------------------------
 struct LayerPlan {
     __half *qkv, *ctx, *ao, *x1, *h2;
-    ActBuffers ln;                  // codes of LayerNorm 1 for FFN1 (LayerNorm 2 reuses them as a dump)
+    ActBuffers ln;                  // codes of LayerNorm 1 for FFN1
     uint8_t *rest;                  // whatever the part that is running needs
     size_t rest_bytes, total;
 };
@@ -180,6 +180,23 @@ LayerPlan plan_layer(void *ws, int M, const w4a4_encoder_layer_weights &L) {
     p.rest = c.take<uint8_t>(r);
     p.total = c.used;
     return p;
+}
+
+// y (and codes of it, if asked for) = LayerNorm(X + R): the kernel of w4a4_layernorm_quantize, symmetric codes in `layout`
+int run_layernorm(const void *X, const void *R, int M, int K, const void *gamma, const void *beta, float eps, void *Y,
+                  const ActBuffers &b, int layout, int codes, const ClearRanges &clear, void *stream) {
+    int lpr = 0, opl = 0;
+    if (K % 32 || K > 4096 || (codes != LN_CODES_NONE && layout == W4A4_LAYOUT_FP6 && !fp6_plan(K, &lpr, &opl))) return W4A4_ERR_UNSUPPORTED_SHAPE;
+    for (const void *p : {X, R, gamma, beta, static_cast<const void *>(Y)})
+        if (!aligned16(p)) return W4A4_ERR_UNSUPPORTED_SHAPE;
+    LnArgs a;
+    a.X = static_cast<const __half *>(X); a.R = static_cast<const __half *>(R); a.ldx = K;
+    a.gamma = static_cast<const __half *>(gamma); a.beta = static_cast<const __half *>(beta);
+    a.eps = eps; a.Y = static_cast<__half *>(Y);
+    a.q = b.q; a.s = b.scale; a.z = nullptr; a.gsum = nullptr; a.ng = 1; a.cpg = K / 8; a.psum = b.osum;
+    a.M = M; a.K = K;
+    a.zero0 = clear.p0; a.n0 = clear.n0; a.zero1 = clear.p1; a.n1 = clear.n1;
+    return layernorm_rows(a, layout, codes, as_stream(stream));
 }
 
 // ---- tuner --------------------------------------------------------------------------------------
@@ -464,42 +481,53 @@ extern "C" int w4a4_encoder_layer(const void *X_f16, int batch, int seq, const w
     if (rc) return rc;
     rc = run_part(p.ctx, M, h, L->attn_out, i1, p.ao, p.rest, stream);
     if (rc) return rc;
-    // x1 = LN1(attn_out + x); its codes are in FFN1's layout whether or not FFN1 reads them
-    rc = w4a4_layernorm_quantize(p.ao, X_f16, M, h, h, L->ln1_gamma_f16, L->ln1_beta_f16, L->ln_eps, p.x1, W4A4_SYM, 0,
-                                 p.ln.q, p.ln.scale, nullptr, nullptr, w1.layout, p.ln.osum, stream);
+    // x1 = LN1(attn_out + x).  Where FFN1 reads INT4 codes from memory, the same kernel writes them: of LayerNorm's fp32
+    // result (fused_ln), or of x1 itself, what w4a4_quantize_act would make of it.  It also clears what FFN1's
+    // requantizing epilogue counts in.  (16384 tokens of 768, layer: 247 us with the separate quantize and fill launches
+    // and LayerNorm 2 writing codes that nothing reads, 233 us so; 465 tokens: 49.6 and 44.3 us.)
+    const bool from_codes = fused_ln || (i2 && (fused_ffn || !one_kernel_shape(M, w1)));
+    const w4a4_act a1 = view_act4(p.ln, M, h, w1);
+    Carver c(p.rest);
+    ActBuffers hb = {};
+    w4a4_epilogue ep1 = {};
+    size_t lin_bytes = 0;
+    void *lin_ws = nullptr;
+    int32_t *h_osum = nullptr;
+    ClearRanges clear = {};
+    if (from_codes && fused_ffn) {
+        if (w2.mode != W4A4_SYM || (w1.layout == W4A4_LAYOUT_FP6) != (w2.layout == W4A4_LAYOUT_FP6)) return W4A4_ERR_UNSUPPORTED_SHAPE;
+        hb = carve_act4(c, M, w2.K, w2);
+        h_osum = w2.layout == W4A4_LAYOUT_MFMA ? hb.osum : nullptr;
+        ep1 = fused_epilogue(L->ffn1, L->ffn2);
+        lin_bytes = w4a4_linear_workspace_bytes(&a1, &w1, &ep1, h_osum != nullptr);
+        lin_ws = c.take<uint8_t>(lin_bytes);
+        clear = linear_clear_ranges(&a1, &w1, &ep1, h_osum, lin_ws);
+    }
+    rc = run_layernorm(p.ao, X_f16, M, h, L->ln1_gamma_f16, L->ln1_beta_f16, L->ln_eps, p.x1, p.ln, w1.layout,
+                       !from_codes ? LN_CODES_NONE : fused_ln ? LN_CODES_F32 : LN_CODES_F16, clear, stream);
     if (rc) return rc;
-    if (!fused_ln) {
+    if (!from_codes) {
         rc = w4a4_ffn(p.x1, M, h, &L->ffn1, &L->ffn2, strategy & W4A4_STRATEGY_ALL_INT4, p.h2, p.rest, p.rest_bytes, stream);
         if (rc) return rc;
+    } else if (fused_ffn) {
+        rc = linear_cleared(&a1, &w1, &ep1, hb.q, hb.scale, h_osum, lin_ws, lin_bytes, stream);
+        if (rc) return rc;
+        const w4a4_act hv = view_act4(hb, M, w2.K, w2);
+        w4a4_epilogue ep2 = {};
+        ep2.bias_f16 = L->ffn2.bias_f16;
+        ep2.act = L->ffn2.act;
+        rc = w4a4_linear(&hv, &w2, &ep2, p.h2, nullptr, nullptr, nullptr, nullptr, 0, stream);
+        if (rc) return rc;
     } else {
-        const w4a4_act a1 = view_act4(p.ln, M, h, w1);
-        Carver c(p.rest);
-        if (fused_ffn) {
-            const ActBuffers hb = carve_act4(c, M, w2.K, w2);
-            const w4a4_epilogue ep1 = fused_epilogue(L->ffn1, L->ffn2);
-            const size_t lin_bytes = w4a4_linear_workspace_bytes(&a1, &w1, &ep1, w2.layout == W4A4_LAYOUT_MFMA);
-            void *lin_ws = c.take<uint8_t>(lin_bytes);
-            rc = w4a4_linear(&a1, &w1, &ep1, hb.q, hb.scale, nullptr, w2.layout == W4A4_LAYOUT_MFMA ? hb.osum : nullptr,
-                             lin_ws, lin_bytes, stream);
-            if (rc) return rc;
-            const w4a4_act hv = view_act4(hb, M, w2.K, w2);
-            w4a4_epilogue ep2 = {};
-            ep2.bias_f16 = L->ffn2.bias_f16;
-            ep2.act = L->ffn2.act;
-            rc = w4a4_linear(&hv, &w2, &ep2, p.h2, nullptr, nullptr, nullptr, nullptr, 0, stream);
-            if (rc) return rc;
-        } else {
-            __half *H = c.take<__half>((size_t)M * w1.N);
-            w4a4_epilogue ep1 = {};
-            ep1.bias_f16 = L->ffn1.bias_f16;
-            ep1.act = L->ffn1.act;
-            rc = w4a4_linear(&a1, &w1, &ep1, H, nullptr, nullptr, nullptr, nullptr, 0, stream);
-            if (rc) return rc;
-            rc = run_part(H, M, w1.N, L->ffn2, i3, p.h2, p.rest + c.used, stream);
-            if (rc) return rc;
-        }
+        __half *H = c.take<__half>((size_t)M * w1.N);
+        ep1.bias_f16 = L->ffn1.bias_f16;
+        ep1.act = L->ffn1.act;
+        rc = w4a4_linear(&a1, &w1, &ep1, H, nullptr, nullptr, nullptr, nullptr, 0, stream);
+        if (rc) return rc;
+        rc = run_part(H, M, w1.N, L->ffn2, i3, p.h2, p.rest + c.used, stream);
+        if (rc) return rc;
     }
-    // out = LN2(ffn2 + x1); the codes go to the buffers FFN1 has finished with (canonical layout, unused)
-    return w4a4_layernorm_quantize(p.h2, p.x1, M, h, h, L->ln2_gamma_f16, L->ln2_beta_f16, L->ln_eps, out_f16, W4A4_SYM, 0,
-                                   p.ln.q, p.ln.scale, nullptr, nullptr, W4A4_LAYOUT_CANONICAL, nullptr, stream);
+    // out = LN2(ffn2 + x1)
+    return run_layernorm(p.h2, p.x1, M, h, L->ln2_gamma_f16, L->ln2_beta_f16, L->ln_eps, out_f16, ActBuffers{},
+                         W4A4_LAYOUT_CANONICAL, LN_CODES_NONE, ClearRanges{}, stream);
 }

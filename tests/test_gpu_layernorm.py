@@ -73,6 +73,23 @@ def test_asymmetric_with_group_sums(B, orc, M, K, group):
     assert np.array_equal(host(A.gsum).astype(np.int64), gc.reshape(M, K // G, G).sum(axis=2))
 
 
+# two tokens per wave (rows of 1 .. 4 whole chunks for 32 lanes), an odd token at the end; a group of code sums wider than
+# the lanes of a row (512 codes), as wide (256), and inside it
+@pytest.mark.parametrize("K,group", [(256, 0), (256, 256), (512, 128), (768, 256), (1024, 512), (1024, 32)])
+@pytest.mark.parametrize("M", [1, 2, 9])
+@pytest.mark.parametrize("mode", [SYM, ASYM])
+def test_rows_shared_by_half_waves(B, orc, M, K, group, mode):
+    rng = np.random.default_rng(M + K + group)
+    x, r, g, b = _inputs(rng, M, K)
+    want = orc.layernorm_quantize(x, r, g, b, 1e-5, mode, group)
+    out = B._new_qact(M, K, mode, group, 0, "cuda")
+    G = K if group == 0 else group
+    out.gsum = torch.empty((M, K // G), dtype=torch.int32, device="cuda")
+    A, y = B.layernorm_quantize(dev(x), dev(r), dev(g), dev(b), 1e-5, mode, group, out=out)
+    gc = _check(orc, host(A.q), host(A.scale), None if mode == SYM else host(A.zero), host(y), want, mode)
+    assert np.array_equal(host(A.gsum).astype(np.int64), gc.reshape(M, K // G, G).sum(axis=2))
+
+
 def test_operand_layout_and_no_fp16_copy(B, orc):
     rng = np.random.default_rng(5)
     M, K = 200, 1024
