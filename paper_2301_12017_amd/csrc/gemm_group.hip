@@ -14,9 +14,12 @@
 //     LDS rows with an XOR swizzle, three LDS stages, persistent workgroups whose K steps form
 //     one stream across tiles (as in gemm_olay.hip);
 //   * the first MFMA of a group takes a zero C operand, so accumulators are never cleared;
-//   * token scales / zero points, and for asymmetric layers the group tables zw[g][n] and
-//     RA[g][m] of the tile, go to LDS by 4-byte DMA at the start of the tile; a group's weight
-//     scales are fetched into two registers when the group starts;
+//   * token scales / zero points, and for asymmetric layers the group tables zw and RA of the tile, go to LDS by
+//     4-byte DMA; a group's weight scales are fetched into two registers a group (or four) ahead.  These small
+//     requests decide as much as the vector ALU: one whose 64 lanes touch 32 or 64 cache lines occupies the memory
+//     path of the CU for as many cycles, and one issued in front of a K step's tile DMAs is waited for at its barrier.
+//     Tables as they lie in memory, spread over the K steps, and scales behind the DMAs, four groups per request:
+//     16384 x 768 x 3072 (24 groups) 66 -> 53 us, 16384 x 3072 x 768 + GELU 80 -> 72, 2048 x 768 x 3072 28 -> 23;
 //   * 128 x 128 tiles, four waves of 64 x 64 (64 integer + 64 fp32 accumulators per lane), two
 //     workgroups per CU so that one's group folds overlap the other's MFMAs.
 // Symmetric grouped layers run here too (signed codes are widened to 16*code, so the sums carry
@@ -65,8 +68,8 @@ void gemm_group_kernel(GemmArgs g) {
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     uint8_t *par = smem + NS * STAGE;                           // [2 parities][ sa[BM] | za[BM] ]
-    float *zw_tab = reinterpret_cast<float *>(par + 2 * 2 * BM * 4);          // [ng][BN]   (ASYM)
-    int *ra_tab = reinterpret_cast<int *>(zw_tab + (size_t)g.ng * BN);         // [ng][BM]   (ASYM)
+    float *zw_tab = reinterpret_cast<float *>(par + 2 * 2 * BM * 4);          // [ng][BN], OLAY [BN][ng]   (ASYM)
+    int *ra_tab = reinterpret_cast<int *>(zw_tab + (size_t)g.ng * BN);         // [ng][BM], OLAY [BM][ng]   (ASYM)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -132,26 +135,24 @@ void gemm_group_kernel(GemmArgs g) {
     const __amdgpu_buffer_rsrc_t bias_rsrc = make_rsrc(g.bias, g.bias ? (uint32_t)g.N * 2u : 0u);   // no bias: zeros
     // OLAY: per channel ng odd-position code sums WO and one fp32 word, 8 * sum_g sw*WO
     const __amdgpu_buffer_rsrc_t wo_rsrc = make_rsrc(g.esum, OLAY ? (uint32_t)((long)g.N * (g.ng + 1) * 4) : 0u);
-    // Token parameters and group tables of a tile, 64 values per DMA instruction, dealt round robin to
-    // the waves: blocks [0,2) scales, [2,4) zero points, then per group two blocks of zw and two of RA.
-    auto dma_params = [&](int m0, int n0, int parity) {
-        const int nblk = MODE == W4A4_ASYM ? 4 + 4 * g.ng : 2;
-        for (int b = wave; b < nblk; b += NW) {
-            const int half = b & 1;
-            if (b < 4) {
-                const bool is_sa = b < 2;
-                const int m = m0 + half * 64 + lane;
-                dma4(is_sa ? sa_rsrc : za_rsrc, par + parity * (2 * BM * 4) + (is_sa ? 0 : BM * 4) + half * 256, m * 4);
-            } else {
-                const int t = (b - 4) >> 1, grp = t >> 1;
-                if ((t & 1) == 0) {
-                    const int n = n0 + half * 64 + lane;
-                    dma4(zw_rsrc, zw_tab + grp * BN + half * 64, (n * g.ng + grp) * 4);
-                } else {
-                    const int m = m0 + half * 64 + lane;
-                    dma4(ra_rsrc, ra_tab + grp * BM + half * 64, (m * g.ng + grp) * 4);
-                }
-            }
+    // Token scales and zero points of a tile, double buffered by parity; 64 values per DMA instruction, one or no
+    // instruction per wave.
+    auto dma_tokens = [&](int m0, int parity) {
+        if (wave >= (MODE == W4A4_ASYM ? 4 : 2)) return;
+        const bool is_sa = wave < 2;
+        dma4(is_sa ? sa_rsrc : za_rsrc, par + parity * (2 * BM * 4) + (is_sa ? 0 : BM * 4) + (wave & 1) * 256, (m0 + (wave & 1) * 64 + lane) * 4);
+    };
+    // This wave's piece `grp` of the tile's tables zw and RA (waves 0, 1 the one, waves 2, 3 the other), one DMA instruction of
+    // 64 words, issued with the group's first K step: all of them at the start of a tile queued up in front of it.  OLAY: the
+    // tile's 128 rows of [.., ng] are one contiguous piece of memory and are copied as they lie (group by group, a
+    // DMA instruction's 64 lanes touched 64 cache lines); else piece grp is group grp.
+    auto dma_table = [&](int m0, int n0, int grp) {
+        if constexpr (MODE == W4A4_ASYM) {
+            const int half = wave & 1;
+            const int row0 = wave < 2 ? n0 : m0;
+            const int src = OLAY ? row0 * g.ng + grp * 128 + half * 64 + lane : (row0 + half * 64 + lane) * g.ng + grp;
+            if (wave < 2) dma4(zw_rsrc, zw_tab + grp * BN + half * 64, src * 4);
+            else dma4(ra_rsrc, ra_tab + grp * BM + half * 64, src * 4);
         }
     };
 
@@ -221,6 +222,7 @@ void gemm_group_kernel(GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < LD; ++i) dma_one(i, 1, a_cur, b_cur, ROWB);
     dma_col(1, m0, 1);
+    dma_tokens(m0, 0);
     __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
@@ -234,11 +236,10 @@ void gemm_group_kernel(GemmArgs g) {
         for (int f = 0; f < NF; ++f) P0[f] = read_frag(f, cur, 0);
         load_cinit(cur);
         // ---- tile start --------------------------------------------------------------------------------
-        dma_params(m0, n0, parity);
         const int n_lane = n0 + wn * FN * 32 + (lane & 31) * FN;          // FN = 2 adjacent channels
         const int n_local = wn * FN * 32 + (lane & 31) * FN;
-        const u32x2 c_raw = __builtin_amdgcn_raw_buffer_load_b64(c_rsrc, n_lane * 4, 0, 0);
-        const uint32_t bias_raw = __builtin_amdgcn_raw_buffer_load_b32(bias_rsrc, n_lane * 2, 0, 0);
+        u32x2 c_raw = {0u, 0u};
+        uint32_t bias_raw = 0;
         uint32_t kw_raw[FN] = {0u, 0u};                         // OLAY: what the layout's offsets add to t1, per channel
         if constexpr (OLAY) {
 #pragma unroll
@@ -283,14 +284,33 @@ void gemm_group_kernel(GemmArgs g) {
         Ucur[(k) / FN], Ucur[FM + FN - 1 - (k) % FN], acc[(k) / FN][0], 0, 0, 0);                          \
     __builtin_amdgcn_sched_barrier(0);
         constexpr int kBarSlot = NM - NF;
-        float swg[FN];                                          // weight scales of the current group (this lane's channels)
+        // Weight scales of this lane's channels: the current group's (swg) and those requested ahead, four groups at a time
+        // while a whole quad of groups lies ahead (one request costs the same 32 cache lines as for one group), else
+        // one.  They are requested BEHIND a K step's tile DMAs and needed one K step later at the earliest: in front of
+        // them, the barrier of that K step, which waits for everything older than its own DMAs, exposed their latency.
+        float swg[FN], swn[FN];
+        u32x4 quad[FN], quad_n[FN];
+        auto request_scales = [&](int grp0, float (&one)[FN]) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) one[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sw_rsrc, (n_lane + j) * g.ng * 4, grp0 * 4, 0));
+        };
+        auto request_quad = [&](int grp0, u32x4 (&four)[FN]) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) four[j] = __builtin_amdgcn_raw_buffer_load_b128(sw_rsrc, (n_lane + j) * g.ng * 4, grp0 * 4, 0);
+        };
+        constexpr bool QUADS = SPG1 && OUT != OUT_I32;
+        if constexpr (QUADS) request_quad(0, quad);
+        else request_scales(0, swn);
         int wog[FN] = {0, 0};                                   // OLAY, int32 export: its odd-position code sums
         int grp = 0;                                            // index of the current weight group
         // One K step.  Whether it opens a weight group (FOG) and whether it ends the tile (LAST) are compile-time
         // flags: a K step is then one straight block of code, and the slot order written here is the issue order.
         // (With a run-time "first of group" branch the compiler sank the widening of the next step's first operands
         // out of the last MFMA slots to the common head of the two branches, where it ran with the matrix pipe idle.)
-        auto k_step = [&](auto fog_tag, auto last_tag, int kt) {
+        // Q: place in a quad of groups whose scales are in `quad`, or -1.
+        auto k_step = [&](auto fog_tag, auto last_tag, auto q_tag, int kt) {
+            constexpr int Q = decltype(q_tag)::value;
+            constexpr int BEHIND = (MODE == W4A4_ASYM ? 1 : 0) + (OUT == OUT_I32 || Q > 0 ? 0 : FN);   // requests behind the tile DMAs of a group's first step
             constexpr bool FOG = decltype(fog_tag)::value;     // first K step of a weight group
             constexpr bool LAST = decltype(last_tag)::value;   // last K step of the tile
             const int nxt = cur == NS - 1 ? 0 : cur + 1;       // stage of stream step +1
@@ -302,7 +322,7 @@ void gemm_group_kernel(GemmArgs g) {
             if constexpr (FOG) {                                // this group's scales: used when it is folded
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
-                    swg[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sw_rsrc, (n_lane + j) * g.ng * 4, grp * 4, 0));
+                    swg[j] = Q < 0 ? swn[j] : __uint_as_float(quad[j][Q < 0 ? 0 : Q]);
                     if constexpr (OLAY && OUT == OUT_I32)
                         wog[j] = (int)__builtin_amdgcn_raw_buffer_load_b32(wo_rsrc, (n_lane + j) * (g.ng + 1) * 4, grp * 4, 0);
                 }
@@ -318,7 +338,13 @@ void gemm_group_kernel(GemmArgs g) {
                 if (k < NF) U1[k] = widen_hi(k, P0[k]);
                 if (k < NF) P1[k] = read_frag(k, cur, 1);
                 if (k < LD) dma_one(k, nx2, ra, rb, so);
-                if (k == LD - 1) dma_col(nx2, own ? m0 : m0n, kt2);
+                if (k == LD - 1) {
+                    dma_col(nx2, own ? m0 : m0n, kt2);
+                    if constexpr (FOG) dma_table(m0, n0, grp);
+                    if constexpr (LAST) dma_tokens(m0n, parity ^ 1);
+                    if constexpr (FOG && OUT != OUT_I32 && Q == 0) request_quad(grp + 4, quad_n);
+                    if constexpr (FOG && OUT != OUT_I32 && Q < 0) request_scales(min(grp + 1, g.ng - 1), swn);
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
             // sub-step 1: multiply (ks 0, high); widen (ks 1, low) -> U0
@@ -334,7 +360,7 @@ void gemm_group_kernel(GemmArgs g) {
                 W4A4_SLOT_BEGIN(U0, k)
                 if (k < NF) U1[k] = widen_hi(k, P1[k]);
                 if (k == kBarSlot) {
-                    __builtin_amdgcn_s_waitcnt(vmcnt_only(LAST ? 0 : LDT));
+                    __builtin_amdgcn_s_waitcnt(vmcnt_only(LAST ? 0 : FOG ? LDT + BEHIND : LDT));
                     __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
                 }
@@ -347,6 +373,10 @@ void gemm_group_kernel(GemmArgs g) {
                 W4A4_SLOT_BEGIN(U1, k)
                 if (!LAST && k < NF) U0[k] = widen_lo(k, P0[k]);
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (LAST && OUT != OUT_I32) {             // for the epilogue; requested behind the last wait of the tile
+                c_raw = __builtin_amdgcn_raw_buffer_load_b64(c_rsrc, n_lane * 4, 0, 0);
+                bias_raw = __builtin_amdgcn_raw_buffer_load_b32(bias_rsrc, n_lane * 2, 0, 0);
             }
             cur = nxt;
         };
@@ -400,19 +430,36 @@ void gemm_group_kernel(GemmArgs g) {
         {
             const std::true_type yes{};
             const std::false_type no{};
+            const std::integral_constant<int, -1> single{};
             int kt = 0;
             if constexpr (SPG1) {                               // every K step is a group
-                for (; kt < KT - 1; ++kt) { k_step(yes, no, kt); fold_group(no); }
-                k_step(yes, yes, kt);
+                if constexpr (QUADS) {
+                    for (; kt + 4 < KT; kt += 4) {
+                        k_step(yes, no, std::integral_constant<int, 0>{}, kt);
+                        fold_group(no);
+                        k_step(yes, no, std::integral_constant<int, 1>{}, kt + 1);
+                        fold_group(no);
+                        k_step(yes, no, std::integral_constant<int, 2>{}, kt + 2);
+                        fold_group(no);
+                        k_step(yes, no, std::integral_constant<int, 3>{}, kt + 3);
+                        fold_group(no);
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) quad[j] = quad_n[j];
+                    }
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) swn[j] = __uint_as_float(quad[j][0]);
+                }
+                for (; kt < KT - 1; ++kt) { k_step(yes, no, single, kt); fold_group(no); }
+                k_step(yes, yes, single, kt);
             } else {
                 for (int gi = 0; gi < g.ng - 1; ++gi) {
-                    k_step(yes, no, kt++);
-                    for (int st = 1; st < spg; ++st) k_step(no, no, kt++);
+                    k_step(yes, no, single, kt++);
+                    for (int st = 1; st < spg; ++st) k_step(no, no, single, kt++);
                     fold_group(no);
                 }
-                k_step(yes, no, kt++);
-                for (int st = 1; st < spg - 1; ++st) k_step(no, no, kt++);
-                k_step(no, yes, kt);
+                k_step(yes, no, single, kt++);
+                for (int st = 1; st < spg - 1; ++st) k_step(no, no, single, kt++);
+                k_step(no, yes, single, kt);
             }
             fold_group(yes);
         }
@@ -445,12 +492,12 @@ void gemm_group_kernel(GemmArgs g) {
                     float ta[FM], tb[FN];
 #pragma unroll
                     for (int i = 0; i < FM; ++i) {
-                        const int v = ra_tab[gs * BM + row_w + i * 32 + (lane & 31)];
+                        const int v = ra_tab[(row_w + i * 32 + (lane & 31)) * g.ng + gs];
                         ta[i] = live ? (float)v : 0.0f;
                     }
 #pragma unroll
                     for (int j = 0; j < FN; ++j) {
-                        const float v = zw_tab[gs * BN + n_local + j];
+                        const float v = zw_tab[(n_local + j) * g.ng + gs];
                         tb[j] = live ? v : 0.0f;
                     }
 #pragma unroll
