@@ -15,7 +15,7 @@ enum Family {
     F_GENERIC,   // any mode / grouping / K % 32: small and odd shapes
     F_OLAY,      // persistent kernel on operands in the MFMA operand layout
     F_GROUP,     // persistent kernel for K-grouped / asymmetric layers
-    F_SMALL,     // small-problem kernel: the waves of a workgroup split K (symmetric per-channel, K % 64 == 0)
+    F_SMALL,     // small-problem kernel: the waves of a workgroup split K (one weight group, K % 64 == 0)
     F_FP6        // persistent kernel on operands in the FP6 operand layout (FP6 matrix pipe, exact integer results)
 };
 struct Schedule {
@@ -50,9 +50,9 @@ static bool pipe_ok(const GemmArgs &g, bool grouped, int kstep = kBK) {
     return !grouped && g.K % kstep == 0 && (long)g.M * g.lda < 0x7fffffffL && (long)g.N * g.ldw < 0x7fffffffL;
 }
 
-// The small-problem kernel: symmetric per-channel layers in the canonical layout, fp16 or int32 output.
-static bool small_ok(const GemmArgs &g, bool grouped, int out_kind) {
-    return !grouped && (out_kind == OUT_F16 || out_kind == OUT_I32) && g.K % 64 == 0 && g.K <= 4096 && g.lda % 16 == 0 &&
+// The small-problem kernel: layers with one weight group in the canonical layout, fp16 or int32 output.
+static bool small_ok(const GemmArgs &g, int out_kind) {
+    return g.ng == 1 && (out_kind == OUT_F16 || out_kind == OUT_I32) && g.K % 64 == 0 && g.K <= 4096 && g.lda % 16 == 0 &&
            (long)g.M * g.lda < 0x7fffffffL && (long)g.N * g.ldw < 0x7fffffffL && ((long)g.M + 32) * g.N * 4 < 0x7fffffffL;
 }
 
@@ -69,23 +69,25 @@ static bool group_ok(const GemmArgs &g, bool grouped) {
 
 // Built-in shape table of the canonical layout: large problems take the pipelined tiles (192 x 128 when the
 // output is narrow, so that a 12288-token problem splits into a whole number of rounds of two
-// workgroups per CU; 128 x 256 otherwise), small ones the generic tiles that still give every
-// CU something to do.
+// workgroups per CU; 128 x 256 otherwise) or the group kernel, a few hundred 32 x 32 tiles the kernel whose waves
+// split K, everything between them 64 x 64 tiles (kernel per shape: launch_generic).
 static int pick_schedule(const GemmArgs &g, bool grouped, int out_kind) {
-    // a few hundred 32 x 32 tiles at most: latency decides, the waves of a workgroup split K
-    if ((long)((g.M + 31) / 32) * ((g.N + 31) / 32) <= 512 && small_ok(g, grouped, out_kind)) return S_SMALL;
+    // a few hundred 32 x 32 tiles at most: latency decides, the waves of a workgroup split K (us at 301 tokens, against
+    // 64 x 64 tiles: 768 x 768 symmetric 3.8 | 4.7, 768 x 3072 4.6 | 7.1; above, at 540 tiles: 6.0 | 4.9)
+    if ((long)((g.M + 31) / 32) * ((g.N + 31) / 32) <= 512 && small_ok(g, out_kind)) return S_SMALL;
     const long big = (long)((g.M + 127) / 128) * ((g.N + 255) / 256);
     if (big >= 256) {
         if (group_ok(g, grouped)) return S_GROUP;
         if (!pipe_ok(g, grouped)) return S_GEN_64x128;   // grouped layers: the 64 x 128 tile leaves LDS for the group tables
         return g.N <= 1024 ? S_PIPE_192x128 : S_PIPE_128x256;
     }
-    const long mid = (long)((g.M + 63) / 64) * ((g.N + 127) / 128);
-    if (mid >= 256) return S_GEN_64x128;
-    // 64 x 64 tiles beat 32 x 32 ones wherever there are a few dozen of them (measured at 384 .. 1536 tokens)
+    // 64 x 128 tiles pay from five rounds of 64 x 64 ones over the CUs (us, 64 x 64 | 64 x 128: 1024 x 3072 x 1024, 768 tiles,
+    // 8.2 | 9.6; 1500 x 3072 x 768, 1152 tiles, 10.1 | 10.9; 1500 x 4096 x 1024, 1536 tiles, 16.1 | 13.3; in groups of 128
+    // 15.7 | 18.6, 21.0 | 22.7, 26.9 | 25.3), never for asymmetric layers with one group, which have their own 64 x 64
+    // kernel.  32 x 32 tiles (12.4 | 12.4 at 64 tokens, slower above) are left with the group tables too large for 64 x 64.
     const long small = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
-    if (small >= 64) return S_GEN_64x64;
-    return S_GEN_32x32;
+    if (small >= 1280 && !(grouped && g.ng == 1)) return S_GEN_64x128;
+    return grouped && g.ng > 160 ? S_GEN_32x32 : S_GEN_64x64;
 }
 
 // The FP6 kernel: both operands in the FP6 layout, whole pairs of 64-code half steps, at least eight of them.
@@ -159,7 +161,7 @@ static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *
     if (sch == 0) sch = fp6 ? pick_fp6(g) : olay ? (grouped ? S_GROUP : pick_olay(g)) : pick_schedule(g, grouped, out_kind);
     if (sch < 1 || sch > kNumSchedules) return W4A4_ERR_INVALID_ARG;
     const Schedule &s = kSchedules[sch - 1];
-    if (grouped && !s.grouped_ok) return W4A4_ERR_INVALID_ARG;
+    if (grouped && !s.grouped_ok && !(s.family == F_SMALL && g.ng == 1)) return W4A4_ERR_INVALID_ARG;
     // a kernel family understands one layout, except the group kernel, which reads grouped layers in either
     if (fp6 != (s.family == F_FP6)) return W4A4_ERR_INVALID_ARG;
     if (!fp6 && (olay ? !(s.family == (grouped ? F_GROUP : F_OLAY)) : s.family == F_OLAY)) return W4A4_ERR_INVALID_ARG;
@@ -189,7 +191,7 @@ static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *
             }
             break;
         case F_SMALL:
-            if (!small_ok(g, grouped, out_kind)) return W4A4_ERR_UNSUPPORTED_SHAPE;
+            if (!small_ok(g, out_kind)) return W4A4_ERR_UNSUPPORTED_SHAPE;
             break;
         case F_GROUP:
             if (!group_ok(g, grouped) || q4) return W4A4_ERR_UNSUPPORTED_SHAPE;
@@ -218,7 +220,7 @@ static int run_gemm(GemmArgs &g, int mode, bool grouped, int out_kind, int sched
     switch (s.family) {
         case F_OLAY: return launch_olay(s.variant, out_kind, g, st);
         case F_FP6: return launch_fp6(s.variant, out_kind, g, st);
-        case F_SMALL: return launch_small_packed(out_kind, g, st);
+        case F_SMALL: return launch_small_packed(mode, out_kind, g, st);
         case F_GROUP: return launch_group(mode, out_kind, g, st);
         case F_PIPE: return launch_pipe(s.variant, out_kind, g, st);
         default: return launch_generic(s.variant, mode, grouped, out_kind, g, st);

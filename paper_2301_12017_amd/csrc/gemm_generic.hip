@@ -1,7 +1,7 @@
 // Generic INT4 x INT4 -> INT32 GEMM kernel with the fused epilogue: any M, any N % 8 == 0,
 // any K % 32 == 0, symmetric or asymmetric codes, weights with or without K-groups.
-// It is the fallback of the pipelined kernel (gemm_pipe.hip) and the kernel for grouped /
-// asymmetric layers and small problems.
+// It is the fallback of the pipelined kernel (gemm_pipe.hip) and the kernel for grouped layers and, where
+// gemm_mid.hip and gemm_small.hip are not faster, small problems.
 //
 //   * Both operands stay packed (two codes per byte) through the 16-byte global loads and
 //     in LDS; they are widened to int8 in registers right before v_mfma_i32_32x32x32_i8.
@@ -228,7 +228,23 @@ static int launch_variant(int variant, GemmArgs &g, hipStream_t st) {
     }
 }
 
+// Layers with one weight group on 64 x 64 tiles: shares of K for the kernel of gemm_mid.hip, 0 = the kernel above.  us,
+// two shares | four | none, at 768 and 1024 tokens and features where nothing else is said:
+//   symmetric    K = 768: 5.0 | 5.3 | 4.9; K = 1024: 5.3 | 5.3 | 5.6; K = 3072: 8.4 | 7.8 | 10.6; K = 4096: 10.0 | 9.0 | 13.4; more tiles
+//                than CUs (1500 tokens, 288): K = 3072 11.3 | 13.6 | 12.6, (465 tokens, 384 tiles) K = 1024 6.8 | 8.6 | 6.4
+//   asymmetric   K = 768: 5.3 | 5.3 | 8.1; K = 3072: 8.6 | 8.0 | 16.6; 465 x 2304 x 768 (288 tiles) 6.5 | 8.8 | 8.5,
+//                1500 x 4096 x 1024 (1536) 18.2 | 25.8 | 20.8
+static int k_shares(const GemmArgs &g, bool asym) {
+    const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+    if (g.ng != 1 || g.lda >= (1 << 24) || g.ldw >= (1 << 24)) return 0;
+    if (tiles <= 256 && g.K >= 1024) return 4;
+    return asym || (tiles <= 512 && g.K >= 2048) ? 2 : 0;
+}
+
 int launch_generic(int variant, int mode, bool grouped, int out_kind, GemmArgs &g, hipStream_t st) {
+    if (variant == 1) {
+        if (const int shares = k_shares(g, mode == W4A4_ASYM)) return launch_mid(shares, mode, out_kind, g, st);
+    }
 #define W4A4_GO(MODE, GR)                                                        \
     switch (out_kind) {                                                          \
         case OUT_F16: return launch_variant<MODE, GR, OUT_F16>(variant, g, st);  \

@@ -10,6 +10,9 @@
 //   * every pair has four LDS stages of its own, filled by 16-byte DMA three steps ahead: 96 KB in flight per
 //     workgroup at KS = 4; unpadded rows with the XOR swizzle of gemm_olay.hip;
 //   * the epilogue is dealt to all waves: a pair finishes 32 / KS rows of each of the tile's halves.
+// What is left is the vector ALU of the widening (72 instructions per wave and step beside eight MFMAs): without the
+// DMA a step takes 5 % less, without the MFMAs 20 %.  1024 x 768 x 3072 10.6 -> 7.8 us against the generic kernel,
+// asymmetric 16.6 -> 8.0; 301 x 2304 x 768 asymmetric 8.0 -> 5.2 (the choice per shape: launch_generic).
 #include "gemm_common.hpp"
 
 namespace w4a4 {

@@ -33,6 +33,8 @@ struct SmallArgs {
     const __half *X; long ldx;       // [M, K] fp16, row stride in elements (fp16-activation form)
     const uint8_t *Aq; long lda;     // [M, K/2] canonical packed codes, row stride in bytes (packed form)
     const float *sa;                 // [M] token scales (packed form)
+    const float *za; const int32_t *RA;   // [M] zero points, code sums (packed unsigned codes)
+    const float *zw, *c;             // [N] weight zero points, row sums (packed unsigned codes)
     int32_t *acc_out;                // packed form only: store the int32 sums P [M, N] instead of fp16 outputs
     const uint8_t *Wq; long ldw;     // canonical packed codes [N, K/2]; INT8 sibling: int8 codes [N, K]
     const float *sw;                 // [N]
@@ -79,7 +81,8 @@ __device__ __forceinline__ void codes8(const u32x4 &x, float inv, uint32_t &even
 // W8: the INT8 sibling.  Tokens are quantized with 127 levels per side (or arrive as one int8 code per
 // byte when PACKED), the weights are one int8 code per byte, and both go into the MFMA as they are (the
 // sums hold P).
-template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false>
+// ASYM (packed codes only): unsigned codes, one weight group; the sums hold P and the epilogue adds the zero-point terms.
+template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false>
 __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     constexpr int NT = NW * 64, LPR = NT / TM;                  // LPR consecutive lanes share a token in pass 1
     constexpr int RV = TM / 2;                                  // accumulator registers per fragment that hold real rows
@@ -89,13 +92,14 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     constexpr int XCH = PACKED ? 1 : small_xchunks(TM);
     constexpr int ACH = PACKED ? (W8 ? 8 : 4) : 1;              // 16-byte chunks of the packed activation tile per lane
     constexpr bool NIBBLES = PACKED && !W8;                     // activation codes arrive two per byte
+    static_assert(!ASYM || NIBBLES, "unsigned codes arrive packed");
     static_assert(LPR <= 64 && (LPR & (LPR - 1)) == 0, "a token's lanes sit in one wave");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int wpitch = (W8 ? a.K : a.K / 2) + 16, pitch = NIBBLES ? a.K / 2 + 16 : a.K + 16;
     uint8_t *codes = smem;                                      // [TM][pitch] int8 activation codes (packed codes if PACKED)
     uint8_t *wt = codes + TM * pitch;                           // [32 FN][wpitch] packed weight codes (WLDS)
     int *s_sum = reinterpret_cast<int *>(wt + (WLDS ? 32 * FN * wpitch : 0));   // [R][64]
-    float *s_S = reinterpret_cast<float *>(s_sum + R * 64);     // [TM]
+    float *s_S = reinterpret_cast<float *>(s_sum + R * 64);     // [TM] (ASYM: scales, zero points, code sums)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m0 = (blockIdx.x / a.tiles_n) * TM, n0 = (blockIdx.x % a.tiles_n) * (32 * FN);
@@ -157,19 +161,32 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     // wave qq % NW), as raw bits: nothing here waits for a load
     const __amdgpu_buffer_rsrc_t sw_rsrc = make_rsrc(a.sw, (uint32_t)a.N * 4u);
     const __amdgpu_buffer_rsrc_t b_rsrc = make_rsrc(a.bias, a.bias ? (uint32_t)a.N * 2u : 0u);   // no bias: reads zero
-    uint32_t sw_raw[RPW];
+    const __amdgpu_buffer_rsrc_t zw_rsrc = make_rsrc(a.zw, ASYM ? (uint32_t)a.N * 4u : 0u);
+    const __amdgpu_buffer_rsrc_t c_rsrc = make_rsrc(a.c, ASYM ? (uint32_t)a.N * 4u : 0u);
+    uint32_t sw_raw[RPW], zw_raw[ASYM ? RPW : 1], c_raw[ASYM ? RPW : 1];
     unsigned short b_raw[RPW];
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
         const int qq = wave + k * NW, n = n0 + 32 * (qq / RV) + r;
         sw_raw[k] = __builtin_amdgcn_raw_buffer_load_b32(sw_rsrc, (uint32_t)n * 4u, 0, 0);
         b_raw[k] = __builtin_amdgcn_raw_buffer_load_b16(b_rsrc, (uint32_t)n * 2u, 0, 0);
+        if constexpr (ASYM) {
+            zw_raw[k] = __builtin_amdgcn_raw_buffer_load_b32(zw_rsrc, (uint32_t)n * 4u, 0, 0);
+            c_raw[k] = __builtin_amdgcn_raw_buffer_load_b32(c_rsrc, (uint32_t)n * 4u, 0, 0);
+        }
     }
     for (int e = tid; e < R * 64; e += NT) s_sum[e] = 0;
 
     // ---- pass 1: ranges, codes into LDS ----------------------------------------------------------------------
     if constexpr (PACKED) {
-        if (tid < TM) s_S[tid] = a.sa[min(m0 + tid, a.M - 1)];
+        if (tid < TM) {
+            const int m = min(m0 + tid, a.M - 1);
+            s_S[tid] = a.sa[m];
+            if constexpr (ASYM) {
+                s_S[TM + tid] = a.za[m];
+                s_S[2 * TM + tid] = (float)a.RA[m];
+            }
+        }
 #pragma unroll
         for (int i = 0; i < ACH; ++i)
             if (i * NT < TM * wcpr && arow_i[i] < TM) *reinterpret_cast<u32x4 *>(codes + adst_i[i]) = ast[i];
@@ -228,8 +245,8 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
         v4i alo, ahi;
         if constexpr (NIBBLES) {
             const u32x4 ap = *reinterpret_cast<const u32x4 *>(arow + b * 32);
-            alo = widen2<true>(ap[0], ap[1]);
-            ahi = widen2<true>(ap[2], ap[3]);
+            alo = widen2<!ASYM>(ap[0], ap[1]);
+            ahi = widen2<!ASYM>(ap[2], ap[3]);
         } else {
             alo = *reinterpret_cast<const v4i *>(arow + b * 64);
             ahi = *reinterpret_cast<const v4i *>(arow + b * 64 + 16);
@@ -264,10 +281,10 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
         }
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(alo, widen2<true>(wv[j][0], wv[j][1]), acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(alo, widen2<!ASYM>(wv[j][0], wv[j][1]), acc[j], 0, 0, 0);
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ahi, widen2<true>(wv[j][2], wv[j][3]), acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ahi, widen2<!ASYM>(wv[j][2], wv[j][3]), acc[j], 0, 0, 0);
         }
     }
 
@@ -293,13 +310,22 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
         const int trow = frag_row(0, q, lane);
         if (ints) {                                              // parity export: P itself
             const uint32_t ioff = n_ok ? ((uint32_t)(m0 + trow) * (uint32_t)a.N + (uint32_t)n) * 4u : kPoison;
-            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(W8 ? s_sum[qq * 64 + lane] : s_sum[qq * 64 + lane] >> 8), o_rsrc, ioff, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(W8 || ASYM ? s_sum[qq * 64 + lane] : s_sum[qq * 64 + lane] >> 8), o_rsrc, ioff, 0, 0);
             continue;
         }
         // the sums hold 16 * P (256 * P if PACKED, P itself for the INT8 sibling); a power of two, so the rescaled
         // weight scale is exact
-        const float swn = __uint_as_float(sw_raw[k]) * (W8 ? 1.0f : PACKED ? 0.00390625f : 0.0625f);
-        float y = ((float)s_sum[qq * 64 + lane] * s_S[trow]) * swn;
+        const float swn = __uint_as_float(sw_raw[k]) * (W8 || ASYM ? 1.0f : PACKED ? 0.00390625f : 0.0625f);
+        float y;
+        if constexpr (ASYM) {                                    // the operation order of tile_epilogue (one weight group)
+            const float t1 = swn * (float)s_sum[qq * 64 + lane], t2 = __uint_as_float(zw_raw[k]) * s_S[2 * TM + trow];
+            y = s_S[trow] * t1;
+            const float u = s_S[trow] * t2, z = s_S[TM + trow] * __uint_as_float(c_raw[k]);
+            y = y + u;
+            y = y + z;
+        } else {
+            y = ((float)s_sum[qq * 64 + lane] * s_S[trow]) * swn;
+        }
         if (a.bias) y = y + __half2float(__ushort_as_half(b_raw[k]));
         const uint32_t off = n_ok ? ((uint32_t)(m0 + trow) * (uint32_t)a.N + (uint32_t)n) * 2u : kPoison;   // rows >= M fall off the end
         if (a.act == W4A4_ACT_GELU) __builtin_amdgcn_raw_buffer_store_b16(gelu_erf_half(y), o_rsrc, off, 0, 0);
@@ -307,14 +333,14 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     }
 }
 
-template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false>
+template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false>
 static int launch_small(SmallArgs &a, hipStream_t st) {
     a.tiles_n = (a.N + 32 * FN - 1) / (32 * FN);
     const long tiles = (long)((a.M + TM - 1) / TM) * a.tiles_n;
     if (tiles > 0x7fffffffL) return W4A4_ERR_UNSUPPORTED_SHAPE;
     const size_t lds = TM * (size_t)((PACKED && !W8 ? a.K / 2 : a.K) + 16) + (WLDS ? 32 * FN * (size_t)((W8 ? a.K : a.K / 2) + 16) : 0) +
-                       (size_t)(TM / 2) * FN * 64 * 4 + TM * 4;
-    auto kern = linear_f16act_kernel<NW, FN, TM, WLDS, PACKED, W8>;
+                       (size_t)(TM / 2) * FN * 64 * 4 + TM * (ASYM ? 12 : 4);
+    auto kern = linear_f16act_kernel<NW, FN, TM, WLDS, PACKED, W8, ASYM>;
     static KernelState ks;
     if (prepare_kernel(reinterpret_cast<const void *>(kern), lds, ks) < 0) return W4A4_ERR_HIP;
     launch_gemm(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, st, a);
@@ -326,7 +352,7 @@ static int launch_small(SmallArgs &a, hipStream_t st) {
 // redundant work, but a tile is one CU's job: 32 x 32 while that gives at most one workgroup per CU, 32 x 64
 // beyond, and 16-token tiles when 32-token tiles would leave more than half of the CUs idle.  The weight
 // tile is staged in LDS (coalesced loads) whenever it fits beside the activation codes.
-template <bool PACKED, bool W8 = false>
+template <bool PACKED, bool W8 = false, bool ASYM = false>
 static int small_dispatch(SmallArgs &a, hipStream_t st) {
     const int M = a.M, N = a.N, K = a.K;
     const long t32 = (long)((M + 31) / 32) * ((N + 31) / 32);
@@ -337,9 +363,9 @@ static int small_dispatch(SmallArgs &a, hipStream_t st) {
     const bool wlds = code_b + wt_b <= 144 * 1024 && wchunks <= small_wchunks(nw);   // beside the sums, within a CU's 160 KB
 #define W4A4_SMALL(NW)                                                                                  \
     do {                                                                                                \
-        if (wide) return wlds ? launch_small<NW, 2, 32, true, PACKED, W8>(a, st) : launch_small<NW, 2, 32, false, PACKED, W8>(a, st); \
-        if (low) return wlds ? launch_small<NW, 1, 16, true, PACKED, W8>(a, st) : launch_small<NW, 1, 16, false, PACKED, W8>(a, st);  \
-        return wlds ? launch_small<NW, 1, 32, true, PACKED, W8>(a, st) : launch_small<NW, 1, 32, false, PACKED, W8>(a, st);     \
+        if (wide) return wlds ? launch_small<NW, 2, 32, true, PACKED, W8, ASYM>(a, st) : launch_small<NW, 2, 32, false, PACKED, W8, ASYM>(a, st); \
+        if (low) return wlds ? launch_small<NW, 1, 16, true, PACKED, W8, ASYM>(a, st) : launch_small<NW, 1, 16, false, PACKED, W8, ASYM>(a, st);  \
+        return wlds ? launch_small<NW, 1, 32, true, PACKED, W8, ASYM>(a, st) : launch_small<NW, 1, 32, false, PACKED, W8, ASYM>(a, st);     \
     } while (0)
     if (K > 1536) W4A4_SMALL(16);
     if (K > 384) W4A4_SMALL(8);
@@ -348,9 +374,9 @@ static int small_dispatch(SmallArgs &a, hipStream_t st) {
 }
 
 // The same kernel on activations that are already quantized (canonical packed codes + token scales): the
-// small-problem schedule of w4a4_linear / w4a4_gemm_i32.  Requires symmetric per-channel operands,
+// small-problem schedule of w4a4_linear / w4a4_gemm_i32.  Requires one weight group,
 // K % 64 == 0, K <= 4096, lda % 16 == 0, 32-bit offsets.
-int launch_small_packed(int out_kind, GemmArgs &g, hipStream_t st) {
+int launch_small_packed(int mode, int out_kind, GemmArgs &g, hipStream_t st) {
     if (out_kind != OUT_F16 && out_kind != OUT_I32) return W4A4_ERR_UNSUPPORTED_SHAPE;
     if (g.K % 64 || g.K > 4096 || g.lda % 16 || (long)g.M * g.lda >= 0x7fffffffL || (long)g.N * g.ldw >= 0x7fffffffL ||
         ((long)g.M + 32) * g.N * 4 >= 0x7fffffffL)
@@ -362,7 +388,9 @@ int launch_small_packed(int out_kind, GemmArgs &g, hipStream_t st) {
     if (out_kind == OUT_I32) a.acc_out = static_cast<int32_t *>(g.out);
     else a.out = static_cast<__half *>(g.out);
     a.M = g.M; a.N = g.N; a.K = g.K;
-    return small_dispatch<true>(a, st);
+    if (mode == W4A4_SYM) return small_dispatch<true>(a, st);
+    a.za = g.za; a.RA = g.RA; a.zw = g.zw; a.c = g.c;
+    return small_dispatch<true, false, true>(a, st);
 }
 
 // The INT8 sibling's small-problem path on int8 codes that are already in memory (w8a8_linear / w8a8_gemm_i32

@@ -431,3 +431,26 @@ def test_quantize_act_many_rows_asymmetric(B, orc, layout, M, K, ldx, group):
         G = K if group == 0 else group
         even = orc.unpack(want["q"], ASYM).astype(np.int64).reshape(M, K // G, G)[:, :, 0::2].sum(axis=2)
         assert np.array_equal(host(A.osum).astype(np.int64), 128 * even.T)
+
+
+@pytest.mark.parametrize("mode", [SYM, ASYM])
+@pytest.mark.parametrize("M,N,K", [
+    (1, 8, 64), (17, 40, 192), (33, 520, 4096), (512, 1024, 128),             # the kernel whose waves split K
+    (513, 520, 1056), (65, 4104, 768), (1000, 1024, 1024), (640, 1640, 1024),  # 64 x 64 tiles: a tail of K, one round, more
+    (577, 1024, 4160), (1100, 1096, 2080), (1024, 1032, 3072)])                # ... K in four shares and in two
+def test_one_weight_group_small_and_mid_sized(B, orc, mode, M, N, K):
+    """Layers with one weight group between one token and a few rounds of 64 x 64 tiles, ragged in M, N and K: int32 sums
+    and fp16 outputs (with a bias; GELU behind it on sampled rows) equal the oracle's bits."""
+    rng = np.random.default_rng(M + N + K + mode)
+    X, W, A, Q = _operands(B, orc, rng, M, N, K, mode, 0)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float16)
+    rows = np.unique(np.concatenate([[0, M - 1], rng.integers(0, M, 14)]))
+    oa, ow = orc.quantize_act(np.ascontiguousarray(X[rows]), mode), orc.quantize_weight(W, mode)
+    assert np.array_equal(host(B.gemm_i32(A, Q))[:, rows], orc.gemm_i32(oa["q"], ow["q"], mode))
+    got = host(B.linear(A, Q, dev(b), 0))[rows]
+    assert np.array_equal(got.view(np.uint16), orc.linear(oa, ow, mode, 0, b, 0)["out"].view(np.uint16))
+    assert_f16(host(B.linear(A, Q, dev(b), 1))[rows], orc.linear(oa, ow, mode, 0, b, 1)["out"], 0.5, str((M, N, K)))
+    if N % 32 == 0:                                               # fp32 rows, then the row quantizer
+        out = B.linear(A, Q, dev(b), 0, requant=True, requant_mode=ASYM)
+        want = orc.linear(oa, ow, mode, 0, b, 0, requant=True, requant_mode=ASYM)
+        assert np.array_equal(host(out.q)[rows], want["q"])
