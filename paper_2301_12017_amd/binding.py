@@ -255,8 +255,10 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """Handle of the current stream of the current device.  (torch.cuda.current_stream() builds a Stream object around it:
+    2.9 us a call, half of what a call of this binding costs on the host; this is 0.3.)"""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check(rc: int, where: str):
