@@ -75,16 +75,16 @@ bool part_ok(const w4a4_part *p) {
     return p && p->w4.N > 0 && p->w4.K > 0 && p->w4.K % 32 == 0 && (p->act == W4A4_ACT_NONE || p->act == W4A4_ACT_GELU);
 }
 
-// One launch for small token counts: up to 512 tiles of 32 x 32, which quantize their tokens' whole rows.  With long rows only
-// up to 128, where the kernel still takes 16-token tiles: 465 x 768 x 3072 11.5 us in one launch, 3.2 + 6.4 in two; 256 tokens
-// 9.4 | 3.2 + 4.4, 160 tokens 6.6 | 3.2 + 4.3; K = 768: 465 tokens 6.0 | 3.2 + 4.4.
-bool one_kernel_tiles(int M, int N, int K) {
+// One launch for small token counts: up to 512 tiles of 32 x 32, which quantize their tokens' whole rows.  INT4 with long rows
+// only up to 128, where the kernel still takes 16-token tiles: 465 x 768 x 3072 10.4 us in one launch, 9.7 in two; 256 tokens
+// 8.7 | 7.7, 160 tokens 6.5 | 7.0; 465 tokens of K = 768 6.1 | 7.3.  INT8: 465 x 768 x 3072 12.8 | 14.5.
+bool one_kernel_tiles(int M, int N, int K, bool int4) {
     const long tiles = (long)((M + 31) / 32) * ((N + 31) / 32);
-    return K % 64 == 0 && K <= 4096 && tiles <= (K > 2048 ? 128 : 512);
+    return K % 64 == 0 && K <= 4096 && tiles <= (int4 && K > 2048 ? 128 : 512);
 }
 // ... symmetric per-channel weights in the canonical layout
 bool one_kernel_shape(int M, const w4a4_weight &w) {
-    return w.layout == W4A4_LAYOUT_CANONICAL && w.mode == W4A4_SYM && groups_of(w) == 1 && one_kernel_tiles(M, w.N, w.K);
+    return w.layout == W4A4_LAYOUT_CANONICAL && w.mode == W4A4_SYM && groups_of(w) == 1 && one_kernel_tiles(M, w.N, w.K, true);
 }
 
 int run_part(const void *X, int M, int ldx, const w4a4_part &p, bool int4, void *out, void *ws, void *stream) {
@@ -106,7 +106,7 @@ int run_part(const void *X, int M, int ldx, const w4a4_part &p, bool int4, void 
         return w4a4_linear(&a, &p.w4, &ep, out, nullptr, nullptr, nullptr, nullptr, 0, stream);
     }
     if (!p.w8q || !p.w8s) return W4A4_ERR_INVALID_ARG;
-    if (one_kernel_tiles(M, N, K)) {
+    if (one_kernel_tiles(M, N, K, false)) {
         const int rc = w8a8_linear_f16act(X, M, K, ldx, p.w8q, p.w8s, N, &ep, out, stream);
         if (rc != W4A4_ERR_UNSUPPORTED_SHAPE) return rc;
     }
