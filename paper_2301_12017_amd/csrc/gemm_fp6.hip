@@ -290,13 +290,14 @@ void gemm_fp6_kernel(GemmArgs g) {
     // descriptors of a tile: from its first panel to the end of the (panel-padded) matrix - for a column slice, to the
     // end of the slice's blocks in the last panel
     const long a_bytes = ((((long)g.M + 63) >> 6) - 1) * a_panel + (long)KB * 3072, b_bytes = (((long)g.N + 127) & ~127L) * KB * 48;
-    auto a_desc = [&](int m0) {
+    // (exists == false: no bytes at all, so that the prefetch of a tile that does not exist touches no memory)
+    auto a_desc = [&](int m0, bool exists = true) {
         const long off = (long)(m0 >> 6) * a_panel;
-        return make_rsrc(g.Aq + off, (uint32_t)(a_bytes > off ? a_bytes - off : 0));
+        return make_rsrc(g.Aq + off, (uint32_t)(exists && a_bytes > off ? a_bytes - off : 0));
     };
-    auto b_desc = [&](int n0) {
+    auto b_desc = [&](int n0, bool exists = true) {
         const long off = (long)(n0 >> 7) * KB * 6144;
-        return make_rsrc(g.Wq + off, (uint32_t)(b_bytes > off ? b_bytes - off : 0));
+        return make_rsrc(g.Wq + off, (uint32_t)(exists && b_bytes > off ? b_bytes - off : 0));
     };
     auto dma_one = [&](int i, int stage, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, int hstep) {
         const int bi = wave + i * NW;
@@ -383,12 +384,14 @@ void gemm_fp6_kernel(GemmArgs g) {
     int m0 = (tile / g.tiles_n) * BM, n0 = (tile % g.tiles_n) * BN;
     __amdgpu_buffer_rsrc_t a_cur = a_desc(m0), b_cur = b_desc(n0);
     // ---- first tile: its first NS half steps and its token scales -----------------------------------
+    // (Beginning with the first half step's arrival instead of all NS, and requesting nothing for the tile after the
+    // last one: four linears at 8191 tokens, 1024 features, 130.0 -> 126.2 us.)
+    dma_params(m0, 0);
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
         for (int i = 0; i < LD; ++i) dma_one(i, s, a_cur, b_cur, s);
-    dma_params(m0, 0);
-    __builtin_amdgcn_s_waitcnt(vmcnt_and_lds(0));
+    __builtin_amdgcn_s_waitcnt(vmcnt_and_lds((NS - 1) * LD));   // the first half step; the others are waited for where they are read
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     v8i Pa[NF], Pb[NF];
@@ -397,6 +400,7 @@ void gemm_fp6_kernel(GemmArgs g) {
 
     int cur = 0;                                                // ring stage of the current half step
     int parity = 0;
+    bool fresh = true;                                          // the workgroup's first tile
     for (;;) {
         const int n_lane = n0 + ((wn * FN) >> 2) * 128 + (lane & 31) * 4 + ((wn * FN) & 3);
         static_assert(FN == 4 || FN == 2, "channel constants are fetched two or four at a time");
@@ -415,7 +419,7 @@ void gemm_fp6_kernel(GemmArgs g) {
         const bool has_next = tile_of(vb_next, tile_next);
         if (!has_next) tile_next = tile;
         const int m0n = (tile_next / g.tiles_n) * BM, n0n = (tile_next % g.tiles_n) * BN;
-        const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n), b_nxt = b_desc(n0n);
+        const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n, has_next), b_nxt = b_desc(n0n, has_next);
 
         // ---- main loop: one half step = 64 codes of K = NM MFMAs ---------------------------------------------
         // Slot k issues MFMA k; slot 0 then waits for this wave's tile DMAs of half step +1 and for its LDS
@@ -428,7 +432,7 @@ void gemm_fp6_kernel(GemmArgs g) {
             constexpr bool LAST = decltype(last_tag)::value;    // last half step of the tile: wait for everything in flight
             const int nxt = cur == NS - 1 ? 0 : cur + 1;
             // stream step +NS is half step hs+NS of this tile, or hs+NS-KT of the next one (when there is none:
-            // a harmless in-bounds re-read, so that the load counting stays uniform)
+            // requests that the descriptor turns away, so that the load counting stays uniform)
             const bool own = hs + NS < KT;
             const __amdgpu_buffer_rsrc_t ra = own ? a_cur : a_nxt, rb = own ? b_cur : b_nxt;
             const int so = own ? hs + NS : hs + NS - KT;
@@ -442,8 +446,11 @@ void gemm_fp6_kernel(GemmArgs g) {
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if (k == 0) {
-                    if constexpr (LAST) __builtin_amdgcn_s_waitcnt(vmcnt_and_lds(0));
-                    else if constexpr (WAIT) __builtin_amdgcn_s_waitcnt(vmcnt_and_lds((NS - 2) * LD));
+                    if constexpr (LAST) {
+                        if (has_next) __builtin_amdgcn_s_waitcnt(vmcnt_and_lds(0));
+                        else __builtin_amdgcn_s_waitcnt(vmcnt_and_lds(63));
+                    }
+                    else if (WAIT || fresh) __builtin_amdgcn_s_waitcnt(vmcnt_and_lds((NS - 2) * LD));
                     else __builtin_amdgcn_s_waitcnt(vmcnt_and_lds(63));
                     __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
@@ -460,9 +467,9 @@ void gemm_fp6_kernel(GemmArgs g) {
         using no = std::false_type;
         using nowait = std::integral_constant<int, 0>;
         using wait = std::integral_constant<int, 1>;
-        // The first NS-2 half steps of a tile find their successor landed (the last half step of the previous tile,
-        // or the prologue, waited for everything); they must not wait on the counter, which the epilogue's stores
-        // have filled since.
+        // The first NS-2 half steps of a tile find their successor landed (the last half step of the previous tile
+        // waited for everything); they must not wait on the counter, which the epilogue's stores have filled since.
+        // In the workgroup's first tile (`fresh`) they wait: the prologue waited for the first half step alone.
         half_step(yes{}, nowait{}, no{}, Pa, Pb, 0);
         // every wave has passed a barrier of this tile, so nobody reads the previous tile's scales any more: fetch
         // the next tile's into that buffer (complete at this tile's last barrier)
@@ -518,7 +525,7 @@ void gemm_fp6_kernel(GemmArgs g) {
             else fp6_epilogue<FM, FN, OUT, true, true>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
         }
         if (!has_next) break;
-        vb = vb_next; tile = tile_next; m0 = m0n; n0 = n0n; a_cur = a_nxt; b_cur = b_nxt; parity ^= 1;
+        vb = vb_next; tile = tile_next; m0 = m0n; n0 = n0n; a_cur = a_nxt; b_cur = b_nxt; parity ^= 1; fresh = false;
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_and_lds(0));               // no DMA may outlive the workgroup's LDS
 }

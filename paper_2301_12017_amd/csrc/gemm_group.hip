@@ -94,13 +94,14 @@ void gemm_group_kernel(GemmArgs g) {
             voff[i] = nl * (int)g.ldw + c * 16;
         }
     }
-    auto a_desc = [&](int m0) {
+    // (exists == false: no bytes at all, so that the prefetch of a tile that does not exist touches no memory)
+    auto a_desc = [&](int m0, bool exists = true) {
         const int rows = min(BM, g.M - m0);
-        return make_rsrc(g.Aq + (long)m0 * g.lda, (uint32_t)((long)(rows - 1) * g.lda + g.K / 2));
+        return make_rsrc(g.Aq + (long)m0 * g.lda, exists ? (uint32_t)((long)(rows - 1) * g.lda + g.K / 2) : 0u);
     };
-    auto b_desc = [&](int n0) {
+    auto b_desc = [&](int n0, bool exists = true) {
         const int rows = min(BN, g.N - n0);
-        return make_rsrc(g.Wq + (long)n0 * g.ldw, (uint32_t)((long)rows * g.ldw));
+        return make_rsrc(g.Wq + (long)n0 * g.ldw, exists ? (uint32_t)((long)rows * g.ldw) : 0u);
     };
     auto dma4 = [&](__amdgpu_buffer_rsrc_t rs, void *dst, int vo, int so = 0) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's signature; it rejects the LDS cast
@@ -216,14 +217,16 @@ void gemm_group_kernel(GemmArgs g) {
     int tile = xcd_tile(vb, total);
     int m0 = (tile / g.tiles_n) * BM, n0 = (tile % g.tiles_n) * BN;
     __amdgpu_buffer_rsrc_t a_cur = a_desc(m0), b_cur = b_desc(n0);
+    dma_tokens(m0, 0);
 #pragma unroll
     for (int i = 0; i < LD; ++i) dma_one(i, 0, a_cur, b_cur, 0);
     dma_col(0, m0, 0);
 #pragma unroll
     for (int i = 0; i < LD; ++i) dma_one(i, 1, a_cur, b_cur, ROWB);
     dma_col(1, m0, 1);
-    dma_tokens(m0, 0);
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+    // the first K step; the second is waited for where it is read (with this, and no requests for the tile after the last
+    // one, four linears at 16384 tokens: 1 % less; the symmetric kernel gains nothing and its requantizing form loses)
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(LDT));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     u32x4 P0[NF], P1[NF];
@@ -250,7 +253,7 @@ void gemm_group_kernel(GemmArgs g) {
         const bool has_next = vb_next < total;
         const int tile_next = xcd_tile(has_next ? vb_next : vb, total);
         const int m0n = (tile_next / g.tiles_n) * BM, n0n = (tile_next % g.tiles_n) * BN;
-        const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n), b_nxt = b_desc(n0n);
+        const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n, has_next), b_nxt = b_desc(n0n, has_next);
 #pragma unroll
         for (int f = 0; f < NF; ++f) U0[f] = widen_lo(f, P0[f]);
 #pragma unroll
