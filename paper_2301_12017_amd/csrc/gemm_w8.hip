@@ -110,13 +110,14 @@ void gemm_w8_kernel(GemmArgs g) {
         }
     }
     // Descriptors of a tile: base at the tile origin, size = its valid rows.
-    auto a_desc = [&](int m0) {
+    // (exists == false: no bytes at all, so that the prefetch of a tile that does not exist touches no memory)
+    auto a_desc = [&](int m0, bool exists = true) {
         const int rows = min(BM, g.M - m0);
-        return make_rsrc(g.Aq + (long)m0 * g.lda, (uint32_t)((long)(rows - 1) * g.lda + g.K));
+        return make_rsrc(g.Aq + (long)m0 * g.lda, exists ? (uint32_t)((long)(rows - 1) * g.lda + g.K) : 0u);
     };
-    auto b_desc = [&](int n0) {
+    auto b_desc = [&](int n0, bool exists = true) {
         const int rows = min(BN, g.N - n0);
-        return make_rsrc(g.Wq + (long)n0 * g.ldw, (uint32_t)((long)rows * g.ldw));
+        return make_rsrc(g.Wq + (long)n0 * g.ldw, exists ? (uint32_t)((long)rows * g.ldw) : 0u);
     };
     auto dma_one = [&](int i, int stage, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, int so) {
         uint8_t *dst = smem + stage * STAGE + (wave + i * NW) * 1024;
@@ -169,12 +170,12 @@ void gemm_w8_kernel(GemmArgs g) {
     if (!tile_of(vb, tile)) return;                             // (uniform) nothing to do for this workgroup
     int m0 = (tile / g.tiles_n) * BM, n0 = (tile % g.tiles_n) * BN;
     __amdgpu_buffer_rsrc_t a_cur = a_desc(m0), b_cur = b_desc(n0);
+    dma_params(m0, 0);
 #pragma unroll
     for (int i = 0; i < LD; ++i) dma_one(i, 0, a_cur, b_cur, 0);
 #pragma unroll
     for (int i = 0; i < LD; ++i) dma_one(i, 1, a_cur, b_cur, ROWB);
-    dma_params(m0, 0);
-    __builtin_amdgcn_s_waitcnt(w8_vmcnt_only(0));
+    __builtin_amdgcn_s_waitcnt(w8_vmcnt_only(LD));              // the first K step; the second is waited for where it is read
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     v4i P0[NF], P1[NF];
@@ -205,7 +206,7 @@ void gemm_w8_kernel(GemmArgs g) {
         const bool has_next = tile_of(vb_next, tile_next);
         if (!has_next) tile_next = tile;
         const int m0n = (tile_next / g.tiles_n) * BM, n0n = (tile_next % g.tiles_n) * BN;
-        const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n), b_nxt = b_desc(n0n);
+        const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n, has_next), b_nxt = b_desc(n0n, has_next);
 
         // ---- main loop: one iteration = 64 codes of K = two sub-steps of NM MFMAs ------------------------
         // The instruction order below is the intended issue order; the scheduling barriers keep the
@@ -226,7 +227,7 @@ void gemm_w8_kernel(GemmArgs g) {
             const int nxt = cur == NS - 1 ? 0 : cur + 1;       // stage of stream step +1
             const int nx2 = nxt == NS - 1 ? 0 : nxt + 1;       // stage of stream step +2 (= step -1)
             // stream step +2 is K step kt+2 of this tile, or K step kt+2-KT of the next one (when there
-            // is none: a harmless in-bounds re-read, so that the load counting stays uniform)
+            // is none: requests that the descriptor turns away, so that the load counting stays uniform)
             const bool own = !LAST && kt + 2 < KT;
             const __amdgpu_buffer_rsrc_t ra = own ? a_cur : a_nxt, rb = own ? b_cur : b_nxt;
             const int so = (own ? kt + 2 : kt + 2 - KT) * ROWB;
@@ -313,19 +314,32 @@ static int launch_one(GemmArgs &g, hipStream_t st) {
 bool small8_ok(const GemmArgs &g);                              // gemm_small.hip: the split-K kernel for small problems
 int launch_small_packed8(int out_kind, GemmArgs &g, hipStream_t st);
 
-// Tile choice as for the INT4 kernel: the largest number of tiles any CU ends up with times the tile area.
+template <int OUT>
+static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
+    switch (tile) {
+        case 0: return launch_one<2, 4, 2, 2, 2, OUT>(g, st);   // 128 x 256, two workgroups per CU
+        case 1: return launch_one<3, 2, 2, 2, 2, OUT>(g, st);   // 192 x 128, two workgroups per CU
+        default: return launch_one<2, 2, 2, 2, 3, OUT>(g, st);  // 128 x 128, three workgroups per CU
+    }
+}
+
+// Tile choice as for the INT4 kernel: n tiles on the busiest CU, worked on by min(n, workgroups per CU) workgroups at a
+// time, cost n * area / (rate * efficiency) with the rate of one / two / three workgroups 0.7 / 1 / 0.95 and the efficiency
+// of the three tiles 1 / 0.9 / 0.8.  Fitted to kernel times over M = 512 .. 16384 on the BERT-base and BERT-large shapes:
+// 0.8 % above the best of the three on average (128 x 256 and 192 x 128 by area alone: 7.4 %).  4096 x 1024 x 4096:
+// 128 x 128 23.8 us, 192 x 128 28.2, 128 x 256 30.4; 4096 x 3072 x 1024: 20.6, 22.4, 19.4.
 // A few hundred 32 x 32 tiles at most go to the small-problem kernel instead (latency decides there).
 static int launch_w8(int out_kind, GemmArgs &g, hipStream_t st) {
     if (small8_ok(g)) return launch_small_packed8(out_kind, g, st);
     const long cus = 256;
-    auto cost = [&](int bm, int bn) {
+    auto cost = [&](int bm, int bn, int occ, double eff) {
         const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
-        return (double)((tiles + cus - 1) / cus) * bm * bn;
+        const long n = (tiles + cus - 1) / cus, together = n < occ ? n : occ;
+        return (double)n * bm * bn / ((together == 1 ? 0.7 : together == 2 ? 1.0 : 0.95) * eff);
     };
-    const bool wide = cost(128, 256) <= cost(192, 128);
-    if (out_kind == OUT_I32)
-        return wide ? launch_one<2, 4, 2, 2, 2, OUT_I32>(g, st) : launch_one<3, 2, 2, 2, 2, OUT_I32>(g, st);
-    return wide ? launch_one<2, 4, 2, 2, 2, OUT_F16>(g, st) : launch_one<3, 2, 2, 2, 2, OUT_F16>(g, st);
+    const double c[3] = {cost(128, 256, 2, 1.0), cost(192, 128, 2, 0.9), cost(128, 128, 3, 0.8)};
+    const int tile = c[2] < c[0] && c[2] < c[1] ? 2 : c[1] < c[0] ? 1 : 0;
+    return out_kind == OUT_I32 ? launch_tile<OUT_I32>(tile, g, st) : launch_tile<OUT_F16>(tile, g, st);
 }
 
 }  // namespace w4a4
