@@ -315,14 +315,20 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &g, v16i (&acc)[FM]
 // wave's atomics to be acknowledged (vmcnt) before the workgroup barrier that precedes the counter increment.
 // The wait never hangs: after g.spin_limit polls the workgroup raises both fault words and carries on (its
 // codes are then invalid; the host learns of it from w4a4_fused_fault_check or the workspace word).
+// What bounds it is the coherence point, which serves the polls of all waiting workgroups and the siblings' maxima and
+// arrivals in one queue: the last to arrive takes its answer from the arrival itself, and the others ask every 24 x 64
+// cycles.  Against asking at once and then every 64 cycles, us: 32768 x 3072 x 1024 121 -> 108, 32768 x 1024 x 1024 36 -> 32,
+// 12288 x 4096 x 1024 61 -> 51, 32768 x 1024 x 4096 (four siblings, long tiles) 102 -> 101; 16 x 64 and 48 x 64 cycles are
+// within 2 us of it.
 __device__ __forceinline__ void panel_arrive_and_wait(const GemmArgs &g, int panel, int tid) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (tid == 0) {
-        __hip_atomic_fetch_add(g.arrived + panel, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int seen = 1 + __hip_atomic_fetch_add(g.arrived + panel, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int spins = 0;
-        while (__hip_atomic_load(g.arrived + panel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < g.wait_for) {
-            __builtin_amdgcn_s_sleep(1);
+        while (seen < g.wait_for) {
+            __builtin_amdgcn_s_sleep(24);
+            seen = __hip_atomic_load(g.arrived + panel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (++spins > g.spin_limit) {
                 *g.fault = 1;
                 *g.fault_sticky = 1;
