@@ -66,6 +66,35 @@ __device__ __forceinline__ void reduce_scatter32(T (&v)[32], int lane, Op op) {
     reduce_scatter_step<1, 0xB1>(v, lane, op);                    // quad permute [1,0,3,2]
 }
 
+// The same where two neighbouring lanes hold different rows already: v[0..15] are summed over the sixteen lanes of a half
+// wave that agree in bit 0, and lane c ends with entry c / 2 in v[0].  Every exchange keeps lane bit 0: rows swapped in
+// place, row rotations by four and by eight (four first: its carry into bit 3 meets lanes that still hold the same
+// entries), the quad permute of bit 1.
+template <int LANE_BIT, int IDX_BIT, int DONE, int CTRL, typename T, typename Op>
+__device__ __forceinline__ void reduce_scatter_bit(T (&v)[16], int lane, Op op) {
+    const bool up = (lane & LANE_BIT) != 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        if (k & (IDX_BIT | DONE)) continue;
+        const T keep = up ? v[k | IDX_BIT] : v[k];
+        const T send = up ? v[k] : v[k | IDX_BIT];
+        v[k] = op(keep, dpp_fetch<CTRL>(send));
+    }
+}
+template <typename T, typename Op>
+__device__ __forceinline__ void reduce_scatter16(T (&v)[16], int lane, Op op) {
+    static_assert(sizeof(T) == 4, "one register per value");
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v[k]),
+                                                         __builtin_bit_cast(unsigned, v[k + 8]), false, false);
+        v[k] = op(__builtin_bit_cast(T, (unsigned)sw[0]), __builtin_bit_cast(T, (unsigned)sw[1]));
+    }
+    reduce_scatter_bit<4, 2, 0, 0x124>(v, lane, op);              // row rotation by 4
+    reduce_scatter_bit<8, 4, 2, 0x128>(v, lane, op);              // row rotation by 8
+    reduce_scatter_bit<2, 1, 6, 0x4E>(v, lane, op);               // quad permute [2,3,0,1]
+}
+
 // op over the LPR (16, 32 or 64) consecutive lanes that own a row, in all of them: quad permutes, half-row and row mirror
 // inside sixteen lanes, then the row and half-wave exchanges.
 template <int LPR, typename T, typename Op>

@@ -193,16 +193,16 @@ __device__ __forceinline__ void olay_epilogue_requant(const GemmArgs &g, v16i (&
         scratch[(tid & ~63) + lane] = rg.inv;
         __builtin_amdgcn_wave_barrier();
     }
-    // packed rows are N/2 bytes; even lanes store a dword of eight codes, everything else is
-    // sent to an offset the bounds check of the descriptor drops
+    // Packed rows are N/2 bytes.  A lane holds four codes of a row, two neighbouring lanes eight: they exchange the codes
+    // of two rows, so that the even lane stores a whole dword of the first row and the odd lane one of the second.
+    // Rows past M and channels past N go to an offset the bounds check of the descriptor drops.
     const __amdgpu_buffer_rsrc_t q_rsrc = make_rsrc(g.out, (uint32_t)((long)g.M * (g.N / 2)));
     const uint32_t row_b = (uint32_t)g.N / 2;
-    const uint32_t lane_q = ((lane & 1) == 0 && n_ok)
-                                ? (uint32_t)(m0 + row_w + 4 * h) * row_b + (uint32_t)(n_lane >> 1) : kPoison;
+    const uint32_t lane_q = n_ok ? (uint32_t)(m0 + row_w + 4 * h + (lane & 1)) * row_b + (uint32_t)((n_lane & ~7) >> 1) : kPoison;
     constexpr float kMagic = 12582912.0f + 8.0f;                  // 1.5 * 2^23 + 8
-    // even lanes fill the low half of a dword of eight codes, odd lanes the high half
-    const uint32_t half_sel = (lane & 1) ? 0x04000c0cu : 0x0c0c0400u;
-    int osum[32];                                                 // 16 * odd-position sums of (code + 8) per row (MFMA)
+    // bytes of the stored dword: 4..7 the lane's own {row 0, row 1}, 0..3 the neighbour's
+    const uint32_t pair_sel = (lane & 1) ? 0x07060302u : 0x01000504u;
+    int osum[16];                                                 // 16 * odd-position sums of (code + 8) per stored dword (MFMA)
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -210,28 +210,31 @@ __device__ __forceinline__ void olay_epilogue_requant(const GemmArgs &g, v16i (&
             const float4 iv4 = *reinterpret_cast<const float4 *>(scratch + (tid & ~63) + h * 32 + i * 16 + q * 4);
             const float ivv[4] = {iv4.x, iv4.y, iv4.z, iv4.w};
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int r = q * 4 + rr;
-                uint32_t u[FN];
+            for (int rr = 0; rr < 4; rr += 2) {
+                uint32_t part[2];                                 // this lane's codes of rows rr and rr + 1, half a dword each
 #pragma unroll
-                for (int j = 0; j < FN; ++j) {
-                    const float t = __int_as_float(acc[i][j][r]) * ivv[rr];
-                    u[j] = __float_as_uint(t + kMagic);           // low byte = rne(t) + 8, in 1 .. 15
+                for (int d = 0; d < 2; ++d) {
+                    uint32_t u[FN];
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        const float t = __int_as_float(acc[i][j][q * 4 + rr + d]) * ivv[rr + d];
+                        u[j] = __float_as_uint(t + kMagic);       // low byte = rne(t) + 8, in 1 .. 15
+                    }
+                    // two codes per byte (bits above the byte are junk), two bytes into the row's half
+                    const uint32_t p01 = (u[1] << 4) | u[0], p23 = (u[3] << 4) | u[2];
+                    part[d] = __builtin_amdgcn_perm(p23, p01, d ? 0x04000c0cu : 0x0c0c0400u);
                 }
-                // two codes per byte (bits above the byte are junk), then the two bytes into this
-                // lane's half of the dword; the neighbour's half arrives through the quad permute
-                const uint32_t p01 = (u[1] << 4) | u[0], p23 = (u[3] << 4) | u[2];
-                const uint32_t half = __builtin_amdgcn_perm(p23, p01, half_sel);
-                if (MFMA) osum[i * 16 + r] = n_ok ? (int)__builtin_amdgcn_sad_u8(half & 0xF0F0F0F0u, 0u, 0u) : 256;
-                uint32_t packed = half | dpp_fetch<0xB1>(half);
+                const uint32_t own = part[0] | part[1];
+                uint32_t packed = __builtin_amdgcn_perm(own, dpp_fetch<0xB1>(own), pair_sel);
+                if (MFMA) osum[i * 8 + q * 2 + rr / 2] = n_ok ? (int)__builtin_amdgcn_sad_u8(packed & 0xF0F0F0F0u, 0u, 0u) : 512;
                 packed ^= MFMA ? 0x80808080u : 0x88888888u;       // offset binary -> two's complement where wanted
                 __builtin_amdgcn_raw_buffer_store_b32(packed, q_rsrc, lane_q + (uint32_t)(i * 32 + 8 * q + rr) * row_b, 0, 0);
             }
         }
     if (MFMA) {
-        // the same butterfly with sums: lane c ends with the sum over the wave's 128 channels of row c
-        reduce_scatter32(osum, lane, [](int a, int b) { return a + b; });
-        // in units of 1/16; every lane added 16 (two offsets of 8, or the neutral 16 of a lane past N)
+        // lane c ends with the sum over the wave's 128 channels of row c, in units of 1/16; each of the sixteen pairs of
+        // lanes added 4 * 8 (its four offsets, or the neutral 512 / 16 of channels past N)
+        reduce_scatter16(osum, lane, [](int a, int b) { return a + b; });
         if (m_c < g.M) atomicAdd(g.out_osum + (long)m_c * g.osum_slices + slice, (osum[0] >> 4) - 32 * 16);
     }
 }
