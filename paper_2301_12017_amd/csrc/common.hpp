@@ -163,7 +163,8 @@ __device__ __forceinline__ int code_of(float x, const Range &r) {
 struct GeluParts { float relu, t, p; };                          // gelu(x) = relu - t * p
 __device__ __forceinline__ GeluParts gelu_parts(float x) {
     GeluParts g;
-    g.t = fminf(fabsf(x), 6.0f);
+    // one instruction: with the limit as a literal the compiler cannot attach the modifier and takes |x| by itself first
+    asm("v_min_f32 %0, |%1|, %2" : "=v"(g.t) : "v"(x), "s"(6.0f));
     float q = -1.889626219e-06f;
     q = __fmaf_rn(q, g.t, 6.268139987e-05f);
     q = __fmaf_rn(q, g.t, -9.388679173e-04f);
