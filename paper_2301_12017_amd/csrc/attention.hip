@@ -120,6 +120,38 @@ __device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, cons
     }
 }
 
+// Eight output features of one query as the definition reads, in FP32 straight from memory: for a lane whose result holds
+// a NaN.  Infinite keys or values can make one above where the definition has none (a block of keys whose scores are all
+// -inf; a weight below the FP16 range, or the negative half of a split one, times an infinite value).
+__device__ void attend_plain(const _Float16 *base, long ld, int h, int seq, int qi, int feature, float (&x)[4], float (&y)[4]) {
+    const _Float16 *q = base + (qi < seq ? qi : seq - 1) * ld;
+    auto score = [&](int key) {
+        float s = 0.0f;
+#pragma unroll 1
+        for (int c = 0; c < kHead; c += 2)
+            s = __builtin_amdgcn_fdot2(*reinterpret_cast<const half2_t *>(q + c), *reinterpret_cast<const half2_t *>(base + key * ld + h + c), s, false);
+        return s * 0.125f;
+    };
+    float m = -INFINITY, l = 0.0f;
+#pragma unroll 1
+    for (int key = 0; key < seq; ++key) m = fmaxf(m, score(key));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = y[i] = 0.0f;
+#pragma unroll 1
+    for (int key = 0; key < seq; ++key) {
+        const float p = expf(score(key) - m);
+        const _Float16 *v = base + key * ld + 2 * h + feature;
+        l += p;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            x[i] = __builtin_fmaf(p, (float)v[i], x[i]);
+            y[i] = __builtin_fmaf(p, (float)v[8 + i], y[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { x[i] /= l; y[i] /= l; }
+}
+
 // One workgroup of four waves per block of queries of one (sequence, head).  SPLIT == 1: a wave per 32 queries, 128
 // queries, keys and values staged 64 rows at a time and shared by the four.  SPLIT == 4: 32 queries, the waves take a
 // quarter of every 128 staged keys each and add up their parts through LDS: for launches that would leave CUs idle.
@@ -195,7 +227,9 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attention_mfma_kernel(const _
     float l = both_halves(Q.l, [](float x, float y) { return x + y; });
     // Two blocks of four features of a lane and of its partner in the other half make eight consecutive ones each:
     // features 8 blk..+7 for the lower half, 8 (blk + 1)..+7 for the upper one, sixteen bytes per lane.
-    auto store16 = [&](const float (&x)[4], const float (&y)[4], int blk) {
+    auto store16 = [&](float (&x)[4], float (&y)[4], int blk) {
+        const float any = ((x[0] + x[1]) + (x[2] + x[3])) + ((y[0] + y[1]) + (y[2] + y[3]));
+        if (any != any) attend_plain(base, ld, h, seq, qi, 8 * blk + 4 * hl, x, y);
         const uint32_t x0 = pack_halves(x[0], x[1]), x1 = pack_halves(x[2], x[3]);
         const uint32_t y0 = pack_halves(y[0], y[1]), y1 = pack_halves(y[2], y[3]);
         const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);

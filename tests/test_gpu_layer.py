@@ -43,6 +43,30 @@ def test_attention_at_the_edges_of_its_tiles(B, orc, batch, heads, seq):
         assert np.all(np.abs(got[b, :, h] - want) <= bound)
 
 
+@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])
+def test_attention_with_infinite_keys_and_values(B, batch, heads):
+    """Keys at -inf score (weight 0, a whole block of them first), an infinite value, a NaN: finite, infinite and NaN where
+    the definition is."""
+    seq, rng = 150, np.random.default_rng(8)
+    x = rng.standard_normal((batch, seq, 3, heads, 64)).astype(np.float16)
+    x[:, :, 0] = np.abs(x[:, :, 0]) + np.float16(0.01)            # queries > 0: a key of -inf scores -inf
+    x[0, :40, 1, 0, 5] = -np.inf
+    x[0, 60, 2, 1, 7] = np.inf
+    x[0, 61, 2, 1, 8] = -np.inf
+    x[0, 70, 2, 2, 9] = np.nan
+    got = host(B.attention(dev(x.reshape(batch * seq, -1)), batch, seq, heads)).reshape(batch, seq, heads, 64)
+    for head in range(3):
+        q, k, v = (x[0, :, i, head].astype(np.float64) for i in range(3))
+        s = q @ k.T / 8
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        want = (p[:, :, None] * v).sum(axis=1) / p.sum(axis=1, keepdims=True)
+        # one rounding to fp16; 150 fp32 terms of at most max|v| each (2^-24)
+        bound = 2.0 ** -11 * np.abs(want) + (seq + 64) * 2.0 ** -24 * np.abs(v[np.isfinite(v)]).max()
+        with np.errstate(invalid="ignore"):
+            near = np.isfinite(want) & (np.abs(got[0, :, head] - want) <= bound)
+        assert np.all(near | (got[0, :, head] == want) | (np.isnan(want) & np.isnan(got[0, :, head])))
+
+
 def test_attention_of_peaked_scores_does_not_overflow(B, orc):
     batch, seq, heads = 1, 64, 2
     rng = np.random.default_rng(3)
