@@ -454,7 +454,7 @@ extern "C" int w4a4_debug_fused_wait(int spin_limit, int extra_arrivals) {
     tl_extra_arrivals = extra_arrivals;
     return W4A4_OK;
 }
-constexpr int kSpinLimit = 1 << 20;                            // of about 1 us each
+constexpr int kSpinLimit = 1 << 21;                            // of about 1.3 us each: some 2.7 s before a wait is given up
 
 extern "C" int w4a4_pick_schedule(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep) {
     int ng = 0;
