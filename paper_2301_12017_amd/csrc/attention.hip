@@ -34,11 +34,6 @@ constexpr int kAttnThreads = 256;
 constexpr int kRowHalves = 72;        // LDS pitch of a key / value row: 144 bytes, rows start in different banks
 constexpr float kScoreScale = 0.125f * 1.44269504f;   // 1 / sqrt(64), base 2
 
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
 __device__ __forceinline__ uint32_t pack_halves(float a, float b) {      // round to nearest even
     const float2_t v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, half2_t));
@@ -72,14 +67,15 @@ __device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, cons
         for (int i = 0; i < 16; ++i)
             if (8 * (i / 4) + 4 * hl + i % 4 >= valid) s[i] = -INFINITY;
     }
-    float mx = max3(s[0], s[1], s[2]);
+    // (v_max3_f32, but by the compiler: it does not see what inline assembly reads and would leave out the wait states that
+    // a read of a matrix instruction's result needs)
+    float mx = Q.m;
 #pragma unroll
-    for (int i = 3; i < 15; i += 2) mx = max3(mx, s[i], s[i + 1]);
-    mx = both_halves(fmaxf(mx, s[15]), [](float x, float y) { return fmaxf(x, y); });
+    for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(mx, s[i]), s[i + 1]);
+    mx = both_halves(mx, [](float x, float y) { return fmaxf(x, y); });
     if (__any(mx > Q.m)) {            // wave-uniform, seldom taken after the first blocks
-        const float m = fmaxf(Q.m, mx);
-        const float a = __builtin_amdgcn_exp2f((Q.m - m) * kScoreScale);
-        Q.m = m;
+        const float a = __builtin_amdgcn_exp2f((Q.m - mx) * kScoreScale);
+        Q.m = mx;
         Q.l *= a;
 #pragma unroll
         for (int f = 0; f < 2; ++f)
