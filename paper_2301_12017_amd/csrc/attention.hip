@@ -21,7 +21,6 @@
 namespace w4a4 {
 namespace {
 
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
@@ -74,7 +73,7 @@ __device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, cons
     for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(mx, s[i]), s[i + 1]);
     mx = both_halves(mx, [](float x, float y) { return fmaxf(x, y); });
     if (__any(mx > Q.m)) {            // wave-uniform, seldom taken after the first blocks
-        const float a = __builtin_amdgcn_exp2f((Q.m - mx) * kScoreScale);
+        const float a = Q.m > -INFINITY ? __builtin_amdgcn_exp2f((Q.m - mx) * kScoreScale) : 0.0f;
         Q.m = mx;
         Q.l *= a;
 #pragma unroll
@@ -82,7 +81,7 @@ __device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, cons
 #pragma unroll
             for (int i = 0; i < 16; ++i) Q.o[f][i] *= a;
     }
-    const float shift = -Q.m * kScoreScale;
+    const float shift = Q.m > -INFINITY ? -Q.m * kScoreScale : 0.0f;   // (keys of score -inf alone: weights 0)
     uint32_t hi[8], lo[8];
     float sum = 0.0f;
 #pragma unroll
@@ -116,43 +115,56 @@ __device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, cons
     }
 }
 
-// Eight output features of one query as the definition reads, in FP32 straight from memory: for a lane whose result holds
-// a NaN.  Infinite keys or values can make one above where the definition has none (a block of keys whose scores are all
-// -inf; a weight below the FP16 range, or the negative half of a split one, times an infinite value).
-__device__ void attend_plain(const _Float16 *base, long ld, int h, int seq, int qi, int feature, float (&x)[4], float (&y)[4]) {
-    const _Float16 *q = base + (qi < seq ? qi : seq - 1) * ld;
-    auto score = [&](int key) {
-        float s = 0.0f;
+// Results that hold a NaN although the row's sum of weights does not: a value among V is infinite or NaN, and a split weight
+// gives NaN where the definition need not (a half of it is negative or zero).  What the definition has in such a feature is
+// decided by those values alone: the sum of weight * value over them, with the weights in FP32.  Each key that has one among the
+// sixteen features 8 blk .. 8 blk + 15 of the wave's two halves is scored again, by the whole wave.  16 x 512 tokens, 12 heads,
+// 33 us: 37 us with a NaN, 39 us with an infinity among each head's values, 1.1 ms with nothing but infinities.
+__device__ void special_values(const _Float16 *base, long ld, int h, int seq, int lane, const half8_t (&q)[4], float m, float l, int blk,
+                               float (&x)[4], float (&y)[4]) {
+    const int hl = lane >> 5;
+    const _Float16 *k = base + h, *v = base + 2 * h + 8 * blk;
+    float sx[4] = {}, sy[4] = {};
+    auto special = [](_Float16 f) { return (__builtin_bit_cast(unsigned short, f) & 0x7C00) == 0x7C00; };
 #pragma unroll 1
-        for (int c = 0; c < kHead; c += 2)
-            s = __builtin_amdgcn_fdot2(*reinterpret_cast<const half2_t *>(q + c), *reinterpret_cast<const half2_t *>(base + key * ld + h + c), s, false);
-        return s * 0.125f;
-    };
-    float m = -INFINITY, l = 0.0f;
-#pragma unroll 1
-    for (int key = 0; key < seq; ++key) m = fmaxf(m, score(key));
+    for (int k0 = 0; k0 < seq; k0 += kWave) {
+        bool found = false;
+        if (k0 + lane < seq) {
+            const half8_t a = *reinterpret_cast<const half8_t *>(v + (k0 + lane) * ld), b = *reinterpret_cast<const half8_t *>(v + (k0 + lane) * ld + 8);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = y[i] = 0.0f;
+            for (int i = 0; i < 8; ++i) found |= special(a[i]) || special(b[i]);
+        }
 #pragma unroll 1
-    for (int key = 0; key < seq; ++key) {
-        const float p = expf(score(key) - m);
-        const _Float16 *v = base + key * ld + 2 * h + feature;
-        l += p;
+        for (unsigned long long todo = __ballot(found); todo; todo &= todo - 1) {
+            const int key = k0 + __builtin_ctzll(todo);
+            float s = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            x[i] = __builtin_fmaf(p, (float)v[i], x[i]);
-            y[i] = __builtin_fmaf(p, (float)v[8 + i], y[i]);
+            for (int t = 0; t < 4; ++t) {
+                const half8_t kt = *reinterpret_cast<const half8_t *>(k + key * ld + 16 * t + 8 * hl);
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) s = __builtin_amdgcn_fdot2(half2_t{q[t][i], q[t][i + 1]}, half2_t{kt[i], kt[i + 1]}, s, false);
+            }
+            const float p = expf((both_halves(s, [](float x, float y) { return x + y; }) - m) * 0.125f);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const _Float16 vx = v[key * ld + 4 * hl + i], vy = v[key * ld + 8 + 4 * hl + i];
+                if (special(vx)) sx[i] = __builtin_fmaf(p, (float)vx, sx[i]);
+                if (special(vy)) sy[i] = __builtin_fmaf(p, (float)vy, sy[i]);
+            }
         }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { x[i] /= l; y[i] /= l; }
+    for (int i = 0; i < 4; ++i) {
+        if (l > 0.0f && sx[i] != 0.0f) x[i] = sx[i];
+        if (l > 0.0f && sy[i] != 0.0f) y[i] = sy[i];
+    }
 }
 
 // One workgroup of four waves per block of queries of one (sequence, head).  SPLIT == 1: a wave per 32 queries, 128
 // queries, keys and values staged 64 rows at a time and shared by the four.  SPLIT == 4: 32 queries, the waves take a
 // quarter of every 128 staged keys each and add up their parts through LDS: for launches that would leave CUs idle.
 template <int SPLIT>
-__global__ __launch_bounds__(kAttnThreads, 3) void attention_mfma_kernel(const __half *qkv, __half *ctx, int seq, int heads,
+__global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mfma_kernel(const __half *qkv, __half *ctx, int seq, int heads,
                                                                       int pairs, int qblocks) {
     constexpr int TILE = SPLIT == 4 ? 128 : 64, CH = TILE / 32;
     extern __shared__ __attribute__((aligned(16))) _Float16 smem[];           // [buffers][keys, values][TILE][kRowHalves]
@@ -223,9 +235,10 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attention_mfma_kernel(const _
     float l = both_halves(Q.l, [](float x, float y) { return x + y; });
     // Two blocks of four features of a lane and of its partner in the other half make eight consecutive ones each:
     // features 8 blk..+7 for the lower half, 8 (blk + 1)..+7 for the upper one, sixteen bytes per lane.
-    auto store16 = [&](float (&x)[4], float (&y)[4], int blk) {
+    auto store16 = [&](float (&x)[4], float (&y)[4], float l, float m, int blk) {
         const float any = ((x[0] + x[1]) + (x[2] + x[3])) + ((y[0] + y[1]) + (y[2] + y[3]));
-        if (any != any) attend_plain(base, ld, h, seq, qi, 8 * blk + 4 * hl, x, y);
+        // (a sum of weights that is NaN or 0 means a NaN in the definition: a score that is NaN or +inf, or only -inf ones)
+        if (__any(any != any && l > 0.0f)) special_values(base, ld, h, seq, lane, Q.q, m, l, blk, x, y);
         const uint32_t x0 = pack_halves(x[0], x[1]), x1 = pack_halves(x[2], x[3]);
         const uint32_t y0 = pack_halves(y[0], y[1]), y1 = pack_halves(y[2], y[3]);
         const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
@@ -242,7 +255,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attention_mfma_kernel(const _
                 float x[4], y[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { x[i] = Q.o[f][4 * g + i] * inv; y[i] = Q.o[f][4 * g + 4 + i] * inv; }
-                store16(x, y, 4 * f + g);
+                store16(x, y, l, Q.m, 4 * f + g);
             }
         return;
     }
@@ -255,7 +268,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attention_mfma_kernel(const _
     float m = ml[lane & 31];
 #pragma unroll
     for (int w = 1; w < 4; ++w) m = fmaxf(m, ml[w * 32 + (lane & 31)]);
-    const float a = __builtin_amdgcn_exp2f((Q.m - m) * kScoreScale);          // 0 for a wave without keys
+    const float a = Q.m > -INFINITY ? __builtin_amdgcn_exp2f((Q.m - m) * kScoreScale) : 0.0f;   // 0 for a wave without keys
     if (hl == 0) ml[128 + wave * 32 + lane] = l * a;
 #pragma unroll
     for (int f = 0; f < 2; ++f)
@@ -278,7 +291,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attention_mfma_kernel(const _
         x[i] = u * inv;
         y[i] = v * inv;
     }
-    store16(x, y, 2 * wave);
+    store16(x, y, l, m, 2 * wave);
 }
 
 constexpr size_t tile_bytes(int tile) { return (size_t)2 * tile * kRowHalves * sizeof(_Float16); }
