@@ -25,6 +25,7 @@ typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef short short4_t __attribute__((__vector_size__(8)));
 typedef __attribute__((address_space(3))) short4_t lds_short4;
 
@@ -45,11 +46,29 @@ __device__ __forceinline__ float both_halves(float x, Op op) {
     return op(__builtin_bit_cast(float, (unsigned)sw[0]), __builtin_bit_cast(float, (unsigned)sw[1]));
 }
 
+// The weight of a key with raw score s is exp2(s * kScoreScale + shift), one FMA, in a row whose largest raw score is m.  The
+// shift is a rounded number, but the same one for every weight and for the sum of them, so that its rounding cancels.  That
+// ends where it moves the largest weight itself (a quarter of a power of two at 2^22, 32 of them at 2^29): there, and for
+// infinite m, the scores are taken relative to m first (`far`).
+__device__ __forceinline__ float weight_shift(float m) { return -m * kScoreScale; }
+__device__ __forceinline__ bool far(float shift) { return !(fabsf(shift) < 4194304.0f); }
+// what turns weights of a row with maximum m0 into those of maximum m (nothing has been summed yet while m0 is -inf)
+__device__ __forceinline__ float weight_ratio(float m0, float m) {
+    const float s0 = weight_shift(m0), s = weight_shift(m);
+    const float e = far(s0) || far(s) ? (m0 - m) * kScoreScale : s - s0;
+    return m0 > -INFINITY ? __builtin_amdgcn_exp2f(e) : 0.0f;
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const _Float16 *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16 *>(p), (short)0, (int)bytes, 0x00020000);
+}
+
 // State of a wave's 32 queries: lane l belongs to query l % 32 and holds features 32 f + 8 (i / 4) + 4 (l / 32) + i % 4.
 struct QueryBlock {
     half8_t q[4];                     // B operands: features 16 s + 8 (l / 32) ..+7 of the lane's query
     float16_t o[2];
     float m, l;                       // running maximum of the raw scores; the lane's half of the sum
+    float shift, settled;             // of its weights; maximum of a block up to which neither changes (far rows: none)
 };
 
 // One block of 32 keys: rows 0..31 of the LDS tiles ks / vs, of which the first `valid` are keys.
@@ -72,22 +91,28 @@ __device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, cons
 #pragma unroll
     for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(mx, s[i]), s[i + 1]);
     mx = both_halves(mx, [](float x, float y) { return fmaxf(x, y); });
-    if (__any(mx > Q.m)) {            // wave-uniform, seldom taken after the first blocks
-        const float a = Q.m > -INFINITY ? __builtin_amdgcn_exp2f((Q.m - mx) * kScoreScale) : 0.0f;
-        Q.m = mx;
+    if (__any(mx > Q.settled)) {      // wave-uniform, seldom taken after the first blocks
+        const float a = weight_ratio(Q.m, mx);
+        Q.m = Q.settled = mx;
+        Q.shift = mx > -INFINITY ? weight_shift(mx) : 0.0f;        // (keys of score -inf alone: weights 0)
         Q.l *= a;
 #pragma unroll
         for (int f = 0; f < 2; ++f)
 #pragma unroll
             for (int i = 0; i < 16; ++i) Q.o[f][i] *= a;
+        if (__builtin_expect(__any(far(Q.shift)), 0) && far(Q.shift)) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] -= mx;
+            Q.shift = weight_shift(0.0f);
+            Q.settled = -INFINITY;
+        }
     }
-    const float shift = Q.m > -INFINITY ? -Q.m * kScoreScale : 0.0f;   // (keys of score -inf alone: weights 0)
     uint32_t hi[8], lo[8];
     float sum = 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i], kScoreScale, shift));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i + 1], kScoreScale, shift));
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i], kScoreScale, Q.shift));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i + 1], kScoreScale, Q.shift));
         sum += p0 + p1;
         hi[i] = pack_halves(p0, p1);
         float r0, r1;                 // p - hi, exact
@@ -178,16 +203,27 @@ __global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mf
     const int q0 = SPLIT == 4 ? qb * 32 : qb * 128 + wave * 32;
     const int qi = q0 + (lane & 31);
 
-    uint4 kreg[CH], vreg[CH];
+    // 32-bit offsets from uniform bases keep SPLIT == 1 within the 128 registers of four waves per SIMD (384 x 32 tokens 13.8 us,
+    // 15.1 with addresses); its descriptors end with the sequence, SPLIT == 4 asks (1 x 32 tokens 3.7 us, 3.85 with descriptors).
+    // Rows behind the sequence are zero in both.
+    u32x4 kreg[CH], vreg[CH];
     const int srow = tid >> 3, scol = (tid & 7) * 8;
+    const uint32_t ld_bytes = (uint32_t)ld * 2, bytes = (uint32_t)(seq - 1) * ld_bytes + kHead * 2, off0 = srow * ld_bytes + scol * 2;
+    const __amdgpu_buffer_rsrc_t k_rsrc = rows_rsrc(base + h, bytes), v_rsrc = rows_rsrc(base + 2 * h, bytes);
     auto fetch = [&](int tile) {
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
-            const int r = tile * TILE + srow + 32 * j;
-            kreg[j] = vreg[j] = uint4{0, 0, 0, 0};
-            if (r < seq) {
-                kreg[j] = *reinterpret_cast<const uint4 *>(base + r * ld + h + scol);
-                vreg[j] = *reinterpret_cast<const uint4 *>(base + r * ld + 2 * h + scol);
+            const int r = tile * TILE + 32 * j;
+            if constexpr (SPLIT == 1) {
+                kreg[j] = __builtin_amdgcn_raw_buffer_load_b128(k_rsrc, off0 + r * ld_bytes, 0, 0);
+                vreg[j] = __builtin_amdgcn_raw_buffer_load_b128(v_rsrc, off0 + r * ld_bytes, 0, 0);
+            } else {
+                const char *kb = reinterpret_cast<const char *>(base + h), *vb = reinterpret_cast<const char *>(base + 2 * h);
+                kreg[j] = vreg[j] = u32x4{0, 0, 0, 0};
+                if (r + srow < seq) {
+                    kreg[j] = *reinterpret_cast<const u32x4 *>(kb + (off0 + r * ld_bytes));
+                    vreg[j] = *reinterpret_cast<const u32x4 *>(vb + (off0 + r * ld_bytes));
+                }
             }
         }
     };
@@ -195,8 +231,8 @@ __global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mf
         _Float16 *d = smem + buf * 2 * TILE * kRowHalves + srow * kRowHalves + scol;
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
-            *reinterpret_cast<uint4 *>(d + 32 * j * kRowHalves) = kreg[j];
-            *reinterpret_cast<uint4 *>(d + (TILE + 32 * j) * kRowHalves) = vreg[j];
+            *reinterpret_cast<u32x4 *>(d + 32 * j * kRowHalves) = kreg[j];
+            *reinterpret_cast<u32x4 *>(d + (TILE + 32 * j) * kRowHalves) = vreg[j];
         }
     };
 
@@ -210,7 +246,8 @@ __global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mf
     Q.o[0] = float16_t{};
     Q.o[1] = float16_t{};
     Q.m = -INFINITY;
-    Q.l = 0.0f;
+    Q.settled = -INFINITY;
+    Q.l = Q.shift = 0.0f;
     put(0);
     const int tiles = (seq + TILE - 1) / TILE;
     if (tiles > 1) fetch(1);
@@ -238,7 +275,7 @@ __global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mf
     auto store16 = [&](float (&x)[4], float (&y)[4], float l, float m, int blk) {
         const float any = ((x[0] + x[1]) + (x[2] + x[3])) + ((y[0] + y[1]) + (y[2] + y[3]));
         // (a sum of weights that is NaN or 0 means a NaN in the definition: a score that is NaN or +inf, or only -inf ones)
-        if (__any(any != any && l > 0.0f)) special_values(base, ld, h, seq, lane, Q.q, m, l, blk, x, y);
+        if (__builtin_expect(__any(any != any && l > 0.0f), 0)) special_values(base, ld, h, seq, lane, Q.q, m, l, blk, x, y);
         const uint32_t x0 = pack_halves(x[0], x[1]), x1 = pack_halves(x[2], x[3]);
         const uint32_t y0 = pack_halves(y[0], y[1]), y1 = pack_halves(y[2], y[3]);
         const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
@@ -268,7 +305,7 @@ __global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mf
     float m = ml[lane & 31];
 #pragma unroll
     for (int w = 1; w < 4; ++w) m = fmaxf(m, ml[w * 32 + (lane & 31)]);
-    const float a = Q.m > -INFINITY ? __builtin_amdgcn_exp2f((Q.m - m) * kScoreScale) : 0.0f;   // 0 for a wave without keys
+    const float a = weight_ratio(Q.m, m);                                     // 0 for a wave without keys
     if (hl == 0) ml[128 + wave * 32 + lane] = l * a;
 #pragma unroll
     for (int f = 0; f < 2; ++f)

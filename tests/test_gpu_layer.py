@@ -67,6 +67,33 @@ def test_attention_with_infinite_keys_and_values(B, batch, heads):
         assert np.all(near | (got[0, :, head] == want) | (np.isnan(want) & np.isnan(got[0, :, head])))
 
 
+@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries; a wave per block
+@pytest.mark.parametrize("order", ["up", "down", "mixed"])
+@pytest.mark.parametrize("query,key", [(100, 1000), (3000, 5000), (4400, 5000), (4700, 5000), (-4700, 5000), (10000, 10000), (12000, 12000),
+                                       (16000, 16000), (20000, 20000), (-20000, 20000), (60000, 60000)])
+def test_attention_of_large_finite_scores(B, batch, heads, query, key, order):
+    """q.k = query * key + step * j, exact in FP32, up to 3.6e9 (and below zero): softmax of the differences, although the scores
+    times a constant are not exact (from 2.3e7 on a rounded one is off by a quarter and more, by 32 at 3e9)."""
+    seq, rng = 150, np.random.default_rng(abs(query) + key)
+    step = max(8, int(2 * np.spacing(np.float32(abs(query) * key))))
+    j = rng.integers(0, 6, seq)
+    j = {"up": np.sort(j), "down": np.sort(j)[::-1], "mixed": j}[order]
+    x = rng.standard_normal((batch, seq, 3, heads, 64)).astype(np.float16)
+    x[:, :, :2] = 0
+    x[:, :, 0, :, 5], x[:, :, 1, :, 5] = query, key
+    x[:, :, 0, :, 60], x[:, :, 1, :, 60] = step, j[None, :, None]
+    x[0, 40:, 1, 0, 5] = -key / 2                                 # one head whose scores cross zero, and the limit
+    got = host(B.attention(dev(x.reshape(batch * seq, -1)), batch, seq, heads)).reshape(batch, seq, heads, 64).astype(np.float64)
+    for b, h in ((0, 0), (0, 1), (batch - 1, heads - 1)):
+        q, k, v = (x[b, :, i, h].astype(np.float64) for i in range(3))
+        s = q @ k.T / 8
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        want = p @ v / p.sum(axis=1, keepdims=True)
+        # one rounding to fp16; exponents of at most 5 * step / 8 to one part in 2^23, `seq` terms of at most max|v|
+        bound = 2.0 ** -11 * np.abs(want) + (seq + 64) * 2.0 ** -24 * np.abs(v).max()
+        assert np.all(np.abs(got[b, :, h] - want) <= bound), np.max(np.abs(got[b, :, h] - want))
+
+
 @pytest.mark.parametrize("batch,heads,seq", [(1, 3, 150), (1, 2, 20), (17, 12, 150), (60, 12, 40)])
 def test_attention_with_infinite_values_of_small_weight(B, batch, heads, seq):
     """Infinite values count where their weight is far below an FP16 number (e^-30) but not zero in FP32, make a NaN where it is
