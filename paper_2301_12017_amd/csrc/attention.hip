@@ -9,8 +9,10 @@
 // first one leaves them in (eight per half: 0..3 and 8..11, or 4..7 and 12..15 of every sixteen); V
 // is read from LDS in the same order with the transposing load.
 //
-// The weights stay at FP32 accuracy: p = hi + lo, two FP16 numbers (22 bits; the matrix instruction
-// takes subnormal halves), so the second product costs two matrix instructions per operand of V.
+// A weight is the sum of two FP16 numbers, p = hi + lo (the matrix instruction takes subnormal ones), so the second
+// product costs two matrix instructions per operand of V.  They hold 2^15 p, p <= 1: 22 bits down to weights of 2^-29, and
+// no worse than 2^-41 below, where p itself would lose 2^-26.  Weights of e^-18 keep the digits that an FP16 result can show,
+// as it does where the largest weight meets a value of zero.
 //
 // Bound by the vector ALU between the products (per score: scale, v_exp at a quarter of the rate, sum,
 // split into two halves), not by memory: 24 x 512 tokens, 16 heads: 55 us, where the kernel it replaced
@@ -33,10 +35,21 @@ constexpr int kHead = 64;             // features per head
 constexpr int kAttnThreads = 256;
 constexpr int kRowHalves = 72;        // LDS pitch of a key / value row: 144 bytes, rows start in different banks
 constexpr float kScoreScale = 0.125f * 1.44269504f;   // 1 / sqrt(64), base 2
+constexpr float kWeightScale = 32768.0f;              // of the largest weight, 1, where weights are split in two halves
 
 __device__ __forceinline__ uint32_t pack_halves(float a, float b) {      // round to nearest even
     const float2_t v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, half2_t));
+}
+
+// Two weights as two pairs of halves: p = hi + lo.  (v_fma_mixlo / mixhi would round both halves in two instructions each and need
+// no multiply, but are slower: 24 x 512 tokens 55 us, 53 so.)
+__device__ __forceinline__ void split(float p0, float p1, uint32_t &hi, uint32_t &lo) {
+    hi = pack_halves(p0, p1);
+    float r0, r1;                     // p - hi, exact
+    asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hi), "v"(p0));
+    asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hi), "v"(p1));
+    lo = pack_halves(r0, r1);
 }
 
 // op over the two lanes l, l + 32 of a wave, in both of them
@@ -83,7 +96,7 @@ __device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, cons
     if (valid < 32) {                 // wave-uniform: the last block of a sequence
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            if (8 * (i / 4) + 4 * hl + i % 4 >= valid) s[i] = -INFINITY;
+            if (8 * (i / 4) + i % 4 >= valid - 4 * hl) s[i] = -INFINITY;
     }
     // (v_max3_f32, but by the compiler: it does not see what inline assembly reads and would leave out the wait states that
     // a read of a matrix instruction's result needs)
@@ -114,11 +127,7 @@ __device__ __forceinline__ void attend32(QueryBlock &Q, const _Float16 *ks, cons
         const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i], kScoreScale, Q.shift));
         const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i + 1], kScoreScale, Q.shift));
         sum += p0 + p1;
-        hi[i] = pack_halves(p0, p1);
-        float r0, r1;                 // p - hi, exact
-        asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hi[i]), "v"(p0));
-        asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hi[i]), "v"(p1));
-        lo[i] = pack_halves(r0, r1);
+        split(p0 * kWeightScale, p1 * kWeightScale, hi[i], lo[i]);
     }
     Q.l += sum;
     // the lane's address in a transposing load: row (lane % 16) / 4 of four, columns 4 (lane % 4) of sixteen
@@ -284,7 +293,7 @@ __global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mf
     };
     if (SPLIT == 1) {
         if (q0 >= seq) return;
-        const float inv = 1.0f / l;
+        const float inv = 1.0f / (l * kWeightScale);
 #pragma unroll
         for (int f = 0; f < 2; ++f)
 #pragma unroll
@@ -315,7 +324,7 @@ __global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mf
     l = 0.0f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) l += ml[128 + w * 32 + (lane & 31)];
-    const float inv = 1.0f / l;
+    const float inv = 1.0f / (l * kWeightScale);
     float x[4], y[4];                                                         // wave w finishes registers 8 w .. 8 w + 7
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

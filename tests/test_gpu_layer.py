@@ -94,6 +94,29 @@ def test_attention_of_large_finite_scores(B, batch, heads, query, key, order):
         assert np.all(np.abs(got[b, :, h] - want) <= bound), np.max(np.abs(got[b, :, h] - want))
 
 
+@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries; a wave per block
+@pytest.mark.parametrize("depth", [2, 6, 9, 11, 14, 17])
+@pytest.mark.parametrize("where", [0, 70, 149])
+def test_attention_of_small_weights(B, batch, heads, depth, where):
+    """The largest weight of a row meets a value of zero, so that the result consists of weights around e^-depth alone."""
+    seq, rng = 150, np.random.default_rng(depth)
+    x = rng.standard_normal((batch, seq, 3, heads, 64)).astype(np.float16)
+    x[:, :, :2] = 0
+    x[:, :, 0, :, 5], x[:, :, 1, :, 5] = 8, np.float16(rng.uniform(-0.5, 0.5, seq))[None, :, None]
+    x[:, :, 2] = rng.uniform(0.5, 1, (batch, seq, heads, 64)) * min(60000, 2.0 ** -10 * np.exp(depth))
+    x[:, where, 1, :, 5], x[:, where, 2] = depth, 0
+    got = host(B.attention(dev(x.reshape(batch * seq, -1)), batch, seq, heads)).reshape(batch, seq, heads, 64).astype(np.float64)
+    for b, h in ((0, 0), (batch - 1, heads - 1)):
+        q, k, v = (x[b, :, i, h].astype(np.float64) for i in range(3))
+        s = q @ k.T / 8
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        want = p @ v / p.sum(axis=1, keepdims=True)
+        assert np.all(want > 2.0 ** -14)
+        # relative: one rounding to fp16; weights of at least e^-(depth + 0.5) to 2^-41 (2^-15.8 of them at depth 17, their sum to less)
+        # and, with exponents of at most 25 to one part in 2^24, to 2^-19
+        assert np.all(np.abs(got[b, :, h] - want) <= want * (2.0 ** -11 + 2.0 ** -15))
+
+
 @pytest.mark.parametrize("batch,heads,seq", [(1, 3, 150), (1, 2, 20), (17, 12, 150), (60, 12, 40)])
 def test_attention_with_infinite_values_of_small_weight(B, batch, heads, seq):
     """Infinite values count where their weight is far below an FP16 number (e^-30) but not zero in FP32, make a NaN where it is
