@@ -371,6 +371,9 @@ extern "C" int w4a4_attention_f16(const void *QKV_f16, int batch, int seq, int h
     // 128 queries per workgroup share each staged tile; below 192 such workgroups most CUs idle and 32 queries per
     // workgroup, keys split over its waves, are faster.  us at 128 | 32 queries, twelve heads: 1 x 128 tokens (12 workgroups
     // of 128) 5.5 | 3.9, 5 x 93 (60) 5.1 | 4.1, 16 x 128 (192) 6.3 | 6.9, 4 x 512 (192) 16.1 | 15.1, 64 x 128 (768) 13.9 | 19.3.
-    if ((long)batch * heads * ((seq + 127) / 128) >= 192) return launch_attention<1>(QKV_f16, ctx_f16, batch, seq, heads, as_stream(stream));
+    // With one block of keys there is nothing to split, and the combination of the waves' parts is left out: 1 x 8 tokens
+    // 3.3 | 3.8, 1 x 32 3.2 | 3.7, 15 x 32 3.3 | 3.8; with two, 1 x 33 4.0 | 3.9, 1 x 64 3.9 | 3.8.
+    if (seq <= 32 || (long)batch * heads * ((seq + 127) / 128) >= 192)
+        return launch_attention<1>(QKV_f16, ctx_f16, batch, seq, heads, as_stream(stream));
     return launch_attention<4>(QKV_f16, ctx_f16, batch, seq, heads, as_stream(stream));
 }
