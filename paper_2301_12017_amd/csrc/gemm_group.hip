@@ -302,6 +302,7 @@ void gemm_group_kernel(GemmArgs g) {
             for (int j = 0; j < FN; ++j) four[j] = __builtin_amdgcn_raw_buffer_load_b128(sw_rsrc, (n_lane + j) * g.ng * 4, grp0 * 4, 0);
         };
         constexpr bool QUADS = SPG1 && OUT != OUT_I32;
+        constexpr int kFinal = -2;
         if constexpr (QUADS) request_quad(0, quad);
         else request_scales(0, swn);
         int wog[FN] = {0, 0};                                   // OLAY, int32 export: its odd-position code sums
@@ -310,10 +311,11 @@ void gemm_group_kernel(GemmArgs g) {
         // flags: a K step is then one straight block of code, and the slot order written here is the issue order.
         // (With a run-time "first of group" branch the compiler sank the widening of the next step's first operands
         // out of the last MFMA slots to the common head of the two branches, where it ran with the matrix pipe idle.)
-        // Q: place in a quad of groups whose scales are in `quad`, or -1.
+        // Q: place in a quad of groups whose scales are in `quad`, -1 outside of quads, kFinal in the tile's last group, behind
+        // which nothing is requested: the count of what may be in flight at the barrier is the count of requests that are there.
         auto k_step = [&](auto fog_tag, auto last_tag, auto q_tag, int kt) {
             constexpr int Q = decltype(q_tag)::value;
-            constexpr int BEHIND = (MODE == W4A4_ASYM ? 1 : 0) + (OUT == OUT_I32 || Q > 0 ? 0 : FN);   // requests behind the tile DMAs of a group's first step
+            constexpr int BEHIND = (MODE == W4A4_ASYM ? 1 : 0) + (OUT == OUT_I32 || Q > 0 || Q == kFinal ? 0 : FN);   // requests behind the tile DMAs of a group's first step
             constexpr bool FOG = decltype(fog_tag)::value;     // first K step of a weight group
             constexpr bool LAST = decltype(last_tag)::value;   // last K step of the tile
             const int nxt = cur == NS - 1 ? 0 : cur + 1;       // stage of stream step +1
@@ -346,7 +348,7 @@ void gemm_group_kernel(GemmArgs g) {
                     if constexpr (FOG) dma_table(m0, n0, grp);
                     if constexpr (LAST) dma_tokens(m0n, parity ^ 1);
                     if constexpr (FOG && OUT != OUT_I32 && Q == 0) request_quad(grp + 4, quad_n);
-                    if constexpr (FOG && OUT != OUT_I32 && Q < 0) request_scales(min(grp + 1, g.ng - 1), swn);
+                    if constexpr (FOG && OUT != OUT_I32 && Q == -1) request_scales(grp + 1, swn);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -434,6 +436,7 @@ void gemm_group_kernel(GemmArgs g) {
             const std::true_type yes{};
             const std::false_type no{};
             const std::integral_constant<int, -1> single{};
+            const std::integral_constant<int, kFinal> final_group{};
             int kt = 0;
             if constexpr (SPG1) {                               // every K step is a group
                 if constexpr (QUADS) {
@@ -453,16 +456,16 @@ void gemm_group_kernel(GemmArgs g) {
                     for (int j = 0; j < FN; ++j) swn[j] = __uint_as_float(quad[j][0]);
                 }
                 for (; kt < KT - 1; ++kt) { k_step(yes, no, single, kt); fold_group(no); }
-                k_step(yes, yes, single, kt);
+                k_step(yes, yes, final_group, kt);
             } else {
                 for (int gi = 0; gi < g.ng - 1; ++gi) {
                     k_step(yes, no, single, kt++);
                     for (int st = 1; st < spg; ++st) k_step(no, no, single, kt++);
                     fold_group(no);
                 }
-                k_step(yes, no, single, kt++);
-                for (int st = 1; st < spg - 1; ++st) k_step(no, no, single, kt++);
-                k_step(no, yes, single, kt);
+                k_step(yes, no, final_group, kt++);
+                for (int st = 1; st < spg - 1; ++st) k_step(no, no, final_group, kt++);
+                k_step(no, yes, final_group, kt);
             }
             fold_group(yes);
         }

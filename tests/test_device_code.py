@@ -81,6 +81,53 @@ def test_inline_assembly_reads_no_matrix_result_too_early(assembly):
     assert sum("v_mfma" in line for lines in assembly.values() for line in lines) > 1000
 
 
+def _loose_barriers(lines):
+    """(line, allowed, requested) of each barrier behind a wait that lets more memory requests stay in flight than were issued
+    since the barrier before it, on the path with the fewest."""
+    found, at = {}, {}
+    for _ in range(4):
+        issued, allowed = 0, None
+        for number, line in enumerate(lines, 1):
+            text = line.split(";")[0].strip()
+            if text.endswith(":"):
+                if text.startswith("_Z"):
+                    issued = 0
+                issued = min(issued, at.get(text[:-1], issued))
+                continue
+            if not line.startswith("\t") or not text or text.startswith("."):
+                continue
+            op, _, rest = text.partition(" ")
+            if op.startswith(("buffer_", "global_", "scratch_")):
+                issued += 1
+            wait = re.search(r"vmcnt\((\d+)\)", rest) if op == "s_waitcnt" else None
+            if wait and int(wait[1]) < 63:                        # (63: no wait)
+                allowed = int(wait[1])
+            if op == "s_barrier":
+                if allowed is not None and allowed > issued:
+                    found[number] = (number, allowed, issued)
+                issued, allowed = 0, None
+            if op.startswith("s_cbranch") or op == "s_branch":
+                at[rest.strip()] = min(issued, at.get(rest.strip(), issued))
+                if op == "s_branch":
+                    issued = 1 << 30                              # nothing falls through to what follows
+    return sorted(found.values())
+
+
+def test_barriers_of_the_group_kernel_publish_what_has_landed(assembly):
+    """Its K step requests the tiles of the step after next and reads, behind the barrier, those requested a step earlier: the
+    wait in front of the barrier must not leave more in flight than this step has requested."""
+    lines = assembly["gemm_group.hip"]
+    assert not _loose_barriers(lines)
+    assert sum(line.strip() == "s_barrier" for line in lines) > 100
+
+
+def test_the_search_for_loose_barriers_finds_one():
+    code = ["_Zkernel:", "\ts_barrier", ".L1:", "\tbuffer_load_dwordx4 v1, s[0:3], 0 offen lds", "\tbuffer_load_dword v2, v1, s[0:3], 0",
+            "\ts_waitcnt vmcnt(2)", "\ts_barrier", "\ts_cbranch_scc1 .L1", "\ts_branch .L3", ".L3:"]
+    assert not _loose_barriers(code)
+    assert _loose_barriers([line.replace("vmcnt(2)", "vmcnt(3)") for line in code]) == [(7, 3, 2)]
+
+
 def test_the_search_for_early_reads_finds_one():
     code = ["_Zkernel:", "\tv_mfma_f32_32x32x16_f16 v[34:49], v[82:85], v[66:69], 0", "\ts_cbranch_scc1 .L1",
             "\ts_nop 11", ".L1:", "\t;;#ASMSTART", "\tv_max3_f32 v82, v34, v35, v36", "\t;;#ASMEND"]
