@@ -257,8 +257,10 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream() -> int:
     """Handle of the current stream of the current device.  (torch.cuda.current_stream() builds a Stream object around it:
-    2.9 us a call, half of what a call of this binding costs on the host; this is 0.3.)"""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    2.9 us a call, half of what a call of this binding costs on the host; this is 0.3.  It is the way of PyTorch's own compiled
+    code, not a documented one: a PyTorch without it goes the documented way.)"""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _check(rc: int, where: str):

@@ -220,3 +220,16 @@ def test_int8_sibling_argument_errors(b):
 def test_workspace_bytes(b):
     assert b.workspace_bytes(128, 768, 768, requant=False) == 0
     assert b.workspace_bytes(128, 768, 768, requant=True) == 128 * 768 * 4
+
+
+def test_current_stream_without_the_undocumented_handle(b, monkeypatch):
+    """A PyTorch without torch._C._cuda_getCurrentRawStream: the documented call, with the same handle."""
+    class Stream:
+        cuda_stream = 0x7f0012345678
+
+    monkeypatch.setattr(b.torch.cuda, "current_stream", lambda *a: Stream)
+    monkeypatch.setattr(b.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(b.torch._C, "_cuda_getCurrentRawStream", lambda device: 0x1000 + device, raising=False)
+    assert b._stream() == 0x1003
+    monkeypatch.delattr(b.torch._C, "_cuda_getCurrentRawStream")
+    assert b._stream() == 0x7f0012345678
