@@ -97,8 +97,8 @@ static bool fp6_ok(const GemmArgs &g, bool grouped) {
            ((long)g.M + 64) * g.lda < 0x7fffffffL && ((long)g.N + 128) * (g.K / 4 * 3) < 0x7fffffffL;
 }
 
-// CU count of the current device (the tile choice of the persistent kernel depends on it); 256 if it cannot be read.
-static int device_cus() {
+// CU count of the current device (the tile choice of the persistent kernels depends on it); 256 if it cannot be read.
+int device_cus() {
     static std::atomic<int> cached[kMaxDevices] = {};
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;

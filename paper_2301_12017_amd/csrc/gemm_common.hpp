@@ -462,6 +462,7 @@ int launch_fp6(int variant, int out_kind, GemmArgs &g, hipStream_t st);
 int launch_group(int mode, int out_kind, GemmArgs &g, hipStream_t st);
 int launch_small_packed(int mode, int out_kind, GemmArgs &g, hipStream_t st);
 int launch_mid(int variant, int mode, int out_kind, GemmArgs &g, hipStream_t st);
+int device_cus();                                               // gemm.hip
 // Residency limits of the fused requantize on the current device (see the definitions)
 int olay_requant_max_tiles_n(bool mfma_out);
 int fp6_requant_max_tiles_n();

@@ -331,7 +331,7 @@ static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
 // A few hundred 32 x 32 tiles at most go to the small-problem kernel instead (latency decides there).
 static int launch_w8(int out_kind, GemmArgs &g, hipStream_t st) {
     if (small8_ok(g)) return launch_small_packed8(out_kind, g, st);
-    const long cus = 256;
+    const long cus = device_cus();
     auto cost = [&](int bm, int bn, int occ, double eff) {
         const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
         const long n = (tiles + cus - 1) / cus, together = n < occ ? n : occ;
