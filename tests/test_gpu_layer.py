@@ -73,14 +73,15 @@ def test_attention_with_infinite_keys_and_values(B, batch, heads):
                                        (16000, 16000), (20000, 20000), (-20000, 20000), (60000, 60000)])
 def test_attention_of_large_finite_scores(B, batch, heads, query, key, order):
     """q.k = query * key + step * j, exact in FP32, up to 3.6e9 (and below zero): softmax of the differences, although the scores
-    times a constant are not exact (from 2.3e7 on a rounded one is off by a quarter and more, by 32 at 3e9)."""
+    times a constant are not exact (from 2.3e7 on a rounded one is off by a quarter and more, by 32 at 3e9).  Neighbouring
+    queries differ in sign and by 1024."""
     seq, rng = 150, np.random.default_rng(abs(query) + key)
     step = max(8, int(2 * np.spacing(np.float32(abs(query) * key))))
     j = rng.integers(0, 6, seq)
     j = {"up": np.sort(j), "down": np.sort(j)[::-1], "mixed": j}[order]
     x = rng.standard_normal((batch, seq, 3, heads, 64)).astype(np.float16)
     x[:, :, :2] = 0
-    x[:, :, 0, :, 5], x[:, :, 1, :, 5] = query, key
+    x[:, :, 0, :, 5], x[:, :, 1, :, 5] = (query * np.array([1, 2.0 ** -10, -1, -2.0 ** -10]))[np.arange(seq) % 4][:, None], key
     x[:, :, 0, :, 60], x[:, :, 1, :, 60] = step, j[None, :, None]
     x[0, 40:, 1, 0, 5] = -key / 2                                 # one head whose scores cross zero, and the limit
     got = host(B.attention(dev(x.reshape(batch * seq, -1)), batch, seq, heads)).reshape(batch, seq, heads, 64).astype(np.float64)
