@@ -192,7 +192,11 @@ __device__ __forceinline__ float gelu_erf(float x) {
 // modifiers, the exact fused result rounded ONCE to fp16).  Every fp16 GELU output of the library goes through
 // here, so all kernels agree bit for bit.  Eight instructions per value; gelu_erf() above (degree 7) remains the
 // form for fp32 results that are quantized afterwards, where its extra accuracy decides codes.
-__device__ __forceinline__ float gelu_tail_f16(float x) {        // Phi(-|x|) to fp16 accuracy
+//
+// v_exp needs a wait state before its result is read, which the compiler keeps for its own instructions only: max(x,0) is
+// computed behind v_exp (the empty assembly ties x to it), so that it stands between the two.
+struct GeluTail { float p, relu; };
+__device__ __forceinline__ GeluTail gelu_tail_f16(float &x) {    // Phi(-|x|) to fp16 accuracy, max(x,0)
     const float t = fabsf(x);
     float q = -3.204851180e-04f;
     q = __fmaf_rn(q, t, 5.827001986e-03f);
@@ -200,21 +204,23 @@ __device__ __forceinline__ float gelu_tail_f16(float x) {        // Phi(-|x|) to
     q = __fmaf_rn(q, t, -4.641228736e-01f);
     q = __fmaf_rn(q, t, -1.149174450e+00f);
     q = __fmaf_rn(q, t, -1.000121072e+00f);
-    return __builtin_amdgcn_exp2f(q);
+    GeluTail g;
+    g.p = __builtin_amdgcn_exp2f(q);
+    asm("" : "+v"(g.p), "+v"(x));
+    g.relu = __int_as_float(max(__float_as_int(x), 0));
+    return g;
 }
 __device__ __forceinline__ uint32_t gelu_erf_half2(float x0, float x1) {
-    const float p0 = gelu_tail_f16(x0), p1 = gelu_tail_f16(x1);
-    const float r0 = __int_as_float(max(__float_as_int(x0), 0)), r1 = __int_as_float(max(__float_as_int(x1), 0));
+    const GeluTail g0 = gelu_tail_f16(x0), g1 = gelu_tail_f16(x1);
     uint32_t d;
-    asm("v_fma_mixlo_f16 %0, -|%1|, %2, %3" : "=v"(d) : "v"(x0), "v"(p0), "v"(r0));
-    asm("v_fma_mixhi_f16 %0, -|%1|, %2, %3" : "+v"(d) : "v"(x1), "v"(p1), "v"(r1));
+    asm("v_fma_mixlo_f16 %0, -|%1|, %2, %3" : "=v"(d) : "v"(x0), "v"(g0.p), "v"(g0.relu));
+    asm("v_fma_mixhi_f16 %0, -|%1|, %2, %3" : "+v"(d) : "v"(x1), "v"(g1.p), "v"(g1.relu));
     return d;
 }
 __device__ __forceinline__ unsigned short gelu_erf_half(float x) {
-    const float p = gelu_tail_f16(x);
-    const float r = __int_as_float(max(__float_as_int(x), 0));
+    const GeluTail g = gelu_tail_f16(x);
     uint32_t d;
-    asm("v_fma_mixlo_f16 %0, -|%1|, %2, %3" : "=v"(d) : "v"(x), "v"(p), "v"(r));
+    asm("v_fma_mixlo_f16 %0, -|%1|, %2, %3" : "=v"(d) : "v"(x), "v"(g.p), "v"(g.relu));
     return (unsigned short)(d & 0xFFFFu);
 }
 

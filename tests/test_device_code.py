@@ -9,15 +9,17 @@ import pytest
 
 from paper_2301_12017_amd import build
 
-# wait states between a matrix instruction and a vector instruction that reads its result: eight passes, and sixteen for
-# the largest format of the scaled ones
-WAIT, WAIT_F8F6F4 = 12, 19
+# Wait states that the compiler keeps between an instruction and a vector instruction that reads its result, and does not keep
+# where one of the two stands in inline assembly: behind a matrix instruction (eight passes, and sixteen for the largest format of
+# the scaled ones), behind a transcendental, and from a vector instruction to a matrix, cross-lane or swap instruction.
+WAIT, WAIT_F8F6F4, WAIT_TRANS, WAIT_ASM = 12, 19, 1, 2
+_TRANS = ("v_exp_", "v_log_", "v_rcp_", "v_rsq_", "v_sqrt_", "v_sin_", "v_cos_")
 _REG = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
 
 
 @pytest.fixture(scope="module")
 def assembly(tmp_path_factory):
-    """{source: lines} of every source with a matrix instruction."""
+    """{source: lines} of every source with kernels that compute."""
     out = tmp_path_factory.mktemp("asm")
 
     def compile_(src):
@@ -28,7 +30,7 @@ def assembly(tmp_path_factory):
             return src, f.read().splitlines()
 
     with ThreadPoolExecutor(max_workers=4) as ex:
-        return dict(ex.map(compile_, [s for s in build.SOURCES if s.startswith("gemm_") or s == "attention.hip"]))
+        return dict(ex.map(compile_, [s for s in build.SOURCES if s not in ("api.hip", "gemm.hip", "strategy.hip", "probe.hip")]))
 
 
 def _regs(text):
@@ -40,11 +42,11 @@ def _regs(text):
 
 
 def _early_reads(lines):
-    """Instructions of inline assembly that touch a matrix instruction's result before its wait states are over, on any
-    path (each label takes over the state of every branch to it).  The compiler keeps them for its own instructions only."""
+    """Instructions that read a register before the wait states behind its writer are over, where the reader or the writer is
+    inline assembly, on any path (each label takes over the state of every branch to it)."""
     bad, at = set(), {}
     for _ in range(3):                                            # branches backwards: again with what the last walk found
-        pending, in_asm = {}, False                               # {(registers, line, wait states needed): passed}
+        pending, in_asm = {}, False                               # {(registers, line, wait states needed, by assembly): passed}
         for number, line in enumerate(lines, 1):
             if "#ASMSTART" in line or "#ASMEND" in line:
                 in_asm = "#ASMSTART" in line
@@ -59,13 +61,20 @@ def _early_reads(lines):
             if not line.startswith("\t") or not text or text.startswith("."):
                 continue
             op, _, rest = text.partition(" ")
-            if in_asm and op.startswith("v_"):
-                touched = _regs(rest)
-                bad |= {(number, text) for (dst, _, _) in pending if dst & touched}
+            dst, _, src = rest.partition(",")
+            if op.startswith("v_"):
+                slow = op.startswith(("v_mfma", "v_permlane")) or "dpp" in op or "row_" in rest or "quad_perm" in rest
+                touched, read = _regs(rest), _regs(src if op.startswith("v_mfma") else rest)
+                bad |= {(number, text) for (reg, _, _, by_asm) in pending
+                        if (not by_asm and in_asm and reg & touched) or (by_asm and slow and reg & read)}
             step = int(rest) + 1 if op == "s_nop" else 1
             pending = {key: age + step for key, age in pending.items() if age + step < key[2]}
             if op.startswith("v_mfma"):
-                pending[_regs(rest.split(",")[0]), number, WAIT_F8F6F4 if "f8f6f4" in op else WAIT] = 0
+                pending[_regs(dst), number, WAIT_F8F6F4 if "f8f6f4" in op else WAIT, False] = 0
+            elif op.startswith(_TRANS):
+                pending[_regs(dst), number, WAIT_TRANS, False] = 0
+            elif in_asm and op.startswith("v_"):
+                pending[_regs(dst), number, WAIT_ASM, True] = 0
             if op.startswith("s_cbranch") or op == "s_branch":
                 d = at.setdefault(rest.strip(), {})
                 for key, age in pending.items():
@@ -75,7 +84,7 @@ def _early_reads(lines):
     return sorted(bad)
 
 
-def test_inline_assembly_reads_no_matrix_result_too_early(assembly):
+def test_inline_assembly_keeps_wait_states(assembly):
     found = {src: _early_reads(lines) for src, lines in assembly.items()}
     assert not any(found.values()), {src: f[:4] for src, f in found.items() if f}
     assert sum("v_mfma" in line for lines in assembly.values() for line in lines) > 1000
@@ -128,8 +137,13 @@ def test_the_search_for_loose_barriers_finds_one():
     assert _loose_barriers([line.replace("vmcnt(2)", "vmcnt(3)") for line in code]) == [(7, 3, 2)]
 
 
-def test_the_search_for_early_reads_finds_one():
-    code = ["_Zkernel:", "\tv_mfma_f32_32x32x16_f16 v[34:49], v[82:85], v[66:69], 0", "\ts_cbranch_scc1 .L1",
-            "\ts_nop 11", ".L1:", "\t;;#ASMSTART", "\tv_max3_f32 v82, v34, v35, v36", "\t;;#ASMEND"]
+def test_the_search_for_early_reads_finds_them():
+    asm = ["\t;;#ASMSTART", "\tv_max3_f32 v82, v34, v35, v36", "\t;;#ASMEND"]
+    code = ["_Zkernel:", "\tv_mfma_f32_32x32x16_f16 v[34:49], v[82:85], v[66:69], 0", "\ts_cbranch_scc1 .L1", "\ts_nop 11", ".L1:", *asm]
     assert _early_reads(code) == [(7, "v_max3_f32 v82, v34, v35, v36")]
     assert not _early_reads([line for line in code if "cbranch" not in line])
+    assert _early_reads(["\tv_exp_f32_e32 v36, v1", *asm]) and not _early_reads(["\tv_exp_f32_e32 v36, v1", "\tv_mov_b32_e32 v2, v3", *asm])
+    for reader in ("v_mfma_f32_32x32x16_f16 v[0:15], v[80:83], v[66:69], 0", "v_permlane32_swap_b32_e32 v1, v82",
+                   "v_mov_b32_dpp v1, v82 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"):
+        assert _early_reads([*asm, "\ts_nop 0", "\t" + reader]) and not _early_reads([*asm, "\ts_nop 1", "\t" + reader])
+    assert not _early_reads([*asm, "\tv_mul_f32_e32 v1, v82, v82"])
