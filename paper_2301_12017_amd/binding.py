@@ -255,12 +255,15 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# The handle of a device's current stream, without the Stream object that torch.cuda.current_stream() builds around it (2.9 us a call,
+# half of what a call of this binding costs on the host, against 0.3).  It is the way of PyTorch's own compiled code, not a
+# documented one: a PyTorch without it goes the documented way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    """Handle of the current stream of the current device.  (torch.cuda.current_stream() builds a Stream object around it:
-    2.9 us a call, half of what a call of this binding costs on the host; this is 0.3.  It is the way of PyTorch's own compiled
-    code, not a documented one: a PyTorch without it goes the documented way.)"""
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
+    """Handle of the current stream of the current device."""
+    return torch.cuda.current_stream().cuda_stream if _raw_stream is None else _raw_stream(torch.cuda.current_device())
 
 
 def _check(rc: int, where: str):

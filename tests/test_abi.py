@@ -223,13 +223,13 @@ def test_workspace_bytes(b):
 
 
 def test_current_stream_without_the_undocumented_handle(b, monkeypatch):
-    """A PyTorch without torch._C._cuda_getCurrentRawStream: the documented call, with the same handle."""
+    """A PyTorch without torch._C._cuda_getCurrentRawStream: the documented call."""
     class Stream:
         cuda_stream = 0x7f0012345678
 
     monkeypatch.setattr(b.torch.cuda, "current_stream", lambda *a: Stream)
     monkeypatch.setattr(b.torch.cuda, "current_device", lambda: 3)
-    monkeypatch.setattr(b.torch._C, "_cuda_getCurrentRawStream", lambda device: 0x1000 + device, raising=False)
+    monkeypatch.setattr(b, "_raw_stream", lambda device: 0x1000 + device)
     assert b._stream() == 0x1003
-    monkeypatch.delattr(b.torch._C, "_cuda_getCurrentRawStream")
+    monkeypatch.setattr(b, "_raw_stream", None)
     assert b._stream() == 0x7f0012345678
