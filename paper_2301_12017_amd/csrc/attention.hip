@@ -14,10 +14,10 @@
 // no worse than 2^-41 below, where p itself would lose 2^-26.  Weights of e^-18 keep the digits that an FP16 result can show,
 // as it does where the largest weight meets a value of zero.
 //
-// Bound by the vector ALU between the products (per score: scale, v_exp at a quarter of the rate, sum,
-// split into two halves), not by memory: 24 x 512 tokens, 16 heads: 55 us, where the kernel it replaced
-// (one query at a time per wave, v_dot2 scores and an FMA per key and feature) took 1896 us and the bytes
-// 19 us; 128 x 128 tokens, 12 heads: 24 us (275 us); 1 x 128: 3.9 us (7.7 us), the launch floor.
+// Bound by the vector ALU between the products (per score: exponent, v_exp at a quarter of the rate, sum, split into two
+// halves), not by memory: 24 x 512 tokens, 16 heads: 54 us, where the kernel it replaced (one query at a time per wave, v_dot2
+// scores and an FMA per key and feature) took 1765 us and the bytes 19 us; 128 x 128 tokens, 12 heads: 22 us (274 us);
+// 1 x 128: 3.9 us (6.1 us), 1 x 32: 3.2 us (3.5 us), near the launch floor.
 #include "common.hpp"
 
 namespace w4a4 {
