@@ -28,7 +28,7 @@ def test_attention_against_the_oracle(B, orc, batch, seq, heads):
     np.testing.assert_allclose(got, want, rtol=2e-3, atol=2e-3 * np.sqrt((want ** 2).mean()))
 
 
-@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries; a wave per block
+@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries (above 32 tokens); a wave per block
 @pytest.mark.parametrize("seq", [1, 31, 32, 33, 64, 65, 127, 128, 129, 255, 257, 511, 512])
 def test_attention_at_the_edges_of_its_tiles(B, orc, batch, heads, seq):
     rng = np.random.default_rng(seq)
@@ -67,7 +67,7 @@ def test_attention_with_infinite_keys_and_values(B, batch, heads):
         assert np.all(near | (got[0, :, head] == want) | (np.isnan(want) & np.isnan(got[0, :, head])))
 
 
-@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries; a wave per block
+@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries (above 32 tokens); a wave per block
 @pytest.mark.parametrize("order", ["up", "down", "mixed"])
 @pytest.mark.parametrize("query,key", [(100, 1000), (3000, 5000), (4400, 5000), (4700, 5000), (-4700, 5000), (10000, 10000), (12000, 12000),
                                        (16000, 16000), (20000, 20000), (-20000, 20000), (60000, 60000)])
@@ -95,7 +95,7 @@ def test_attention_of_large_finite_scores(B, batch, heads, query, key, order):
         assert np.all(np.abs(got[b, :, h] - want) <= bound), np.max(np.abs(got[b, :, h] - want))
 
 
-@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries; a wave per block
+@pytest.mark.parametrize("batch,heads", [(1, 3), (17, 12)])     # waves share a block of queries (above 32 tokens); a wave per block
 @pytest.mark.parametrize("depth", [2, 6, 9, 11, 14, 17])
 @pytest.mark.parametrize("where", [0, 70, 149])
 def test_attention_of_small_weights(B, batch, heads, depth, where):
