@@ -212,9 +212,10 @@ __global__ __launch_bounds__(kAttnThreads, SPLIT == 1 ? 4 : 3) void attention_mf
     const int q0 = SPLIT == 4 ? qb * 32 : qb * 128 + wave * 32;
     const int qi = q0 + (lane & 31);
 
-    // 32-bit offsets from uniform bases keep SPLIT == 1 within the 128 registers of four waves per SIMD (384 x 32 tokens 13.8 us,
-    // 15.1 with addresses); its descriptors end with the sequence, SPLIT == 4 asks (1 x 32 tokens 3.7 us, 3.85 with descriptors).
-    // Rows behind the sequence are zero in both.
+    // 32-bit offsets from uniform bases; for SPLIT == 1 through descriptors that end with the sequence, for SPLIT == 4 under a
+    // condition (rows behind the sequence are zero in both).  Descriptors | conditions | 64-bit addresses, us: 24 x 512 tokens
+    // 53.6 | 54.2 | 55.4, 9 x 371 16.1 | 16.6 | 16.7, 1 x 32 3.17 | 3.22 | 3.27; with keys split over the waves, 1 x 128,
+    // descriptors cost 0.1.
     u32x4 kreg[CH], vreg[CH];
     const int srow = tid >> 3, scol = (tid & 7) * 8;
     const uint32_t ld_bytes = (uint32_t)ld * 2, bytes = (uint32_t)(seq - 1) * ld_bytes + kHead * 2, off0 = srow * ld_bytes + scol * 2;
