@@ -110,43 +110,49 @@ int device_cus() {
     return cus;
 }
 
-// Tile choice of the persistent kernel.  What counts is the CU that ends up with the most tiles: n tiles
-// of area a, worked on by min(n, workgroups per CU) co-resident workgroups.  Fitted to kernel times over
-// M = 512 .. 16384 on the BERT-base and BERT-large shapes: one workgroup alone gets about half of what two
-// get out of a CU's matrix pipe, three get 0.85 of it (LDS and cache contention); per unit of area the
-// 192 x 128 tile is 8 % dearer than the 128 x 256 one (more operand registers unpacked per MFMA) and the
-// 128 x 128 tile 6 % cheaper in the mid range, where it also leaves fewer CUs idle.  Below about 1500
-// tokens a tile's K loop is latency-bound and the small tile gains nothing.
+// Tile choice of the persistent kernels.  What counts is the CU that ends up with the most tiles: n tiles of area a, worked
+// on by min(n, workgroups per CU) co-resident workgroups, cost n * a / (rate * eff): `rate` what that many workgroups get out
+// of a CU together (two: 1), `eff` of a tile against 128 x 256.  A single workgroup counts about as much as two: in these
+// rounds every CU has a tile or none, and what a second one adds the first one's latency takes.  Fitted per kernel to the times
+// of all its tiles at some twenty token counts from 1024 to 32768 on the four linears of BERT-base and BERT-large, with bias
+// and GELU, once back to back and once behind the quantize of another set of activations.  Above the best tile on average,
+// back to back and behind the quantize: int8 0.6 and 0.5 % (before 2.3 and 1.5), FP6 0.9 and 1.4 % (before 4.7 %).
+struct TileRates {
+    double one, three;                                          // workgroups per CU (two: 1)
+    double eff_192x128, eff_128x128, eff_192x256;
+};
+static double tile_cost(const GemmArgs &g, const TileRates &r, int bm, int bn, int occ, double eff, long cus) {
+    const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+    const long n = (tiles + cus - 1) / cus, together = n < occ ? n : occ;
+    return (double)n * bm * bn / ((together == 1 ? r.one : together == 2 ? 1.0 : r.three) * eff);
+}
+
+// int8 kernel.  (12288 x 3072 x 768 + GELU 40.8 us on 192 x 128 -> 34.8 on 128 x 256; 6144 x 768 x 3072 18.3 on 128 x 128 -> 15.7
+// on 192 x 128.)  Below about 1500 tokens a tile's K loop is latency-bound and the small tile gains nothing.
 static int pick_olay(const GemmArgs &g) {
     const long cus = device_cus();
-    auto cost = [&](int bm, int bn, int occ, double eff) {
-        const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
-        const long n = (tiles + cus - 1) / cus;
-        const long together = n < occ ? n : occ;
-        const double rate = together == 1 ? 0.5 : together == 2 ? 1.0 : 0.85;
-        return (double)n * bm * bn / (rate * eff);
-    };
+    const TileRates r = {1.05, 0.81, 0.93, 1.10, 0.0};
     int best = S_OLAY_128x256;
-    double c = cost(128, 256, 2, 1.0);
-    const double c192 = cost(192, 128, 2, 0.92);
+    double c = tile_cost(g, r, 128, 256, 2, 1.0, cus);
+    const double c192 = tile_cost(g, r, 192, 128, 2, r.eff_192x128, cus);
     if (c192 < c) { best = S_OLAY_192x128; c = c192; }
-    if (g.M >= 1536 && cost(128, 128, 3, 1.06) < c) best = S_OLAY_128x128;
+    if (g.M >= 1536 && tile_cost(g, r, 128, 128, 3, r.eff_128x128, cus) < c) best = S_OLAY_128x128;
     return best;
 }
 
-// Tile choice of the FP6 kernel, from kernel times on the BERT-large shapes at 12288 tokens (TOP/s of 192 x 256 with
-// one wave per SIMD / 128 x 256 / 192 x 128): K = 4096 3350 / 3040 / 3110; K = 1024 with N = 3072 2450 / 2490 / 1950, with
-// N = 4096 + GELU 2030 / 2260 / 2080, with N = 1024 1890 / 1960 / 1790.  Long K favours the big tile (least operand traffic per
-// product, one workgroup per CU); otherwise two 128 x 256 workgroups per CU, whose epilogues and stores overlap better;
-// few tiles fall back to the mid-range rule of the int8 kernel.
+// FP6 kernel.  The 192 x 256 tile (one wave per SIMD, least operand traffic per product) pays for long K and whole rounds of
+// one tile per CU: 12288 x 1024 x 4096, 256 tiles, 32.5 us against 34.3 on 128 x 256; 16384 x 768 x 3072, 258 tiles,
+// 43.4 against 28.6 (28.0 on 128 x 128); 16384 x 1024 x 4096 56.5 against 39.5.
 static int pick_fp6(const GemmArgs &g) {
     const long cus = device_cus();
-    const long big = (long)((g.M + 191) / 192) * ((g.N + 255) / 256);
-    if (g.K >= 2048 && g.K / 64 >= 9 && big * 4 >= 3 * cus) return S_FP6_192x256;
-    const long mid = (long)((g.M + 127) / 128) * ((g.N + 255) / 256);
-    if (mid >= cus) return S_FP6_128x256;
-    const int o = pick_olay(g);
-    return o == S_OLAY_128x256 ? S_FP6_128x256 : o == S_OLAY_192x128 ? S_FP6_192x128 : S_FP6_128x128;
+    const TileRates r = {1.31, 0.62, 0.83, 1.25, 0.745};
+    int best = S_FP6_128x256;
+    double c = tile_cost(g, r, 128, 256, 2, 1.0, cus);
+    const double c192 = tile_cost(g, r, 192, 128, 2, r.eff_192x128, cus), c128 = tile_cost(g, r, 128, 128, 3, r.eff_128x128, cus);
+    if (c192 < c) { best = S_FP6_192x128; c = c192; }
+    if (c128 < c) { best = S_FP6_128x128; c = c128; }
+    if (g.K >= 2048 && tile_cost(g, r, 192, 256, 1, r.eff_192x256, cus) < c) best = S_FP6_192x256;
+    return best;
 }
 
 // Resolves schedule 0 to the table's choice and checks everything a launcher of that family requires, so that
