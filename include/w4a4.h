@@ -314,6 +314,10 @@ typedef struct {
     float ln_eps;
 } w4a4_encoder_layer_weights;
 
+/* 1 if a layer of these sizes runs faster with all four weights in the FP6 operand layout than in the layouts that
+ * w4a4_preferred_layout names part by part, and can (every strategy); else 0.  Asks the current device. */
+int w4a4_encoder_layer_prefers_fp6(int M, int hidden, int ffn);
+
 /* out_f16 [batch*seq, h] = LN2(x1 + ffn2(ffn1(x1))),  x1 = LN1(x + attn_out(attention(qkv(x)))),
  * every part run as `strategy` says (bits of w4a4_strategy_pick plus W4A4_STRATEGY_FUSED_LN).
  * X_f16 [batch*seq, h] dense.  Workspace 256-byte aligned, w4a4_encoder_layer_workspace_bytes

@@ -107,6 +107,7 @@ _SIGNATURES = {
     "w4a4_strategy_tune": (_i, [_i, _i, _i, _i, ctypes.POINTER(_StrategyCosts), _vp]),
     "w4a4_strategy_lookup": (_i, [_i, _i, _i]),
     "w4a4_attention_f16": (_i, [_vp, _i, _i, _i, _vp, _vp]),
+    "w4a4_encoder_layer_prefers_fp6": (_i, [_i, _i, _i]),
     "w4a4_encoder_layer_workspace_bytes": (_sz, [_i, _i, ctypes.POINTER(_LayerWeights)]),
     "w4a4_encoder_layer": (_i, [_vp, _i, _i, ctypes.POINTER(_LayerWeights), _i, _vp, _vp, _sz, _vp]),
     "w4a4_fused_fault_check": (_i, [_vp]),
@@ -709,12 +710,15 @@ def attention(QKV: torch.Tensor, batch: int, seq: int, heads: int, out=None) -> 
 
 
 class EncoderLayer:
-    """The weights of one encoder layer (w4a4_encoder_layer_weights) and a workspace for `batch` x `seq` tokens."""
+    """The weights of one encoder layer (w4a4_encoder_layer_weights) and a workspace for `batch` x `seq` tokens.  The INT4
+    weights take the layout asked for, or the fastest: FP6 for all four where the library says so, else part by part."""
 
     def __init__(self, batch, seq, heads, Wqkv, bqkv, Wao, bao, W1, b1, W2, b2, g1, be1, g2, be2, eps=1e-12,
                  layout: Optional[int] = None):
         M = batch * seq
         self.batch, self.seq, self.heads, self.hidden, self.ffn = batch, seq, heads, Wao.shape[0], W1.shape[0]
+        if layout is None and lib().w4a4_encoder_layer_prefers_fp6(M, self.hidden, self.ffn):
+            layout = LAYOUT_FP6
         self.qkv, self.attn_out = Part(Wqkv, M, bqkv, layout=layout), Part(Wao, M, bao, layout=layout)
         self.ffn1, self.ffn2 = Part(W1, M, b1, ACT_GELU, layout=layout), Part(W2, M, b2, layout=layout)
         self.ln = (g1, be1, g2, be2)

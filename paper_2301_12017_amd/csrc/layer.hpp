@@ -30,4 +30,7 @@ ClearRanges linear_clear_ranges(const w4a4_act *A, const w4a4_weight *W, const w
 int linear_cleared(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, void *out, float *out_scale,
                    int32_t *out_gsum, void *workspace, size_t workspace_bytes, void *stream);
 
+// Column tiles of a row panel that the FP6 kernel's requantizing epilogue can keep co-resident (-1: HIP error).
+int fp6_requant_max_tiles_n();
+
 }  // namespace w4a4

@@ -459,6 +459,22 @@ extern "C" int w4a4_strategy_tune(int M, int hidden, int ffn, int iters, w4a4_st
     return pick;
 }
 
+// Many tokens: the whole layer with its weights in the FP6 operand layout, if every part can take it (both FFN weights, so that
+// the fused pair stays possible).  The FP6 kernels run the four GEMMs in less time once they fill the chip; below, their
+// epilogue of separately rounded operations and the wider codes cost what the shorter main loop gives.  Layer in the layouts
+// that w4a4_preferred_layout names | in FP6, sequences of 128, built-in strategy, us: hidden 1024: 6144 tokens 137 | 141,
+// 8192 171 | 166, 12288 242 | 227, 16384 310 | 283; hidden 768: 8192 130 | 134, 12288 181 | 178, 16384 230 | 216, 24576 315 | 300.
+extern "C" int w4a4_encoder_layer_prefers_fp6(int M, int hidden, int ffn) {
+    if (!shape_ok(M, hidden, ffn) || M < (hidden >= 1024 ? 8192 : 12288)) return 0;
+    int lpr = 0, opl = 0;
+    for (int k : {hidden, ffn})
+        if (k % 128 || k < 512 || !fp6_plan(k, &lpr, &opl)) return 0;
+    const int widest = ffn > 3 * hidden ? ffn : 3 * hidden;
+    // sizes the FP6 kernel addresses with 32 bits, and FFN1's requantized output: whole column tiles that fit side by side
+    if (((long)M + 512) * widest * 4 >= 0x80000000L || ((long)widest + 128) * (widest / 4 * 3) >= 0x7fffffffL || ffn % 256) return 0;
+    return ffn / 256 <= fp6_requant_max_tiles_n() ? 1 : 0;
+}
+
 extern "C" size_t w4a4_encoder_layer_workspace_bytes(int batch, int seq, const w4a4_encoder_layer_weights *L) {
     if (batch <= 0 || seq <= 0 || (long)batch * seq > 0x7fffffffL / 4 || !layer_ok(L)) return 0;
     return plan_layer(nullptr, batch * seq, *L).total;

@@ -286,3 +286,20 @@ def test_layer_with_weights_in_the_fp6_layout(B, shape, strategy):
     _, _, L0 = _layer(B, sum(shape), batch, seq, heads, h, f, layout=B.LAYOUT_CANONICAL)
     assert torch.equal(got, L0(d["X"], strategy))
     assert B.fused_fault_check() is False
+
+
+@pytest.mark.parametrize("shape,fp6", [((64, 128, 16, 1024, 4096), True), ((63, 130, 16, 1024, 4096), False),
+                                       ((24, 512, 12, 768, 3072), True), ((96, 127, 12, 768, 3072), False),
+                                       ((64, 192, 6, 384, 1536), False)])
+def test_layer_takes_the_fp6_layout_from_many_tokens_on(B, shape, fp6):
+    """From 8192 tokens at hidden size 1024, 12288 below it, the default layout of a layer is FP6 where every part can take it
+    (384 features cannot: the GEMM wants 512); the outputs are those of the layer asked for in the canonical layout, whose
+    kernels follow the same operation order, bit for bit, in every strategy."""
+    batch, seq, heads, h, f = shape
+    t, d, L = _layer(B, 1, batch, seq, heads, h, f)
+    assert [p.w4.layout == B.LAYOUT_FP6 for p in (L.qkv, L.attn_out, L.ffn1, L.ffn2)] == [fp6] * 4
+    if fp6:
+        _, _, L0 = _layer(B, 1, batch, seq, heads, h, f, layout=B.LAYOUT_CANONICAL)
+        for strategy in (15, 31, 31 | 32, 7):
+            assert torch.equal(L(d["X"], strategy), L0(d["X"], strategy)), strategy
+    assert B.fused_fault_check() is False
