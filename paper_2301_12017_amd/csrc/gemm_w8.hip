@@ -1,22 +1,29 @@
 // Persistent INT8 x INT8 -> INT32 GEMM with the fused symmetric epilogue: the INT8 sibling of the
 // INT4 path (the pipeline the paper measures INT4 against, Sec. 4.1 / 4.3).  On gfx950 both run on the
 // same int8 MFMA, so this kernel is gemm_olay.hip with the nibble handling taken out:
-//   * same persistent skeleton: HBM -> LDS by `buffer_load_dwordx4 ... lds` with scalar addressing, three
-//     LDS stages of 64-byte rows with the XOR swizzle, the K steps of successive tiles as one stream, one
-//     barrier per K step, two workgroups of four waves per CU, priority alternation, non-temporal stores;
-//   * a K step is 64 codes (64 bytes per row, where the INT4 kernel moves 128 codes in the same bytes):
-//     a 16-byte LDS read IS an MFMA operand, so there is no widening VALU work at all, but twice the
-//     LDS reads, DMA instructions and barriers per MFMA;
+//   * same persistent skeleton: HBM -> LDS by `buffer_load_dwordx4 ... lds` with scalar addressing, LDS
+//     stages with the XOR swizzle, the K steps of successive tiles as one stream, one
+//     barrier per K step, non-temporal stores;
+//   * a 16-byte LDS read IS an MFMA operand, so there is no widening VALU work at all;
 //   * no code-sum corrections: the accumulators hold P itself.
+//
+// What bounds it is the path from L2 into the CU.  Operands arrive in cache lines of 128 bytes; a K step of 64 codes takes half
+// a line of every row, and the other half, wanted one step later, has left the 32 KB vector cache by then as often as not
+// (2.4 million L2 requests for the 1.6 million lines of 4096 x 1024 x 3072).  A K step is therefore 128 codes, whole lines,
+// wherever K allows: 4096 x 1024 x 4096 in 128 x 128 tiles 24.9 -> 19.0 us, 16384 x 1024 x 4096 71 -> 62.  The 256 x 256 tile of
+// eight waves asks for half as many operand bytes per product as 128 x 128 and reads 3/4 as many from LDS: 56 us.  Deeper
+// prefetch of half lines (eight stages) or operands read a whole step ahead, on the other hand, gave 21.
 #include "gemm_common.hpp"
 
 namespace w4a4 {
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
-constexpr int kW8Step = 64;                                       // codes (= bytes) per row per K step
+constexpr int kW8Step = 64;                                       // codes (= bytes) per row per K step, at least
 
-// s_waitcnt immediate for "vmcnt <= n", lgkmcnt and expcnt unconstrained (gfx9 encoding)
+// s_waitcnt immediate for "vmcnt <= n and lgkmcnt == 0", expcnt unconstrained (gfx9 encoding)
+constexpr int w8_vmcnt_and_lds(int n) { return (n & 0xF) | (0x7 << 4) | (0x0 << 8) | (((n >> 4) & 0x3) << 14); }
+// ... for "vmcnt <= n", lgkmcnt and expcnt unconstrained
 constexpr int w8_vmcnt_only(int n) { return (n & 0xF) | (0x7 << 4) | (0xF << 8) | (((n >> 4) & 0x3) << 14); }
 
 template <int FN>
@@ -65,19 +72,23 @@ __device__ __forceinline__ void w8_epilogue(const GemmArgs &g, v16i (&acc)[FM][F
         }
 }
 
-template <int FM, int FN, int WM, int WN, int OCC, int OUT>
-__global__ __attribute__((amdgpu_flat_work_group_size(WM *WN * 64, WM *WN * 64), amdgpu_waves_per_eu(OCC, OCC)))
+// WPS: waves per SIMD (all workgroups of a CU together).  ROWB: codes (= bytes) of a row per K step.  NS: LDS stages.
+template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int OUT>
+__global__ __attribute__((amdgpu_flat_work_group_size(WM *WN * 64, WM *WN * 64), amdgpu_waves_per_eu(WPS, WPS)))
 void gemm_w8_kernel(GemmArgs g) {
     constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
-    constexpr int ROWB = kW8Step;                               // 64 bytes = 64 codes per row per K step
-    constexpr int STAGE = (BM + BN) * ROWB, NS = 3;
-    constexpr int BLOCKS = (BM + BN) / 16;                      // 1 KB DMA blocks per stage
+    constexpr int STAGE = (BM + BN) * ROWB;                     // ROWB codes (= bytes) per row per K step
+    constexpr int CPR = ROWB / 16, RPB = 1024 / ROWB;           // 16-byte chunks of a row, rows of a 1 KB DMA block
+    constexpr int SUB = ROWB / 32;                              // sub-steps of 32 codes
+    constexpr int SWZ = CPR == 8 ? 1 : 2;                       // rows that share a swizzle, log2: 256 bytes of LDS
+    constexpr int BLOCKS = (BM + BN) / RPB;                     // 1 KB DMA blocks per stage
     constexpr int LD = BLOCKS / NW;                             // tile DMA instructions per wave per K step
-    constexpr int A_LD = (BM / 16) / NW;                        // the first A_LD of them fetch activations
+    constexpr int A_LD = (BM / RPB) / NW;                       // the first A_LD of them fetch activations
+    constexpr int DPS = (LD + SUB - 2) / (SUB - 1);             // DMA instructions per sub-step, the last one's excepted
     constexpr int NF = FM + FN, NM = FM * FN;
     constexpr int PB = BM / 64;                                 // 64-row blocks of token scales
-    static_assert(BLOCKS % NW == 0 && (BM / 16) % NW == 0, "DMA blocks must split evenly over the waves");
-    static_assert(NF <= NM && LD <= NM, "not enough MFMA slots to hide the memory operations");
+    static_assert(BLOCKS % NW == 0 && (BM / RPB) % NW == 0, "DMA blocks must split evenly over the waves");
+    static_assert(NF <= NM && DPS <= NM, "not enough MFMA slots to hide the memory operations");
     static_assert(BM % 64 == 0, "token parameters are fetched 64 rows per DMA instruction");
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -88,16 +99,17 @@ void gemm_w8_kernel(GemmArgs g) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int total = g.tiles_m * g.tiles_n, stride = gridDim.x;
-    const int KT = g.K / kW8Step;
+    const int KT = g.K / ROWB;
 
     // ---- global -> LDS plan (fixed for the whole kernel) -------------------------------------------
-    // DMA instruction i of this wave fills block b = wave + i*NW of a stage: tile rows 16b..16b+15.
-    // Lane l supplies physical slot (r = l>>2, pc = l&3) of the block = logical chunk pc ^ ((row>>2)&3).
+    // DMA instruction i of this wave fills block b = wave + i*NW of a stage: tile rows RPB b .. RPB b + RPB-1.
+    // Lane l supplies physical slot (r = l / CPR, pc = l % CPR) of the block = logical chunk pc ^ (row >> SWZ) % CPR:
+    // the eight lanes of one LDS cycle, rows r .. r+7 of one chunk, fall into eight different 16-byte slots of 256 bytes.
     int voff[LD];
 #pragma unroll
     for (int i = 0; i < LD; ++i) {
-        const int row = (wave + i * NW) * 16 + (lane >> 2);
-        const int c = (lane & 3) ^ ((row >> 2) & 3);
+        const int row = (wave + i * NW) * RPB + lane / CPR;
+        const int c = (lane % CPR) ^ ((row >> SWZ) & (CPR - 1));
         if (i < A_LD) {
             voff[i] = row * (int)g.lda + c * 16;
         } else {
@@ -145,8 +157,8 @@ void gemm_w8_kernel(GemmArgs g) {
 
     // ---- operand fragments -----------------------------------------------------------------------
     // lane (r = lane&31, h = lane>>5) reads logical chunk ks*2 + h of its row
-    const int swz = ((lane & 31) >> 2) & 3;
-    const int rd0 = (lane & 31) * ROWB + (((lane >> 5) ^ swz) << 4);   // ks = 0;  ks = 1 is rd0 ^ 32
+    const int swz = ((lane & 31) >> SWZ) & (CPR - 1);
+    const int rd0 = (lane & 31) * ROWB + (((lane >> 5) ^ swz) << 4);   // ks = 0;  ks is rd0 ^ (32 * ks)
     int frag_off[NF];
 #pragma unroll
     for (int f = 0; f < FM; ++f) frag_off[f] = (wm * FM * 32 + f * 32) * ROWB + rd0;
@@ -172,10 +184,10 @@ void gemm_w8_kernel(GemmArgs g) {
     __amdgpu_buffer_rsrc_t a_cur = a_desc(m0), b_cur = b_desc(n0);
     dma_params(m0, 0);
 #pragma unroll
-    for (int i = 0; i < LD; ++i) dma_one(i, 0, a_cur, b_cur, 0);
+    for (int s = 0; s < NS - 1; ++s)
 #pragma unroll
-    for (int i = 0; i < LD; ++i) dma_one(i, 1, a_cur, b_cur, ROWB);
-    __builtin_amdgcn_s_waitcnt(w8_vmcnt_only(LD));              // the first K step; the second is waited for where it is read
+        for (int i = 0; i < LD; ++i) dma_one(i, s, a_cur, b_cur, s * ROWB);
+    __builtin_amdgcn_s_waitcnt(w8_vmcnt_only((NS - 2) * LD));   // the first K step; the others are waited for where they are read
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     v4i P0[NF], P1[NF];
@@ -208,7 +220,7 @@ void gemm_w8_kernel(GemmArgs g) {
         const int m0n = (tile_next / g.tiles_n) * BM, n0n = (tile_next % g.tiles_n) * BN;
         const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n, has_next), b_nxt = b_desc(n0n, has_next);
 
-        // ---- main loop: one iteration = 64 codes of K = two sub-steps of NM MFMAs ------------------------
+        // ---- main loop: one iteration = ROWB codes of K = SUB sub-steps of NM MFMAs ------------------------
         // The instruction order below is the intended issue order; the scheduling barriers keep the
         // compiler from regrouping it.  The operands need no widening: a 16-byte LDS read is an operand.
 #define W8_SLOT(P, k)                                                                                     \
@@ -225,30 +237,36 @@ void gemm_w8_kernel(GemmArgs g) {
             constexpr bool FIRST = decltype(first_tag)::value; // first K step of the tile
             constexpr bool LAST = decltype(last_tag)::value;   // last K step of the tile
             const int nxt = cur == NS - 1 ? 0 : cur + 1;       // stage of stream step +1
-            const int nx2 = nxt == NS - 1 ? 0 : nxt + 1;       // stage of stream step +2 (= step -1)
-            // stream step +2 is K step kt+2 of this tile, or K step kt+2-KT of the next one (when there
+            const int free = cur == 0 ? NS - 1 : cur - 1;      // stage of stream step +NS-1 (= step -1)
+            // stream step +NS-1 is K step kt+NS-1 of this tile, or K step kt+NS-1-KT of the next one (when there
             // is none: requests that the descriptor turns away, so that the load counting stays uniform)
-            const bool own = !LAST && kt + 2 < KT;
+            const bool own = !LAST && kt + NS - 1 < KT;
             const __amdgpu_buffer_rsrc_t ra = own ? a_cur : a_nxt, rb = own ? b_cur : b_nxt;
-            const int so = (own ? kt + 2 : kt + 2 - KT) * ROWB;
-            // sub-step 0: multiply codes 0..31 of the step; fetch codes 32..63 -> P1; request stream step +2
-            //             into the stage every wave finished reading before the last barrier.
+            const int so = (own ? kt + NS - 1 : kt + NS - 1 - KT) * ROWB;
+            // sub-steps 0 .. SUB-2: multiply 32 codes, fetch the next 32; request stream step +NS-1
+            // into the stage every wave finished reading before the last barrier.
 #pragma unroll
-            for (int k = 0; k < NM; ++k) {
-                if constexpr (FIRST) { W8_SLOT_ZERO(P0, k) } else { W8_SLOT(P0, k) }
-                if (k < NF) P1[k] = read_frag(k, cur, 1);
-                if (k < LD) dma_one(k, nx2, ra, rb, so);
-                __builtin_amdgcn_sched_barrier(0);
+            for (int ss = 0; ss < SUB - 1; ++ss) {
+                v4i (&Pc)[NF] = ss & 1 ? P1 : P0;
+                v4i (&Pn)[NF] = ss & 1 ? P0 : P1;
+#pragma unroll
+                for (int k = 0; k < NM; ++k) {
+                    if constexpr (FIRST) { if (ss == 0) { W8_SLOT_ZERO(Pc, k) } else { W8_SLOT(Pc, k) } } else { W8_SLOT(Pc, k) }
+                    if (k < NF) Pn[k] = read_frag(k, cur, ss + 1);
+                    if (k < DPS && ss * DPS + k < LD) dma_one(ss * DPS + k, free, ra, rb, so);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            // sub-step 1: multiply codes 32..63; this wave's loads of stream step +1 have landed (vmcnt), and
-            //             after the barrier everyone's have: fetch its codes 0..31 -> P0.  At the end of a tile
-            //             BOTH prefetched steps of the next tile are waited for; the next tile reads its first
-            //             fragments itself.
+            // the last sub-step: this wave's loads of stream step +1 have landed (vmcnt) and its reads of this step have
+            // returned, and after the barrier everyone's have: fetch its codes 0..31 -> P0.  At the end of a tile
+            // all prefetched steps of the next tile are waited for; the next tile reads its first
+            // fragments itself.
+            static_assert(SUB % 2 == 0, "P0 holds the first operands of every step");
 #pragma unroll
             for (int k = 0; k < NM; ++k) {
                 W8_SLOT(P1, k)
                 if (k == kBarSlot) {
-                    __builtin_amdgcn_s_waitcnt(w8_vmcnt_only(LAST ? 0 : LD));
+                    __builtin_amdgcn_s_waitcnt(w8_vmcnt_and_lds(LAST ? 0 : (NS - 2) * LD));
                     __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
                 }
@@ -293,17 +311,20 @@ void gemm_w8_kernel(GemmArgs g) {
 }
 
 
-template <int FM, int FN, int WM, int WN, int OCC, int OUT>
+template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int OUT>
 static int launch_one(GemmArgs &g, hipStream_t st) {
-    constexpr int BM = WM * FM * 32, BN = WN * FN * 32;
-    constexpr size_t lds = 3 * (size_t)(BM + BN) * kW8Step + 2 * BM * 4;
+    constexpr int BM = WM * FM * 32, BN = WN * FN * 32, PER_CU = WPS * 4 / (WM * WN);
+    constexpr size_t lds = NS * (size_t)(BM + BN) * ROWB + 2 * BM * 4;
+    static_assert(lds * PER_CU <= 160 * 1024, "the workgroups of a CU share 160 KB of LDS");
+    const int steps = g.K / ROWB;                               // a tile has a first and a last step, and as many as are requested ahead
+    if (g.K % ROWB || steps < 2 || steps < NS - 1) return W4A4_ERR_UNSUPPORTED_SHAPE;
     g.tiles_m = (g.M + BM - 1) / BM;
     g.tiles_n = (g.N + BN - 1) / BN;
-    auto kern = gemm_w8_kernel<FM, FN, WM, WN, OCC, OUT>;
+    auto kern = gemm_w8_kernel<FM, FN, WM, WN, WPS, ROWB, NS, OUT>;
     static KernelState ks;
     const int cus = prepare_kernel(reinterpret_cast<const void *>(kern), lds, ks);
     if (cus < 0) return W4A4_ERR_HIP;
-    const int slots = cus * OCC;                                // workgroups that are resident at once on this device
+    const int slots = cus * PER_CU;                             // workgroups that are resident at once on this device
     const long tiles = (long)g.tiles_m * g.tiles_n;
     if (tiles > 0x7fffffffL) return W4A4_ERR_UNSUPPORTED_SHAPE;
     const unsigned grid = (unsigned)(tiles < slots ? tiles : slots);
@@ -314,31 +335,48 @@ static int launch_one(GemmArgs &g, hipStream_t st) {
 bool small8_ok(const GemmArgs &g);                              // gemm_small.hip: the split-K kernel for small problems
 int launch_small_packed8(int out_kind, GemmArgs &g, hipStream_t st);
 
+enum { W8_128x128, W8_128x128_PAIR, W8_256x128, W8_256x256, W8_64_128x256, W8_64_128x128 };
 template <int OUT>
 static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
     switch (tile) {
-        case 0: return launch_one<2, 4, 2, 2, 2, OUT>(g, st);   // 128 x 256, two workgroups per CU
-        case 1: return launch_one<3, 2, 2, 2, 2, OUT>(g, st);   // 192 x 128, two workgroups per CU
-        default: return launch_one<2, 2, 2, 2, 3, OUT>(g, st);  // 128 x 128, three workgroups per CU
+        case W8_128x128: return launch_one<2, 2, 2, 2, 1, 128, 4, OUT>(g, st);      // alone on its CU: three steps ahead
+        case W8_128x128_PAIR: return launch_one<2, 2, 2, 2, 2, 128, 2, OUT>(g, st); // two workgroups per CU
+        case W8_256x128: return launch_one<2, 2, 4, 2, 2, 128, 3, OUT>(g, st);      // one of eight waves, two steps ahead
+        case W8_256x256: return launch_one<2, 4, 4, 2, 2, 128, 2, OUT>(g, st);      // one workgroup of eight waves per CU
+        case W8_64_128x256: return launch_one<2, 4, 2, 2, 2, 64, 3, OUT>(g, st);    // half lines, two per CU
+        default: return launch_one<2, 2, 2, 2, 3, 64, 3, OUT>(g, st);               // half lines, three per CU
     }
 }
 
-// Tile choice as for the INT4 kernel: n tiles on the busiest CU, worked on by min(n, workgroups per CU) workgroups at a
-// time, cost n * area / (rate * efficiency) with the rate of one / two / three workgroups 0.7 / 1 / 0.95 and the efficiency
-// of the three tiles 1 / 0.9 / 0.8.  Fitted to kernel times over M = 512 .. 16384 on the BERT-base and BERT-large shapes:
-// 0.8 % above the best of the three on average (128 x 256 and 192 x 128 by area alone: 7.4 %).  4096 x 1024 x 4096:
-// 128 x 128 23.8 us, 192 x 128 28.2, 128 x 256 30.4; 4096 x 3072 x 1024: 20.6, 22.4, 19.4.
+// Tile choice: n tiles on the busiest CU.  128 x 128 in pairs takes 1 (area 128 x 128) per tile and 1 / 0.39 for one that is left
+// over, a 128 x 128 tile alone on its CU with the deeper prefetch 1 / 0.4 each, 256 x 256 4 / 1.1, and for
+// long K 256 x 128 2 / 1.07 (6144 x 1024 x 4096 with its quantizer 38.7 us, 41.1 in pairs; 8192 x 1024 x 1024 20.3 | 18.2).  Fitted to the times of all
+// at eighteen token counts from 600 to 16384 on the BERT-base and BERT-large linears: 0.2 % above the best of them on
+// average, 8 % at worst.  Four linears with their quantizers against half lines in 128 x 256, 192 x 128 and 128 x 128 tiles: 800
+// tokens 63.4 -> 52.6 us, 4096 102.6 -> 91.1, 16384 314.5 -> 277.2 (BERT-large); 16384 218.5 -> 192.1 (BERT-base).
+// K in 64s but not in 128s, or below 256, keeps half lines (n tiles on the busiest CU, worked on by min(n, workgroups per CU) at a time: cost
+// n * area / (rate * efficiency), rate of one / two / three 0.7 / 1 / 0.95, efficiency of 128 x 128 0.8).
 // A few hundred 32 x 32 tiles at most go to the small-problem kernel instead (latency decides there).
 static int launch_w8(int out_kind, GemmArgs &g, hipStream_t st) {
     if (small8_ok(g)) return launch_small_packed8(out_kind, g, st);
     const long cus = device_cus();
-    auto cost = [&](int bm, int bn, int occ, double eff) {
-        const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
-        const long n = (tiles + cus - 1) / cus, together = n < occ ? n : occ;
-        return (double)n * bm * bn / ((together == 1 ? 0.7 : together == 2 ? 1.0 : 0.95) * eff);
-    };
-    const double c[3] = {cost(128, 256, 2, 1.0), cost(192, 128, 2, 0.9), cost(128, 128, 3, 0.8)};
-    const int tile = c[2] < c[0] && c[2] < c[1] ? 2 : c[1] < c[0] ? 1 : 0;
+    auto busiest = [&](int bm, int bn) { return ((long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) + cus - 1) / cus; };
+    const double n128 = (double)busiest(128, 128), n256 = (double)busiest(256, 256);
+    int tile;
+    if (g.K % 128 == 0 && g.K >= 256) {
+        const long pairs = busiest(128, 128) / 2, odd = busiest(128, 128) % 2;
+        const double pair = 2.0 * pairs + odd / 0.39, alone = g.K >= 384 ? n128 / 0.4 : 1e30, big = 4.0 * n256 / 1.1;
+        const double tall = g.K >= 2048 ? 2.0 * (double)busiest(256, 128) / 1.07 : 1e30;
+        double c = pair;
+        tile = W8_128x128_PAIR;
+        if (alone < c) { c = alone; tile = W8_128x128; }
+        if (tall < c) { c = tall; tile = W8_256x128; }
+        if (big < c) tile = W8_256x256;
+    } else {
+        const double n = (double)busiest(128, 256);
+        const double wide = 2.0 * n / (n == 1 ? 0.7 : 1.0), narrow = n128 / ((n128 == 1 ? 0.7 : n128 == 2 ? 1.0 : 0.95) * 0.8);
+        tile = narrow < wide ? W8_64_128x128 : W8_64_128x256;
+    }
     return out_kind == OUT_I32 ? launch_tile<OUT_I32>(tile, g, st) : launch_tile<OUT_F16>(tile, g, st);
 }
 

@@ -132,3 +132,23 @@ def test_small_problem_path_reads_a_column_slice_of_codes(B, orc):
     got = host(B.linear8(view, dev(sa), dev(W), dev(sw)))
     want = orc.linear8(dict(q=np.ascontiguousarray(A[:, K:2 * K]), s=sa), dict(q=W, s=sw))["out"]
     assert np.array_equal(got.view(np.uint16), want.view(np.uint16))
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (700, 1032, 384), (1153, 520, 4096), (700, 1032, 896),      # 128 x 128, one per CU: shortest K, long K, ragged
+    (700, 1032, 256), (4200, 1032, 256), (4097, 2056, 640),     # in pairs: one tile, two tiles, and five on the busiest CU
+    (4200, 1032, 2048), (4097, 1032, 2176),                     # 256 x 128: long K
+    (8100, 2040, 256), (16130, 2040, 384),                      # 256 x 256: one and two tiles per workgroup
+    (700, 1032, 128), (700, 1032, 448), (4200, 2056, 320),      # half lines: K below 256 or in 64s only, both tiles
+])
+def test_every_tile_of_the_persistent_kernel(B, M, N, K):
+    """Int32 sums equal an exact product in float64, outputs the definition's operations in fp32 (each separately rounded)."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    Aq = torch.randint(-127, 128, (M, K), dtype=torch.int8, device="cuda", generator=g)
+    Wq = torch.randint(-127, 128, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    sa, sw = torch.rand(M, device="cuda", generator=g) + 0.5, (torch.rand(N, device="cuda", generator=g) + 0.5) * 1e-4
+    bias = torch.randn(N, device="cuda", generator=g).half()
+    P = Aq.double() @ Wq.double().t().contiguous()
+    assert torch.equal(B.gemm8_i32(Aq, sa, Wq, sw).double(), P)
+    want = (P.float() * sa[:, None]) * sw[None, :] + bias.float()[None, :]
+    assert torch.equal(B.linear8(Aq, sa, Wq, sw, bias), want.half())
