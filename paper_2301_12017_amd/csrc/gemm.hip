@@ -40,10 +40,11 @@ static const Schedule kSchedules[] = {
     {"fp6_192x128", F_FP6, 1, false},
     {"fp6_128x128", F_FP6, 2, false},
     {"fp6_192x256", F_FP6, 3, false},
+    {"olay_256x256", F_OLAY, 3, false},
 };
 constexpr int kNumSchedules = sizeof(kSchedules) / sizeof(kSchedules[0]);
 enum { S_PIPE_128x256 = 1, S_PIPE_192x128, S_GEN_64x128, S_GEN_64x64, S_GEN_32x32, S_OLAY_128x256, S_OLAY_192x128,
-       S_OLAY_128x128, S_GROUP, S_SMALL, S_FP6_128x256, S_FP6_192x128, S_FP6_128x128, S_FP6_192x256 };
+       S_OLAY_128x128, S_GROUP, S_SMALL, S_FP6_128x256, S_FP6_192x128, S_FP6_128x128, S_FP6_192x256, S_OLAY_256x256 };
 
 static bool pipe_ok(const GemmArgs &g, bool grouped, int kstep = kBK) {
     // 32-bit buffer offsets and whole K steps
@@ -129,10 +130,27 @@ static double tile_cost(const GemmArgs &g, const TileRates &r, int bm, int bn, i
 
 // int8 kernel.  (12288 x 3072 x 768 + GELU 40.8 us on 192 x 128 -> 34.8 on 128 x 256; 6144 x 768 x 3072 18.3 on 128 x 128 -> 15.7
 // on 192 x 128.)  Below about 1500 tokens a tile's K loop is latency-bound and the small tile gains nothing.
+// Where K comes in whole cache lines (256 codes) 128 x 128 and 256 x 256 take them (see the kernel), and the cost is a start of some us
+// and n tiles of so many us per 128 x 128 x 1024, a tile alone on a CU somewhat more than one of a pair; at most one 128 x 128 tile per
+// CU is always the best choice.  Fitted to eighteen token counts as above, mostly behind the quantize of other activations (1 % above the
+// best tile).  Four linears with their quantizers: BERT-large 16384 tokens 245 -> 236 us, 12288 194 -> 187; BERT-base 16384 169 -> 160.
+bool olay_whole_lines(int K);
 static int pick_olay(const GemmArgs &g) {
     const long cus = device_cus();
-    const TileRates r = {1.05, 0.81, 0.93, 1.10, 0.0};
     int best = S_OLAY_128x256;
+    if (olay_whole_lines(g.K)) {
+        auto cost = [&](int bm, int bn, double start, double alone, double each) {
+            const long tiles = (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn), n = (tiles + cus - 1) / cus;
+            return start + (n == 1 ? alone : (double)n) * each * bm * bn / 16384.0 * g.K / 1024.0;
+        };
+        double c = cost(128, 256, 6.3, 1.36, 4.4);
+        const double c192 = cost(192, 128, 6.1, 1.28, 4.85), c128 = cost(128, 128, 5.7, 0.0, 4.86), c256 = cost(256, 256, 8.0, 1.0, 4.2);
+        if (c192 < c) { best = S_OLAY_192x128; c = c192; }
+        if (g.M >= 1536 && c128 < c) { best = S_OLAY_128x128; c = c128; }
+        if (c256 < c) best = S_OLAY_256x256;
+        return best;
+    }
+    const TileRates r = {1.05, 0.81, 0.93, 1.10, 0.0};
     double c = tile_cost(g, r, 128, 256, 2, 1.0, cus);
     const double c192 = tile_cost(g, r, 192, 128, 2, r.eff_192x128, cus);
     if (c192 < c) { best = S_OLAY_192x128; c = c192; }

@@ -16,14 +16,19 @@
 //     K offset in the instruction's scalar offset.  Rows past M / channels past N fall
 //     outside the descriptor and read as zero.
 //   * LDS rows are unpadded; bank conflicts are avoided by an XOR swizzle of the 16-byte
-//     slots of a row (physical slot = logical chunk ^ ((row >> 2) & 3)).
+//     slots of a row (rows that share 256 bytes of LDS share it).
 //   * Workgroups are persistent and the K steps of successive tiles form ONE stream through
-//     the three LDS stages: while the last two K steps of a tile are multiplied, the first
-//     two of the next tile are already being fetched, so a tile has no load prologue.
+//     the LDS stages: while the last K steps of a tile are multiplied, the first
+//     of the next tile are already being fetched, so a tile has no load prologue.
 //     Token scales / odd sums go to LDS by 4-byte DMA one tile ahead (the odd sums are needed
 //     by the first MFMAs of the tile), channel constants to registers at the start of the tile.
-//   * Two workgroups share a CU (2 x 74 KB of LDS), four waves of 64 x 128 each, so one
+//   * 128 x 256: two workgroups share a CU (2 x 74 KB of LDS), four waves of 64 x 128 each, so one
 //     workgroup's epilogue stores overlap the other's main loop.
+//   * K steps of 128 codes fetch 64 bytes of every row, half a cache line, and the other half is often fetched again a step
+//     later (the CU's vector cache holds 256 lines, a step touches 256 to 384).  Where K is a multiple of 256 two tiles
+//     walk K in steps of 256 codes, whole lines, with two stages: 128 x 128 (pairs of workgroups per CU) and 256 x 256
+//     (one workgroup of eight waves: 2/3 of the operand bytes per product of 128 x 256).  16384 x 1024 x 4096 52 -> 48 us, 16384 x 4096 x 1024
+//     + GELU 76.6 -> 68.1, 12288 x 768 x 3072 28.9 -> 27.4.
 #include "gemm_common.hpp"
 
 namespace w4a4 {
@@ -32,6 +37,9 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
 // s_waitcnt immediate for "vmcnt <= n", lgkmcnt and expcnt unconstrained (gfx9 encoding)
 constexpr int vmcnt_only(int n) { return (n & 0xF) | (0x7 << 4) | (0xF << 8) | (((n >> 4) & 0x3) << 14); }
+
+// ... for "vmcnt <= n and lgkmcnt == 0"
+constexpr int vmcnt_and_lds(int n) { return (n & 0xF) | (0x7 << 4) | (0x0 << 8) | (((n >> 4) & 0x3) << 14); }
 
 // One v_and per register: activations give (even codes + 8, 16 * odd codes), weights give
 // (16 * even codes, odd codes + 8); register r of one meets register r of the other.
@@ -239,19 +247,23 @@ __device__ __forceinline__ void olay_epilogue_requant(const GemmArgs &g, v16i (&
     }
 }
 
-template <int FM, int FN, int WM, int WN, int OCC, int OUT>
-__global__ __attribute__((amdgpu_flat_work_group_size(WM *WN * 64, WM *WN * 64), amdgpu_waves_per_eu(OCC, OCC)))
+// WPS: waves per SIMD (all workgroups of a CU together).  ROWB: bytes (two codes each) of a row per K step.  NS: LDS stages.
+template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int OUT>
+__global__ __attribute__((amdgpu_flat_work_group_size(WM *WN * 64, WM *WN * 64), amdgpu_waves_per_eu(WPS, WPS)))
 void gemm_olay_kernel(GemmArgs g) {
     constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
-    constexpr int ROWB = kBK / 2;                               // 64 bytes of codes per row per K step
-    constexpr int STAGE = (BM + BN) * ROWB, NS = 3;
-    constexpr int BLOCKS = (BM + BN) / 16;                      // 1 KB DMA blocks per stage
+    constexpr int STAGE = (BM + BN) * ROWB;
+    constexpr int CPR = ROWB / 16, RPB = 1024 / ROWB;           // 16-byte chunks of a row, rows of a 1 KB DMA block
+    constexpr int KS = ROWB / 32;                               // pairs of sub-steps: 64 codes, low and high halves of 32 bytes
+    constexpr int SWZ = CPR == 8 ? 1 : 2;                       // rows that share a swizzle, log2: 256 bytes of LDS
+    constexpr int BLOCKS = (BM + BN) / RPB;                     // 1 KB DMA blocks per stage
     constexpr int LD = BLOCKS / NW;                             // tile DMA instructions per wave per K step
-    constexpr int A_LD = (BM / 16) / NW;                        // the first A_LD of them fetch activations
+    constexpr int A_LD = (BM / RPB) / NW;                       // the first A_LD of them fetch activations
+    constexpr int DPS = (LD + KS - 2) / (KS - 1);               // DMA instructions per pair of sub-steps, the last one's excepted
     constexpr int NF = FM + FN, NM = FM * FN;
     constexpr int PB = BM / 64;                                 // 64-row blocks of token scales (and as many of odd sums)
-    static_assert(BLOCKS % NW == 0 && (BM / 16) % NW == 0, "DMA blocks must split evenly over the waves");
-    static_assert(NF <= NM && LD <= NM, "not enough MFMA slots to hide the memory operations");
+    static_assert(BLOCKS % NW == 0 && (BM / RPB) % NW == 0, "DMA blocks must split evenly over the waves");
+    static_assert(NF <= NM && DPS <= NM && KS % 2 == 0, "not enough MFMA slots to hide the memory operations");
     static_assert(BM % 64 == 0, "token parameters are fetched 64 rows per DMA instruction");
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -262,16 +274,17 @@ void gemm_olay_kernel(GemmArgs g) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int total = g.tiles_m * g.tiles_n, stride = gridDim.x;
-    const int KT = g.K / kBK;
+    const int KT = g.K / (2 * ROWB);
 
     // ---- global -> LDS plan (fixed for the whole kernel) -------------------------------------------
-    // DMA instruction i of this wave fills block b = wave + i*NW of a stage: tile rows 16b..16b+15.
-    // Lane l supplies physical slot (r = l>>2, pc = l&3) of the block = logical chunk pc ^ ((row>>2)&3).
+    // DMA instruction i of this wave fills block b = wave + i*NW of a stage: tile rows RPB b .. RPB b + RPB-1.
+    // Lane l supplies physical slot (r = l / CPR, pc = l % CPR) of the block = logical chunk pc ^ (row >> SWZ) % CPR:
+    // the eight lanes of one LDS cycle, rows r .. r+7 of one chunk, fall into eight different 16-byte slots of 256 bytes.
     int voff[LD];
 #pragma unroll
     for (int i = 0; i < LD; ++i) {
-        const int row = (wave + i * NW) * 16 + (lane >> 2);
-        const int c = (lane & 3) ^ ((row >> 2) & 3);
+        const int row = (wave + i * NW) * RPB + lane / CPR;
+        const int c = (lane % CPR) ^ ((row >> SWZ) & (CPR - 1));
         if (i < A_LD) {
             voff[i] = row * (int)g.lda + c * 16;
         } else {
@@ -327,8 +340,8 @@ void gemm_olay_kernel(GemmArgs g) {
 
     // ---- operand fragments -----------------------------------------------------------------------
     // lane (r = lane&31, h = lane>>5) reads logical chunk ks*2 + h of its row
-    const int swz = ((lane & 31) >> 2) & 3;
-    const int rd0 = (lane & 31) * ROWB + (((lane >> 5) ^ swz) << 4);   // ks = 0;  ks = 1 is rd0 ^ 32
+    const int swz = ((lane & 31) >> SWZ) & (CPR - 1);
+    const int rd0 = (lane & 31) * ROWB + (((lane >> 5) ^ swz) << 4);   // ks = 0;  ks is rd0 ^ (32 * ks)
     int frag_off[NF];
 #pragma unroll
     for (int f = 0; f < FM; ++f) frag_off[f] = (wm * FM * 32 + f * 32) * ROWB + rd0;
@@ -366,9 +379,9 @@ void gemm_olay_kernel(GemmArgs g) {
     int m0 = (tile / g.tiles_n) * BM, n0 = (tile % g.tiles_n) * BN;
     __amdgpu_buffer_rsrc_t a_cur = a_desc(m0), b_cur = b_desc(n0);
 #pragma unroll
-    for (int i = 0; i < LD; ++i) dma_one(i, 0, a_cur, b_cur, 0);
+    for (int s = 0; s < NS - 1; ++s)
 #pragma unroll
-    for (int i = 0; i < LD; ++i) dma_one(i, 1, a_cur, b_cur, ROWB);
+        for (int i = 0; i < LD; ++i) dma_one(i, s, a_cur, b_cur, s * ROWB);
     dma_params(m0, 0);
     __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
     __builtin_amdgcn_s_barrier();
@@ -424,7 +437,7 @@ void gemm_olay_kernel(GemmArgs g) {
 #pragma unroll
         for (int f = 0; f < NF; ++f) U0[f] = widen_lo(f, P0[f]);
 
-        // ---- main loop: one iteration = 128 codes of K = four sub-steps of NM MFMAs -------------
+        // ---- main loop: one iteration = 2 ROWB codes of K = 2 KS sub-steps of NM MFMAs -------------
         // The instruction order below is the intended issue order; the scheduling barriers keep
         // the compiler from regrouping it.  Slot k of a sub-step issues MFMA k and, behind it, the
         // widening of fragment k for the NEXT sub-step plus at most one LDS read and one DMA.
@@ -444,52 +457,46 @@ void gemm_olay_kernel(GemmArgs g) {
             constexpr bool FIRST = decltype(first_tag)::value; // first K step of the tile
             constexpr bool LAST = decltype(last_tag)::value;   // last K step of the tile
             const int nxt = cur == NS - 1 ? 0 : cur + 1;       // stage of stream step +1
-            const int nx2 = nxt == NS - 1 ? 0 : nxt + 1;       // stage of stream step +2 (= step -1)
-            // stream step +2 is K step kt+2 of this tile, or K step kt+2-KT of the next one (when there
+            const int free = cur == 0 ? NS - 1 : cur - 1;      // stage of stream step +NS-1 (= step -1)
+            // stream step +NS-1 is K step kt+NS-1 of this tile, or K step kt+NS-1-KT of the next one (when there
             // is none: a harmless in-bounds re-read, so that the load counting stays uniform)
-            const bool own = !LAST && kt + 2 < KT;
+            const bool own = !LAST && kt + NS - 1 < KT;
             const __amdgpu_buffer_rsrc_t ra = own ? a_cur : a_nxt, rb = own ? b_cur : b_nxt;
-            const int so = (own ? kt + 2 : kt + 2 - KT) * ROWB;
-            // sub-step 0: multiply (ks 0, low); widen (ks 0, high) -> U1; fetch ks 1 -> P1; request
-            //             stream step +2 into the stage every wave finished reading before the last barrier.
+            const int so = (own ? kt + NS - 1 : kt + NS - 1 - KT) * ROWB;
 #pragma unroll
-            for (int k = 0; k < NM; ++k) {
-                if constexpr (FIRST) { W4A4_SLOT_BEGIN_FIRST(U0, k) } else { W4A4_SLOT_BEGIN(U0, k) }
-                if (k < NF) U1[k] = widen_hi(k, P0[k]);
-                if (k < NF) P1[k] = read_frag(k, cur, 1);
-                if (k < LD) dma_one(k, nx2, ra, rb, so);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // sub-step 1: multiply (ks 0, high); widen (ks 1, low) -> U0
+            for (int ks = 0; ks < KS; ++ks) {
+                u32x4 (&Pc)[NF] = ks & 1 ? P1 : P0;
+                u32x4 (&Pn)[NF] = ks & 1 ? P0 : P1;
+                // multiply (ks, low); widen (ks, high) -> U1; fetch ks + 1; request stream step +NS-1 into the
+                // stage every wave finished reading before the last barrier.  In the last pair this wave's loads of
+                // stream step +1 have landed (vmcnt) and its reads of this one have returned, and after the barrier
+                // everyone's have: fetch the next step's first operands.  At the end of a tile ALL prefetched steps of
+                // the next tile are waited for, so that the next tile's first barrier does not have to wait for this
+                // tile's stores; the next tile reads its first fragments itself.
 #pragma unroll
-            for (int k = 0; k < NM; ++k) {
-                W4A4_SLOT_BEGIN(U1, k)
-                if (k < NF) U0[k] = widen_lo(k, P1[k]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // sub-step 2: multiply (ks 1, low); widen (ks 1, high) -> U1; this wave's loads of stream
-            //             step +1 have landed (vmcnt), and after the barrier everyone's have: fetch its ks 0.
-            //             At the end of a tile BOTH prefetched steps of the next tile are waited for, so
-            //             that the next tile's first barrier does not have to wait for this tile's stores;
-            //             the next tile reads its first fragments itself.
-#pragma unroll
-            for (int k = 0; k < NM; ++k) {
-                W4A4_SLOT_BEGIN(U0, k)
-                if (k < NF) U1[k] = widen_hi(k, P1[k]);
-                if (k == kBarSlot) {
-                    __builtin_amdgcn_s_waitcnt(vmcnt_only(LAST ? 0 : LD));
-                    __builtin_amdgcn_s_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                for (int k = 0; k < NM; ++k) {
+                    if constexpr (FIRST) { if (ks == 0) { W4A4_SLOT_BEGIN_FIRST(U0, k) } else { W4A4_SLOT_BEGIN(U0, k) } } else { W4A4_SLOT_BEGIN(U0, k) }
+                    if (k < NF) U1[k] = widen_hi(k, Pc[k]);
+                    if (ks < KS - 1) {
+                        if (k < NF) Pn[k] = read_frag(k, cur, ks + 1);
+                        if (k < DPS && ks * DPS + k < LD) dma_one(ks * DPS + k, free, ra, rb, so);
+                    } else {
+                        if (k == kBarSlot) {
+                            __builtin_amdgcn_s_waitcnt(vmcnt_and_lds(LAST ? 0 : (NS - 2) * LD));
+                            __builtin_amdgcn_s_barrier();
+                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                        }
+                        if (!LAST && k >= kBarSlot) Pn[k - kBarSlot] = read_frag(k - kBarSlot, nxt, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                if (!LAST && k >= kBarSlot) P0[k - kBarSlot] = read_frag(k - kBarSlot, nxt, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // sub-step 3: multiply (ks 1, high); widen (next step's ks 0, low) -> U0
+                // multiply (ks, high); widen (ks + 1, low) -> U0
 #pragma unroll
-            for (int k = 0; k < NM; ++k) {
-                W4A4_SLOT_BEGIN(U1, k)
-                if (!LAST && k < NF) U0[k] = widen_lo(k, P0[k]);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int k = 0; k < NM; ++k) {
+                    W4A4_SLOT_BEGIN(U1, k)
+                    if ((ks < KS - 1 || !LAST) && k < NF) U0[k] = widen_lo(k, Pn[k]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
             cur = nxt;
         };
@@ -541,26 +548,27 @@ void gemm_olay_kernel(GemmArgs g) {
 // of a row panel wait for each other, so every workgroup of their grid must be resident: the grid is sized from
 // what the runtime reports for this kernel (hipOccupancyMaxActiveBlocksPerMultiprocessor), capped by the
 // occupancy the kernel was compiled for, and a panel's tiles_n tiles must fit into one XCD's share of it.
-template <int FM, int FN, int WM, int WN, int OCC, int OUT>
+template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int OUT>
 struct OlayLaunch {
-    static constexpr int BM = WM * FM * 32, BN = WN * FN * 32;
-    static constexpr size_t lds = 3 * (size_t)(BM + BN) * (kBK / 2) + 2 * 2 * BM * 4 + (OUT == OUT_Q4 || OUT == OUT_Q4M ? 1024 : 0);
+    static constexpr int BM = WM * FM * 32, BN = WN * FN * 32, PER_CU = WPS * 4 / (WM * WN);
+    static constexpr size_t lds = NS * (size_t)(BM + BN) * ROWB + 2 * 2 * BM * 4 + (OUT == OUT_Q4 || OUT == OUT_Q4M ? WM * WN * 256 : 0);
+    static_assert(lds * PER_CU <= 160 * 1024, "the workgroups of a CU share 160 KB of LDS");
     static KernelState &state() { static KernelState ks; return ks; }
-    static auto kernel() { return gemm_olay_kernel<FM, FN, WM, WN, OCC, OUT>; }
+    static auto kernel() { return gemm_olay_kernel<FM, FN, WM, WN, WPS, ROWB, NS, OUT>; }
     // resident workgroups on the current device (-1: HIP error)
     static int slots() {
         const int cus = prepare_kernel(reinterpret_cast<const void *>(kernel()), lds, state());
         if (cus < 0) return -1;
-        if (OUT != OUT_Q4 && OUT != OUT_Q4M) return cus * OCC;    // no workgroup waits for another: any grid is safe
+        if (OUT != OUT_Q4 && OUT != OUT_Q4M) return cus * PER_CU;    // no workgroup waits for another: any grid is safe
         const int occ = resident_per_cu(reinterpret_cast<const void *>(kernel()), WM * WN * 64, lds, state());
         if (occ < 0) return -1;
-        return cus * (occ < OCC ? occ : OCC);
+        return cus * (occ < PER_CU ? occ : PER_CU);
     }
 };
 
-template <int FM, int FN, int WM, int WN, int OCC, int OUT>
+template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int OUT>
 static int launch_one(GemmArgs &g, hipStream_t st) {
-    using L = OlayLaunch<FM, FN, WM, WN, OCC, OUT>;
+    using L = OlayLaunch<FM, FN, WM, WN, WPS, ROWB, NS, OUT>;
     g.tiles_m = (g.M + L::BM - 1) / L::BM;
     g.tiles_n = (g.N + L::BN - 1) / L::BN;
     const int slots = L::slots();
@@ -581,21 +589,63 @@ static int launch_one(GemmArgs &g, hipStream_t st) {
     return launch_status();
 }
 
+// Whether the kernel can walk K in steps of whole cache lines.
+bool olay_whole_lines(int K) { return K % 256 == 0 && K >= 512; }
+
+template <int OUT>
+using Olay128x256 = OlayLaunch<2, 4, 2, 2, 2, 64, 3, OUT>;
+template <int OUT>
+static int launch_128x256(GemmArgs &g, hipStream_t st) { return launch_one<2, 4, 2, 2, 2, 64, 3, OUT>(g, st); }
+template <int OUT>
+static int launch_256x256_lines(GemmArgs &g, hipStream_t st) { return launch_one<2, 4, 4, 2, 2, 128, 2, OUT>(g, st); }
+
 // Column tiles of a row panel that the fused requantize of the persistent kernel can keep co-resident on the
 // current device (0 = the kernel does not fit, -1 = HIP error): the limit on ceil(N / 256).
 int olay_requant_max_tiles_n(bool mfma_out) {
-    const int slots = mfma_out ? OlayLaunch<2, 4, 2, 2, 2, OUT_Q4M>::slots() : OlayLaunch<2, 4, 2, 2, 2, OUT_Q4>::slots();
+    const int slots = mfma_out ? Olay128x256<OUT_Q4M>::slots() : Olay128x256<OUT_Q4>::slots();
     return slots < 0 ? -1 : (slots & ~(kXcd - 1)) / kXcd;
 }
 
 template <int OUT>
 static int launch_variant(int variant, GemmArgs &g, hipStream_t st) {
+    const bool lines = olay_whole_lines(g.K);
     switch (variant) {
-        case 0: return launch_one<2, 4, 2, 2, 2, OUT>(g, st);   // 128 x 256, two workgroups per CU
-        case 1: return launch_one<3, 2, 2, 2, 2, OUT>(g, st);   // 192 x 128, two workgroups per CU
-        case 2: return launch_one<2, 2, 2, 2, 3, OUT>(g, st);   // 128 x 128, three workgroups per CU: mid-sized problems
+        case 0: return launch_128x256<OUT>(g, st);                  // two workgroups per CU
+        case 1: return launch_one<3, 2, 2, 2, 2, 64, 3, OUT>(g, st);   // 192 x 128, two workgroups per CU
+        case 2:                                                     // 128 x 128, two or three workgroups per CU
+            // whole lines leave two stages, i.e. one step of prefetch, too little for a tile that is alone on its CU
+            // (4096 x 1024 x 4096 with its quantizer 25.7 us against 24.9, 3000 x 1024 x 1024 14.0 | 11.8)
+            return lines && (long)((g.M + 127) / 128) * ((g.N + 127) / 128) > device_cus()
+                       ? launch_one<2, 2, 2, 2, 2, 128, 2, OUT>(g, st) : launch_one<2, 2, 2, 2, 3, 64, 3, OUT>(g, st);
+        case 3:                                                     // 256 x 256, one workgroup of eight waves per CU
+            return lines ? launch_256x256_lines<OUT>(g, st) : launch_one<2, 4, 4, 2, 2, 64, 3, OUT>(g, st);
         default: return W4A4_ERR_INVALID_ARG;
     }
+}
+
+// Tile of the requantizing outputs.  The waves of a 256 x 256 tile wait for their row panel with nothing else on the CU, so it pays
+// only where an XCD's 32 workgroups hold whole panels (up to two of them idle) and the rounds come out even.  In units of about 1 us: a
+// round of 256 x 256 tiles 15 per 1024 codes of K and 3 (4.5 with GELU) for its epilogue, a 128 x 256 tile 8.8 and 1.5 (one alone on a CU
+// 1.6 times that), before them 6.6 and 4.2.  128 x 256 | 256 x 256: 32768 x 1024 x 4096 104.6 | 94.6 us, 16000 x 1024 x 4096 56.0 | 50.8,
+// 8000 x 1024 x 4096 33.8 | 42.1, 32768 x 4096 x 1024 + GELU 168.9 | 162.4; with panels of twelve tiles, 32768 x 3072 x 1024 116 | 119.
+template <int OUT>
+static bool requant_takes_256x256(const GemmArgs &g) {
+    using L = OlayLaunch<2, 4, 4, 2, 2, 128, 2, OUT>;
+    if (!olay_whole_lines(g.K)) return false;
+    const int tn = (g.N + 255) / 256, slots = L::slots();
+    if (slots < kXcd || tn > slots / kXcd || (slots / kXcd) % tn > 2) return false;
+    auto per_cu = [&](int bm) {                                  // tiles on the busiest CU
+        const int panels = ((g.M + bm - 1) / bm + kXcd - 1) / kXcd;
+        return (panels * tn + slots / kXcd - 1) / (slots / kXcd);
+    };
+    const double k = g.K / 1024.0;
+    const int n = per_cu(128);
+    return 6.6 + per_cu(256) * (15.0 * k + (g.act == W4A4_ACT_GELU ? 4.5 : 3.0)) < 4.2 + (n / 2 * 2 + n % 2 * 1.6) * (8.8 * k + 1.5);
+}
+template <int OUT>
+static int launch_requant(int variant, GemmArgs &g, hipStream_t st) {
+    if (variant != 0) return W4A4_ERR_INVALID_ARG;
+    return requant_takes_256x256<OUT>(g) ? launch_256x256_lines<OUT>(g, st) : launch_128x256<OUT>(g, st);
 }
 
 // Requires: MFMA operand layout on both sides (symmetric codes, per-channel weight scales),
@@ -605,8 +655,8 @@ int launch_olay(int variant, int out_kind, GemmArgs &g, hipStream_t st) {
         case OUT_F16: return launch_variant<OUT_F16>(variant, g, st);
         case OUT_F32: return launch_variant<OUT_F32>(variant, g, st);
         case OUT_I32: return launch_variant<OUT_I32>(variant, g, st);
-        case OUT_Q4: return variant == 0 ? launch_one<2, 4, 2, 2, 2, OUT_Q4>(g, st) : W4A4_ERR_INVALID_ARG;
-        case OUT_Q4M: return variant == 0 ? launch_one<2, 4, 2, 2, 2, OUT_Q4M>(g, st) : W4A4_ERR_INVALID_ARG;
+        case OUT_Q4: return launch_requant<OUT_Q4>(variant, g, st);
+        case OUT_Q4M: return launch_requant<OUT_Q4M>(variant, g, st);
         default: return W4A4_ERR_INVALID_ARG;
     }
 }

@@ -426,3 +426,32 @@ def test_kernel_timer_stamps_one_gemm(B, layout, M, N, K):
     again = host(B.linear(A, Q, None, 0))                         # not armed any more
     assert t.elapsed_ms() == ms
     assert np.array_equal(plain.view(np.uint16), again.view(np.uint16))
+
+
+@pytest.mark.parametrize("M,N,K,rlayout,gelu", [(2100, 4096, 1280, MFMA, 0), (2304, 4000, 1792, MFMA, 1), (1100, 8192, 1280, 0, 0),
+                                                (9001, 1024, 1280, MFMA, 0), (33000, 256, 1792, 0, 1)])
+def test_fused_requantize_on_256_row_panels(B, M, N, K, rlayout, gelu):
+    """Sizes that the fused requantize takes in 256 x 256 tiles (K in whole cache lines, whole panels per XCD): ragged rows and
+    columns, the widest and the narrowest panel.  Equal to the two-kernel path bit for bit; the bounded wait gives up cleanly."""
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    X = torch.randn((M, K), device="cuda", generator=gen).half()
+    W = (torch.randn((N, K), device="cuda", generator=gen) * 0.02).half()
+    bias = (torch.randn((N,), device="cuda", generator=gen) * 0.01).half()
+    A, Q = B.quantize_act(X, SYM, layout=MFMA), B.quantize_weight(W, SYM, 0, layout=MFMA)
+    assert B.linear_workspace_bytes(A, Q, requant_layout=rlayout) < 8 * M                 # fused
+    run = lambda schedule=0: B.linear(A, Q, bias, gelu, requant=True, requant_layout=rlayout, schedule=schedule)
+    plain = run(B.schedule_number("olay_128x128"))                                        # fp32 rows, then the row quantizer
+    for _ in range(3):
+        fused = run()
+        assert torch.equal(fused.q, plain.q)
+        assert torch.equal(fused.scale.view(torch.int32), plain.scale.view(torch.int32))
+        if rlayout == MFMA:
+            assert torch.equal(fused.osum.reshape(M), plain.osum.reshape(M))
+    assert B.fused_fault_check() is False
+    B.debug_fused_wait(2, 1)
+    try:
+        run()
+        assert B.fused_fault_check() is True
+    finally:
+        B.debug_fused_wait()
+    assert torch.equal(run().q, plain.q) and B.fused_fault_check() is False
