@@ -26,6 +26,7 @@
 //   * the int32 partial sums of the waves are added in LDS and the accumulator registers of the
 //     tile are dealt round robin to the waves for the epilogue.
 #include "gemm_common.hpp"
+#include "layer.hpp"
 
 namespace w4a4 {
 
@@ -41,6 +42,10 @@ struct SmallArgs {
     const __half *bias; int act;
     __half *out;                     // [M, N]
     int M, N, K, tiles_n;
+    // LayerNorm form: the activations are LN(X + R) gamma + beta in fp16, which also go to Y
+    const __half *R, *gamma, *beta;  // [M, K] dense, [K], [K]
+    float eps;
+    __half *Y;                       // [M, K]
 };
 
 // 16-byte chunks held by one lane: of its token row (K <= 4096: 512 chunks over 2 NW * 32 / TM lanes), and of
@@ -73,6 +78,75 @@ __device__ __forceinline__ void codes8(const u32x4 &x, float inv, uint32_t &even
     }
 }
 
+// The LayerNorm form.  X + R, normalised, scaled and shifted: bit for bit what layernorm_quantize_kernel makes of a row of K = 512,
+// 768 or 1024, whose thirty-two lanes hold chunks l + 32 it.  Here LPR = 32 lanes hold the same chunks, or sixteen hold
+// l + 16 i, of which the even i are lane l's there and the odd i lane l + 16's: the sums are formed apart and joined last.
+// Every operation is rounded as there; v_fma_mix_f32 takes its fp16 operands without converting them first (with a factor
+// of 1 or an addend of -0, which leave one rounding).  On return x holds the row's fp16 values.
+__device__ __forceinline__ float mix_add(uint32_t a, uint32_t b, int hi) {          // fp16 half of a + fp16 half of b
+    float d;
+    if (hi) asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(a), "v"(b));
+    else asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+__device__ __forceinline__ float mix_mul(float y, uint32_t g, int hi) {             // y * fp16 half of g
+    float d;
+    const float nzero = -0.0f;
+    if (hi) asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]" : "=v"(d) : "v"(y), "v"(g), "v"(nzero));
+    else asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,1,0]" : "=v"(d) : "v"(y), "v"(g), "v"(nzero));
+    return d;
+}
+__device__ __forceinline__ float mix_add_half(float y, uint32_t b, int hi) {        // y + fp16 half of b
+    float d;
+    if (hi) asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(d) : "v"(y), "v"(b));
+    else asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(d) : "v"(y), "v"(b));
+    return d;
+}
+template <int LPR>
+__device__ __forceinline__ float row_total(float s0, float s1) {
+    auto add = [](float p, float q) { return p + q; };
+    if constexpr (LPR == 32) return lanes_reduce<32>(s0, add);
+    return lanes_reduce<16>(s0, add) + lanes_reduce<16>(s1, add);
+}
+template <int LPR, int XCH, int K>
+__device__ __forceinline__ void layernorm_row(u32x4 (&x)[XCH], const u32x4 (&r)[XCH], const u32x4 (&g)[XCH], const u32x4 (&b)[XCH], float eps) {
+    static_assert((LPR == 16 || LPR == 32) && XCH * LPR * 8 == K, "lanes of a row");
+    float v[XCH][8];
+    constexpr float inv_k = 1.0f / (float)K;
+    float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+    for (int i = 0; i < XCH; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[i][e] = mix_add(x[i][e / 2], r[i][e / 2], e & 1);
+            if (LPR == 32 || i % 2 == 0) s0 += v[i][e];
+            else s1 += v[i][e];
+        }
+    const float mean = row_total<LPR>(s0, s1) * inv_k;
+    s0 = s1 = 0.0f;
+#pragma unroll
+    for (int i = 0; i < XCH; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[i][e] = v[i][e] - mean;
+            const float d2 = v[i][e] * v[i][e];
+            if (LPR == 32 || i % 2 == 0) s0 += d2;
+            else s1 += d2;
+        }
+    const float var = row_total<LPR>(s0, s1) * inv_k;
+    const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll
+    for (int i = 0; i < XCH; ++i)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            float y[2];
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) y[hi] = mix_add_half(mix_mul(v[i][2 * p + hi] * rstd, g[i][p], hi), b[i][p], hi);
+            const __half2 h = __floats2half2_rn(y[0], y[1]);
+            x[i][p] = *reinterpret_cast<const uint32_t *>(&h);
+        }
+}
+
 // NW waves, FN column fragments of 32 channels, TM = 32 or 16 tokens per workgroup (with 16 the upper
 // half of the MFMA rows repeats the lower one and is not stored), WLDS: the weight tile is staged in LDS.
 // PACKED: the activations arrive already quantized (packed codes + token scales, the output of
@@ -82,14 +156,18 @@ __device__ __forceinline__ void codes8(const u32x4 &x, float inv, uint32_t &even
 // byte when PACKED), the weights are one int8 code per byte, and both go into the MFMA as they are (the
 // sums hold P).
 // ASYM (packed codes only): unsigned codes, one weight group; the sums hold P and the epilogue adds the zero-point terms.
-template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false>
+// LNK: 0, or K (512, 768 or 1024): the activations are the LayerNorm of X + R, which every workgroup forms for its tokens; the
+// first column tile stores them.
+template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false, int LNK = 0>
 __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     constexpr int NT = NW * 64, LPR = NT / TM;                  // LPR consecutive lanes share a token in pass 1
     constexpr int RV = TM / 2;                                  // accumulator registers per fragment that hold real rows
     constexpr int R = RV * FN;                                  // ... of the tile
     constexpr int RPW = (R + NW - 1) / NW;                      // ... finished by one wave
     constexpr int WCH = WLDS ? small_wchunks(NW) : 1;
-    constexpr int XCH = PACKED ? 1 : small_xchunks(TM);
+    constexpr int XCH = PACKED ? 1 : LNK ? LNK / 8 / LPR : small_xchunks(TM);
+    constexpr bool LN = LNK != 0;
+    static_assert(!LN || (!PACKED && !W8 && NW == 8), "fp16 activations of up to 1024 features");
     constexpr int ACH = PACKED ? (W8 ? 8 : 4) : 1;              // 16-byte chunks of the packed activation tile per lane
     constexpr bool NIBBLES = PACKED && !W8;                     // activation codes arrive two per byte
     static_assert(!ASYM || NIBBLES, "unsigned codes arrive packed");
@@ -111,9 +189,10 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
 
     // ---- requests, in the order they are needed: activation rows, weights, channel constants ----------------
     const int row = tid / LPR, c0 = tid % LPR;
-    const int nchunks = a.K / 8;                                // 16-byte chunks of an activation row
+    const int nchunks = LN ? LNK / 8 : a.K / 8;                 // 16-byte chunks of an activation row
     const int wcpr = W8 ? a.K / 16 : a.K / 32;                  // 16-byte chunks of a row of weight codes
     u32x4 x[XCH];
+    [[maybe_unused]] u32x4 rx[LN ? XCH : 1], gx[LN ? XCH : 1], bx[LN ? XCH : 1];
     u32x4 ast[ACH];
     int arow_i[ACH];
     uint32_t adst_i[ACH];
@@ -122,6 +201,20 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
 #pragma unroll
         for (int i = 0; i < XCH; ++i)               // (chunks past the row are requested but never used)
             if (i * LPR < nchunks) x[i] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, base + (uint32_t)(c0 + i * LPR) * 16, 0, 0);
+        if constexpr (LN) {
+            const __amdgpu_buffer_rsrc_t r_rsrc = make_rsrc(a.R, (uint32_t)((long)a.M * a.K * 2));
+            const __amdgpu_buffer_rsrc_t g_rsrc = make_rsrc(a.gamma, (uint32_t)a.K * 2u), be_rsrc = make_rsrc(a.beta, (uint32_t)a.K * 2u);
+            const uint32_t rbase = (uint32_t)min(m0 + row, a.M - 1) * (uint32_t)a.K * 2u;
+#pragma unroll
+            for (int i = 0; i < XCH; ++i)
+                if (i * LPR < nchunks) rx[i] = __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, rbase + (uint32_t)(c0 + i * LPR) * 16, 0, 0);
+#pragma unroll
+            for (int i = 0; i < XCH; ++i)
+                if (i * LPR < nchunks) {
+                    gx[i] = __builtin_amdgcn_raw_buffer_load_b128(g_rsrc, (uint32_t)(c0 + i * LPR) * 16, 0, 0);
+                    bx[i] = __builtin_amdgcn_raw_buffer_load_b128(be_rsrc, (uint32_t)(c0 + i * LPR) * 16, 0, 0);
+                }
+        }
     } else {
         // the packed tile, coalesced like the weight tile below (rows past M fall outside the descriptor: zeros)
         const int stepq = NT / wcpr, stepr = NT % wcpr;
@@ -191,6 +284,14 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
         for (int i = 0; i < ACH; ++i)
             if (i * NT < TM * wcpr && arow_i[i] < TM) *reinterpret_cast<u32x4 *>(codes + adst_i[i]) = ast[i];
     } else {
+        if constexpr (LN) {
+            layernorm_row<LPR, XCH, LNK>(x, rx, gx, bx, a.eps);
+            if (n0 == 0 && m0 + row < a.M) {
+#pragma unroll
+                for (int i = 0; i < XCH; ++i)
+                    if (i * LPR < nchunks) *reinterpret_cast<u32x4 *>(a.Y + (long)(m0 + row) * a.K + (c0 + i * LPR) * 8) = x[i];
+            }
+        }
         typedef _Float16 h2 __attribute__((ext_vector_type(2)));
         uint32_t zero = 0;
         h2 mx = *reinterpret_cast<const h2 *>(&zero);
@@ -333,14 +434,14 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     }
 }
 
-template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false>
+template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false, int LNK = 0>
 static int launch_small(SmallArgs &a, hipStream_t st) {
     a.tiles_n = (a.N + 32 * FN - 1) / (32 * FN);
     const long tiles = (long)((a.M + TM - 1) / TM) * a.tiles_n;
     if (tiles > 0x7fffffffL) return W4A4_ERR_UNSUPPORTED_SHAPE;
     const size_t lds = TM * (size_t)((PACKED && !W8 ? a.K / 2 : a.K) + 16) + (WLDS ? 32 * FN * (size_t)((W8 ? a.K : a.K / 2) + 16) : 0) +
                        (size_t)(TM / 2) * FN * 64 * 4 + TM * (ASYM ? 12 : 4);
-    auto kern = linear_f16act_kernel<NW, FN, TM, WLDS, PACKED, W8, ASYM>;
+    auto kern = linear_f16act_kernel<NW, FN, TM, WLDS, PACKED, W8, ASYM, LNK>;
     static KernelState ks;
     if (prepare_kernel(reinterpret_cast<const void *>(kern), lds, ks) < 0) return W4A4_ERR_HIP;
     launch_gemm(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, st, a);
@@ -371,6 +472,32 @@ static int small_dispatch(SmallArgs &a, hipStream_t st) {
     if (K > 384) W4A4_SMALL(8);
     W4A4_SMALL(4);
 #undef W4A4_SMALL
+}
+
+// The LayerNorm form (layer.hpp): the tiles of small_dispatch, eight waves, the weight tile in LDS (K <= 1024: it fits).
+template <int K>
+static int launch_layernorm(SmallArgs &a, hipStream_t st) {
+    const long t32 = (long)((a.M + 31) / 32) * ((a.N + 31) / 32);
+    if (t32 > 256) return launch_small<8, 2, 32, true, false, false, false, K>(a, st);
+    if (t32 <= 128) return launch_small<8, 1, 16, true, false, false, false, K>(a, st);
+    return launch_small<8, 1, 32, true, false, false, false, K>(a, st);
+}
+int linear_layernorm_f16act(const LnArgs &ln, const w4a4_weight &W, const w4a4_epilogue &ep, void *out, hipStream_t st) {
+    SmallArgs a{};
+    a.X = ln.X; a.ldx = ln.ldx; a.R = ln.R; a.gamma = ln.gamma; a.beta = ln.beta; a.eps = ln.eps; a.Y = ln.Y;
+    a.Wq = W.q; a.ldw = ln.K / 2; a.sw = W.scale;
+    a.bias = static_cast<const __half *>(ep.bias_f16); a.act = ep.act;
+    a.out = static_cast<__half *>(out);
+    a.M = ln.M; a.N = W.N; a.K = ln.K;
+    return ln.K == 512 ? launch_layernorm<512>(a, st) : ln.K == 768 ? launch_layernorm<768>(a, st) : launch_layernorm<1024>(a, st);
+}
+bool linear_layernorm_f16act_ok(const LnArgs &ln, const w4a4_weight &W, const w4a4_epilogue &ep, const void *out) {
+    const int M = ln.M, K = ln.K, N = W.N;
+    if ((K != 512 && K != 768 && K != 1024) || ln.ldx != K || !ln.R || N % 8) return false;
+    for (const void *p : {static_cast<const void *>(ln.X), static_cast<const void *>(ln.R), static_cast<const void *>(ln.gamma),
+                          static_cast<const void *>(ln.beta), static_cast<const void *>(ln.Y), static_cast<const void *>(W.q), out})
+        if (!p || !aligned16(p)) return false;
+    return W.scale && (long)M * K * 2 < 0x7fffffffL && (long)N * (K / 2) < 0x7fffffffL && ((long)M + 32) * N * 2 < 0x7fffffffL;
 }
 
 // The same kernel on activations that are already quantized (canonical packed codes + token scales): the

@@ -23,6 +23,11 @@ enum LnCodes { LN_CODES_NONE, LN_CODES_F32, LN_CODES_F16 };
 // Launches the kernel for symmetric codes in `layout`; the caller has checked the arguments as w4a4_layernorm_quantize does.
 int layernorm_rows(const LnArgs &a, int layout, int codes, hipStream_t st);
 
+// w4a4_linear_f16act on the fp16 result of a LayerNorm with residual, which is formed in the same launch and goes to ln.Y (ln.q and the
+// code sums are not used).  Symmetric per-channel weights in the canonical layout; _ok: the sizes and pointers it takes.
+bool linear_layernorm_f16act_ok(const LnArgs &ln, const w4a4_weight &W, const w4a4_epilogue &ep, const void *out);
+int linear_layernorm_f16act(const LnArgs &ln, const w4a4_weight &W, const w4a4_epilogue &ep, void *out, hipStream_t st);
+
 // Words that a requantizing w4a4_linear needs cleared (none if its requantize is not fused), and that call for a caller
 // whose previous kernel on the stream has cleared them.
 struct ClearRanges { uint32_t *p0, *p1; int n0, n1; };

@@ -303,3 +303,14 @@ def test_layer_takes_the_fp6_layout_from_many_tokens_on(B, shape, fp6):
         for strategy in (15, 31, 31 | 32, 7):
             assert torch.equal(L(d["X"], strategy), L0(d["X"], strategy)), strategy
     assert B.fused_fault_check() is False
+
+
+@pytest.mark.parametrize("shape", [(1, 17, 8, 512, 2048), (1, 3, 16, 1024, 256), (1, 45, 12, 768, 3072), (3, 15, 8, 512, 3072),
+                                   (5, 31, 12, 768, 3072), (2, 50, 16, 1024, 4096), (1, 31, 16, 1024, 4096)])
+def test_layernorm_inside_ffn1(B, shape):
+    """Few tokens: LayerNorm 1 is formed inside FFN1's kernel, in tiles of 16 x 32, 32 x 32 and 32 x 64, with ragged tokens: the
+    layer equals the entry points it is made of (a LayerNorm launch of its own) bit for bit."""
+    batch, seq, heads, h, f = shape
+    for seed, strategy in ((1, 15), (2, 7)):
+        t, d, L = _layer(B, seed, batch, seq, heads, h, f)
+        assert torch.equal(L(d["X"], strategy), _blocks(B, L, d, strategy))
