@@ -438,6 +438,22 @@ int w4a4_linear(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep
                 void *out, float *out_scale, float *out_zero, int32_t *out_gsum,
                 void *workspace, size_t workspace_bytes, void *stream);
 
+/* A chain of requantizing linears: step i runs w4a4_linear(requant = 1, symmetric codes, the layout of the weights) on the
+ * W.K columns from in_first on of step i-1's output (step 0: on A, in_first 0).  All weights are symmetric and in A's layout; a
+ * column slice starts at a multiple of 32 (FP6: 64) columns, in the MFMA layout it is one of W.N / W.K equal slices.  The last step's codes, scales
+ * and (MFMA layout) odd-position code sums [M] go to out, out_scale and out_osum, everything between into the
+ * workspace (256-byte aligned, w4a4_linear_chain_workspace_bytes large; one call per workspace at a time).  Same bits as
+ * the calls one by one; what all steps count in is cleared by one launch instead of one per step. */
+typedef struct {
+    w4a4_weight W;
+    const void *bias_f16;      /* [W.N] or NULL */
+    int act;
+    int in_first;
+} w4a4_chain_step;
+size_t w4a4_linear_chain_workspace_bytes(const w4a4_act *A, const w4a4_chain_step *steps, int n);
+int w4a4_linear_chain(const w4a4_act *A, const w4a4_chain_step *steps, int n, void *out, float *out_scale, int32_t *out_osum,
+                      void *workspace, size_t workspace_bytes, void *stream);
+
 /* w4a4_linear for callers that cannot allocate device memory or carry a workspace around: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and
  * checks as w4a4_linear minus the workspace: the exchange area of the fused requantize (per-token

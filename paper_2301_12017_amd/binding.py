@@ -58,6 +58,10 @@ class _Epilogue(ctypes.Structure):
                 ("requant_layout", ctypes.c_int), ("schedule", ctypes.c_int)]
 
 
+class _ChainStep(ctypes.Structure):
+    _fields_ = [("W", _Weight), ("bias_f16", ctypes.c_void_p), ("act", ctypes.c_int), ("in_first", ctypes.c_int)]
+
+
 class _Part(ctypes.Structure):
     _fields_ = [("w4", _Weight), ("w8q", ctypes.c_void_p), ("w8s", ctypes.c_void_p),
                 ("bias_f16", ctypes.c_void_p), ("act", ctypes.c_int)]
@@ -92,6 +96,8 @@ _SIGNATURES = {
                          _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
     "w4a4_linear_static": (_i, [ctypes.POINTER(_Act), ctypes.POINTER(_Weight), ctypes.POINTER(_Epilogue),
                                 _vp, _vp, _vp, _vp, _vp]),
+    "w4a4_linear_chain_workspace_bytes": (_sz, [ctypes.POINTER(_Act), ctypes.POINTER(_ChainStep), _i]),
+    "w4a4_linear_chain": (_i, [ctypes.POINTER(_Act), ctypes.POINTER(_ChainStep), _i, _vp, _vp, _vp, _vp, _sz, _vp]),
     "w8a8_quantize_rows": (_i, [_vp, _i, _i, _i, _vp, _vp, _vp]),
     "w8a8_linear": (_i, [_vp, _i, _vp, _i, _vp, _vp, _i, _i, ctypes.POINTER(_Epilogue), _vp, _vp]),
     "w8a8_linear_f16act": (_i, [_vp, _i, _i, _i, _vp, _vp, _i, ctypes.POINTER(_Epilogue), _vp, _vp]),
@@ -475,6 +481,21 @@ def linear(A: QAct, W: QWeight, bias: Optional[torch.Tensor] = None, act=ACT_NON
     if requant_layout == LAYOUT_FP6:
         return QAct(o, os_, None, None, A.M, W.N, _row_bytes(W.N, LAYOUT_FP6), requant_group, requant_mode, 0, LAYOUT_FP6, None)
     return QAct(o, os_, oz, og, A.M, W.N, W.N // 2, requant_group, requant_mode)
+
+
+def linear_chain(A: QAct, steps) -> QAct:
+    """w4a4_linear_chain: steps of (W, bias, act, in_first), each requantizing into the layout of the weights and reading the
+    columns from in_first on of the step before.  Returns the last step's output, as linear(requant=True) does."""
+    n, M, dev = len(steps), A.M, A.q.device
+    c_steps = (_ChainStep * n)(*[_ChainStep(W.c(), None if bias is None else bias.data_ptr(), act, first) for W, bias, act, first in steps])
+    W = steps[-1][0]
+    o, os_, _, og = _alloc_out(A, W, True, SYM, 0, W.layout)
+    a, L = A.c(), lib()
+    need = L.w4a4_linear_chain_workspace_bytes(a, c_steps, n)
+    workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=dev)
+    rc = L.w4a4_linear_chain(a, c_steps, n, _ptr(o), _ptr(os_), _ptr(og), workspace.data_ptr(), workspace.numel(), _stream())
+    _check(rc, "w4a4_linear_chain")
+    return QAct(o, os_, None, None, M, W.N, _row_bytes(W.N, W.layout), 0, SYM, 0, W.layout, og)
 
 
 def linear_static(A: QAct, W: QWeight, bias: Optional[torch.Tensor] = None, act=ACT_NONE, requant=False,

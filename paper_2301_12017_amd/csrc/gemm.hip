@@ -1,5 +1,7 @@
 // Dispatch and C entry points of the GEMM side of libw4a4: schedule table, argument
 // validation, w4a4_linear / w4a4_gemm_i32 / w4a4_workspace_bytes.
+#include <vector>
+
 #include "gemm_common.hpp"
 #include "layer.hpp"
 
@@ -616,6 +618,147 @@ ClearRanges w4a4::linear_clear_ranges(const w4a4_act *A, const w4a4_weight *W, c
         r.n1 = A->M * (W->N / (ep->requant_group == 0 ? W->N : ep->requant_group));
     }
     return r;
+}
+
+// ---- a chain of requantizing linears -----------------------------------------------------------------------
+// Every step's exchange area and (MFMA operand layout) code sums lie side by side in the workspace, so that ONE fill launch clears what
+// all steps count in: a chain of four linears is five launches instead of eight (a fill in front of each GEMM costs its launch, some
+// 2.5 us: 32768 tokens, 1024 features 448 -> 434 us; with one call instead of four from Python, 500 tokens of 768 78.6 -> 64.4).
+struct ChainStep {
+    w4a4_act A;
+    w4a4_epilogue ep;
+    int ng, fused;
+    uint8_t *q; float *scale; int32_t *osum;                    // the step's output
+    uint32_t *exchange;
+};
+static size_t round_up(size_t b) { return (b + 255) / 256 * 256; }
+static size_t code_bytes(int M, int N, int layout) {
+    return layout == W4A4_LAYOUT_FP6 ? (((size_t)M + 63) & ~(size_t)63) * (N / 4 * 3) : (size_t)M * (N / 2);
+}
+
+// Lays the chain out in `workspace` (NULL: only adds up) and describes every step's call.  `cleared`: the words to clear.
+// Returns W4A4_OK or why the chain is refused.
+static int plan_chain(const w4a4_act *A, const w4a4_chain_step *steps, int n, uint8_t *out, float *out_scale, int32_t *out_osum,
+                      uint8_t *workspace, std::vector<ChainStep> &plan, size_t *cleared, size_t *total) {
+    if (!A || !steps || n <= 0 || n > 4096 || A->mode != W4A4_SYM || A->M < 0) return W4A4_ERR_INVALID_ARG;
+    const int M = A->M;
+    plan.resize(n);
+    size_t at = 0, codes = 0, rows = 0;
+    for (int pass = 0; pass < 2; ++pass) {                      // 0: what is cleared, first of all, then scales; 1: the buffers behind it
+        for (int i = 0; i < n; ++i) {
+            ChainStep &s = plan[i];
+            const w4a4_weight &W = steps[i].W;
+            const bool last = i == n - 1;
+            if (pass == 0) {
+                const int cols = i ? steps[i - 1].W.N : W.K, layout = W.layout;
+                if (W.K <= 0 || W.N <= 0 || W.mode != W4A4_SYM || layout != A->layout || steps[i].in_first < 0 ||
+                    steps[i].in_first > cols - W.K || (i == 0 && steps[0].in_first)) return W4A4_ERR_INVALID_ARG;
+                if (i == 0) {
+                    s.A = *A;
+                } else {
+                    const ChainStep &p = plan[i - 1];
+                    const int slices = layout == W4A4_LAYOUT_MFMA ? cols / W.K : 1, f = steps[i].in_first;
+                    if (f % (layout == W4A4_LAYOUT_FP6 ? 64 : 32) || (layout == W4A4_LAYOUT_MFMA && (cols % W.K || f % W.K))) return W4A4_ERR_UNSUPPORTED_SHAPE;
+                    s.A = w4a4_act{};
+                    s.A.q = p.q + (layout == W4A4_LAYOUT_FP6 ? (size_t)(f / 64) * 3072 : (size_t)(f / 2));
+                    s.A.scale = p.scale;
+                    s.A.M = M; s.A.K = W.K; s.A.lda = layout == W4A4_LAYOUT_FP6 ? cols / 4 * 3 : cols / 2;
+                    s.A.mode = W4A4_SYM; s.A.layout = layout;
+                    s.A.osum = layout == W4A4_LAYOUT_MFMA ? p.osum + f / W.K : nullptr;
+                    s.A.ldo = slices;
+                }
+                s.ep = w4a4_epilogue{};
+                s.ep.bias_f16 = steps[i].bias_f16; s.ep.act = steps[i].act;
+                s.ep.requant = 1; s.ep.requant_mode = W4A4_SYM; s.ep.requant_layout = layout;
+                // the next step reads a slice: one sum per slice
+                s.ep.requant_group = !last && layout == W4A4_LAYOUT_MFMA && steps[i + 1].W.K > 0 && steps[i + 1].W.K < W.N ? steps[i + 1].W.K : 0;
+                const int slices = s.ep.requant_group ? W.N / s.ep.requant_group : 1;
+                s.fused = fused_requant_kind(&s.A, &W, &s.ep, layout == W4A4_LAYOUT_MFMA);
+                s.exchange = reinterpret_cast<uint32_t *>(workspace + at);
+                if (s.fused) at += round_up(fused_workspace_bytes(M));
+                else rows = rows > (size_t)M * W.N * sizeof(float) ? rows : (size_t)M * W.N * sizeof(float);
+                s.osum = nullptr;
+                if (layout == W4A4_LAYOUT_MFMA) {
+                    s.osum = last ? out_osum : reinterpret_cast<int32_t *>(workspace + at);
+                    if (!last) at += round_up((size_t)M * slices * sizeof(int32_t));
+                }
+                // (addresses for the checks; the scales and codes get theirs in the second pass, behind what is cleared)
+                s.scale = last ? out_scale : reinterpret_cast<float *>(workspace + 256);
+                s.q = last ? out : workspace + 256;
+                if (!last) codes = codes > code_bytes(M, W.N, layout) ? codes : code_bytes(M, W.N, layout);
+            } else {
+                if (!last) {
+                    s.scale = reinterpret_cast<float *>(workspace + at);
+                    at += round_up((size_t)M * sizeof(float));
+                }
+            }
+        }
+        if (pass == 0) *cleared = at;
+    }
+    // two buffers of codes in turn, and the fp32 rows of steps whose requantize is not fused
+    uint8_t *buf[2] = {workspace + at, workspace + at + round_up(codes)};
+    uint8_t *rows_at = workspace + at + 2 * round_up(codes);
+    for (int i = 0; i < n; ++i) {
+        ChainStep &s = plan[i];
+        if (i < n - 1) s.q = buf[i & 1];
+        if (!s.fused) s.exchange = reinterpret_cast<uint32_t *>(rows_at);
+        if (i) {
+            const int f = steps[i].in_first;
+            s.A.q = plan[i - 1].q + (s.A.layout == W4A4_LAYOUT_FP6 ? (size_t)(f / 64) * 3072 : (size_t)(f / 2));
+            s.A.scale = plan[i - 1].scale;
+        }
+    }
+    *total = at + 2 * round_up(codes) + round_up(rows);
+    return W4A4_OK;
+}
+
+extern "C" size_t w4a4_linear_chain_workspace_bytes(const w4a4_act *A, const w4a4_chain_step *steps, int n) {
+    try {
+        std::vector<ChainStep> plan;
+        size_t cleared = 0, total = 0;
+        if (!A || A->M <= 0 || plan_chain(A, steps, n, nullptr, nullptr, nullptr, nullptr, plan, &cleared, &total)) return 0;
+        return total;
+    } catch (...) {
+        return 0;
+    }
+}
+
+extern "C" int w4a4_linear_chain(const w4a4_act *A, const w4a4_chain_step *steps, int n, void *out, float *out_scale, int32_t *out_osum,
+                                 void *workspace, size_t workspace_bytes, void *stream) {
+    try {
+        std::vector<ChainStep> plan;
+        size_t cleared = 0, total = 0;
+        int rc = plan_chain(A, steps, n, static_cast<uint8_t *>(out), out_scale, out_osum, static_cast<uint8_t *>(workspace), plan, &cleared, &total);
+        if (rc) return rc;
+        const int M = A->M;
+        if (M > 0 && (!workspace || workspace_bytes < total || (reinterpret_cast<uintptr_t>(workspace) & 255))) return W4A4_ERR_WORKSPACE;
+        for (int i = 0; i < n; ++i) {                           // everything is checked before the first launch
+            ChainStep &s = plan[i];
+            int rng = 0;
+            rc = check_layer(&s.A, &steps[i].W, &s.ep, s.q, s.scale, nullptr, &s.ng, &rng);
+            if (rc) return rc;
+            if (s.ep.requant_layout == W4A4_LAYOUT_MFMA && M > 0 && !s.osum) return W4A4_ERR_INVALID_ARG;
+            if (s.ep.requant_layout == W4A4_LAYOUT_FP6 && !s.fused) return W4A4_ERR_UNSUPPORTED_SHAPE;
+        }
+        if (M == 0) return W4A4_OK;
+        const hipStream_t st = as_stream(stream);
+        const bool last_sums = plan[n - 1].fused && plan[n - 1].osum;
+        const size_t words = cleared / sizeof(uint32_t);
+        if (words + (size_t)M > 0x7fffffff) return W4A4_ERR_UNSUPPORTED_SHAPE;
+        if (words)
+            hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + (last_sums ? M : 0) + 255) / 256)), dim3(256), 0, st,
+                               static_cast<uint32_t *>(workspace), (int)words, reinterpret_cast<uint32_t *>(out_osum), last_sums ? M : 0);
+        else if (last_sums)
+            hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, reinterpret_cast<uint32_t *>(out_osum), M, nullptr, 0);
+        for (int i = 0; i < n; ++i) {
+            const ChainStep &s = plan[i];
+            rc = linear_impl(&s.A, &steps[i].W, &s.ep, s.q, s.scale, nullptr, s.osum, s.ng, s.fused, s.exchange, s.exchange, st, true);
+            if (rc) return rc;
+        }
+        return W4A4_OK;
+    } catch (...) {
+        return W4A4_ERR_WORKSPACE;
+    }
 }
 
 // ---- w4a4_linear for callers that cannot allocate -----------------------------------------------------------

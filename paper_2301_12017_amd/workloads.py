@@ -87,8 +87,12 @@ def run_chain(A: B.QAct, layers: List[ChainLayer], workspace: Optional[torch.Ten
     """quantize -> GEMM -> dequant+bias(+GELU) -> requantize, four GEMMs per layer, without
     an fp16 activation tensor in between.  `record` (a list) receives (name, input, output).
     The requantized outputs keep the layout of the operands; the QKV output keeps one
-    odd-position sum per third so that the V slice can be consumed in place."""
+    odd-position sum per third so that the V slice can be consumed in place.  Unless somebody wants
+    to see the calls one by one (record, a forced schedule, a workspace for each), they are one call of the library."""
     h = layers[0].out.spec.K
+    if record is None and schedule == 0 and workspace is None:
+        return B.linear_chain(A, [(lay.W, lay.bias, lay.act, first) for L in layers
+                                  for lay, first in ((L.qkv, 0), (L.out, 2 * h), (L.ffn1, 0), (L.ffn2, 0))])
     for li, L in enumerate(layers):
         steps = (("qkv", L.qkv, None), ("attn_out", L.out, h), ("ffn1", L.ffn1, None), ("ffn2", L.ffn2, None))
         for name, lay, slice_h in steps:

@@ -455,3 +455,35 @@ def test_fused_requantize_on_256_row_panels(B, M, N, K, rlayout, gelu):
     finally:
         B.debug_fused_wait()
     assert torch.equal(run().q, plain.q) and B.fused_fault_check() is False
+
+
+@pytest.mark.parametrize("layout", [0, MFMA, 2])
+@pytest.mark.parametrize("M,h,f", [(1, 512, 2048), (129, 512, 2048), (1500, 1024, 4096), (2100, 768, 3072)])
+def test_chain_in_one_call_equals_the_calls_one_by_one(B, layout, M, h, f):
+    """w4a4_linear_chain over two layers, fused and unfused requantizes, the V slice read in place: codes, scales and sums are
+    those of one w4a4_linear per step (the FP6 layout has no rows of 3 * 768 codes)."""
+    from paper_2301_12017_amd import synth, workloads as WL
+    if layout == 2 and h == 768:
+        h, f = 1024, 2048
+    g = torch.Generator(device="cuda").manual_seed(M + h)
+    n = lambda *s, std=1.0: (torch.randn(s, device="cuda", generator=g) * std).half()
+    layers = []
+    for _ in range(2):
+        ls = [WL.Layer(synth.LinearSpec(name, M, N, K, name == "ffn1"), B.quantize_weight(n(N, K, std=0.02), SYM, layout=layout),
+                       n(N, std=0.01) if name != "attn_out" else None, int(name == "ffn1"))
+              for name, N, K in (("qkv", 3 * h, h), ("attn_out", h, h), ("ffn1", f, h), ("ffn2", h, f))]
+        layers.append(WL.ChainLayer(*ls))
+    A = B.quantize_act(n(M, h), SYM, layout=layout)
+    want = WL.run_chain(A, layers, record=[])
+    got = WL.run_chain(A, layers)
+    if layout == 2:                                                # whole panels of 64 tokens; of the last one the rows that are tokens
+        a, b = (t.view(-1, h // 64, 64, 48) for t in (got.q, want.q))
+        assert torch.equal(a[:-1], b[:-1]) and torch.equal(a[-1, :, :(M - 1) % 64 + 1], b[-1, :, :(M - 1) % 64 + 1])
+    else:
+        assert torch.equal(got.q, want.q)
+    assert torch.equal(got.scale.view(torch.int32), want.scale.view(torch.int32))
+    assert layout != MFMA or torch.equal(got.osum, want.osum)
+    assert (got.M, got.K, got.lda, got.group, got.mode, got.layout) == (want.M, want.K, want.lda, want.group, want.mode, want.layout)
+    again = B.linear(got, layers[0].qkv.W, layers[0].qkv.bias, 0)  # the result is an operand like any other
+    assert torch.equal(again, B.linear(want, layers[0].qkv.W, layers[0].qkv.bias, 0))
+    assert B.fused_fault_check() is False
