@@ -673,6 +673,12 @@ static int plan_chain(const w4a4_act *A, const w4a4_chain_step *steps, int n, ui
                 // the next step reads a slice: one sum per slice
                 s.ep.requant_group = !last && layout == W4A4_LAYOUT_MFMA && steps[i + 1].W.K > 0 && steps[i + 1].W.K < W.N ? steps[i + 1].W.K : 0;
                 const int slices = s.ep.requant_group ? W.N / s.ep.requant_group : 1;
+                // Long K and at most one 128 x 128 tile per CU: two launches (fp32 rows, then their quantize) take less than 128 x 256
+                // tiles on half of the CUs and the wait for their panel: 500 x 768 x 3072 22 -> 16 us, 4000 x 1024 x 4096 29 -> 25;
+                // with 1024 codes of K they are even (2000 x 1024 x 1024 13 | 13)
+                if (layout == W4A4_LAYOUT_MFMA && !s.ep.requant_group && W.K >= 2048 && olay_whole_lines(W.K) &&
+                    (long)((M + 127) / 128) * ((W.N + 127) / 128) <= device_cus())
+                    s.ep.schedule = S_OLAY_128x128;
                 s.fused = fused_requant_kind(&s.A, &W, &s.ep, layout == W4A4_LAYOUT_MFMA);
                 s.exchange = reinterpret_cast<uint32_t *>(workspace + at);
                 if (s.fused) at += round_up(fused_workspace_bytes(M));
