@@ -241,8 +241,12 @@ static int k_shares(const GemmArgs &g, bool asym) {
     return asym || (tiles <= 512 && g.K >= 2048) ? 2 : 0;
 }
 
+bool small_grouped_ok(const GemmArgs &g, int mode, int out_kind);   // gemm_small.hip: a wave per weight group
+int launch_small_grouped(int mode, GemmArgs &g, hipStream_t st);
+
 int launch_generic(int variant, int mode, bool grouped, int out_kind, GemmArgs &g, hipStream_t st) {
     if (variant == 1) {
+        if (grouped && small_grouped_ok(g, mode, out_kind)) return launch_small_grouped(mode, g, st);
         if (const int shares = k_shares(g, mode == W4A4_ASYM)) return launch_mid(shares, mode, out_kind, g, st);
     }
 #define W4A4_GO(MODE, GR)                                                        \

@@ -474,6 +474,171 @@ static int small_dispatch(SmallArgs &a, hipStream_t st) {
 #undef W4A4_SMALL
 }
 
+// Several weight groups, few tokens: a wave owns whole groups.  At these sizes the kernel with one K loop per workgroup spends its time on
+// one 128-code step after the other with a barrier each (24 steps at K = 3072: 27 us whatever the tokens), so a group here is
+// one wave's work: both operand tiles are parked in LDS as above, wave w multiplies groups w, w + NW, .. and leaves their
+// exact sums in LDS, and every thread adds up its outputs' groups in ascending order, each product and sum rounded on its own, as the
+// definition has it (same bits as gemm_kernel).  NW groups are in LDS at a time.
+template <int NW, int TM, int MODE>
+__global__ __launch_bounds__(NW * 64) void grouped_small_kernel(GemmArgs g) {
+    constexpr bool SGN = MODE == W4A4_SYM;
+    constexpr int NT = NW * 64, RV = TM / 2;                    // accumulator registers that hold real rows
+    constexpr int RPW = (RV + NW - 1) / NW;                     // ... finished by one wave
+    constexpr int CH = 4;                                       // 16-byte chunks of an operand tile per thread (the launcher checks)
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int Kb = g.K / 2, pitch = Kb + 16, ng = g.ng, ngp = ng | 1;   // (an odd pitch: the table reads of 32 lanes spread over the banks)
+    uint8_t *at = smem, *wt = at + TM * pitch;                  // [TM][pitch], [32][pitch]
+    int *s_P = reinterpret_cast<int *>(wt + 32 * pitch);        // [NW][RV][64]
+    float *sw_tab = reinterpret_cast<float *>(s_P + NW * RV * 64);      // [32][ngp]
+    float *zw_tab = sw_tab + 32 * ngp, *ra_tab = zw_tab + (SGN ? 0 : 32 * ngp);   // [32][ngp], [TM][ngp]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int m0 = (blockIdx.x / g.tiles_n) * TM, n0 = (blockIdx.x % g.tiles_n) * 32;
+    const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(g.Aq, (uint32_t)((long)(g.M - 1) * g.lda + Kb));
+    const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(g.Wq, (uint32_t)((long)g.N * g.ldw));
+
+    // ---- requests: both operand tiles (rows past M, channels past N: zeros), constants -------------------------------
+    const int cpr = g.K / 32;                                   // 16-byte chunks of a row
+    u32x4 av[CH], wv[CH];
+    int row_i[CH];
+    uint32_t dst_i[CH];
+    {
+        const int stepq = NT / cpr, stepr = NT % cpr;
+        int row = tid / cpr, c = tid % cpr;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            row_i[i] = row;
+            dst_i[i] = (uint32_t)(row * pitch + c * 16);
+            if (i * NT < TM * cpr) av[i] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (uint32_t)(m0 + row) * (uint32_t)g.lda + (uint32_t)c * 16, 0, 0);
+            if (i * NT < 32 * cpr) wv[i] = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, (uint32_t)(n0 + row) * (uint32_t)g.ldw + (uint32_t)c * 16, 0, 0);
+            row += stepq; c += stepr;
+            if (c >= cpr) { c -= cpr; ++row; }
+        }
+    }
+    for (int e = tid; e < 32 * ng; e += NT) {                   // a tile's 32 rows of [N][ng] are one piece of memory
+        const int n = e / ng, at_tab = n * ngp + e % ng;
+        const bool in = n0 + n < g.N;
+        sw_tab[at_tab] = in ? g.sw[(long)n0 * ng + e] : 0.0f;
+        if constexpr (!SGN) zw_tab[at_tab] = in ? g.zw[(long)n0 * ng + e] : 0.0f;
+    }
+    if constexpr (!SGN) {
+        for (int e = tid; e < TM * ng; e += NT) {
+            const int m = e / ng;
+            ra_tab[m * ngp + e % ng] = m0 + m < g.M ? (float)g.RA[(long)m0 * ng + e] : 0.0f;
+        }
+    }
+    const int n = n0 + r;
+    const bool n_ok = n < g.N;
+    const float bias = g.bias && n_ok ? __half2float(g.bias[n]) : 0.0f, c_n = !SGN && n_ok ? g.c[n] : 0.0f;
+    float sa[RPW], za[RPW];
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) {
+        const int m = min(m0 + frag_row(0, wave + k * NW, lane), g.M - 1);
+        sa[k] = g.sa[m];
+        za[k] = SGN ? 0.0f : g.za[m];
+    }
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        if (i * NT < TM * cpr && row_i[i] < TM) *reinterpret_cast<u32x4 *>(at + dst_i[i]) = av[i];
+        if (i * NT < 32 * cpr && row_i[i] < 32) *reinterpret_cast<u32x4 *>(wt + dst_i[i]) = wv[i];
+    }
+    __syncthreads();
+
+    // ---- groups: NW at a time ---------------------------------------------------------------------------------------
+    const uint8_t *arow = at + (r % TM) * pitch + h * 16, *wrow = wt + r * pitch + h * 16;
+    const int blocks = g.K / ng / 64;                           // blocks of 64 codes in a group
+    float t1[RPW];
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) t1[k] = 0.0f;
+    for (int g0 = 0; g0 < ng; g0 += NW) {
+        if (g0 + wave < ng) {
+            v16i acc;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[q] = 0;
+            const int b0 = (g0 + wave) * blocks;
+            for (int b = b0; b < b0 + blocks; ++b) {
+                const u32x4 a = *reinterpret_cast<const u32x4 *>(arow + b * 32), w = *reinterpret_cast<const u32x4 *>(wrow + b * 32);
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(widen2<SGN>(a[0], a[1]), widen2<SGN>(w[0], w[1]), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(widen2<SGN>(a[2], a[3]), widen2<SGN>(w[2], w[3]), acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < RV; ++q) s_P[(wave * RV + q) * 64 + lane] = SGN ? acc[q] >> 8 : acc[q];
+        }
+        __syncthreads();
+        const int here = min(NW, ng - g0);
+#pragma unroll
+        for (int k = 0; k < RPW; ++k) {
+            const int qq = wave + k * NW;
+            if (qq >= RV) break;
+            for (int s = 0; s < here; ++s) {
+                const float u = sw_tab[r * ngp + g0 + s] * (float)s_P[(s * RV + qq) * 64 + lane];
+                t1[k] = t1[k] + u;
+            }
+        }
+        if (g0 + NW < ng) __syncthreads();                       // the next groups' sums go to the same place
+    }
+
+    // ---- outputs, in the operation order of tile_epilogue ---------------------------------------------------------
+    const __amdgpu_buffer_rsrc_t o_rsrc = make_rsrc(g.out, (uint32_t)((long)g.M * g.N * 2));
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) {
+        const int qq = wave + k * NW;
+        if (qq >= RV) break;
+        const int row = frag_row(0, qq, lane);
+        float y = sa[k] * t1[k];
+        if constexpr (!SGN) {
+            float t2 = 0.0f;
+            for (int gi = 0; gi < ng; ++gi) {
+                const float w = zw_tab[r * ngp + gi] * ra_tab[row * ngp + gi];
+                t2 = t2 + w;
+            }
+            const float p = sa[k] * t2, z = za[k] * c_n;
+            y = y + p;
+            y = y + z;
+        }
+        if (g.bias) y = y + bias;
+        const uint32_t off = n_ok ? ((uint32_t)(m0 + row) * (uint32_t)g.N + (uint32_t)n) * 2u : kPoison;   // rows >= M fall off the end
+        if (g.act == W4A4_ACT_GELU) __builtin_amdgcn_raw_buffer_store_b16(gelu_erf_half(y), o_rsrc, off, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b16(__half_as_ushort(__float2half_rn(y)), o_rsrc, off, 0, 0);
+    }
+}
+
+template <int NW, int TM>
+static size_t grouped_small_lds(const GemmArgs &g, bool asym) {
+    return (size_t)(TM + 32) * (g.K / 2 + 16) + (size_t)NW * (TM / 2) * 64 * 4 + (size_t)(g.ng | 1) * (asym ? 64 + TM : 32) * 4;
+}
+template <int NW, int TM, int MODE>
+static int launch_grouped(GemmArgs &g, hipStream_t st) {
+    g.tiles_m = (g.M + TM - 1) / TM;
+    g.tiles_n = (g.N + 31) / 32;
+    const size_t lds = grouped_small_lds<NW, TM>(g, MODE == W4A4_ASYM);
+    auto kern = grouped_small_kernel<NW, TM, MODE>;
+    static KernelState ks;
+    if (prepare_kernel(reinterpret_cast<const void *>(kern), lds, ks) < 0) return W4A4_ERR_HIP;
+    launch_gemm(kern, dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(NW * 64), lds, st, g);
+    return launch_status();
+}
+// Rows of up to 1024 codes leave room for tiles of 32 tokens, three workgroups of eight waves to a CU; longer ones take sixteen
+// waves and 16 tokens, one to a CU.
+static bool grouped_short(const GemmArgs &g) { return g.K <= 1024; }
+// fp16 outputs of canonical codes in several weight groups, up to as many tiles as it wins with against 64 x 64 tiles of gemm_kernel (us, groups
+// of 128; asymmetric: 128 x 768 x 768 5.7 | 12.2, 128 x 768 x 3072 6.5 | 27.0, 301 x 3072 x 1024 (960 tiles) 10.5 | 12.1, 450 x 2304 x 768 (1080)
+// 13.2 | 13.4, 600 x 3072 x 1024 (1824) 18.6 | 13.3, 600 x 1024 x 4096 (1216) 29.6 | 34.5, 800 x 1024 x 4096 (1600) 40.4 | 34.7; symmetric: 128 x 768 x 3072
+// 6.0 | 20.4, 200 x 3072 x 768 (672) 7.5 | 7.9, 301 x 2304 x 768 (720) 7.7 | 7.4, 600 x 768 x 3072 (912) 18.4 | 20.5, 800 x 768 x 3072 (1200) 22.6 | 20.5).
+bool small_grouped_ok(const GemmArgs &g, int mode, int out_kind) {
+    const bool asym = mode == W4A4_ASYM;
+    if (out_kind != OUT_F16 || g.layout != W4A4_LAYOUT_CANONICAL || g.ng < 2 || g.K % (64 * g.ng) || g.K > 4096 || g.lda % 16 ||
+        ((long)g.M + 32) * g.lda >= 0x7fffffffL || ((long)g.N + 32) * g.ldw >= 0x7fffffffL || ((long)g.M + 32) * g.N * 2 >= 0x7fffffffL) return false;
+    const long rows = grouped_short(g) ? (g.M + 31) / 32 : (g.M + 15) / 16, tiles = rows * ((g.N + 31) / 32);
+    const size_t lds = grouped_short(g) ? grouped_small_lds<8, 32>(g, asym) : grouped_small_lds<16, 16>(g, asym);
+    return lds <= 160 * 1024 && tiles <= (grouped_short(g) ? (asym ? 1024 : 704) : (asym ? 1216 : 1024));
+}
+int launch_small_grouped(int mode, GemmArgs &g, hipStream_t st) {
+    if (mode == W4A4_SYM) return grouped_short(g) ? launch_grouped<8, 32, W4A4_SYM>(g, st) : launch_grouped<16, 16, W4A4_SYM>(g, st);
+    return grouped_short(g) ? launch_grouped<8, 32, W4A4_ASYM>(g, st) : launch_grouped<16, 16, W4A4_ASYM>(g, st);
+}
+
 // The LayerNorm form (layer.hpp): the tiles of small_dispatch, eight waves, the weight tile in LDS (K <= 1024: it fits).
 template <int K>
 static int launch_layernorm(SmallArgs &a, hipStream_t st) {

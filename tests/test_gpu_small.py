@@ -83,3 +83,26 @@ def test_fused_non_finite_inputs_do_not_fault(B):
     rows = np.ones(64, bool)
     rows[[3, 5]] = False
     assert np.isfinite(got[rows]).all()                             # the other tokens are unaffected
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K,group,act,with_bias", [
+    (1, 8, 256, 128, 0, True), (17, 40, 1024, 128, 1, True), (33, 264, 768, 128, 0, False), (32, 32, 1024, 512, 0, True),
+    (16, 96, 1152, 128, 0, True), (31, 520, 3072, 128, 1, False), (5, 72, 4096, 128, 0, True), (100, 200, 4096, 2048, 0, True),
+    (301, 768, 2304, 384, 0, True)])
+def test_several_weight_groups_of_a_few_tokens(mode, M, N, K, group, act, with_bias):
+    """The kernel whose waves own whole weight groups (schedule 0 and 64 x 64 tiles of few tokens), in both of its tiles, with
+    fewer groups than waves, as many and more: bit for bit what the 64 x 128 tiles of the general kernel give."""
+    from paper_2301_12017_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    X = torch.randn((M, K), device="cuda", generator=g).half()
+    X[:, ::7] *= 8
+    W = (torch.randn((N, K), device="cuda", generator=g) * 0.02).half()
+    bias = (torch.randn(N, device="cuda", generator=g) * 0.01).half() if with_bias else None
+    A, Q = B.quantize_act(X, mode, group), B.quantize_weight(W, mode, group)
+    want = B.linear(A, Q, bias, act, schedule=B.schedule_number("generic_64x128"))
+    assert B.pick_schedule(A, Q) == "generic_64x64"
+    got = torch.full((M + 2, N), 7.0, dtype=torch.float16, device="cuda")
+    B.linear(A, Q, bias, act, out=(got[:M], None, None, None))
+    assert torch.equal(got[:M].view(torch.int16), want.view(torch.int16))
+    assert (got[M:] == 7.0).all()                                  # nothing behind the last row
