@@ -175,6 +175,15 @@ static int pick_fp6(const GemmArgs &g) {
     return best;
 }
 
+// Few tokens, no schedule asked for: the FP6 kernel whose waves split K takes the place of 128 x 128 tiles, up to 512 tiles
+// of 32 x 64, two workgroups to a CU (us, 128 x 128 | 32 x 64: 128 x 768 x 768 6.3 | 4.0, 128 x 1024 x 4096 14.4 | 6.9, 301 x 3072 x 1024 (480 tiles) 7.2 |
+// 6.0, 1024 x 1024 x 4096 (512) 14.5 | 13.2; 450 x 2304 x 768 (540) 6.6 | 7.5, 1400 x 768 x 3072 (528) 12.0 | 16.4).
+static bool fp6_few_tokens(const GemmArgs &g, int out_kind) {
+    if (g.layout != W4A4_LAYOUT_FP6 || (out_kind != OUT_F16 && out_kind != OUT_I32)) return false;
+    const long tiles = (long)((g.M + 31) / 32) * ((g.N + 127) / 128 * 2);
+    return tiles <= 512;
+}
+
 // Resolves schedule 0 to the table's choice and checks everything a launcher of that family requires, so that
 // a caller can still refuse the call with its outputs untouched.  Nothing is launched here.
 static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *schedule) {
@@ -240,12 +249,13 @@ static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *
 }
 
 static int run_gemm(GemmArgs &g, int mode, bool grouped, int out_kind, int schedule, hipStream_t st) {
+    const bool few = schedule == 0 && fp6_few_tokens(g, out_kind);
     const int rc = resolve_schedule(g, grouped, out_kind, &schedule);
     if (rc) return rc;
     const Schedule &s = kSchedules[schedule - 1];
     switch (s.family) {
         case F_OLAY: return launch_olay(s.variant, out_kind, g, st);
-        case F_FP6: return launch_fp6(s.variant, out_kind, g, st);
+        case F_FP6: return launch_fp6(few ? kFp6FewTokens : s.variant, out_kind, g, st);
         case F_SMALL: return launch_small_packed(mode, out_kind, g, st);
         case F_GROUP: return launch_group(mode, out_kind, g, st);
         case F_PIPE: return launch_pipe(s.variant, out_kind, g, st);

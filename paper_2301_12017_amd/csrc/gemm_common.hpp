@@ -465,6 +465,7 @@ int launch_mid(int variant, int mode, int out_kind, GemmArgs &g, hipStream_t st)
 int device_cus();                                               // gemm.hip
 // Residency limits of the fused requantize on the current device (see the definitions)
 int olay_requant_max_tiles_n(bool mfma_out);
+constexpr int kFp6FewTokens = 4;                                 // gemm_fp6.hip: the variant that no schedule names
 int fp6_requant_max_tiles_n();
 int pipe_requant_max_tiles();
 

@@ -530,6 +530,120 @@ void gemm_fp6_kernel(GemmArgs g) {
     __builtin_amdgcn_s_waitcnt(vmcnt_and_lds(0));               // no DMA may outlive the workgroup's LDS
 }
 
+// Few tokens: 32 x 64 tiles whose NW waves split K.  A workgroup of the kernel above walks K one block of 64 codes after the other
+// with a barrier each, which takes 8 us at K = 768 and 18 at 4096 whatever the tokens.  Here a wave fetches the operands of its blocks
+// itself, four blocks ahead (the layout's rows of 48 bytes follow each other, so a fragment is 1.5 KB of consecutive memory), the waves'
+// exact sums are added up in LDS as integers, and the accumulator registers are dealt round robin to the waves for the
+// epilogue.  A lane holds two adjacent channels.
+template <int NW, int OUT>
+__global__ __launch_bounds__(NW * 64) void gemm_fp6_small_kernel(GemmArgs g) {
+    constexpr int FN = 2, AHEAD = 4, RPW = 16 / (NW < 16 ? NW : 16);   // rows' registers that one wave finishes
+    __shared__ int s_sum[FN * 16 * 64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = (blockIdx.x / g.tiles_n) * 32, gf = (blockIdx.x % g.tiles_n) * FN;   // first token; first fragment: 32 storage rows of a channel panel
+    const int KB = g.K / kHalf, a_panel = (int)g.lda * 64;
+    const long a_bytes = ((((long)g.M + 63) >> 6) - 1) * a_panel + (long)KB * 3072, b_bytes = (((long)g.N + 127) & ~127L) * KB * 48;
+    const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(g.Aq, (uint32_t)a_bytes), b_rsrc = make_rsrc(g.Wq, (uint32_t)b_bytes);
+    // this lane's operand in block 0: 16 bytes, and 8 bytes `tail` behind (see gemm_fp6_kernel)
+    const int tail = 32 + (((lane >> 5) ^ (lane >> 4)) & 1) * 8 - (lane >> 5) * 16;
+    const int a_off = (m0 >> 6) * a_panel + ((m0 & 63) + (lane & 31)) * kRow6 + (lane >> 5) * 16;
+    int b_off[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) b_off[j] = ((gf + j) >> 2) * KB * 6144 + (((gf + j) & 3) * 32 + (lane & 31)) * kRow6 + (lane >> 5) * 16;
+    u32x4 a16[AHEAD], b16[AHEAD][FN];
+    u32x2 a8[AHEAD], b8[AHEAD][FN];
+    auto request = [&](int s, int b) {                          // (a block past K is requested but never used: outside the descriptor or another block)
+        a16[s] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off, b * 3072, 0);
+        a8[s] = __builtin_amdgcn_raw_buffer_load_b64(a_rsrc, a_off + tail, b * 3072, 0);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            b16[s][j] = __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, b_off[j], b * 6144, 0);
+            b8[s][j] = __builtin_amdgcn_raw_buffer_load_b64(b_rsrc, b_off[j] + tail, b * 6144, 0);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s)
+        if (wave + s * NW < KB) request(s, wave + s * NW);
+    // constants of the rows and channels this wave finishes
+    const int n = (gf >> 2) * 128 + (lane & 31) * 4 + (gf & 3);
+    const bool n_ok = n < g.N;                                  // (N is a multiple of 8: both channels or none)
+    float sw[FN], bias[FN], sa[RPW];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        sw[j] = n_ok ? g.sw[n + j] : 0.0f;
+        bias[j] = n_ok && g.bias ? __half2float(g.bias[n + j]) : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) sa[k] = g.sa[min(m0 + frag_row(0, wave + k * NW, lane), g.M - 1)];
+    for (int e = tid; e < FN * 16 * 64; e += NW * 64) s_sum[e] = 0;
+    __syncthreads();
+
+    v16f acc[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[j][q] = 0.0f;
+    for (int b = wave; b < KB; b += AHEAD * NW) {
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) {
+            if (b + s * NW < KB) {
+                const v8i A = {(int)a16[s][0], (int)a16[s][1], (int)a16[s][2], (int)a16[s][3], (int)a8[s][0], (int)a8[s][1], 0, 0};
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const v8i W = {(int)b16[s][j][0], (int)b16[s][j][1], (int)b16[s][j][2], (int)b16[s][j][3], (int)b8[s][j][0], (int)b8[s][j][1], 0, 0};
+                    acc[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, W, acc[j], 2, 2, 0, 0, 0, 0);
+                }
+                if (b + (s + AHEAD) * NW < KB) request(s, b + (s + AHEAD) * NW);
+            }
+        }
+    }
+    if (wave < KB) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) atomicAdd(&s_sum[(j * 16 + q) * 64 + lane], (int)acc[j][q]);
+    }
+    __syncthreads();
+    constexpr int ESZ = OUT == OUT_F16 ? 2 : 4;
+    const __amdgpu_buffer_rsrc_t o_rsrc = make_rsrc(g.out, (uint32_t)((long)g.M * g.N * ESZ));
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) {
+        const int q = wave + k * NW;
+        const uint32_t off = n_ok ? ((uint32_t)(m0 + frag_row(0, q, lane)) * (uint32_t)g.N + (uint32_t)n) * ESZ : kPoison;   // rows >= M fall off the end
+        if constexpr (OUT == OUT_I32) {
+            const uint32_t w[FN] = {(uint32_t)s_sum[q * 64 + lane], (uint32_t)s_sum[(16 + q) * 64 + lane]};
+            store_words<FN>(o_rsrc, off, w);
+        } else {
+            float y[FN];
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const float t = (float)s_sum[(j * 16 + q) * 64 + lane] * sa[k];
+                y[j] = t * sw[j];
+                if (g.bias) y[j] = y[j] + bias[j];
+            }
+            if constexpr (OUT == OUT_F32) {
+                const bool gelu = g.act == W4A4_ACT_GELU;
+                const uint32_t w[FN] = {__float_as_uint(gelu ? gelu_erf(y[0]) : y[0]), __float_as_uint(gelu ? gelu_erf(y[1]) : y[1])};
+                store_words<FN>(o_rsrc, off, w);
+            } else if (g.act == W4A4_ACT_GELU) {
+                store_gelu_halves<FN>(o_rsrc, off, y);
+            } else {
+                store_halves<FN>(o_rsrc, off, y);
+            }
+        }
+    }
+}
+template <int NW, int OUT>
+static int launch_small6(GemmArgs &g, hipStream_t st) {
+    g.tiles_m = (g.M + 31) / 32;
+    g.tiles_n = (g.N + 127) / 128 * 2;
+    const long tiles = (long)g.tiles_m * g.tiles_n;
+    if (tiles > 0x7fffffffL) return W4A4_ERR_UNSUPPORTED_SHAPE;
+    launch_gemm(gemm_fp6_small_kernel<NW, OUT>, dim3((unsigned)tiles), dim3(NW * 64), 0, st, g);
+    return launch_status();
+}
+
 template <int FM, int FN, int WM, int WN, int OCC, int NS, int OUT>
 struct Fp6Launch {
     static constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
@@ -588,6 +702,7 @@ static int launch_variant6(int variant, GemmArgs &g, hipStream_t st) {
         case 1: return launch_one6<3, 2, 2, 2, 2, 5, OUT>(g, st);   // 192 x 128, two workgroups per CU
         case 2: return launch_one6<2, 2, 2, 2, 3, 4, OUT>(g, st);   // 128 x 128, three workgroups per CU
         case 3: return launch_one6<3, 4, 2, 2, 1, 7, OUT>(g, st);   // 192 x 256, one workgroup per CU, one wave per SIMD
+        case kFp6FewTokens: return g.K > 1536 ? launch_small6<16, OUT>(g, st) : launch_small6<8, OUT>(g, st);   // 32 x 64
         default: return W4A4_ERR_INVALID_ARG;
     }
 }

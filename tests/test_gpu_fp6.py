@@ -381,3 +381,28 @@ def test_layernorm_quantize_into_the_fp6_layout(B, orc, M, K, res):
         assert torch.equal(B.gemm_i32(A6, Q6), B.gemm_i32(A0, Q0))
     with pytest.raises(RuntimeError):                          # unsigned codes do not exist in this layout
         B.layernorm_quantize(*args, 1, 0, layout=FP6)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 8, 512), (31, 136, 1280), (33, 64, 768), (65, 1032, 1536), (96, 520, 2560), (200, 264, 4096), (7, 72, 10240)])
+def test_few_tokens_split_k(B, M, N, K):
+    """Without a schedule asked for, few tokens take the kernel whose waves split K (eight or sixteen waves; fewer blocks of 64
+    codes than waves, as many, several rounds): int32 sums and outputs, with and without bias and GELU, are those of the 128 x 128
+    tiles bit for bit, for a column slice of a wider matrix too."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    X = torch.randn((M, K), device="cuda", generator=g).half()
+    W = (torch.randn((N, K), device="cuda", generator=g) * 0.02).half()
+    bias = (torch.randn(N, device="cuda", generator=g) * 0.01).half()
+    A, Q = B.quantize_act(X, SYM, layout=FP6), B.quantize_weight(W, SYM, 0, layout=FP6)
+    tiles = B.schedule_number("fp6_128x128")
+    assert torch.equal(B.gemm_i32(A, Q), B.gemm_i32(A, Q, schedule=tiles))
+    for b, act in ((None, 0), (bias, 0), (bias, 1)):
+        got = torch.full((M + 2, N), 7.0, dtype=torch.float16, device="cuda")
+        B.linear(A, Q, b, act, out=(got[:M], None, None, None))
+        assert torch.equal(got[:M].view(torch.int16), B.linear(A, Q, b, act, schedule=tiles).view(torch.int16))
+        assert (got[M:] == 7.0).all()                              # nothing behind the last row
+    if K == 768:
+        from paper_2301_12017_amd import workloads as WL
+        wide = B.quantize_act(torch.randn((M, 3 * 1024), device="cuda", generator=g).half(), SYM, layout=FP6)
+        V = WL.v_slice(wide, 1024)
+        Q3 = B.quantize_weight((torch.randn((N, 1024), device="cuda", generator=g) * 0.02).half(), SYM, 0, layout=FP6)
+        assert torch.equal(B.gemm_i32(V, Q3), B.gemm_i32(V, Q3, schedule=tiles))
