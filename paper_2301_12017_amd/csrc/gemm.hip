@@ -59,15 +59,14 @@ static bool small_ok(const GemmArgs &g, int out_kind) {
            (long)g.M * g.lda < 0x7fffffffL && (long)g.N * g.ldw < 0x7fffffffL && ((long)g.M + 32) * g.N * 4 < 0x7fffffffL;
 }
 
-// LDS of the group kernel: three stages of a 128 x 128 tile (plus, in the operand layout, a column of token sums
-// each), token parameters, and the group tables zw[ng][128] and RA[ng][128]; two workgroups share a CU's 160 KB.
-static bool group_tables_fit(int ng, bool olay) {
-    return (size_t)ng * 256 * 4 + 3 * (256 * 64 + (olay ? 512 : 0)) + 2048 <= 80 * 1024;
+// Whether the group kernel takes ng weight groups: their tables fit its LDS, or (operand layout) it reads them from memory.
+static bool group_tables_fit(int K, int ng, bool olay) {
+    return group_lds(ng, true, olay, false) <= kGroupLds || (olay && group_memtab_ok(K, ng));
 }
 static bool group_ok(const GemmArgs &g, bool grouped) {
     return grouped && g.K % kBK == 0 && g.K >= 2 * kBK && (long)g.M * g.lda < 0x7fffffffL &&
            (long)g.N * g.ldw < 0x7fffffffL && (long)g.N * (g.ng + 1) * 4 < 0x7fffffffL && (long)g.M * g.ng * 4 < 0x7fffffffL &&
-           group_tables_fit(g.ng, g.osum != nullptr);
+           group_tables_fit(g.K, g.ng, g.osum != nullptr);
 }
 
 // Built-in shape table of the canonical layout: large problems take the pipelined tiles (192 x 128 when the
@@ -286,7 +285,7 @@ static int check_operands(const w4a4_act *A, const w4a4_weight *W, int *ng_out) 
             if (W->group != 0 && W->group != W->K) return W4A4_ERR_UNSUPPORTED_SHAPE;
         } else {                                                // unsigned codes: whole K steps per weight group
             const int G = W->group == 0 ? W->K : W->group;
-            if (G % kBK || W->K % G || !group_tables_fit(W->K / G, true)) return W4A4_ERR_UNSUPPORTED_SHAPE;
+            if (G % kBK || W->K % G || !group_tables_fit(W->K, W->K / G, true)) return W4A4_ERR_UNSUPPORTED_SHAPE;
         }
     }
     const int K = A->K;
@@ -375,7 +374,7 @@ extern "C" int w4a4_preferred_layout(int M, int N, int K, int mode, int group) {
         if (group != 0 && group != K) return W4A4_LAYOUT_CANONICAL;
     } else {
         const int G = group == 0 ? K : group;
-        if (G <= 0 || G % kBK || K % G || !group_tables_fit(K / G, true)) return W4A4_LAYOUT_CANONICAL;
+        if (G <= 0 || G % kBK || K % G || !group_tables_fit(K, K / G, true)) return W4A4_LAYOUT_CANONICAL;
     }
     return M >= 1536 ? W4A4_LAYOUT_MFMA : W4A4_LAYOUT_CANONICAL;   // (measured crossover between 1024 and 1536 tokens)
 }

@@ -52,21 +52,30 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 // s_waitcnt immediate for "vmcnt <= n", lgkmcnt and expcnt unconstrained (gfx9 encoding)
 static constexpr int vmcnt_only(int n) { return (n & 0xF) | (0x7 << 4) | (0xF << 8) | (((n >> 4) & 0x3) << 14); }
 
-template <int MODE, int OUT, bool OLAY, bool SPG1>
+// LINES (OLAY): rows of 128 bytes, whole cache lines, i.e. two K steps per LDS stage and DMA; two stages.  MEMTAB (OLAY): the
+// zero-point tables are read from memory in the epilogue.
+template <int MODE, int OUT, bool OLAY, bool SPG1, bool LINES, bool MEMTAB>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void gemm_group_kernel(GemmArgs g) {
     static_assert(!OLAY || MODE == W4A4_ASYM, "the symmetric operand layout has its own kernel");
     constexpr bool SGN = MODE == W4A4_SYM;
     constexpr int FM = 2, FN = 2, WM = 2, WN = 2;
     constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
-    constexpr int ROWB = kBK / 2;                               // 64 bytes of codes per row per K step
+    static_assert(OLAY || (!LINES && !MEMTAB), "canonical codes take half lines and LDS tables");
+    static_assert(!SPG1 || !LINES, "groups of one K step take half lines");
+    constexpr int STEPB = kBK / 2;                              // 64 bytes of codes per row per K step
+    constexpr int SPS = LINES ? 2 : 1, ROWB = SPS * STEPB;      // K steps per stage
+    constexpr int CPR = ROWB / 16, RPB = 1024 / ROWB;           // 16-byte chunks of a row, rows of a 1 KB DMA block
+    constexpr int SWZ = LINES ? 1 : 2;                          // rows that share a swizzle, log2: 256 bytes of LDS
     constexpr int CODES = (BM + BN) * ROWB;                     // code bytes of a stage
-    constexpr int STAGE = CODES + (OLAY ? BM * 4 : 0), NS = 3; // OLAY: + the step's column of 128*AE, one word per row
-    constexpr int LD = (BM + BN) / 16 / NW;                     // tile DMA instructions per wave per K step
+    constexpr int STAGE = CODES + (OLAY ? BM * 4 : 0);         // OLAY: + the (first) step's column of 128*AE, one word per row
+    constexpr int NS = LINES ? 2 : 3;
+    constexpr int LD = (BM + BN) / RPB / NW;                    // tile DMA instructions per wave per stage
     constexpr int LDT = LD + (OLAY ? 1 : 0);                    // ... the token-sum column included
-    constexpr int A_LD = (BM / 16) / NW;                        // the first A_LD of them fetch activations
+    constexpr int DPS = LINES ? 2 : 1;                          // ... per MFMA slot
+    constexpr int A_LD = (BM / RPB) / NW;                       // the first A_LD of them fetch activations
     constexpr int NF = FM + FN, NM = FM * FN;
-    static_assert(NF <= NM && LD <= NM, "not enough MFMA slots to hide the memory operations");
+    static_assert(NF <= NM && LD <= DPS * NM, "not enough MFMA slots to hide the memory operations");
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     uint8_t *par = smem + NS * STAGE;                           // [2 parities][ sa[BM] | za[BM] ]
@@ -80,22 +89,24 @@ void gemm_group_kernel(GemmArgs g) {
     const int KT = g.K / kBK, spg = g.steps_per_group;
 
     // ---- global -> LDS plan (fixed for the whole kernel) -------------------------------------------
-    int voff[LD];
-#pragma unroll
-    for (int i = 0; i < LD; ++i) {
-        const int row = (wave + i * NW) * 16 + (lane >> 2);
-        const int c = (lane & 3) ^ ((row >> 2) & 3);
-        if (i < A_LD) {
-            voff[i] = row * (int)g.lda + c * 16;
-        } else {
-            // LDS row p of the weight tile holds output channel nl: MFMA column cc of fragment f
-            // is channel cc*FN + f of the wave's span, so a lane ends up with FN adjacent channels.
-            const int p = row - BM;
-            const int w = p / (FN * 32), rem = p % (FN * 32), f = rem / 32, cc = rem % 32;
-            const int nl = w * (FN * 32) + cc * FN + f;
-            voff[i] = nl * (int)g.ldw + c * 16;
-        }
-    }
+    // DMA instruction i of this wave fills block wave + i*NW of a stage, rows RPB (wave + i*NW) ..: what i adds is the same for
+    // all lanes (and leaves the swizzle alone).  LINES: one address register serves the activations and one the weights, and
+    // dma_voff() adds it where it is needed, to the vector offset, which is what the range check of a row past the last one
+    // looks at; half lines have registers for all of them (groups of 128, 16384 x 768: 1 % less).  LDS row p of the weight tile
+    // holds output channel nl: MFMA column cc of fragment f is channel cc*FN + f of the wave's span, so a lane ends up with
+    // FN adjacent channels.
+    constexpr int STRIDE = NW * RPB;                            // rows from one instruction to the next: 32 or 64
+    static_assert(STRIDE % 32 == 0 && FN == 2, "whole fragments, two to a span");
+    const int row0 = wave * RPB + lane / CPR, chunk = (lane % CPR) ^ ((row0 >> SWZ) & (CPR - 1));
+    const int voff_a = row0 * (int)g.lda + chunk * 16;
+    const int voff_b = ((row0 % 32) * FN + row0 / 32) * (int)g.ldw + chunk * 16;
+    auto dma_voff = [&](int i) {
+        int v = i < A_LD ? voff_a : voff_b;
+        if constexpr (LINES) asm volatile("" : "+v"(v));        // (not a sum to keep in a register for the whole loop)
+        if (i < A_LD) return v + i * STRIDE * (int)g.lda;
+        const int p = (i - A_LD) * STRIDE;
+        return v + (p / 64 * 64 + p % 64 / 32) * (int)g.ldw;
+    };
     // (exists == false: no bytes at all, so that the prefetch of a tile that does not exist touches no memory)
     auto a_desc = [&](int m0, bool exists = true) {
         const int rows = min(BM, g.M - m0);
@@ -117,7 +128,7 @@ void gemm_group_kernel(GemmArgs g) {
     auto dma_one = [&](int i, int stage, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, int so) {
         uint8_t *dst = smem + stage * STAGE + (wave + i * NW) * 1024;
 #if defined(__HIP_DEVICE_COMPILE__)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(i < A_LD ? ra : rb, (lds_ptr_t)dst, 16, voff[i], so, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(i < A_LD ? ra : rb, (lds_ptr_t)dst, 16, dma_voff(i), so, 0, 0);
 #else
         (void)dst; (void)ra; (void)rb; (void)so;
 #endif
@@ -150,7 +161,7 @@ void gemm_group_kernel(GemmArgs g) {
     // tile's 128 rows of [.., ng] are one contiguous piece of memory and are copied as they lie (group by group, a
     // DMA instruction's 64 lanes touched 64 cache lines); else piece grp is group grp.
     auto dma_table = [&](int m0, int n0, int grp) {
-        if constexpr (MODE == W4A4_ASYM) {
+        if constexpr (MODE == W4A4_ASYM && !MEMTAB) {
             const int half = wave & 1;
             const int row0 = wave < 2 ? n0 : m0;
             const int src = OLAY ? row0 * g.ng + grp * 128 + half * 64 + lane : (row0 + half * 64 + lane) * g.ng + grp;
@@ -160,8 +171,8 @@ void gemm_group_kernel(GemmArgs g) {
     };
 
     // ---- operand fragments -----------------------------------------------------------------------
-    const int swz = ((lane & 31) >> 2) & 3;
-    const int rd0 = (lane & 31) * ROWB + (((lane >> 5) ^ swz) << 4);   // ks = 0;  ks = 1 is rd0 ^ 32
+    const int swz = ((lane & 31) >> SWZ) & (CPR - 1);
+    const int rd0 = (lane & 31) * ROWB + (((lane >> 5) ^ swz) << 4);   // ks = 0;  ks is rd0 ^ (32 * ks)
     int frag_off[NF];
 #pragma unroll
     for (int f = 0; f < FM; ++f) frag_off[f] = (wm * FM * 32 + f * 32) * ROWB + rd0;
@@ -223,12 +234,14 @@ void gemm_group_kernel(GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < LD; ++i) dma_one(i, 0, a_cur, b_cur, 0);
     dma_col(0, m0, 0);
+    if constexpr (!LINES) {
 #pragma unroll
-    for (int i = 0; i < LD; ++i) dma_one(i, 1, a_cur, b_cur, ROWB);
-    dma_col(1, m0, 1);
+        for (int i = 0; i < LD; ++i) dma_one(i, 1, a_cur, b_cur, ROWB);
+        dma_col(1, m0, 1);
+    }
     // the first K step; the second is waited for where it is read (with this, and no requests for the tile after the last
     // one, four linears at 16384 tokens: 1 % less; the symmetric kernel gains nothing and its requantizing form loses)
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(LDT));
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(LINES ? 0 : LDT));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     u32x4 P0[NF], P1[NF];
@@ -309,23 +322,27 @@ void gemm_group_kernel(GemmArgs g) {
         else request_scales(0, swn);
         int wog[FN] = {0, 0};                                   // OLAY, int32 export: its odd-position code sums
         int grp = 0;                                            // index of the current weight group
+        // LINES: ODD steps read the second half of their stage and request nothing; an even step requests the next stage (whose group
+        // started with an even step, so one column of token sums serves both), and there is a barrier in the odd ones alone.
         // One K step.  Whether it opens a weight group (FOG) and whether it ends the tile (LAST) are compile-time
         // flags: a K step is then one straight block of code, and the slot order written here is the issue order.
         // (With a run-time "first of group" branch the compiler sank the widening of the next step's first operands
         // out of the last MFMA slots to the common head of the two branches, where it ran with the matrix pipe idle.)
         // Q: place in a quad of groups whose scales are in `quad`, -1 outside of quads, kFinal in the tile's last group, behind
         // which nothing is requested: the count of what may be in flight at the barrier is the count of requests that are there.
-        auto k_step = [&](auto fog_tag, auto last_tag, auto q_tag, int kt) {
+        auto k_step = [&](auto fog_tag, auto last_tag, auto q_tag, int kt, auto odd_tag) {
             constexpr int Q = decltype(q_tag)::value;
-            constexpr int BEHIND = (MODE == W4A4_ASYM ? 1 : 0) + (OUT == OUT_I32 || Q > 0 || Q == kFinal ? 0 : FN);   // requests behind the tile DMAs of a group's first step
+            constexpr bool ODD = LINES && decltype(odd_tag)::value, EVEN = LINES && !ODD;
+            constexpr int KS0 = ODD ? 2 : 0;                    // first 64 codes of the step in its stage
+            constexpr int BEHIND = (MODE == W4A4_ASYM && !MEMTAB ? 1 : 0) + (OUT == OUT_I32 || Q > 0 || Q == kFinal ? 0 : FN);   // requests behind the tile DMAs of a group's first step
             constexpr bool FOG = decltype(fog_tag)::value;     // first K step of a weight group
             constexpr bool LAST = decltype(last_tag)::value;   // last K step of the tile
             const int nxt = cur == NS - 1 ? 0 : cur + 1;       // stage of stream step +1
-            const int nx2 = nxt == NS - 1 ? 0 : nxt + 1;       // stage of stream step +2 (= step -1)
+            const int nx2 = LINES ? nxt : nxt == NS - 1 ? 0 : nxt + 1;   // stage of stream step +2 (half lines: = step -1)
             const bool own = !LAST && kt + 2 < KT;
             const __amdgpu_buffer_rsrc_t ra = own ? a_cur : a_nxt, rb = own ? b_cur : b_nxt;
             const int kt2 = own ? kt + 2 : kt + 2 - KT;
-            const int so = kt2 * ROWB;
+            const int so = kt2 * STEPB;
             if constexpr (FOG) {                                // this group's scales: used when it is folded
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
@@ -343,10 +360,13 @@ void gemm_group_kernel(GemmArgs g) {
                 else if constexpr (FOG) { W4A4_SLOT_BEGIN_ZERO(U0, k) }
                 else { W4A4_SLOT_BEGIN(U0, k) }
                 if (k < NF) U1[k] = widen_hi(k, P0[k]);
-                if (k < NF) P1[k] = read_frag(k, cur, 1);
-                if (k < LD) dma_one(k, nx2, ra, rb, so);
-                if (k == LD - 1) {
-                    dma_col(nx2, own ? m0 : m0n, kt2);
+                if (k < NF) P1[k] = read_frag(k, cur, KS0 + 1);
+                if constexpr (!ODD) {
+#pragma unroll
+                    for (int d = k * DPS; d < (k + 1) * DPS && d < LD; ++d) dma_one(d, nx2, ra, rb, so);
+                }
+                if (k == NM - 1) {
+                    if constexpr (!ODD) dma_col(nx2, own ? m0 : m0n, kt2);
                     if constexpr (FOG) dma_table(m0, n0, grp);
                     if constexpr (LAST) dma_tokens(m0n, parity ^ 1);
                     if constexpr (FOG && OUT != OUT_I32 && Q == 0) request_quad(grp + 4, quad_n);
@@ -366,12 +386,13 @@ void gemm_group_kernel(GemmArgs g) {
             for (int k = 0; k < NM; ++k) {
                 W4A4_SLOT_BEGIN(U0, k)
                 if (k < NF) U1[k] = widen_hi(k, P1[k]);
-                if (k == kBarSlot) {
-                    __builtin_amdgcn_s_waitcnt(vmcnt_only(LAST ? 0 : FOG ? LDT + BEHIND : LDT));
+                if (k == kBarSlot && !EVEN) {
+                    constexpr int IN_FLIGHT = (LINES ? 0 : LDT) + (FOG ? BEHIND : 0);
+                    __builtin_amdgcn_s_waitcnt(vmcnt_only(LAST ? 0 : IN_FLIGHT));
                     __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
                 }
-                if (!LAST && k >= kBarSlot) P0[k - kBarSlot] = read_frag(k - kBarSlot, nxt, 0);
+                if (!LAST && k >= kBarSlot) P0[k - kBarSlot] = EVEN ? read_frag(k - kBarSlot, cur, 2) : read_frag(k - kBarSlot, nxt, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
             // sub-step 3: multiply (ks 1, high); widen (next step's ks 0, low) -> U0
@@ -385,7 +406,7 @@ void gemm_group_kernel(GemmArgs g) {
                 c_raw = __builtin_amdgcn_raw_buffer_load_b64(c_rsrc, n_lane * 4, 0, 0);
                 bias_raw = __builtin_amdgcn_raw_buffer_load_b32(bias_rsrc, n_lane * 2, 0, 0);
             }
-            cur = nxt;
+            if constexpr (!EVEN) cur = nxt;
         };
         // group boundary: t1 += sw[n,g] * (float)P_g.  Canonical codes: one multiply, one add, each rounded, as the
         // definition has it.  Operand layout: a conversion and one fused multiply-add on 16*(P_g - 8*WO).
@@ -440,34 +461,54 @@ void gemm_group_kernel(GemmArgs g) {
             const std::integral_constant<int, -1> single{};
             const std::integral_constant<int, kFinal> final_group{};
             int kt = 0;
+            auto step_and_fold = [&](auto q_tag) {
+                k_step(yes, no, q_tag, kt++, no);
+                fold_group(no);
+            };
             if constexpr (SPG1) {                               // every K step is a group
                 if constexpr (QUADS) {
-                    for (; kt + 4 < KT; kt += 4) {
-                        k_step(yes, no, std::integral_constant<int, 0>{}, kt);
-                        fold_group(no);
-                        k_step(yes, no, std::integral_constant<int, 1>{}, kt + 1);
-                        fold_group(no);
-                        k_step(yes, no, std::integral_constant<int, 2>{}, kt + 2);
-                        fold_group(no);
-                        k_step(yes, no, std::integral_constant<int, 3>{}, kt + 3);
-                        fold_group(no);
+                    while (kt + 4 < KT) {
+                        step_and_fold(std::integral_constant<int, 0>{});
+                        step_and_fold(std::integral_constant<int, 1>{});
+                        step_and_fold(std::integral_constant<int, 2>{});
+                        step_and_fold(std::integral_constant<int, 3>{});
 #pragma unroll
                         for (int j = 0; j < FN; ++j) quad[j] = quad_n[j];
                     }
 #pragma unroll
                     for (int j = 0; j < FN; ++j) swn[j] = __uint_as_float(quad[j][0]);
                 }
-                for (; kt < KT - 1; ++kt) { k_step(yes, no, single, kt); fold_group(no); }
-                k_step(yes, yes, final_group, kt);
-            } else {
+                while (kt < KT - 1) step_and_fold(single);
+                k_step(yes, yes, final_group, kt, no);
+            } else if constexpr (LINES) {                       // an even number of steps per group
                 for (int gi = 0; gi < g.ng - 1; ++gi) {
-                    k_step(yes, no, single, kt++);
-                    for (int st = 1; st < spg; ++st) k_step(no, no, single, kt++);
+                    k_step(yes, no, single, kt++, no);
+                    k_step(no, no, single, kt++, yes);
+                    for (int st = 2; st < spg; st += 2) {
+                        k_step(no, no, single, kt++, no);
+                        k_step(no, no, single, kt++, yes);
+                    }
                     fold_group(no);
                 }
-                k_step(yes, no, final_group, kt++);
-                for (int st = 1; st < spg - 1; ++st) k_step(no, no, final_group, kt++);
-                k_step(no, yes, final_group, kt);
+                k_step(yes, no, final_group, kt++, no);
+                if (spg > 2) {
+                    k_step(no, no, final_group, kt++, yes);
+                    for (int st = 2; st < spg - 2; st += 2) {
+                        k_step(no, no, final_group, kt++, no);
+                        k_step(no, no, final_group, kt++, yes);
+                    }
+                    k_step(no, no, final_group, kt++, no);
+                }
+                k_step(no, yes, final_group, kt, yes);
+            } else {
+                for (int gi = 0; gi < g.ng - 1; ++gi) {
+                    k_step(yes, no, single, kt++, no);
+                    for (int st = 1; st < spg; ++st) k_step(no, no, single, kt++, no);
+                    fold_group(no);
+                }
+                k_step(yes, no, final_group, kt++, no);
+                for (int st = 1; st < spg - 1; ++st) k_step(no, no, final_group, kt++, no);
+                k_step(no, yes, final_group, kt, no);
             }
             fold_group(yes);
         }
@@ -489,7 +530,27 @@ void gemm_group_kernel(GemmArgs g) {
             const float cv[FN] = {__uint_as_float(c_raw[0]), __uint_as_float(c_raw[1])};
             const float bv[FN] = {__half2float(__ushort_as_half((unsigned short)(bias_raw & 0xFFFFu))),
                                   __half2float(__ushort_as_half((unsigned short)(bias_raw >> 16)))};
-            if constexpr (OLAY) {
+            if constexpr (MEMTAB) {
+                // as below, from memory: a lane takes four consecutive groups per request (lanes 0-31 groups 8t .. 8t+3, lanes
+                // 32-63 8t+4 .. 8t+7: ng is a multiple of 8)
+                const uint32_t g0 = (uint32_t)(lane >> 5) * 16u;
+                for (int t = 0; t * 8 < g.ng; ++t) {
+                    u32x4 ra4[FM], zw4[FN];
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+                        ra4[i] = __builtin_amdgcn_raw_buffer_load_b128(ra_rsrc, (uint32_t)(m0 + row_w + i * 32 + (lane & 31)) * (uint32_t)g.ng * 4u + g0, t * 32, 0);
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        zw4[j] = __builtin_amdgcn_raw_buffer_load_b128(zw_rsrc, (uint32_t)(n_lane + j) * (uint32_t)g.ng * 4u + g0, t * 32, 0);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int i = 0; i < FM; ++i)
+#pragma unroll
+                            for (int j = 0; j < FN; ++j)
+                                facc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32((float)(int)ra4[i][u], __uint_as_float(zw4[j][u]), facc[i][j], 0, 0, 0);
+                }
+            } else if constexpr (OLAY) {
                 // sum_g zw[n,g] * RA[m,g]: a rank-ng product of the tile's two group tables, continued into the fp32
                 // accumulators by the fp32 MFMA, two groups per instruction (lanes 0-31 carry group gp, lanes 32-63
                 // group gp + 1; a missing last group contributes zeros)
@@ -593,21 +654,20 @@ void gemm_group_kernel(GemmArgs g) {
                 }
         }
         if (!has_next) break;
-        if constexpr (MODE == W4A4_ASYM) __syncthreads();       // the group tables are single: every wave is done reading them
+        if constexpr (MODE == W4A4_ASYM && !MEMTAB) __syncthreads();   // the group tables are single: every wave is done reading them
         vb = vb_next; tile = tile_next; m0 = m0n; n0 = n0n; a_cur = a_nxt; b_cur = b_nxt; parity ^= 1;
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_only(0));                  // no DMA may outlive the workgroup's LDS
 }
 
-template <int MODE, int OUT, bool OLAY, bool SPG1>
-static int launch_spg(GemmArgs &g, hipStream_t st) {
+template <int MODE, int OUT, bool OLAY, bool SPG1, bool LINES, bool MEMTAB>
+static int launch_kernel(GemmArgs &g, hipStream_t st) {
     constexpr int BM = 128, BN = 128;
-    const size_t tables = MODE == W4A4_ASYM ? (size_t)g.ng * (BM + BN) * 4 : 0;
-    const size_t lds = 3 * ((size_t)(BM + BN) * (kBK / 2) + (OLAY ? BM * 4 : 0)) + 2 * 2 * BM * 4 + tables;
-    if (lds > 80 * 1024) return W4A4_ERR_UNSUPPORTED_SHAPE;       // the group tables do not fit beside two workgroups' stages
+    const size_t lds = group_lds(g.ng, MODE == W4A4_ASYM && !MEMTAB, OLAY, LINES);
+    if (lds > kGroupLds) return W4A4_ERR_UNSUPPORTED_SHAPE;       // the group tables do not fit beside two workgroups' stages
     g.tiles_m = (g.M + BM - 1) / BM;
     g.tiles_n = (g.N + BN - 1) / BN;
-    auto kern = gemm_group_kernel<MODE, OUT, OLAY, SPG1>;
+    auto kern = gemm_group_kernel<MODE, OUT, OLAY, SPG1, LINES, MEMTAB>;
     static KernelState ks;
     const int cus = prepare_kernel(reinterpret_cast<const void *>(kern), lds, ks);
     if (cus < 0) return W4A4_ERR_HIP;
@@ -617,6 +677,24 @@ static int launch_spg(GemmArgs &g, hipStream_t st) {
     const unsigned grid = (unsigned)(tiles < slots ? tiles : slots);
     launch_gemm(kern, dim3(grid), dim3(256), lds, st, g);
     return launch_status();
+}
+
+// Operand layout.  Groups of several K steps (one group, above all) take rows of whole cache lines where the groups are pairs of
+// K steps and the tables fit beside them: asymmetric per-channel, 16384 x 4096 x 1024 + GELU 94.7 -> 91.6 us, 16384 x 1024 x
+// 4096 61.9 -> 57.9, 16384 x 768 x 3072 36.8 -> 34.5; the four linears at 2048 tokens of 1024 70.2 -> 67.1.  Groups of one K
+// step do not (16384 x 3072 x 768 + GELU 82.0 | 87.3 with whole lines, K = 3072 the same: the fold leaves no registers for the
+// second half's addresses, and it has the time to wait for half lines).  Their tables stay in LDS where they fit; more than
+// 28 groups (K = 4096 in groups of 128) read them from memory in the epilogue: 16384 x 1024 x 4096 229 us on the general
+// kernel, the only other one that takes so many groups, 89 here; 2048 x 1024 x 4096 39 | 30.
+template <int MODE, int OUT, bool OLAY, bool SPG1>
+static int launch_spg(GemmArgs &g, hipStream_t st) {
+    if constexpr (OLAY && !SPG1) {
+        if (group_lines_ok(g.K, g.ng) && group_lds(g.ng, true, true, true) <= kGroupLds) return launch_kernel<MODE, OUT, true, false, true, false>(g, st);
+    }
+    if constexpr (OLAY && SPG1) {
+        if (group_lds(g.ng, true, true, false) > kGroupLds && group_memtab_ok(g.K, g.ng)) return launch_kernel<MODE, OUT, true, true, false, true>(g, st);
+    }
+    return launch_kernel<MODE, OUT, OLAY, SPG1, false, false>(g, st);
 }
 
 template <int MODE, int OUT, bool OLAY>

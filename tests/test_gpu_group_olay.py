@@ -153,3 +153,28 @@ def test_many_tiles_and_the_canonical_kernel(B, orc, group, K):
         assert np.array_equal(canon[rows].view(np.uint16), want["out"].view(np.uint16)) or act == 1
         worst = np.abs(got.astype(np.float64) - canon.astype(np.float64)).max(axis=1)    # per token, against the sampled budget
         assert worst.max() <= 1e-2 * np.abs(canon.astype(np.float64)).max() + 4 * budget.max(), float(worst.max())
+
+
+@pytest.mark.parametrize("M,N,K,group", [(133, 136, 4096, 128), (1536 + 61, 2304 + 40, 4096, 128),      # tables from memory: one tile each, several
+                                         (133, 136, 256, 256), (2100, 4096 + 8, 512, 0), (300, 264, 4096, 256),   # rows of whole cache lines
+                                         (140, 264, 768, 384), (140, 264, 3072, 1536)])                 # ... groups of 3 and 12 K steps
+def test_whole_lines_and_tables_from_memory(B, orc, M, N, K, group):
+    """Every way the kernel reads its tiles and group tables, against the canonical codes' int32 planes (exact), and sampled
+    rows against the oracle and the float64 evaluation."""
+    rng = np.random.default_rng(900 + M + K + group)
+    X, W = _x(rng, M, K), _w(rng, N, K)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float16)
+    A, Q = B.quantize_act(dev(X), ASYM, group, layout=MFMA), B.quantize_weight(dev(W), ASYM, group, layout=MFMA)
+    assert B.pick_schedule(A, Q) == "group_128x128" and B.preferred_layout(2048, N, K, ASYM, group) == MFMA
+    assert torch.equal(B.gemm_i32(A, Q), B.gemm_i32(B.quantize_act(dev(X), ASYM, group), B.quantize_weight(dev(W), ASYM, group)))
+    rows = np.sort(np.concatenate([[0, M - 1], rng.choice(np.arange(1, M - 1), 30, replace=False)]))
+    a, w = qact_host(A), qweight_host(Q)
+    a = {k: (None if v is None else v[rows]) for k, v in a.items()}
+    want = orc.linear(a, w, ASYM, group, b, 0)["out"]
+    got = host(B.linear(A, Q, dev(b), 0))
+    assert np.isfinite(got).all()
+    ok, ratio = f16_close_budget(got[rows], want, asym_budget(orc, a, w, group))
+    assert ok, ratio
+    truth = orc.truth64(a, w, ASYM, b, 0)
+    e_gpu, e_orc = (np.sqrt(np.mean((v.astype(np.float64) - truth) ** 2)) for v in (got[rows], want))
+    assert e_gpu <= 1.5 * e_orc + 1e-7, (e_gpu, e_orc)
