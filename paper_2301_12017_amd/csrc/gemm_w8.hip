@@ -350,7 +350,9 @@ static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
 
 // Tile choice: n tiles on the busiest CU.  128 x 128 in pairs takes 1 (area 128 x 128) per tile and 1 / 0.39 for one that is left
 // over, a 128 x 128 tile alone on its CU with the deeper prefetch 1 / 0.4 each, 256 x 256 4 / 1.1, and for
-// long K 256 x 128 2 / 1.07 (6144 x 1024 x 4096 with its quantizer 38.7 us, 41.1 in pairs; 8192 x 1024 x 1024 20.3 | 18.2).  Fitted to the times of all
+// long K 256 x 128 2 / 1.07 (6144 x 1024 x 4096 with its quantizer 38.7 us, 41.1 in pairs; 8192 x 1024 x 1024 20.3 | 18.2), but not where
+// every CU has one 128 x 128 tile at most and it would leave half of them idle (4096 x 1024 x 4096 32.9 | 29.3, 2048 x 1024 x 4096 27.7 | 22.7,
+// 2048 x 768 x 3072 23.2 | 18.1).  Fitted to the times of all
 // at eighteen token counts from 600 to 16384 on the BERT-base and BERT-large linears: 0.2 % above the best of them on
 // average, 8 % at worst.  Four linears with their quantizers against half lines in 128 x 256, 192 x 128 and 128 x 128 tiles: 800
 // tokens 63.4 -> 52.6 us, 4096 102.6 -> 91.1, 16384 314.5 -> 277.2 (BERT-large); 16384 218.5 -> 192.1 (BERT-base).
@@ -366,7 +368,7 @@ static int launch_w8(int out_kind, GemmArgs &g, hipStream_t st) {
     if (g.K % 128 == 0 && g.K >= 256) {
         const long pairs = busiest(128, 128) / 2, odd = busiest(128, 128) % 2;
         const double pair = 2.0 * pairs + odd / 0.39, alone = g.K >= 384 ? n128 / 0.4 : 1e30, big = 4.0 * n256 / 1.1;
-        const double tall = g.K >= 2048 ? 2.0 * (double)busiest(256, 128) / 1.07 : 1e30;
+        const double tall = g.K >= 2048 && n128 > 1 ? 2.0 * (double)busiest(256, 128) / 1.07 : 1e30;
         double c = pair;
         tile = W8_128x128_PAIR;
         if (alone < c) { c = alone; tile = W8_128x128; }
