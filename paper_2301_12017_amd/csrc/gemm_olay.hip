@@ -50,6 +50,21 @@ __device__ __forceinline__ v4i widen_wgt(uint32_t x, uint32_t y) {
     return v4i{(int)(x & 0xF0F0F0F0u), (int)(x & 0x0F0F0F0Fu), (int)(y & 0xF0F0F0F0u), (int)(y & 0x0F0F0F0Fu)};
 }
 
+// fma(u, s, b) of two channels as a pair of fp16 values, each rounded once.  Written out because the compiler makes these
+// instructions of most pairs and two roundings, fp32 and fp16, of some, and which ones depends on the tile.
+template <bool BIAS>
+__device__ __forceinline__ uint32_t fma_half2(float u0, float u1, float s, float b0, float b1) {
+    uint32_t d;
+    if constexpr (BIAS) {
+        asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(d) : "v"(u0), "v"(s), "v"(b0));
+        asm("v_fma_mixhi_f16 %0, %1, %2, %3" : "+v"(d) : "v"(u1), "v"(s), "v"(b1));
+    } else {
+        asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(d) : "v"(u0), "v"(s));
+        asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(d) : "v"(u1), "v"(s));
+    }
+    return d;
+}
+
 template <int FN>
 struct ChanParams {
     float sw[FN];      // weight scale / 16 (the accumulators hold 16 * P; a power of two, so exact)
@@ -65,8 +80,9 @@ struct ChanParams {
 //   fp16 stores: three instructions per value instead of five,
 //     y = fma(fma((float)acc, sw[n]/16, -128*esum[n]*sw[n]/16), sa[m], bias[n]),
 //     the same real number evaluated with two roundings less and the channel term moved behind the conversion
-//     (its product with the scale is formed once per tile).  The fp32 value differs from the definition's by a
-//     few units in the last place, the fp16 result by at most one step and only on near-ties of the fp16 grid.
+//     (its product with the scale is formed once per tile).  The outer one rounds once, to fp16 (fma_half2; in front of
+//     GELU to fp32), whatever the tile.  The real number rounded differs from the definition's by a few units in
+//     fp32's last place, the fp16 result by at most one step and only on near-ties of the fp16 grid.
 template <int FM, int FN, int OUT, bool BIAS, bool GELU>
 __device__ __forceinline__ void olay_epilogue(const GemmArgs &g, v16i (&acc)[FM][FN], const ChanParams<FN> &cp,
                                               uint32_t col_off, int m0, int row_w, int lane,
@@ -108,12 +124,20 @@ __device__ __forceinline__ void olay_epilogue(const GemmArgs &g, v16i (&acc)[FM]
                     }
                     store_words<FN, kStreamed>(o_rsrc, off, w);
                 } else {
-                    float y[FN];
+                    float u[FN];
 #pragma unroll
-                    for (int j = 0; j < FN; ++j)
-                        y[j] = __fmaf_rn(__fmaf_rn((float)acc[i][j][r], cp.sw[j], nsw[j]), sav[rr], bj[j]);
-                    if constexpr (GELU) store_gelu_halves<FN, kStreamed>(o_rsrc, off, y);
-                    else store_halves<FN, kStreamed>(o_rsrc, off, y);
+                    for (int j = 0; j < FN; ++j) u[j] = __fmaf_rn((float)acc[i][j][r], cp.sw[j], nsw[j]);
+                    if constexpr (GELU) {
+                        float y[FN];
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) y[j] = __fmaf_rn(u[j], sav[rr], bj[j]);
+                        store_gelu_halves<FN, kStreamed>(o_rsrc, off, y);
+                    } else {
+                        uint32_t w[FN / 2];
+#pragma unroll
+                        for (int j = 0; j < FN / 2; ++j) w[j] = fma_half2<BIAS>(u[2 * j], u[2 * j + 1], sav[rr], bj[2 * j], bj[2 * j + 1]);
+                        store_words<FN / 2, kStreamed>(o_rsrc, off, w);
+                    }
                 }
             }
         }

@@ -130,6 +130,14 @@ def test_barriers_of_the_group_kernel_publish_what_has_landed(assembly):
     assert sum(line.strip() == "s_barrier" for line in lines) > 100
 
 
+def test_fp16_stores_of_the_operand_layout_round_once(assembly):
+    """Its epilogue ends in a fused multiply-add whose result goes to fp16.  Left to the compiler, most pairs become instructions that
+    round once and some (which ones depends on the tile) a fp32 instruction and a conversion, which rounds twice."""
+    lines = assembly["gemm_olay.hip"]
+    assert not [line.strip() for line in lines if re.search(r"v_cvt_(pk_)?f16_f32", line)]
+    assert sum("v_fma_mixhi_f16" in line for line in lines) > 500
+
+
 def test_the_search_for_loose_barriers_finds_one():
     code = ["_Zkernel:", "\ts_barrier", ".L1:", "\tbuffer_load_dwordx4 v1, s[0:3], 0 offen lds", "\tbuffer_load_dword v2, v1, s[0:3], 0",
             "\ts_waitcnt vmcnt(2)", "\ts_barrier", "\ts_cbranch_scc1 .L1", "\ts_branch .L3", ".L3:"]

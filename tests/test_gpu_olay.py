@@ -142,6 +142,21 @@ def test_linear_fp16(B, orc, act, with_bias):
         assert_f16(got, want["out"], OLAY_SAME if act == 0 else GELU_SAME, f"schedule {sch}")
 
 
+@pytest.mark.parametrize("M,N,K", [(1541, 1288, 512), (1300, 776, 384)])
+def test_fp16_outputs_do_not_depend_on_the_tile(B, M, N, K):
+    """Every tile shape rounds an output once: the same bits whichever the cost rule picks (about one value in 2^13 lies so close
+    to the middle of two fp16 values that rounding it to fp32 first would move it)."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+    A = B.quantize_act(torch.randn((M, K), device="cuda", generator=g).half(), SYM, layout=MFMA)
+    Q = B.quantize_weight((torch.randn((N, K), device="cuda", generator=g) * 0.02).half(), SYM, 0, layout=MFMA)
+    bias = torch.randn(N, device="cuda", generator=g).half()
+    for b, act in ((None, 0), (bias, 0), (None, 1), (bias, 1)):
+        got = [B.linear(A, Q, b, act, schedule=sch) for sch in _olay_schedules(B, K)]
+        for sch, y in zip(_olay_schedules(B, K)[1:], got[1:]):
+            differ = (y.view(torch.int16) != got[0].view(torch.int16)).sum().item()
+            assert differ == 0, (B.schedule_names()[sch - 1], differ)
+
+
 @pytest.mark.parametrize("K", [256, 768])
 def test_many_tiles_per_workgroup(B, orc, K):
     """More tiles than resident workgroups (at most 3 x 256 CUs): every workgroup walks several tiles, so
