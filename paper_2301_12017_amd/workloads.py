@@ -88,11 +88,16 @@ def run_chain(A: B.QAct, layers: List[ChainLayer], workspace: Optional[torch.Ten
     an fp16 activation tensor in between.  `record` (a list) receives (name, input, output).
     The requantized outputs keep the layout of the operands; the QKV output keeps one
     odd-position sum per third so that the V slice can be consumed in place.  Unless somebody wants
-    to see the calls one by one (record, a forced schedule, a workspace for each), they are one call of the library."""
+    to see the calls one by one (record, a forced schedule, a workspace for each) or a layer has unsigned codes,
+    they are one call of the library."""
     h = layers[0].out.spec.K
-    if record is None and schedule == 0 and workspace is None:
-        return B.linear_chain(A, [(lay.W, lay.bias, lay.act, first) for L in layers
-                                  for lay, first in ((L.qkv, 0), (L.out, 2 * h), (L.ffn1, 0), (L.ffn2, 0))])
+    linears = [lay for L in layers for lay in (L.qkv, L.out, L.ffn1, L.ffn2)]
+    if record is None and schedule == 0 and workspace is None and all(m == B.SYM for m in (A.mode, *(lay.W.mode for lay in linears))):
+        # linear_chain reads W.K columns of the step before, whatever its N: here that is the V third or all of them
+        for i, lay in enumerate(linears):
+            if lay.W.K != (h if i % 4 == 1 else linears[i - 1].W.N if i else A.K):
+                raise B.W4A4Error(-1, "run_chain")
+        return B.linear_chain(A, [(lay.W, lay.bias, lay.act, 2 * h if i % 4 == 1 else 0) for i, lay in enumerate(linears)])
     for li, L in enumerate(layers):
         steps = (("qkv", L.qkv, None), ("attn_out", L.out, h), ("ffn1", L.ffn1, None), ("ffn2", L.ffn2, None))
         for name, lay, slice_h in steps:

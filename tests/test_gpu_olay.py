@@ -15,7 +15,7 @@ from tests.gpu_util import (GELU_SAME, OLAY_SAME, act_to_canonical, assert_f16, 
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
 
-SYM = 0
+SYM, ASYM = 0, 1
 MFMA = 1
 
 
@@ -502,3 +502,30 @@ def test_chain_in_one_call_equals_the_calls_one_by_one(B, layout, M, h, f):
     again = B.linear(got, layers[0].qkv.W, layers[0].qkv.bias, 0)  # the result is an operand like any other
     assert torch.equal(again, B.linear(want, layers[0].qkv.W, layers[0].qkv.bias, 0))
     assert B.fused_fault_check() is False
+
+
+def test_chain_takes_and_refuses_what_the_calls_one_by_one_do(B):
+    """Layers that do not fit each other are refused (a narrower W.K is no column slice: only the V third is), and a first layer with
+    unsigned codes, which the one call has no form for, still runs."""
+    from paper_2301_12017_amd import synth, workloads as WL
+    M, h, f = 40, 256, 512
+    g = torch.Generator(device="cuda").manual_seed(5)
+    n = lambda *s, std=1.0: (torch.randn(s, device="cuda", generator=g) * std).half()
+
+    def layer(modes=(SYM,) * 4, **sizes):
+        dims = {"qkv": (3 * h, h), "attn_out": (h, h), "ffn1": (f, h), "ffn2": (h, f), **sizes}
+        ls = [WL.Layer(synth.LinearSpec(name, M, N, K), B.quantize_weight(n(N, K, std=0.02), mode), None, 0)
+              for (name, (N, K)), mode in zip(dims.items(), modes)]
+        return WL.ChainLayer(*ls)
+
+    A = B.quantize_act(n(M, h), SYM)
+    good = layer()
+    for bad in (dict(ffn1=(f, h // 2)), dict(ffn2=(h, f // 2)), dict(ffn1=(f, 2 * h)), dict(qkv=(3 * h, h // 2)), dict(ffn2=(2 * h, f))):
+        layers = [good, layer(**bad)] if "qkv" in bad else [layer(**bad), good]
+        for record in ([], None):
+            with pytest.raises(B.W4A4Error):
+                WL.run_chain(A, layers, record=record)
+    first = layer((ASYM, SYM, SYM, SYM))
+    A = B.quantize_act(n(M, h), ASYM)
+    want, got = WL.run_chain(A, [first, good], record=[]), WL.run_chain(A, [first, good])
+    assert torch.equal(got.q, want.q) and torch.equal(got.scale, want.scale)
