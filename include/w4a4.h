@@ -443,7 +443,8 @@ int w4a4_linear(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep
  * column slice starts at a multiple of 32 (FP6: 64) columns, in the MFMA layout it is one of W.N / W.K equal slices.  The last step's codes, scales
  * and (MFMA layout) odd-position code sums [M] go to out, out_scale and out_osum, everything between into the
  * workspace (256-byte aligned, w4a4_linear_chain_workspace_bytes large; one call per workspace at a time).  Same bits as
- * the calls one by one; what all steps count in is cleared by one launch instead of one per step. */
+ * the calls one by one; what all steps count in is cleared by one launch instead of one per step.  A chain with a step that
+ * w4a4_linear would refuse is refused as a whole, before anything is launched; the workspace query answers 0 for it. */
 typedef struct {
     w4a4_weight W;
     const void *bias_f16;      /* [W.N] or NULL */

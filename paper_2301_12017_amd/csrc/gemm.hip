@@ -422,6 +422,12 @@ static int fused_requant_kind(const w4a4_act *A, const w4a4_weight *W, const w4a
     if (ep->schedule != 0 && ep->schedule != S_PIPE_128x256) return 0;
     return (long)((A->M + 127) / 128) * tn <= pipe_requant_max_tiles() ? 1 : 0;
 }
+// What a fused requantize of that kind runs as.
+static int fused_out_kind(int fused, const w4a4_epilogue *ep) {
+    return fused == 3 ? OUT_Q6 : fused == 2 && ep->requant_layout == W4A4_LAYOUT_MFMA ? OUT_Q4M : OUT_Q4;
+}
+static int fused_schedule(int fused) { return fused == 1 ? S_PIPE_128x256 : fused == 3 ? S_FP6_128x256 : S_OLAY_128x256; }
+
 static size_t fused_workspace_bytes(int M) {
     return ((size_t)M + (size_t)(M + 127) / 128 + 4) * sizeof(uint32_t);
 }
@@ -504,8 +510,8 @@ extern "C" int w4a4_pick_schedule(const w4a4_act *A, const w4a4_weight *W, const
     int out_kind = OUT_F16, schedule = ep->schedule;
     if (ep->requant) {
         const int fused = fused_requant_kind(A, W, ep, false);
-        out_kind = !fused ? OUT_F32 : fused == 3 ? OUT_Q6 : (fused == 2 && ep->requant_layout == W4A4_LAYOUT_MFMA) ? OUT_Q4M : OUT_Q4;
-        if (fused) schedule = fused == 1 ? S_PIPE_128x256 : fused == 3 ? S_FP6_128x256 : S_OLAY_128x256;
+        out_kind = fused ? fused_out_kind(fused, ep) : OUT_F32;
+        if (fused) schedule = fused_schedule(fused);
     }
     const int rc = resolve_schedule(g, grouped, out_kind, &schedule);
     return rc ? rc : schedule;
@@ -525,6 +531,21 @@ extern "C" int w4a4_gemm_i32(const w4a4_act *A, const w4a4_weight *W, int32_t *a
     return run_gemm(g, A->mode, grouped, OUT_I32, schedule, as_stream(stream));
 }
 
+// Everything that linear_impl can refuse of a requantizing layer behind check_layer.  Nothing is launched.
+static int check_requant(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, int ng, int fused) {
+    GemmArgs g;
+    fill_args(g, A, W, ng);
+    if (fused) {
+        int schedule = fused_schedule(fused);
+        return resolve_schedule(g, false, fused_out_kind(fused, ep), &schedule);
+    }
+    // FP6 codes exist only fused, and the row quantizer makes one odd-position sum per row
+    if (ep->requant_layout == W4A4_LAYOUT_FP6) return W4A4_ERR_UNSUPPORTED_SHAPE;
+    if (ep->requant_layout == W4A4_LAYOUT_MFMA && ep->requant_group != 0 && ep->requant_group != W->N) return W4A4_ERR_UNSUPPORTED_SHAPE;
+    int schedule = ep->schedule;
+    return resolve_schedule(g, A->mode == W4A4_ASYM || ng > 1, OUT_F32, &schedule);
+}
+
 // w4a4_linear behind its argument checks.  `exchange` is the area the fused requantize exchanges row maxima
 // through (fused_workspace_bytes(M) bytes, cleared here by a fill kernel together with the code sums, unless a kernel
 // before it on the stream has done so: `cleared`); `rows_f32` receives the fp32 rows of a requantize that cannot be
@@ -541,10 +562,9 @@ static int linear_impl(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilo
         g.out = out;
         return run_gemm(g, A->mode, grouped, OUT_F16, ep->schedule, st);
     }
-    if (ep->requant_layout == W4A4_LAYOUT_MFMA) {
-        if (!out_gsum) return W4A4_ERR_INVALID_ARG;            // receives the odd-position code sums
-        if (!fused && ep->requant_group != 0 && ep->requant_group != W->N) return W4A4_ERR_UNSUPPORTED_SHAPE;
-    }
+    if (ep->requant_layout == W4A4_LAYOUT_MFMA && !out_gsum) return W4A4_ERR_INVALID_ARG;   // receives the odd-position code sums
+    // everything that can refuse the launches is checked before the outputs are touched
+    if (const int rc = check_requant(A, W, ep, ng, fused)) return rc;
     if (fused) {
         // One kernel: the column tiles of a row panel exchange their row maxima through the exchange area and
         // pack the codes from registers.
@@ -564,20 +584,14 @@ static int linear_impl(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilo
         g.out_scale = out_scale;
         g.out = out;
         g.out_osum = out_gsum; g.osum_slices = slices; g.slice_tiles = sums && slices > 1 ? rg / 256 : 0x40000000;
-        const int out_kind = fused == 3 ? OUT_Q6 : fused == 1 ? OUT_Q4 : (sums ? OUT_Q4M : OUT_Q4);
-        int schedule = fused == 1 ? S_PIPE_128x256 : fused == 3 ? S_FP6_128x256 : S_OLAY_128x256;
-        // everything that can refuse the launch is checked before the outputs are touched
-        const int rc = resolve_schedule(g, false, out_kind, &schedule);
-        if (rc) return rc;
         if (!cleared)
             hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + n2 + 255) / 256)), dim3(256), 0, st, exchange, words,
                                reinterpret_cast<uint32_t *>(out_gsum), (int)n2);
-        return run_gemm(g, A->mode, false, out_kind, schedule, st);
+        return run_gemm(g, A->mode, false, fused_out_kind(fused, ep), fused_schedule(fused), st);
     }
     // Requantize: the per-token range needs the whole output row, which no single tile
     // sees.  The GEMM leaves the fp32 rows in the workspace and the row quantizer turns
     // them into packed codes.
-    if (ep->requant_layout == W4A4_LAYOUT_FP6) return W4A4_ERR_UNSUPPORTED_SHAPE;   // FP6 codes exist only fused
     g.out = rows_f32;
     const int rc = run_gemm(g, A->mode, grouped, OUT_F32, ep->schedule, st);
     if (rc) return rc;
@@ -649,7 +663,7 @@ static size_t code_bytes(int M, int N, int layout) {
 // Returns W4A4_OK or why the chain is refused.
 static int plan_chain(const w4a4_act *A, const w4a4_chain_step *steps, int n, uint8_t *out, float *out_scale, int32_t *out_osum,
                       uint8_t *workspace, std::vector<ChainStep> &plan, size_t *cleared, size_t *total) {
-    if (!A || !steps || n <= 0 || n > 4096 || A->mode != W4A4_SYM || A->M < 0) return W4A4_ERR_INVALID_ARG;
+    if (!A || !steps || n <= 0 || A->mode != W4A4_SYM || A->M < 0) return W4A4_ERR_INVALID_ARG;
     const int M = A->M;
     plan.resize(n);
     size_t at = 0, codes = 0, rows = 0;
@@ -732,6 +746,10 @@ extern "C" size_t w4a4_linear_chain_workspace_bytes(const w4a4_act *A, const w4a
         std::vector<ChainStep> plan;
         size_t cleared = 0, total = 0;
         if (!A || A->M <= 0 || plan_chain(A, steps, n, nullptr, nullptr, nullptr, nullptr, plan, &cleared, &total)) return 0;
+        for (int i = 0; i < n; ++i) {
+            const int G = steps[i].W.group ? steps[i].W.group : steps[i].W.K;
+            if (G < 0 || steps[i].W.K % G || check_requant(&plan[i].A, &steps[i].W, &plan[i].ep, steps[i].W.K / G, plan[i].fused)) return 0;
+        }
         return total;
     } catch (...) {
         return 0;
@@ -746,16 +764,17 @@ extern "C" int w4a4_linear_chain(const w4a4_act *A, const w4a4_chain_step *steps
         int rc = plan_chain(A, steps, n, static_cast<uint8_t *>(out), out_scale, out_osum, static_cast<uint8_t *>(workspace), plan, &cleared, &total);
         if (rc) return rc;
         const int M = A->M;
-        if (M > 0 && (!workspace || workspace_bytes < total || (reinterpret_cast<uintptr_t>(workspace) & 255))) return W4A4_ERR_WORKSPACE;
+        if (M > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255))) return W4A4_ERR_WORKSPACE;
         for (int i = 0; i < n; ++i) {                           // everything is checked before the first launch
             ChainStep &s = plan[i];
             int rng = 0;
             rc = check_layer(&s.A, &steps[i].W, &s.ep, s.q, s.scale, nullptr, &s.ng, &rng);
             if (rc) return rc;
             if (s.ep.requant_layout == W4A4_LAYOUT_MFMA && M > 0 && !s.osum) return W4A4_ERR_INVALID_ARG;
-            if (s.ep.requant_layout == W4A4_LAYOUT_FP6 && !s.fused) return W4A4_ERR_UNSUPPORTED_SHAPE;
+            if (M > 0 && (rc = check_requant(&s.A, &steps[i].W, &s.ep, s.ng, s.fused))) return rc;
         }
         if (M == 0) return W4A4_OK;
+        if (workspace_bytes < total) return W4A4_ERR_WORKSPACE;
         const hipStream_t st = as_stream(stream);
         const bool last_sums = plan[n - 1].fused && plan[n - 1].osum;
         const size_t words = cleared / sizeof(uint32_t);

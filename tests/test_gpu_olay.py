@@ -529,3 +529,29 @@ def test_chain_takes_and_refuses_what_the_calls_one_by_one_do(B):
     A = B.quantize_act(n(M, h), ASYM)
     want, got = WL.run_chain(A, [first, good], record=[]), WL.run_chain(A, [first, good])
     assert torch.equal(got.q, want.q) and torch.equal(got.scale, want.scale)
+
+
+@pytest.mark.parametrize("layout,M,steps", [
+    (MFMA, 300, ((512, 512, 0), (1152, 512, 0), (512, 384, 768))),      # thirds of 384 columns: their sums need whole tiles of 256
+    (0, 131072, ((256, 128, 0), (4096, 256, 0))),                       # fp32 rows past 32-bit offsets
+    (2, 300, ((512, 512, 0), (640, 512, 0))),                           # FP6 codes in whole tiles of 256 columns
+])
+def test_chain_is_refused_before_anything_is_launched(B, layout, M, steps):
+    """A later step that cannot run: no size from the workspace query, an error from the call, and neither the outputs nor the
+    workspace touched by the steps before it.  steps: (N, K, first column)."""
+    g = torch.Generator(device="cuda").manual_seed(6)
+    n = lambda *s: torch.randn(s, device="cuda", generator=g).half()
+    W = [B.quantize_weight(n(N, K), SYM, layout=layout) for N, K, _ in steps]
+    A = B.quantize_act(n(M, steps[0][1]), SYM, layout=layout)
+    c = (B._ChainStep * len(steps))(*[B._ChainStep(w.c(), None, 0, first) for w, (_, _, first) in zip(W, steps)])
+    a, L = A.c(), B.lib()
+    assert L.w4a4_linear_chain_workspace_bytes(a, c, len(steps)) == 0
+    o, scale, _, osum = B._alloc_out(A, W[-1], True, SYM, 0, layout)
+    workspace = torch.empty((M * 4096 * 4 + (1 << 28),), dtype=torch.uint8, device="cuda")
+    touched = [t for t in (o, scale, osum, workspace) if t is not None]
+    for t in touched:
+        t.fill_(7)
+    rc = L.w4a4_linear_chain(a, c, len(steps), B._ptr(o), B._ptr(scale), B._ptr(osum), workspace.data_ptr(), workspace.numel(), B._stream())
+    assert rc == -2
+    assert all((t == 7).all() for t in touched)
+    assert L.w4a4_linear_chain_workspace_bytes(a, c, 1) > 0        # the first step alone runs
