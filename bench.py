@@ -246,7 +246,7 @@ def chain_leg(steps, warmup, settle_ms, layout=None):
             out = B._alloc_out(a_in, lay.W, True, B.SYM, rg, lay.W.layout)
             calls.append(B.PreparedLinear(a_in, lay.W, lay.bias, lay.act, requant=True, requant_mode=B.SYM,
                                           requant_group=rg, out=out, workspace=ws, requant_layout=lay.W.layout))
-            scheds.append(B.pick_schedule(a_in, lay.W, requant=True, requant_group=rg, requant_layout=lay.W.layout))
+            scheds.append(B.pick_schedule(a_in, lay.W, requant=True, requant_group=rg, requant_layout=lay.W.layout, act=lay.act))
             names.append(name)
             A = B.QAct(out[0], out[1], None, None, M, lay.spec.N, B._row_bytes(lay.spec.N, lay.W.layout), 0, B.SYM, 0, lay.W.layout,
                        out[3] if mfma else None)

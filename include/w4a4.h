@@ -180,7 +180,9 @@ typedef struct {
 const char *w4a4_version(void);
 const char *w4a4_status_string(int status);
 
-/* Number of GEMM tile schedules compiled in, and a short name of schedule i (1-based). */
+/* Number of GEMM tile schedules compiled in, and a short name of schedule i (1-based).  Numbers behind the count name kernels for
+ * few tokens ("fp6_32x64": fp16 and int32 outputs), which w4a4_pick_schedule reports and a caller may ask for like any other;
+ * "" behind the last of them. */
 int         w4a4_schedule_count(void);
 const char *w4a4_schedule_name(int schedule);
 

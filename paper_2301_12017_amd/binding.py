@@ -205,7 +205,12 @@ def schedule_names():
 
 def schedule_number(name: str) -> int:
     """1-based number of the schedule called `name` (what w4a4_epilogue.schedule takes)."""
-    return schedule_names().index(name) + 1
+    i = 1
+    while (found := lib().w4a4_schedule_name(i).decode()) != name:
+        if not found:
+            raise ValueError(f"no schedule {name!r}")
+        i += 1
+    return i
 
 
 def fused_fault_check() -> bool:
@@ -221,14 +226,14 @@ def debug_fused_wait(spin_limit: int = 0, extra_arrivals: int = 0):
 
 
 def pick_schedule(A: "QAct", W: "QWeight", requant=False, requant_mode=SYM, requant_group=0, schedule=0,
-                  requant_layout=LAYOUT_CANONICAL) -> str:
+                  requant_layout=LAYOUT_CANONICAL, act=ACT_NONE) -> str:
     """Name of the schedule w4a4_linear runs this layer on."""
-    ep = _Epilogue(None, 0, int(requant), requant_mode, requant_group, requant_layout, schedule)
+    ep = _Epilogue(None, act, int(requant), requant_mode, requant_group, requant_layout, schedule)
     a, w = A.c(), W.c()
     rc = lib().w4a4_pick_schedule(ctypes.byref(a), ctypes.byref(w), ctypes.byref(ep))
     if rc < 0:
         raise W4A4Error(rc, "w4a4_pick_schedule")
-    return schedule_names()[rc - 1]
+    return lib().w4a4_schedule_name(rc).decode()
 
 
 def probe_mfma(operands: torch.Tensor, iters: int, sink: torch.Tensor) -> int:

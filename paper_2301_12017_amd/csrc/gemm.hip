@@ -43,10 +43,12 @@ static const Schedule kSchedules[] = {
     {"fp6_128x128", F_FP6, 2, false},
     {"fp6_192x256", F_FP6, 3, false},
     {"olay_256x256", F_OLAY, 3, false},
+    // behind w4a4_schedule_count: a kernel for few tokens, not a tile of its layout that a sweep over all sizes would try
+    {"fp6_32x64", F_FP6, kFp6FewTokens, false},
 };
-constexpr int kNumSchedules = sizeof(kSchedules) / sizeof(kSchedules[0]);
+constexpr int kNumSchedules = sizeof(kSchedules) / sizeof(kSchedules[0]), kTileSchedules = kNumSchedules - 1;
 enum { S_PIPE_128x256 = 1, S_PIPE_192x128, S_GEN_64x128, S_GEN_64x64, S_GEN_32x32, S_OLAY_128x256, S_OLAY_192x128,
-       S_OLAY_128x128, S_GROUP, S_SMALL, S_FP6_128x256, S_FP6_192x128, S_FP6_128x128, S_FP6_192x256, S_OLAY_256x256 };
+       S_OLAY_128x128, S_GROUP, S_SMALL, S_FP6_128x256, S_FP6_192x128, S_FP6_128x128, S_FP6_192x256, S_OLAY_256x256, S_FP6_32x64 };
 
 static bool pipe_ok(const GemmArgs &g, bool grouped, int kstep = kBK) {
     // 32-bit buffer offsets and whole K steps
@@ -136,7 +138,8 @@ static double tile_cost(const GemmArgs &g, const TileRates &r, int bm, int bn, i
 // CU is always the best choice.  Fitted to eighteen token counts as above, mostly behind the quantize of other activations (1 % above the
 // best tile).  Four linears with their quantizers: BERT-large 16384 tokens 245 -> 236 us, 12288 194 -> 187; BERT-base 16384 169 -> 160.
 bool olay_whole_lines(int K);
-static int pick_olay(const GemmArgs &g) {
+static int pick_olay(const GemmArgs &g, int out_kind) {
+    if (out_kind == OUT_Q4 || out_kind == OUT_Q4M) return olay_requant_takes_256x256(g, out_kind) ? S_OLAY_256x256 : S_OLAY_128x256;
     const long cus = device_cus();
     int best = S_OLAY_128x256;
     if (olay_whole_lines(g.K)) {
@@ -159,10 +162,21 @@ static int pick_olay(const GemmArgs &g) {
     return best;
 }
 
+// Few tokens: the FP6 kernel whose waves split K takes the place of 128 x 128 tiles, up to 512 tiles of 32 x 64, two
+// workgroups to a CU (us, 128 x 128 | 32 x 64: 128 x 768 x 768 6.3 | 4.0, 128 x 1024 x 4096 14.4 | 6.9, 301 x 3072 x 1024 (480 tiles)
+// 7.2 | 6.0, 1024 x 1024 x 4096 (512) 14.5 | 13.2; 450 x 2304 x 768 (540) 6.6 | 7.5, 1400 x 768 x 3072 (528) 12.0 | 16.4).
+static bool fp6_few_tokens(const GemmArgs &g, int out_kind) {
+    if (out_kind != OUT_F16 && out_kind != OUT_I32) return false;
+    const long tiles = (long)((g.M + 31) / 32) * ((g.N + 127) / 128 * 2);
+    return tiles <= 512;
+}
+
 // FP6 kernel.  The 192 x 256 tile (one wave per SIMD, least operand traffic per product) pays for long K and whole rounds of
 // one tile per CU: 12288 x 1024 x 4096, 256 tiles, 32.5 us against 34.3 on 128 x 256; 16384 x 768 x 3072, 258 tiles,
 // 43.4 against 28.6 (28.0 on 128 x 128); 16384 x 1024 x 4096 56.5 against 39.5.
-static int pick_fp6(const GemmArgs &g) {
+static int pick_fp6(const GemmArgs &g, int out_kind) {
+    if (out_kind == OUT_Q6) return S_FP6_128x256;
+    if (fp6_few_tokens(g, out_kind)) return S_FP6_32x64;
     const long cus = device_cus();
     const TileRates r = {1.31, 0.62, 0.83, 1.25, 0.745};
     int best = S_FP6_128x256;
@@ -174,15 +188,6 @@ static int pick_fp6(const GemmArgs &g) {
     return best;
 }
 
-// Few tokens, no schedule asked for: the FP6 kernel whose waves split K takes the place of 128 x 128 tiles, up to 512 tiles
-// of 32 x 64, two workgroups to a CU (us, 128 x 128 | 32 x 64: 128 x 768 x 768 6.3 | 4.0, 128 x 1024 x 4096 14.4 | 6.9, 301 x 3072 x 1024 (480 tiles) 7.2 |
-// 6.0, 1024 x 1024 x 4096 (512) 14.5 | 13.2; 450 x 2304 x 768 (540) 6.6 | 7.5, 1400 x 768 x 3072 (528) 12.0 | 16.4).
-static bool fp6_few_tokens(const GemmArgs &g, int out_kind) {
-    if (g.layout != W4A4_LAYOUT_FP6 || (out_kind != OUT_F16 && out_kind != OUT_I32)) return false;
-    const long tiles = (long)((g.M + 31) / 32) * ((g.N + 127) / 128 * 2);
-    return tiles <= 512;
-}
-
 // Resolves schedule 0 to the table's choice and checks everything a launcher of that family requires, so that
 // a caller can still refuse the call with its outputs untouched.  Nothing is launched here.
 static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *schedule) {
@@ -192,7 +197,7 @@ static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *
     const bool fp6 = g.layout == W4A4_LAYOUT_FP6;
     int sch = *schedule;
     // operand layout: symmetric per-channel layers run on the persistent kernel, unsigned (grouped) ones on the group kernel
-    if (sch == 0) sch = fp6 ? pick_fp6(g) : olay ? (grouped ? S_GROUP : pick_olay(g)) : pick_schedule(g, grouped, out_kind);
+    if (sch == 0) sch = fp6 ? pick_fp6(g, out_kind) : olay ? (grouped ? S_GROUP : pick_olay(g, out_kind)) : pick_schedule(g, grouped, out_kind);
     if (sch < 1 || sch > kNumSchedules) return W4A4_ERR_INVALID_ARG;
     const Schedule &s = kSchedules[sch - 1];
     if (grouped && !s.grouped_ok && !(s.family == F_SMALL && g.ng == 1)) return W4A4_ERR_INVALID_ARG;
@@ -203,7 +208,7 @@ static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *
     if ((out_kind == OUT_Q6) != (q4 && fp6)) return W4A4_ERR_UNSUPPORTED_SHAPE;   // FP6 codes come from the FP6 kernel, and only they
     switch (s.family) {
         case F_FP6:
-            if (!fp6_ok(g, grouped)) return W4A4_ERR_UNSUPPORTED_SHAPE;
+            if (!fp6_ok(g, grouped) || (s.variant == kFp6FewTokens && out_kind == OUT_F32)) return W4A4_ERR_UNSUPPORTED_SHAPE;
             if (q4) {
                 int lpr = 0, opl = 0;
                 if (s.variant != 0) return W4A4_ERR_INVALID_ARG;
@@ -218,10 +223,11 @@ static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *
         case F_OLAY:
             if (!pipe_ok(g, grouped) || g.K < 2 * kBK || (long)g.M * g.ldo * 4 >= 0x7fffffffL) return W4A4_ERR_UNSUPPORTED_SHAPE;
             if (q4) {
-                if (s.variant != 0) return W4A4_ERR_INVALID_ARG;
+                if (s.variant != 0 && s.variant != 3) return W4A4_ERR_INVALID_ARG;
                 const int lim = olay_requant_max_tiles_n(out_kind == OUT_Q4M);
                 if (lim < 0) return W4A4_ERR_HIP;
                 if ((g.N + 255) / 256 > lim) return W4A4_ERR_UNSUPPORTED_SHAPE;
+                if (s.variant == 3 && !olay_requant_256x256_ok(g.N, g.K, out_kind)) return W4A4_ERR_UNSUPPORTED_SHAPE;
             }
             break;
         case F_SMALL:
@@ -248,13 +254,12 @@ static int resolve_schedule(const GemmArgs &g, bool grouped, int out_kind, int *
 }
 
 static int run_gemm(GemmArgs &g, int mode, bool grouped, int out_kind, int schedule, hipStream_t st) {
-    const bool few = schedule == 0 && fp6_few_tokens(g, out_kind);
     const int rc = resolve_schedule(g, grouped, out_kind, &schedule);
     if (rc) return rc;
     const Schedule &s = kSchedules[schedule - 1];
     switch (s.family) {
         case F_OLAY: return launch_olay(s.variant, out_kind, g, st);
-        case F_FP6: return launch_fp6(few ? kFp6FewTokens : s.variant, out_kind, g, st);
+        case F_FP6: return launch_fp6(s.variant, out_kind, g, st);
         case F_SMALL: return launch_small_packed(mode, out_kind, g, st);
         case F_GROUP: return launch_group(mode, out_kind, g, st);
         case F_PIPE: return launch_pipe(s.variant, out_kind, g, st);
@@ -362,7 +367,7 @@ static void fill_args(GemmArgs &g, const w4a4_act *A, const w4a4_weight *W, int 
 
 using namespace w4a4;
 
-extern "C" int w4a4_schedule_count(void) { return kNumSchedules; }
+extern "C" int w4a4_schedule_count(void) { return kTileSchedules; }
 
 extern "C" int w4a4_preferred_layout(int M, int N, int K, int mode, int group) {
     (void)N;
@@ -408,9 +413,10 @@ static int fused_requant_kind(const w4a4_act *A, const w4a4_weight *W, const w4a
     if (((long)A->M + 512) * W->N * 4 >= 0x80000000L) return 0;
     const int tn = (W->N + 255) / 256;
     if (A->layout == W4A4_LAYOUT_MFMA) {
-        if (ep->schedule != 0 && ep->schedule != S_OLAY_128x256) return 0;
-        if (A->K < 2 * kBK || (long)A->M * A->ldo * 4 >= 0x7fffffffL) return 0;
         const bool mfma_out = ep->requant_layout == W4A4_LAYOUT_MFMA;
+        if (ep->schedule != 0 && ep->schedule != S_OLAY_128x256 &&
+            !(ep->schedule == S_OLAY_256x256 && olay_requant_256x256_ok(W->N, W->K, mfma_out ? OUT_Q4M : OUT_Q4))) return 0;
+        if (A->K < 2 * kBK || (long)A->M * A->ldo * 4 >= 0x7fffffffL) return 0;
         if (tn > olay_requant_max_tiles_n(mfma_out)) return 0;
         if (mfma_out) {
             const int rg = ep->requant_group == 0 ? W->N : ep->requant_group;
@@ -426,7 +432,7 @@ static int fused_requant_kind(const w4a4_act *A, const w4a4_weight *W, const w4a
 static int fused_out_kind(int fused, const w4a4_epilogue *ep) {
     return fused == 3 ? OUT_Q6 : fused == 2 && ep->requant_layout == W4A4_LAYOUT_MFMA ? OUT_Q4M : OUT_Q4;
 }
-static int fused_schedule(int fused) { return fused == 1 ? S_PIPE_128x256 : fused == 3 ? S_FP6_128x256 : S_OLAY_128x256; }
+static int fused_schedule(int fused, const w4a4_epilogue *ep) { return fused == 1 ? S_PIPE_128x256 : ep->schedule; }
 
 static size_t fused_workspace_bytes(int M) {
     return ((size_t)M + (size_t)(M + 127) / 128 + 4) * sizeof(uint32_t);
@@ -506,12 +512,13 @@ extern "C" int w4a4_pick_schedule(const w4a4_act *A, const w4a4_weight *W, const
     ng = A->K / G;
     GemmArgs g;
     fill_args(g, A, W, ng);
+    g.act = ep->act;
     const bool grouped = A->mode == W4A4_ASYM || ng > 1;
     int out_kind = OUT_F16, schedule = ep->schedule;
     if (ep->requant) {
         const int fused = fused_requant_kind(A, W, ep, false);
         out_kind = fused ? fused_out_kind(fused, ep) : OUT_F32;
-        if (fused) schedule = fused_schedule(fused);
+        if (fused) schedule = fused_schedule(fused, ep);
     }
     const int rc = resolve_schedule(g, grouped, out_kind, &schedule);
     return rc ? rc : schedule;
@@ -536,7 +543,7 @@ static int check_requant(const w4a4_act *A, const w4a4_weight *W, const w4a4_epi
     GemmArgs g;
     fill_args(g, A, W, ng);
     if (fused) {
-        int schedule = fused_schedule(fused);
+        int schedule = fused_schedule(fused, ep);
         return resolve_schedule(g, false, fused_out_kind(fused, ep), &schedule);
     }
     // FP6 codes exist only fused, and the row quantizer makes one odd-position sum per row
@@ -587,7 +594,7 @@ static int linear_impl(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilo
         if (!cleared)
             hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + n2 + 255) / 256)), dim3(256), 0, st, exchange, words,
                                reinterpret_cast<uint32_t *>(out_gsum), (int)n2);
-        return run_gemm(g, A->mode, false, fused_out_kind(fused, ep), fused_schedule(fused), st);
+        return run_gemm(g, A->mode, false, fused_out_kind(fused, ep), fused_schedule(fused, ep), st);
     }
     // Requantize: the per-token range needs the whole output row, which no single tile
     // sees.  The GEMM leaves the fp32 rows in the workspace and the row quantizer turns

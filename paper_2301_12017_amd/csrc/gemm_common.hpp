@@ -465,6 +465,8 @@ int launch_mid(int variant, int mode, int out_kind, GemmArgs &g, hipStream_t st)
 int device_cus();                                               // gemm.hip
 // Residency limits of the fused requantize on the current device (see the definitions)
 int olay_requant_max_tiles_n(bool mfma_out);
+bool olay_requant_256x256_ok(int N, int K, int out_kind);
+bool olay_requant_takes_256x256(const GemmArgs &g, int out_kind);
 // The group kernel (gemm_group.hip).  LDS of a workgroup: stages of a 128 x 128 tile (three of one K step, or two of two whose rows are
 // whole cache lines; in the operand layout with a column of token sums per K step), token parameters and - asymmetric layers - the
 // group tables zw[ng][128] and RA[ng][128].  Two workgroups share a CU's 160 KB.
@@ -477,7 +479,7 @@ inline bool group_lines_ok(int K, int ng) { return K / ng % 256 == 0; }
 // ... groups of one K step: the tables may be read from memory, four groups per request
 inline bool group_memtab_ok(int K, int ng) { return K / ng == 128 && ng % 8 == 0 && K <= 4096; }
 
-constexpr int kFp6FewTokens = 4;                                 // gemm_fp6.hip: the variant that no schedule names
+constexpr int kFp6FewTokens = 4;                                 // gemm_fp6.hip: the variant whose waves split K
 int fp6_requant_max_tiles_n();
 int pipe_requant_max_tiles();
 

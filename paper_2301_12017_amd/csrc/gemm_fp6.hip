@@ -537,6 +537,7 @@ void gemm_fp6_kernel(GemmArgs g) {
 // epilogue.  A lane holds two adjacent channels.
 template <int NW, int OUT>
 __global__ __launch_bounds__(NW * 64) void gemm_fp6_small_kernel(GemmArgs g) {
+    static_assert(OUT == OUT_F16 || OUT == OUT_I32, "rows that are quantized afterwards come from the large tiles");
     constexpr int FN = 2, AHEAD = 4, RPW = 16 / (NW < 16 ? NW : 16);   // rows' registers that one wave finishes
     __shared__ int s_sum[FN * 16 * 64];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -553,7 +554,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_fp6_small_kernel(GemmArgs g) {
     for (int j = 0; j < FN; ++j) b_off[j] = ((gf + j) >> 2) * KB * 6144 + (((gf + j) & 3) * 32 + (lane & 31)) * kRow6 + (lane >> 5) * 16;
     u32x4 a16[AHEAD], b16[AHEAD][FN];
     u32x2 a8[AHEAD], b8[AHEAD][FN];
-    auto request = [&](int s, int b) {                          // (a block past K is requested but never used: outside the descriptor or another block)
+    auto request = [&](int s, int b) {
         a16[s] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off, b * 3072, 0);
         a8[s] = __builtin_amdgcn_raw_buffer_load_b64(a_rsrc, a_off + tail, b * 3072, 0);
 #pragma unroll
@@ -622,15 +623,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_fp6_small_kernel(GemmArgs g) {
                 y[j] = t * sw[j];
                 if (g.bias) y[j] = y[j] + bias[j];
             }
-            if constexpr (OUT == OUT_F32) {
-                const bool gelu = g.act == W4A4_ACT_GELU;
-                const uint32_t w[FN] = {__float_as_uint(gelu ? gelu_erf(y[0]) : y[0]), __float_as_uint(gelu ? gelu_erf(y[1]) : y[1])};
-                store_words<FN>(o_rsrc, off, w);
-            } else if (g.act == W4A4_ACT_GELU) {
-                store_gelu_halves<FN>(o_rsrc, off, y);
-            } else {
-                store_halves<FN>(o_rsrc, off, y);
-            }
+            if (g.act == W4A4_ACT_GELU) store_gelu_halves<FN>(o_rsrc, off, y);
+            else store_halves<FN>(o_rsrc, off, y);
         }
     }
 }
@@ -702,7 +696,8 @@ static int launch_variant6(int variant, GemmArgs &g, hipStream_t st) {
         case 1: return launch_one6<3, 2, 2, 2, 2, 5, OUT>(g, st);   // 192 x 128, two workgroups per CU
         case 2: return launch_one6<2, 2, 2, 2, 3, 4, OUT>(g, st);   // 128 x 128, three workgroups per CU
         case 3: return launch_one6<3, 4, 2, 2, 1, 7, OUT>(g, st);   // 192 x 256, one workgroup per CU, one wave per SIMD
-        case kFp6FewTokens: return g.K > 1536 ? launch_small6<16, OUT>(g, st) : launch_small6<8, OUT>(g, st);   // 32 x 64
+        case kFp6FewTokens:                                         // 32 x 64, fp16 and int32 outputs
+            if constexpr (OUT != OUT_F32) return g.K > 1536 ? launch_small6<16, OUT>(g, st) : launch_small6<8, OUT>(g, st);
         default: return W4A4_ERR_INVALID_ARG;
     }
 }

@@ -647,17 +647,23 @@ static int launch_variant(int variant, GemmArgs &g, hipStream_t st) {
     }
 }
 
+static int requant_slots_256x256(int out_kind) {
+    return out_kind == OUT_Q4M ? OlayLaunch<2, 4, 4, 2, 2, 128, 2, OUT_Q4M>::slots() : OlayLaunch<2, 4, 4, 2, 2, 128, 2, OUT_Q4>::slots();
+}
+// Whether a requantizing output can take the 256 x 256 tile at all.
+bool olay_requant_256x256_ok(int N, int K, int out_kind) {
+    const int slots = requant_slots_256x256(out_kind);
+    return olay_whole_lines(K) && slots >= kXcd && (N + 255) / 256 <= slots / kXcd;
+}
 // Tile of the requantizing outputs.  The waves of a 256 x 256 tile wait for their row panel with nothing else on the CU, so it pays
 // only where an XCD's 32 workgroups hold whole panels (up to two of them idle) and the rounds come out even.  In units of about 1 us: a
 // round of 256 x 256 tiles 15 per 1024 codes of K and 3 (4.5 with GELU) for its epilogue, a 128 x 256 tile 8.8 and 1.5 (one alone on a CU
 // 1.6 times that), before them 6.6 and 4.2.  128 x 256 | 256 x 256: 32768 x 1024 x 4096 104.6 | 94.6 us, 16000 x 1024 x 4096 56.0 | 50.8,
 // 8000 x 1024 x 4096 33.8 | 42.1, 32768 x 4096 x 1024 + GELU 168.9 | 162.4; with panels of twelve tiles, 32768 x 3072 x 1024 116 | 119.
-template <int OUT>
-static bool requant_takes_256x256(const GemmArgs &g) {
-    using L = OlayLaunch<2, 4, 4, 2, 2, 128, 2, OUT>;
-    if (!olay_whole_lines(g.K)) return false;
-    const int tn = (g.N + 255) / 256, slots = L::slots();
-    if (slots < kXcd || tn > slots / kXcd || (slots / kXcd) % tn > 2) return false;
+bool olay_requant_takes_256x256(const GemmArgs &g, int out_kind) {
+    if (!olay_requant_256x256_ok(g.N, g.K, out_kind)) return false;
+    const int tn = (g.N + 255) / 256, slots = requant_slots_256x256(out_kind);
+    if ((slots / kXcd) % tn > 2) return false;
     auto per_cu = [&](int bm) {                                  // tiles on the busiest CU
         const int panels = ((g.M + bm - 1) / bm + kXcd - 1) / kXcd;
         return (panels * tn + slots / kXcd - 1) / (slots / kXcd);
@@ -668,8 +674,7 @@ static bool requant_takes_256x256(const GemmArgs &g) {
 }
 template <int OUT>
 static int launch_requant(int variant, GemmArgs &g, hipStream_t st) {
-    if (variant != 0) return W4A4_ERR_INVALID_ARG;
-    return requant_takes_256x256<OUT>(g) ? launch_256x256_lines<OUT>(g, st) : launch_128x256<OUT>(g, st);
+    return variant == 3 ? launch_256x256_lines<OUT>(g, st) : variant == 0 ? launch_128x256<OUT>(g, st) : W4A4_ERR_INVALID_ARG;
 }
 
 // Requires: MFMA operand layout on both sides (symmetric codes, per-channel weight scales),

@@ -394,6 +394,8 @@ def test_few_tokens_split_k(B, M, N, K):
     bias = (torch.randn(N, device="cuda", generator=g) * 0.01).half()
     A, Q = B.quantize_act(X, SYM, layout=FP6), B.quantize_weight(W, SYM, 0, layout=FP6)
     tiles = B.schedule_number("fp6_128x128")
+    assert B.pick_schedule(A, Q) == B.pick_schedule(A, Q, schedule=B.schedule_number("fp6_32x64")) == "fp6_32x64"
+    assert B.pick_schedule(A, Q, schedule=tiles) == "fp6_128x128"
     assert torch.equal(B.gemm_i32(A, Q), B.gemm_i32(A, Q, schedule=tiles))
     for b, act in ((None, 0), (bias, 0), (bias, 1)):
         got = torch.full((M + 2, N), 7.0, dtype=torch.float16, device="cuda")

@@ -455,6 +455,8 @@ def test_fused_requantize_on_256_row_panels(B, M, N, K, rlayout, gelu):
     A, Q = B.quantize_act(X, SYM, layout=MFMA), B.quantize_weight(W, SYM, 0, layout=MFMA)
     assert B.linear_workspace_bytes(A, Q, requant_layout=rlayout) < 8 * M                 # fused
     run = lambda schedule=0: B.linear(A, Q, bias, gelu, requant=True, requant_layout=rlayout, schedule=schedule)
+    name = lambda schedule=0: B.pick_schedule(A, Q, requant=True, requant_layout=rlayout, act=gelu, schedule=schedule)
+    assert name() == "olay_256x256"
     plain = run(B.schedule_number("olay_128x128"))                                        # fp32 rows, then the row quantizer
     for _ in range(3):
         fused = run()
@@ -470,6 +472,27 @@ def test_fused_requantize_on_256_row_panels(B, M, N, K, rlayout, gelu):
     finally:
         B.debug_fused_wait()
     assert torch.equal(run().q, plain.q) and B.fused_fault_check() is False
+
+
+@pytest.mark.parametrize("M,N,K,fused_256", [(700, 768, 512, True), (300, 1024, 384, False)])
+def test_requantizing_schedules_run_as_named(B, M, N, K, fused_256):
+    """The schedule that pick_schedule reports, handed back, is the one that runs; both fused tiles can be asked for (256 x 256 only
+    where K comes in whole cache lines: else fp32 rows and the row quantizer), and all of them write the same codes."""
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A = B.quantize_act(torch.randn((M, K), device="cuda", generator=g).half(), SYM, layout=MFMA)
+    Q = B.quantize_weight((torch.randn((N, K), device="cuda", generator=g) * 0.02).half(), SYM, 0, layout=MFMA)
+    want = None
+    for name in ("olay_128x128", "olay_128x256", "olay_256x256", None):
+        sch = 0 if name is None else B.schedule_number(name)
+        picked = B.pick_schedule(A, Q, requant=True, requant_layout=MFMA, schedule=sch)
+        assert picked == (name or "olay_128x256")
+        fused = B.linear_workspace_bytes(A, Q, requant_layout=MFMA, schedule=sch) < 4 * M * N
+        assert fused == (picked == "olay_128x256" or (picked == "olay_256x256" and fused_256))
+        out = B.linear(A, Q, None, 0, requant=True, requant_layout=MFMA, schedule=sch)
+        want = want or out
+        for a, b in ((out.q, want.q), (out.scale, want.scale), (out.osum.reshape(M), want.osum.reshape(M))):
+            assert torch.equal(a, b), name
+    assert B.fused_fault_check() is False
 
 
 @pytest.mark.parametrize("layout", [0, MFMA, 2])
