@@ -275,7 +275,8 @@ int w4a4_strategy_pick(const w4a4_strategy_costs *costs);
 
 /* Measures all options for an encoder layer of this shape (hidden size h: QKV h -> 3h, attention
  * output h -> h, FFN1 h -> ffn with GELU, FFN2 ffn -> h; symmetric per-channel weights, biases)
- * on the current device with synthetic operands: `iters` timed runs per option after two warm-up
+ * on the current device with synthetic operands, INT4 weights in the layout that w4a4_encoder_layer_prefers_fp6 and
+ * w4a4_preferred_layout name for the shape: `iters` timed runs per option after two warm-up
  * runs, HIP events on `stream`.  Allocates and frees its own device buffers and synchronizes the
  * stream.  Timings that differ by at most 3 % count as equal (a part's two precisions; the fused
  * pair against its two INT4 parts), so that the tie rules of w4a4_strategy_pick decide and not the

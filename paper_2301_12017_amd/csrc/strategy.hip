@@ -247,19 +247,19 @@ struct Arena {
 
 unsigned fill_grid(size_t n) { const size_t b = (n + 255) / 256; return (unsigned)(b > 4096 ? 4096 : (b ? b : 1)); }
 
-// A synthetic part: random codes in both precisions, scales of the size trained layers have.
-bool make_part(Arena &ar, int M, int N, int K, int act, uint32_t seed, hipStream_t st, w4a4_part *out) {
+// A synthetic part: random codes in both precisions (any bits are a number in the FP6 layout, too), scales of the size trained
+// layers have.
+bool make_part(Arena &ar, int N, int K, int layout, int act, uint32_t seed, hipStream_t st, w4a4_part *out) {
     w4a4_part p = {};
-    const int layout = w4a4_preferred_layout(M, N, K, W4A4_SYM, 0);
-    uint8_t *q4 = ar.get<uint8_t>((size_t)N * (K / 2));
+    const size_t bytes4 = layout == W4A4_LAYOUT_FP6 ? (((size_t)N + 127) & ~(size_t)127) * (K / 4 * 3) : (size_t)N * (K / 2);
+    uint8_t *q4 = ar.get<uint8_t>(bytes4);
     float *s4 = ar.get<float>(N);
     int32_t *es = ar.get<int32_t>(N);
     int8_t *q8 = ar.get<int8_t>((size_t)N * K);
     float *s8 = ar.get<float>(N);
     __half *bias = ar.get<__half>(N);
     if (!ar.ok) return false;
-    hipLaunchKernelGGL(fill_bytes_kernel, dim3(fill_grid((size_t)N * K / 8)), dim3(256), 0, st,
-                       reinterpret_cast<uint32_t *>(q4), (size_t)N * K / 8, seed);
+    hipLaunchKernelGGL(fill_bytes_kernel, dim3(fill_grid(bytes4 / 4)), dim3(256), 0, st, reinterpret_cast<uint32_t *>(q4), bytes4 / 4, seed);
     hipLaunchKernelGGL(fill_bytes_kernel, dim3(fill_grid((size_t)N * K / 4)), dim3(256), 0, st,
                        reinterpret_cast<uint32_t *>(q8), (size_t)N * K / 4, seed + 1);
     hipLaunchKernelGGL(fill_floats_kernel, dim3(fill_grid(N)), dim3(256), 0, st, s4, (size_t)N, 0.02f);
@@ -386,7 +386,9 @@ extern "C" int w4a4_strategy_lookup(int M, int hidden, int ffn) {
     // measured on MI355X for BERT-base and BERT-large shapes: INT4 wins every part at every token
     // count (by 2x and more below a few hundred tokens, where the INT4 part is one kernel); handing
     // the codes over in FFN1's epilogue beats a separate quantize of the fp16 intermediate only
-    // for many tokens: from about 6144 at hidden size 1024, from about 16384 at 768
+    // for many tokens: from about 6144 at hidden size 1024, from about 16384 at 768.  Layer with weights in the layout it
+    // takes, separate | fused, us: hidden 1024: 8192 tokens 166.2 | 164.4, 12288 239.6 | 227.9, 16384 291.0 | 284.8;
+    // hidden 768: 12288 178.3 | 181.8, 14336 199.8 | 196.6, 16384 217.3 | 214.9, 20480 252.6 | 253.3, 24576 305.6 | 301.8
     const bool fused = hidden >= 1024 ? M >= 6144 : M >= 16384;
     return fused ? W4A4_STRATEGY_ALL_INT4 : 15;
 }
@@ -399,9 +401,12 @@ extern "C" int w4a4_strategy_tune(int M, int hidden, int ffn, int iters, w4a4_st
     Arena ar;
     const int dims[4][2] = {{3 * hidden, hidden}, {hidden, hidden}, {ffn, hidden}, {hidden, ffn}};   // {N, K}
     w4a4_part parts[4];
-    for (int p = 0; p < 4; ++p)
-        if (!make_part(ar, M, dims[p][0], dims[p][1], p == W4A4_PART_FFN1 ? W4A4_ACT_GELU : W4A4_ACT_NONE, 1000u * (p + 1), st, &parts[p]))
+    const bool fp6 = w4a4_encoder_layer_prefers_fp6(M, hidden, ffn) != 0;   // the INT4 kernels that a layer of this size runs on
+    for (int p = 0; p < 4; ++p) {
+        const int N = dims[p][0], K = dims[p][1], layout = fp6 ? W4A4_LAYOUT_FP6 : w4a4_preferred_layout(M, N, K, W4A4_SYM, 0);
+        if (!make_part(ar, N, K, layout, p == W4A4_PART_FFN1 ? W4A4_ACT_GELU : W4A4_ACT_NONE, 1000u * (p + 1), st, &parts[p]))
             return W4A4_ERR_HIP;
+    }
     const int widest = ffn > 3 * hidden ? ffn : 3 * hidden;
     __half *X = ar.get<__half>((size_t)M * widest);
     __half *Y = ar.get<__half>((size_t)M * widest);

@@ -169,6 +169,15 @@ def test_tuner_picks_what_its_timings_say(B, orc):
     assert B.strategy_lookup(136, 768, 3072) == 15                     # untuned shape: the built-in table
 
 
+@pytest.mark.parametrize("M,h,f", [(12288, 512, 2048), (8200, 1024, 4096)])
+def test_tuner_where_the_layer_takes_the_fp6_layout(B, orc, M, h, f):
+    """Its synthetic INT4 weights are in that layout, too: sizes of their own, every option runs, the pick is remembered."""
+    assert B.lib().w4a4_encoder_layer_prefers_fp6(M, h, f) == 1
+    pick, part_us, fused_us = B.strategy_tune(M, h, f, iters=3)
+    assert all(0 < t < 1e5 for row in part_us for t in row) and 0 < fused_us < 1e5
+    assert B.strategy_lookup(M, h, f) == pick and B.fused_fault_check() is False
+
+
 def _big(seed, M, h, f):
     """Full-size operands made on the device (the host copy of the weights and of the sampled rows goes to the oracle)."""
     g = torch.Generator(device="cuda").manual_seed(seed)
