@@ -203,6 +203,10 @@ int w8a8_quantize_rows(const void *X_f16, int M, int K, int ldx, int8_t *q, floa
 int w8a8_linear(const int8_t *Aq, int lda, const float *sa, int M, const int8_t *Wq, const float *sw,
                 int N, int K, const w4a4_epilogue *ep, void *out, void *stream);
 
+/* Name of the tile that w8a8_linear and w8a8_gemm_i32 run a problem of this size in, "" for sizes they refuse.  Host
+ * arithmetic on the current device's CU count. */
+const char *w8a8_tile_name(int M, int N, int K);
+
 /* w8a8_quantize_rows + w8a8_linear in ONE kernel for small token counts, as w4a4_linear_f16act does it
  * for INT4 (Sec. 4.2: at small batch x sequence launch overhead and the quantize kernels decide): the
  * result equals those two calls bit for bit.  X_f16 [M, ldx] fp16, Wq [N, K] int8, sw [N]; K % 64 == 0,

@@ -98,6 +98,7 @@ _SIGNATURES = {
                                 _vp, _vp, _vp, _vp, _vp]),
     "w4a4_linear_chain_workspace_bytes": (_sz, [ctypes.POINTER(_Act), ctypes.POINTER(_ChainStep), _i]),
     "w4a4_linear_chain": (_i, [ctypes.POINTER(_Act), ctypes.POINTER(_ChainStep), _i, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "w8a8_tile_name": (ctypes.c_char_p, [_i, _i, _i]),
     "w8a8_quantize_rows": (_i, [_vp, _i, _i, _i, _vp, _vp, _vp]),
     "w8a8_linear": (_i, [_vp, _i, _vp, _i, _vp, _vp, _i, _i, ctypes.POINTER(_Epilogue), _vp, _vp]),
     "w8a8_linear_f16act": (_i, [_vp, _i, _i, _i, _vp, _vp, _i, ctypes.POINTER(_Epilogue), _vp, _vp]),

@@ -335,7 +335,9 @@ static int launch_one(GemmArgs &g, hipStream_t st) {
 bool small8_ok(const GemmArgs &g);                              // gemm_small.hip: the split-K kernel for small problems
 int launch_small_packed8(int out_kind, GemmArgs &g, hipStream_t st);
 
-enum { W8_128x128, W8_128x128_PAIR, W8_256x128, W8_256x256, W8_64_128x256, W8_64_128x128 };
+enum { W8_128x128, W8_128x128_PAIR, W8_256x128, W8_256x256, W8_64_128x256, W8_64_192x128, W8_64_128x128, W8_SMALL };
+static const char *const kTileNames[] = {"128x128", "128x128_pairs", "256x128", "256x256", "half_lines_128x256", "half_lines_192x128",
+                                         "half_lines_128x128", "small"};
 template <int OUT>
 static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
     switch (tile) {
@@ -344,6 +346,7 @@ static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
         case W8_256x128: return launch_one<2, 2, 4, 2, 2, 128, 3, OUT>(g, st);      // one of eight waves, two steps ahead
         case W8_256x256: return launch_one<2, 4, 4, 2, 2, 128, 2, OUT>(g, st);      // one workgroup of eight waves per CU
         case W8_64_128x256: return launch_one<2, 4, 2, 2, 2, 64, 3, OUT>(g, st);    // half lines, two per CU
+        case W8_64_192x128: return launch_one<3, 2, 2, 2, 2, 64, 3, OUT>(g, st);    // half lines, two per CU
         default: return launch_one<2, 2, 2, 2, 3, 64, 3, OUT>(g, st);               // half lines, three per CU
     }
 }
@@ -354,31 +357,37 @@ static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
 // every CU has one 128 x 128 tile at most and it would leave half of them idle (4096 x 1024 x 4096 32.9 | 29.3, 2048 x 1024 x 4096 27.7 | 22.7,
 // 2048 x 768 x 3072 23.2 | 18.1).  Fitted to the times of all
 // at eighteen token counts from 600 to 16384 on the BERT-base and BERT-large linears: 0.2 % above the best of them on
-// average, 8 % at worst.  Four linears with their quantizers against half lines in 128 x 256, 192 x 128 and 128 x 128 tiles: 800
+// average, the condition on 256 x 128 tiles not counted, which takes out the worst misses (22 %).  Four linears with their quantizers against half lines in 128 x 256, 192 x 128 and 128 x 128 tiles: 800
 // tokens 63.4 -> 52.6 us, 4096 102.6 -> 91.1, 16384 314.5 -> 277.2 (BERT-large); 16384 218.5 -> 192.1 (BERT-base).
 // K in 64s but not in 128s, or below 256, keeps half lines (n tiles on the busiest CU, worked on by min(n, workgroups per CU) at a time: cost
-// n * area / (rate * efficiency), rate of one / two / three 0.7 / 1 / 0.95, efficiency of 128 x 128 0.8).
+// n * area / (rate * efficiency), rate of one / two / three 0.7 / 1 / 0.95, efficiency of 192 x 128 and 128 x 128 0.9 and 0.8; without
+// 192 x 128 tiles 6144 x 704 x 960 7.9 -> 9.5 us, 12288 x 704 x 1088 14.2 -> 16.5, 8192 x 1088 x 3008 35.3 -> 40.6).
 // A few hundred 32 x 32 tiles at most go to the small-problem kernel instead (latency decides there).
-static int launch_w8(int out_kind, GemmArgs &g, hipStream_t st) {
-    if (small8_ok(g)) return launch_small_packed8(out_kind, g, st);
+static int pick_tile(const GemmArgs &g) {
+    if (small8_ok(g)) return W8_SMALL;
     const long cus = device_cus();
     auto busiest = [&](int bm, int bn) { return ((long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) + cus - 1) / cus; };
-    const double n128 = (double)busiest(128, 128), n256 = (double)busiest(256, 256);
-    int tile;
+    const double n128 = (double)busiest(128, 128);
     if (g.K % 128 == 0 && g.K >= 256) {
         const long pairs = busiest(128, 128) / 2, odd = busiest(128, 128) % 2;
-        const double pair = 2.0 * pairs + odd / 0.39, alone = g.K >= 384 ? n128 / 0.4 : 1e30, big = 4.0 * n256 / 1.1;
+        const double pair = 2.0 * pairs + odd / 0.39, alone = g.K >= 384 ? n128 / 0.4 : 1e30, big = 4.0 * (double)busiest(256, 256) / 1.1;
         const double tall = g.K >= 2048 && n128 > 1 ? 2.0 * (double)busiest(256, 128) / 1.07 : 1e30;
         double c = pair;
-        tile = W8_128x128_PAIR;
+        int tile = W8_128x128_PAIR;
         if (alone < c) { c = alone; tile = W8_128x128; }
         if (tall < c) { c = tall; tile = W8_256x128; }
-        if (big < c) tile = W8_256x256;
-    } else {
-        const double n = (double)busiest(128, 256);
-        const double wide = 2.0 * n / (n == 1 ? 0.7 : 1.0), narrow = n128 / ((n128 == 1 ? 0.7 : n128 == 2 ? 1.0 : 0.95) * 0.8);
-        tile = narrow < wide ? W8_64_128x128 : W8_64_128x256;
+        return big < c ? W8_256x256 : tile;
     }
+    auto cost = [&](int bm, int bn, int occ, double eff) {
+        const long n = busiest(bm, bn), together = n < occ ? n : occ;
+        return (double)n * bm * bn / ((together == 1 ? 0.7 : together == 2 ? 1.0 : 0.95) * eff);
+    };
+    const double wide = cost(128, 256, 2, 1.0), c192 = cost(192, 128, 2, 0.9), c128 = cost(128, 128, 3, 0.8);
+    return c128 < wide && c128 < c192 ? W8_64_128x128 : c192 < wide ? W8_64_192x128 : W8_64_128x256;
+}
+static int launch_w8(int out_kind, GemmArgs &g, hipStream_t st) {
+    const int tile = pick_tile(g);
+    if (tile == W8_SMALL) return launch_small_packed8(out_kind, g, st);
     return out_kind == OUT_I32 ? launch_tile<OUT_I32>(tile, g, st) : launch_tile<OUT_F16>(tile, g, st);
 }
 
@@ -405,6 +414,13 @@ static void w8_fill(GemmArgs &g, const int8_t *Aq, int lda, const float *sa, int
     g.Wq = reinterpret_cast<const uint8_t *>(Wq); g.ldw = K;
     g.M = M; g.N = N; g.K = K; g.ng = 1; g.steps_per_group = K / kW8Step;
     g.sa = sa; g.sw = sw; g.act = W4A4_ACT_NONE;
+}
+
+extern "C" const char *w8a8_tile_name(int M, int N, int K) {
+    if (M <= 0 || N <= 0 || K < 2 * kW8Step || K % kW8Step || N % 8) return "";
+    GemmArgs g;
+    w8_fill(g, nullptr, K, nullptr, M, nullptr, nullptr, N, K);
+    return kTileNames[pick_tile(g)];
 }
 
 extern "C" int w8a8_linear(const int8_t *Aq, int lda, const float *sa, int M, const int8_t *Wq, const float *sw,

@@ -152,3 +152,14 @@ def test_every_tile_of_the_persistent_kernel(B, M, N, K):
     assert torch.equal(B.gemm8_i32(Aq, sa, Wq, sw).double(), P)
     want = (P.float() * sa[:, None]) * sw[None, :] + bias.float()[None, :]
     assert torch.equal(B.linear8(Aq, sa, Wq, sw, bias), want.half())
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(4097, 1032, 192, "half_lines_192x128"), (4097, 4104, 320, "half_lines_192x128"),   # one and three a CU
+                                        (20000, 1032, 448, "half_lines_192x128"), (6100, 1032, 192, "half_lines_128x128"),
+                                        (6100, 2056, 448, "half_lines_128x256")])
+def test_tiles_of_half_lines(B, M, N, K, tile):
+    """K that does not come in whole cache lines: all three tiles are there, chosen by the busiest CU (192 x 128 takes up to a fifth
+    less time than the others), and exact."""
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert B.lib().w8a8_tile_name(M, N, K).decode() == tile
+    test_every_tile_of_the_persistent_kernel(B, M, N, K)
