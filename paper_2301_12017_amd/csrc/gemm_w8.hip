@@ -357,7 +357,7 @@ static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
 // every CU has one 128 x 128 tile at most and it would leave half of them idle (4096 x 1024 x 4096 32.9 | 29.3, 2048 x 1024 x 4096 27.7 | 22.7,
 // 2048 x 768 x 3072 23.2 | 18.1).  Fitted to the times of all
 // at eighteen token counts from 600 to 16384 on the BERT-base and BERT-large linears: 0.2 % above the best of them on
-// average, the condition on 256 x 128 tiles not counted, which takes out the worst misses (22 %).  Four linears with their quantizers against half lines in 128 x 256, 192 x 128 and 128 x 128 tiles: 800
+// average, the condition on 256 x 128 tiles not counted, which takes out the worst misses (up to 28 %).  Four linears with their quantizers against half lines in 128 x 256, 192 x 128 and 128 x 128 tiles: 800
 // tokens 63.4 -> 52.6 us, 4096 102.6 -> 91.1, 16384 314.5 -> 277.2 (BERT-large); 16384 218.5 -> 192.1 (BERT-base).
 // K in 64s but not in 128s, or below 256, keeps half lines (n tiles on the busiest CU, worked on by min(n, workgroups per CU) at a time: cost
 // n * area / (rate * efficiency), rate of one / two / three 0.7 / 1 / 0.95, efficiency of 192 x 128 and 128 x 128 0.9 and 0.8; without

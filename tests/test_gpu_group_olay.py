@@ -155,7 +155,8 @@ def test_many_tiles_and_the_canonical_kernel(B, orc, group, K):
         assert worst.max() <= 1e-2 * np.abs(canon.astype(np.float64)).max() + 4 * budget.max(), float(worst.max())
 
 
-@pytest.mark.parametrize("M,N,K,group", [(133, 136, 4096, 128), (1536 + 61, 2304 + 40, 4096, 128),      # tables from memory: one tile each, several
+@pytest.mark.parametrize("M,N,K,group", [(133, 136, 4096, 128), (1536 + 61, 2304 + 40, 4096, 128),      # tables from memory: a tile per workgroup
+                                         (4200, 2304 + 40, 4096, 128),                                  # ... more tiles than workgroups
                                          (133, 136, 256, 256), (2100, 4096 + 8, 512, 0), (300, 264, 4096, 256),   # rows of whole cache lines
                                          (140, 264, 768, 384), (140, 264, 3072, 1536)])                 # ... groups of 3 and 12 K steps
 def test_whole_lines_and_tables_from_memory(B, orc, M, N, K, group):
@@ -165,6 +166,8 @@ def test_whole_lines_and_tables_from_memory(B, orc, M, N, K, group):
     X, W = _x(rng, M, K), _w(rng, N, K)
     b = (rng.standard_normal(N) * 0.01).astype(np.float16)
     A, Q = B.quantize_act(dev(X), ASYM, group, layout=MFMA), B.quantize_weight(dev(W), ASYM, group, layout=MFMA)
+    if M == 4200:                                                  # two workgroups per CU: some walk two tiles
+        assert -(-M // 128) * -(-N // 128) > 2 * torch.cuda.get_device_properties(0).multi_processor_count
     assert B.pick_schedule(A, Q) == "group_128x128" and B.preferred_layout(2048, N, K, ASYM, group) == MFMA
     assert torch.equal(B.gemm_i32(A, Q), B.gemm_i32(B.quantize_act(dev(X), ASYM, group), B.quantize_weight(dev(W), ASYM, group)))
     rows = np.sort(np.concatenate([[0, M - 1], rng.choice(np.arange(1, M - 1), 30, replace=False)]))
