@@ -35,7 +35,7 @@
 //     costs nothing: 128*AE[m,g] arrives with the group's K step in LDS (one 4-byte DMA per row, the array is kept
 //     group-major for that) and is the C operand of the group's first MFMAs, shared by the column fragments.  The
 //     channel term is a constant per channel over all groups, 8 * sum_g sw[n,g]*WO[n,g], precomputed with the
-//     weights; the fp32 accumulators start from it.
+//     weights; the fp32 accumulators start from it (with the tables in memory, 32 groups, it comes last).
 //   * the fold is a conversion and ONE fused multiply-add per accumulator and group,
 //     t1 = fma(sw[n,g]/16, (float)acc, t1), and the zero-point sum, the token scale, the zero-point product and
 //     the bias are fused multiply-adds as well:  y = fma(sa, fma-chain(zw[n,g], RA[m,g], t1), fma(za, c[n], b[n])).
@@ -259,11 +259,12 @@ void gemm_group_kernel(GemmArgs g) {
         u32x2 c_raw = {0u, 0u};
         uint32_t bias_raw = 0;
         uint32_t kw_raw[FN] = {0u, 0u};                         // OLAY: what the layout's offsets add to t1, per channel
-        if constexpr (OLAY) {
+        auto request_kw = [&]() {
 #pragma unroll
             for (int j = 0; j < FN; ++j)
                 kw_raw[j] = __builtin_amdgcn_raw_buffer_load_b32(wo_rsrc, ((n_lane + j) * (g.ng + 1) + g.ng) * 4, 0, 0);
-        }
+        };
+        if constexpr (OLAY && !MEMTAB) request_kw();
         const int vb_next = vb + stride;
         const bool has_next = vb_next < total;
         const int tile_next = xcd_tile(has_next ? vb_next : vb, total);
@@ -276,7 +277,7 @@ void gemm_group_kernel(GemmArgs g) {
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) facc[i][j][r] = OLAY ? __uint_as_float(kw_raw[j]) : 0.0f;
+                for (int r = 0; r < 16; ++r) facc[i][j][r] = OLAY && !MEMTAB ? __uint_as_float(kw_raw[j]) : 0.0f;
 
         // ---- main loop ---------------------------------------------------------------------------------
 #define W4A4_SLOT_BEGIN(Ucur, k)                                                                          \
@@ -532,7 +533,12 @@ void gemm_group_kernel(GemmArgs g) {
                                   __half2float(__ushort_as_half((unsigned short)(bias_raw >> 16)))};
             if constexpr (MEMTAB) {
                 // as below, from memory: a lane takes four consecutive groups per request (lanes 0-31 groups 8t .. 8t+3, lanes
-                // 32-63 8t+4 .. 8t+7: ng is a multiple of 8)
+                // 32-63 8t+4 .. 8t+7: ng is a multiple of 8).  With so many groups the order of the sum decides its rounding noise:
+                // the groups' sums (half of t1), the zero-point sum (minus t1, nearly) and what the layout's offsets add (the other
+                // half) in this order keep the partial sums at half of t1, where starting from the offsets takes them up to t1.
+                // Error against float64, K = 4096 in 32 groups: canonical kernel 4.11e-4, from the offsets 4.51e-4, so 2.92e-4; times unchanged
+                // (16384 x 1024 x 4096 86 | 86 us, 2048 x 1024 x 4096 27 | 27).
+                request_kw();
                 const uint32_t g0 = (uint32_t)(lane >> 5) * 16u;
                 for (int t = 0; t * 8 < g.ng; ++t) {
                     u32x4 ra4[FM], zw4[FN];
@@ -550,6 +556,12 @@ void gemm_group_kernel(GemmArgs g) {
                             for (int j = 0; j < FN; ++j)
                                 facc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32((float)(int)ra4[i][u], __uint_as_float(zw4[j][u]), facc[i][j], 0, 0, 0);
                 }
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) facc[i][j][r] = facc[i][j][r] + __uint_as_float(kw_raw[j]);
             } else if constexpr (OLAY) {
                 // sum_g zw[n,g] * RA[m,g]: a rank-ng product of the tile's two group tables, continued into the fp32
                 // accumulators by the fp32 MFMA, two groups per instruction (lanes 0-31 carry group gp, lanes 32-63

@@ -181,3 +181,17 @@ def test_whole_lines_and_tables_from_memory(B, orc, M, N, K, group):
     truth = orc.truth64(a, w, ASYM, b, 0)
     e_gpu, e_orc = (np.sqrt(np.mean((v.astype(np.float64) - truth) ** 2)) for v in (got[rows], want))
     assert e_gpu <= 1.5 * e_orc + 1e-7, (e_gpu, e_orc)
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+def test_many_groups_lose_no_precision(B, orc, seed):
+    """32 groups: the large terms of the unsigned mapping cancel, and an order of summation that stays near its largest partial sum
+    carries more rounding noise than the canonical kernel's, which is the oracle's.  Root mean square errors against float64."""
+    rng = np.random.default_rng(seed)
+    M, N, K, group = 256, 512, 4096, 128
+    A, Q, a, w = _layer(B, orc, rng, M, N, K, group)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float16)
+    truth = orc.truth64(a, w, ASYM, b, 0)
+    e_gpu, e_orc = (np.sqrt(np.mean((v.astype(np.float64) - truth) ** 2))
+                    for v in (host(B.linear(A, Q, dev(b), 0)), orc.linear(a, w, ASYM, group, b, 0)["out"]))
+    assert e_gpu <= e_orc, (e_gpu, e_orc)
