@@ -658,7 +658,7 @@ int linear_layernorm_f16act(const LnArgs &ln, const w4a4_weight &W, const w4a4_e
 }
 bool linear_layernorm_f16act_ok(const LnArgs &ln, const w4a4_weight &W, const w4a4_epilogue &ep, const void *out) {
     const int M = ln.M, K = ln.K, N = W.N;
-    if ((K != 512 && K != 768 && K != 1024) || ln.ldx != K || !ln.R || N % 8) return false;
+    if ((K != 512 && K != 768 && K != 1024) || ln.ldx != K || !ln.R || N % 8 || (W.group != 0 && W.group != K)) return false;
     for (const void *p : {static_cast<const void *>(ln.X), static_cast<const void *>(ln.R), static_cast<const void *>(ln.gamma),
                           static_cast<const void *>(ln.beta), static_cast<const void *>(ln.Y), static_cast<const void *>(W.q), out})
         if (!p || !aligned16(p)) return false;

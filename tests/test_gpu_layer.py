@@ -314,3 +314,21 @@ def test_layernorm_inside_ffn1(B, shape):
     for seed, strategy in ((1, 15), (2, 7)):
         t, d, L = _layer(B, seed, batch, seq, heads, h, f)
         assert torch.equal(L(d["X"], strategy), _blocks(B, L, d, strategy))
+
+
+def test_layernorm_inside_ffn1_takes_and_refuses_what_the_parts_do(B):
+    """Infinities, NaN and sums past fp16's range give what the launches one by one give; a weight group that is no divisor of K
+    is refused by that path as by every other."""
+    batch, seq, heads, h, f = 1, 45, 12, 768, 3072
+    t, d, L = _layer(B, 3, batch, seq, heads, h, f)
+    for i, v in enumerate((np.inf, -np.inf, np.nan, 65504.0)):
+        d["X"][7 * i + 2, 5 + 100 * i] = float(v)
+        d["X"][7 * i + 3, 5 + 100 * i: 9 + 100 * i] = float(v)
+    d["be1"][9], d["g1"][600] = 60000.0, 60000.0
+    got, want = L(d["X"], 15), _blocks(B, L, d, 15)
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.isnan(got).any()
+    assert torch.equal(torch.nan_to_num(got, nan=1.0).view(torch.int16), torch.nan_to_num(want, nan=1.0).view(torch.int16))
+    L.c.ffn1.w4.group = 2 * h
+    L.workspace = torch.empty((1 << 26,), dtype=torch.uint8, device="cuda")
+    with pytest.raises(B.W4A4Error):
+        L(d["X"], 15)
