@@ -76,9 +76,10 @@ typedef enum { W4A4_SYM = 0, W4A4_ASYM = 1 } w4a4_mode;
  *              The sums travel beside the codes (osum / esum below) and the GEMM removes
  *              their terms again; int32 results (w4a4_gemm_i32) are exact in both layouts.
  * The MFMA layout needs K % 128 == 0 and, for symmetric codes, per-channel weight scales
- * (group == 0); for unsigned codes, weight groups that are multiples of 128 (or one group) whose
- * tables fit the kernel (K / group <= 32 at K <= 4096).  w4a4_preferred_layout tells whether
- * w4a4_linear is faster in it for a shape.
+ * (group == 0); for unsigned codes, weight groups that are multiples of 128 (or one group), up to 28
+ * of them, whose tables the kernel keeps on chip, or 32 of 128 (K == 4096), which it reads from memory;
+ * other numbers are UNSUPPORTED_SHAPE.  w4a4_preferred_layout tells whether w4a4_linear is faster in it
+ * for a shape.
  *   FP6        not a nibble encoding: every symmetric code c in [-7, 7] (the range the quantizers
  *              produce; -8 does not exist here) is stored as the 6-bit FP6 E2M3 number of the same
  *              value (sign, two exponent bits, three mantissa bits), 3/4 byte per code, so that the

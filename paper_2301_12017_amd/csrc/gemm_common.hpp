@@ -476,7 +476,7 @@ inline size_t group_lds(int ng, bool tables, bool olay, bool lines) {
 }
 // Operand layout, groups of several K steps: K and the groups in pairs of K steps
 inline bool group_lines_ok(int K, int ng) { return K / ng % 256 == 0; }
-// ... groups of one K step: the tables may be read from memory, four groups per request
+// ... groups of one K step: the tables may be read from memory, eight groups a turn.  As LDS holds those of 28 groups, that is K = 4096
 inline bool group_memtab_ok(int K, int ng) { return K / ng == 128 && ng % 8 == 0 && K <= 4096; }
 
 constexpr int kFp6FewTokens = 4;                                 // gemm_fp6.hip: the variant whose waves split K

@@ -379,7 +379,7 @@ void gemm_olay_kernel(GemmArgs g) {
 
     v16i acc[FM][FN];                                           // written by the first K step of every tile
 
-    // ---- first tile: its first two K steps and parameters --------------------------------------------
+    // ---- first tile: requests for its first NS-1 K steps and its parameters ---------------------------
     // Tile of virtual block id vb (workgroup id + k * grid size; vb % 8 = the XCD it runs on).  Every XCD
     // owns a contiguous range of tiles, so that the tiles of a row panel run on one XCD and share its
     // L2.  For the requantizing outputs the ranges are whole row panels: the column tiles of a panel
@@ -416,7 +416,7 @@ void gemm_olay_kernel(GemmArgs g) {
     int cur = 0;                                                // LDS stage of the current K step
     int parity = 0;
     for (;;) {
-        // first fragments of the tile (its first two K steps are in LDS and published)
+        // first fragments of the tile (its first NS-1 K steps are in LDS and published)
 #pragma unroll
         for (int f = 0; f < NF; ++f) P0[f] = read_frag(f, cur, 0);
         // ---- tile start: C operand of the first MFMAs, channel constants, origin of the next tile -----

@@ -170,7 +170,7 @@ void gemm_w8_kernel(GemmArgs g) {
 
     v16i acc[FM][FN];                                           // written by the first K step of every tile
 
-    // ---- first tile: its first two K steps and parameters --------------------------------------------
+    // ---- first tile: requests for its first NS-1 K steps and its parameters ---------------------------
     // Tile of virtual block id vb (workgroup id + k * grid size; vb % 8 = the XCD it runs on): every XCD
     // owns a contiguous range of tiles, so that the tiles of a row panel run on one XCD and share its L2.
     auto tile_of = [&](int v, int &t) {
@@ -195,7 +195,7 @@ void gemm_w8_kernel(GemmArgs g) {
     int cur = 0;                                                // LDS stage of the current K step
     int parity = 0;
     for (;;) {
-        // first fragments of the tile (its first two K steps are in LDS and published)
+        // first fragments of the tile (its first K step is in LDS and published; the NS-2 requested behind it are waited for at the barrier in front of each)
 #pragma unroll
         for (int f = 0; f < NF; ++f) P0[f] = read_frag(f, cur, 0);
         // ---- tile start: channel constants, origin of the next tile ------------------------------------
