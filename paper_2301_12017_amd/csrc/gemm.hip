@@ -652,8 +652,8 @@ ClearRanges w4a4::linear_clear_ranges(const w4a4_act *A, const w4a4_weight *W, c
 
 // ---- a chain of requantizing linears -----------------------------------------------------------------------
 // Every step's exchange area and (MFMA operand layout) code sums lie side by side in the workspace, so that ONE fill launch clears what
-// all steps count in: a chain of four linears is five launches instead of eight (a fill in front of each GEMM costs its launch, some
-// 2.5 us: 32768 tokens, 1024 features 448 -> 434 us; with one call instead of four from Python, 500 tokens of 768 78.6 -> 64.4).
+// all steps count in: a chain of four linears is five launches instead of eight (three fills less: 32768 tokens, 1024 features
+// 448 -> 434 us; with one call instead of four from Python, 500 tokens of 768 78.6 -> 64.4).
 struct ChainStep {
     w4a4_act A;
     w4a4_epilogue ep;
