@@ -169,7 +169,7 @@ def test_tuner_picks_what_its_timings_say(B, orc):
     assert B.strategy_lookup(136, 768, 3072) == 15                     # untuned shape: the built-in table
 
 
-@pytest.mark.parametrize("M,h,f", [(12288, 512, 2048), (8200, 1024, 4096)])
+@pytest.mark.parametrize("M,h,f", [(12288, 768, 2048), (8200, 1024, 4096)])
 def test_tuner_where_the_layer_takes_the_fp6_layout(B, orc, M, h, f):
     """Its synthetic INT4 weights are in that layout, too: sizes of their own, every option runs, the pick is remembered."""
     assert B.lib().w4a4_encoder_layer_prefers_fp6(M, h, f) == 1
