@@ -622,17 +622,27 @@ static int launch_grouped(GemmArgs &g, hipStream_t st) {
 // Rows of up to 1024 codes leave room for tiles of 32 tokens, three workgroups of eight waves to a CU; longer ones take sixteen
 // waves and 16 tokens, one to a CU.
 static bool grouped_short(const GemmArgs &g) { return g.K <= 1024; }
-// fp16 outputs of canonical codes in several weight groups, up to as many tiles as it wins with against 64 x 64 tiles of gemm_kernel (us, groups
-// of 128; asymmetric: 128 x 768 x 768 5.7 | 12.2, 128 x 768 x 3072 6.5 | 27.0, 301 x 3072 x 1024 (960 tiles) 10.5 | 12.1, 450 x 2304 x 768 (1080)
-// 13.2 | 13.4, 600 x 3072 x 1024 (1824) 18.6 | 13.3, 600 x 1024 x 4096 (1216) 29.6 | 34.5, 800 x 1024 x 4096 (1600) 40.4 | 34.7; symmetric: 128 x 768 x 3072
-// 6.0 | 20.4, 200 x 3072 x 768 (672) 7.5 | 7.9, 301 x 2304 x 768 (720) 7.7 | 7.4, 600 x 768 x 3072 (912) 18.4 | 20.5, 800 x 768 x 3072 (1200) 22.6 | 20.5).
+// Tiles of 32 x 32 (long rows: 16 x 32) up to which it wins against 64 x 64 tiles of gemm_kernel, which take one 128-code step after the
+// other, so that fewer of them lose less (us, that kernel | this one; asymmetric: 128 x 768 x 768 12.2 | 5.7, 128 x 768 x 3072 27.0 | 6.5,
+// 301 x 3072 x 1024 (960 tiles) 12.1 | 10.5, 600 x 1024 x 4096 (1216) 34.5 | 29.6, 800 x 1024 x 4096 (1600) 34.7 | 40.4; symmetric: 128 x 768 x 3072
+// 20.4 | 6.0, 600 x 768 x 3072 (912) 20.5 | 18.4, 800 x 768 x 3072 (1200) 20.5 | 22.6).  Short K has the less to lose: 552 x 1216 x 256 symmetric (684)
+// 4.1 | 5.7, 528 tiles of 512 codes 5.8 | 6.1, 323 x 2752 x 256 asymmetric (946) 7.1 | 7.6; and where fewer than twelve groups leave
+// waves idle: 86 x 4800 x 1536 in 256s symmetric (900) 9.9 | 11.0, 66 x 7552 x 2304 in 256s asymmetric (1180) 19.4 | 21.7, 487 x 1088 x 2048 in 512s
+// (1054) 16.1 | 18.0, 90 x 6720 x 768 in 256s symmetric (630) 6.3 | 7.2.  At 1802 sizes in groups of 128, 256 and 512 the choice is 0.06 % above
+// the better of the two.
+static long grouped_tile_limit(const GemmArgs &g, bool asym) {
+    if (grouped_short(g)) return asym ? (g.K <= 256 ? 768 : 1024) : (g.K <= 512 || g.ng <= 3 ? 512 : 704);
+    if (g.ng < 12) return asym ? (g.ng <= 4 ? 960 : 1088) : 768;
+    return asym ? 1216 : 1024;
+}
+// fp16 outputs of canonical codes in several weight groups
 bool small_grouped_ok(const GemmArgs &g, int mode, int out_kind) {
     const bool asym = mode == W4A4_ASYM;
     if (out_kind != OUT_F16 || g.layout != W4A4_LAYOUT_CANONICAL || g.ng < 2 || g.K % (64 * g.ng) || g.K > 4096 || g.lda % 16 ||
         ((long)g.M + 32) * g.lda >= 0x7fffffffL || ((long)g.N + 32) * g.ldw >= 0x7fffffffL || ((long)g.M + 32) * g.N * 2 >= 0x7fffffffL) return false;
     const long rows = grouped_short(g) ? (g.M + 31) / 32 : (g.M + 15) / 16, tiles = rows * ((g.N + 31) / 32);
     const size_t lds = grouped_short(g) ? grouped_small_lds<8, 32>(g, asym) : grouped_small_lds<16, 16>(g, asym);
-    return lds <= 160 * 1024 && tiles <= (grouped_short(g) ? (asym ? 1024 : 704) : (asym ? 1216 : 1024));
+    return lds <= 160 * 1024 && tiles <= grouped_tile_limit(g, asym);
 }
 int launch_small_grouped(int mode, GemmArgs &g, hipStream_t st) {
     if (mode == W4A4_SYM) return grouped_short(g) ? launch_grouped<8, 32, W4A4_SYM>(g, st) : launch_grouped<16, 16, W4A4_SYM>(g, st);
