@@ -359,8 +359,10 @@ static int launch_tile(int tile, GemmArgs &g, hipStream_t st) {
 // at eighteen token counts from 600 to 16384 on the BERT-base and BERT-large linears: 0.2 % above the best of them on
 // average, the condition on 256 x 128 tiles not counted, which takes out the worst misses (up to 28 %).  Four linears with their quantizers against half lines in 128 x 256, 192 x 128 and 128 x 128 tiles: 800
 // tokens 63.4 -> 52.6 us, 4096 102.6 -> 91.1, 16384 314.5 -> 277.2 (BERT-large); 16384 218.5 -> 192.1 (BERT-base).
-// K in 64s but not in 128s, or below 256, keeps half lines (n tiles on the busiest CU, worked on by min(n, workgroups per CU) at a time: cost
-// n * area / (rate * efficiency), rate of one / two / three 0.7 / 1 / 0.95, efficiency of 192 x 128 and 128 x 128 0.9 and 0.8; without
+// K in 64s but not in 128s keeps half lines, and so does K of at most four whole-line steps, where a tile is over before the deeper stages pay
+// (half lines | whole: 1720 x 384 x 384 4.5 | 4.9 us, 537 x 6848 x 384 6.0 | 6.8, 1813 x 4480 x 256 10.1 | 11.4, 380 x 1472 x 512 5.9 | 6.3; at 512
+// with several tiles on a CU even or better, at 640 likewise).  There n tiles on the busiest CU, worked on by min(n, workgroups per CU) at a
+// time, cost n * area / (rate * efficiency), rate of one / two / three 0.7 / 1 / 0.95, efficiency of 192 x 128 and 128 x 128 0.9 and 0.8 (without
 // 192 x 128 tiles 6144 x 704 x 960 7.9 -> 9.5 us, 12288 x 704 x 1088 14.2 -> 16.5, 8192 x 1088 x 3008 35.3 -> 40.6).
 // A few hundred 32 x 32 tiles at most go to the small-problem kernel instead (latency decides there).
 static int pick_tile(const GemmArgs &g) {
@@ -368,9 +370,9 @@ static int pick_tile(const GemmArgs &g) {
     const long cus = device_cus();
     auto busiest = [&](int bm, int bn) { return ((long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) + cus - 1) / cus; };
     const double n128 = (double)busiest(128, 128);
-    if (g.K % 128 == 0 && g.K >= 256) {
+    if (g.K % 128 == 0 && (g.K >= 640 || (g.K == 512 && n128 > 1))) {
         const long pairs = busiest(128, 128) / 2, odd = busiest(128, 128) % 2;
-        const double pair = 2.0 * pairs + odd / 0.39, alone = g.K >= 384 ? n128 / 0.4 : 1e30, big = 4.0 * (double)busiest(256, 256) / 1.1;
+        const double pair = 2.0 * pairs + odd / 0.39, alone = n128 / 0.4, big = 4.0 * (double)busiest(256, 256) / 1.1;
         const double tall = g.K >= 2048 && n128 > 1 ? 2.0 * (double)busiest(256, 128) / 1.07 : 1e30;
         double c = pair;
         int tile = W8_128x128_PAIR;

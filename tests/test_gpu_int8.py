@@ -135,10 +135,10 @@ def test_small_problem_path_reads_a_column_slice_of_codes(B, orc):
 
 
 @pytest.mark.parametrize("M,N,K", [
-    (700, 1032, 384), (1153, 520, 4096), (700, 1032, 896),      # 128 x 128, one per CU: shortest K, long K, ragged
-    (700, 1032, 256), (4200, 1032, 256),                        # in pairs: one and two on the busiest CU, a tile per workgroup
+    (700, 1032, 384), (1153, 520, 4096), (700, 1032, 896),      # 128 x 128, one per CU: half lines, long K, ragged
+    (700, 1032, 256), (4200, 1032, 256),                        # half lines: one and two on the busiest CU
     (4200, 1032, 2048), (4097, 1032, 2176),                     # 256 x 128: long K
-    (4097, 2056, 640), (8100, 2040, 256), (16130, 2040, 384),   # 256 x 256: one and two tiles per workgroup
+    (4097, 2056, 640), (8100, 2040, 256), (16130, 2040, 384),   # 256 x 256; half lines again
     (700, 1032, 128), (700, 1032, 448), (4200, 2056, 320),      # half lines: K below 256 or in 64s only, both tiles
 ])
 def test_every_tile_of_the_persistent_kernel(B, M, N, K):
@@ -155,8 +155,8 @@ def test_every_tile_of_the_persistent_kernel(B, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K,tile,slots", [(4200, 4088, 1024, "128x128_pairs", 512), (7169, 2296, 768, "128x128_pairs", 512),
-                                              (4200, 4088, 256, "128x128_pairs", 512), (9500, 2040, 2176, "256x128", 256),
-                                              (16130, 2040, 384, "256x256", 256)])
+                                              (4200, 4088, 512, "128x128_pairs", 512), (9500, 2040, 2176, "256x128", 256),
+                                              (16130, 2040, 512, "256x256", 256)])
 def test_workgroups_of_whole_lines_walk_several_tiles(B, M, N, K, tile, slots):
     """More tiles than workgroups fit the chip: a workgroup's next tile is requested under its last (first steps of the next tile
     behind the last ones of this, token scales in turn), ragged rows and columns."""
@@ -169,10 +169,12 @@ def test_workgroups_of_whole_lines_walk_several_tiles(B, M, N, K, tile, slots):
 
 @pytest.mark.parametrize("M,N,K,tile", [(4097, 1032, 192, "half_lines_192x128"), (4097, 4104, 320, "half_lines_192x128"),   # one and three a CU
                                         (20000, 1032, 448, "half_lines_192x128"), (6100, 1032, 192, "half_lines_128x128"),
-                                        (6100, 2056, 448, "half_lines_128x256")])
+                                        (6100, 2056, 448, "half_lines_128x256"), (700, 1032, 384, "half_lines_128x128"),
+                                        (700, 1032, 512, "half_lines_128x128"), (4200, 4088, 256, "half_lines_192x128"),
+                                        (700, 1032, 640, "128x128"), (4200, 1032, 512, "128x128_pairs")])
 def test_tiles_of_half_lines(B, M, N, K, tile):
-    """K that does not come in whole cache lines: all three tiles are there, chosen by the busiest CU (192 x 128 takes up to a fifth
-    less time than the others), and exact."""
+    """K that does not come in whole cache lines, or in four of them: all three tiles are there, chosen by the busiest CU (192 x 128
+    takes up to a fifth less time than the others), and exact; whole lines from the shortest K on that takes them."""
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert B.lib().w8a8_tile_name(M, N, K).decode() == tile
     test_every_tile_of_the_persistent_kernel(B, M, N, K)
