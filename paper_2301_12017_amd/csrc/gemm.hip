@@ -164,16 +164,20 @@ static int pick_olay(const GemmArgs &g, int out_kind) {
 
 // Few tokens: the FP6 kernel whose waves split K takes the place of 128 x 128 tiles, up to 512 tiles of 32 x 64, two
 // workgroups to a CU (us, 128 x 128 | 32 x 64: 128 x 768 x 768 6.3 | 4.0, 128 x 1024 x 4096 14.4 | 6.9, 301 x 3072 x 1024 (480 tiles)
-// 7.2 | 6.0, 1024 x 1024 x 4096 (512) 14.5 | 13.2; 450 x 2304 x 768 (540) 6.6 | 7.5, 1400 x 768 x 3072 (528) 12.0 | 16.4).
+// 7.2 | 6.0, 1024 x 1024 x 4096 (512) 14.5 | 13.2; 450 x 2304 x 768 (540) 6.6 | 7.5, 1400 x 768 x 3072 (528) 12.0 | 16.4).  Sixteen waves (K > 1536) on
+// the fewest blocks of K have the least to share out: below 3072 they win only while each tile has a CU to itself (1913 x 448 x 2048 (480)
+// 9.6 | 10.9, 232 x 3904 x 2560 (496) 10.8 | 13.8).
 static bool fp6_few_tokens(const GemmArgs &g, int out_kind) {
     if (out_kind != OUT_F16 && out_kind != OUT_I32) return false;
     const long tiles = (long)((g.M + 31) / 32) * ((g.N + 127) / 128 * 2);
-    return tiles <= 512;
+    return tiles <= (g.K > 1536 && g.K < 3072 ? 256 : 512);
 }
 
 // FP6 kernel.  The 192 x 256 tile (one wave per SIMD, least operand traffic per product) pays for long K and whole rounds of
 // one tile per CU: 12288 x 1024 x 4096, 256 tiles, 32.5 us against 34.3 on 128 x 256; 16384 x 768 x 3072, 258 tiles,
-// 43.4 against 28.6 (28.0 on 128 x 128); 16384 x 1024 x 4096 56.5 against 39.5.
+// 43.4 against 28.6 (28.0 on 128 x 128); 16384 x 1024 x 4096 56.5 against 39.5.  It pays more where the weights are past
+// 8 MB, twice an XCD's L2, and come from further away each time (128 x 256 | 192 x 256: 6557 x 6208 x 4096 129 | 113 us, 7244 x 7424 x 10240
+// 440 | 341).
 static int pick_fp6(const GemmArgs &g, int out_kind) {
     if (out_kind == OUT_Q6) return S_FP6_128x256;
     if (fp6_few_tokens(g, out_kind)) return S_FP6_32x64;
@@ -184,7 +188,8 @@ static int pick_fp6(const GemmArgs &g, int out_kind) {
     const double c192 = tile_cost(g, r, 192, 128, 2, r.eff_192x128, cus), c128 = tile_cost(g, r, 128, 128, 3, r.eff_128x128, cus);
     if (c192 < c) { best = S_FP6_192x128; c = c192; }
     if (c128 < c) { best = S_FP6_128x128; c = c128; }
-    if (g.K >= 2048 && tile_cost(g, r, 192, 256, 1, r.eff_192x256, cus) < c) best = S_FP6_192x256;
+    const double eff_big = (long)g.N * (g.K / 4 * 3) > 8000000 ? 0.85 : r.eff_192x256;
+    if (g.K >= 2048 && tile_cost(g, r, 192, 256, 1, eff_big, cus) < c) best = S_FP6_192x256;
     return best;
 }
 

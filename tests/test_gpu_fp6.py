@@ -408,3 +408,18 @@ def test_few_tokens_split_k(B, M, N, K):
         V = WL.v_slice(wide, 1024)
         Q3 = B.quantize_weight((torch.randn((N, 1024), device="cuda", generator=g) * 0.02).half(), SYM, 0, layout=FP6)
         assert torch.equal(B.gemm_i32(V, Q3), B.gemm_i32(V, Q3, schedule=tiles))
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(301, 3072, 1024, "fp6_32x64"), (232, 3904, 2560, "fp6_128x128"), (512, 1024, 2048, "fp6_32x64"),
+                                        (544, 1024, 2048, "fp6_128x128"), (512, 2048, 3072, "fp6_32x64"), (3224, 6400, 5120, "fp6_192x256"),
+                                        (6557, 6208, 4096, "fp6_192x256"), (12288, 1024, 4096, "fp6_192x256"), (12288, 4096, 1024, "fp6_128x256")])
+def test_tile_by_what_a_cu_and_the_cache_hold(B, M, N, K, tile):
+    """Few tokens, their limit where sixteen waves share few blocks of K, and the largest tile where the weights do not stay in an
+    XCD's L2; outputs as on 128 x 256 tiles."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule counts tiles per CU")
+    g = torch.Generator(device="cuda").manual_seed(M)
+    A = B.quantize_act(torch.randn((M, K), device="cuda", generator=g).half(), SYM, layout=FP6)
+    Q = B.quantize_weight((torch.randn((N, K), device="cuda", generator=g) * 0.02).half(), SYM, 0, layout=FP6)
+    assert B.pick_schedule(A, Q) == tile
+    assert torch.equal(B.linear(A, Q).view(torch.int16), B.linear(A, Q, schedule=B.schedule_number("fp6_128x256")).view(torch.int16))
