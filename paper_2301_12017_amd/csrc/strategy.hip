@@ -474,12 +474,11 @@ extern "C" int w4a4_strategy_tune(int M, int hidden, int ffn, int iters, w4a4_st
 // epilogue of separately rounded operations and the wider codes cost what the shorter main loop gives.  Layer in the layouts
 // that w4a4_preferred_layout names | in FP6, sequences of 128, built-in strategy, us: hidden 1024: 6144 tokens 137 | 141,
 // 8192 171 | 166, 12288 242 | 227, 16384 310 | 283; hidden 768: 8192 130 | 134, 12288 181 | 178, 16384 230 | 216, 24576 315 | 300.
-// Not at 512 features, where short K leaves the wider codes nothing to win (12288 tokens 113 | 125, 24576 191 | 194), nor from 3072 on, where
-// operands outgrow an XCD's L2 and the int8 kernel's 256 x 256 tiles fetch less of them (3072: 12288 tokens 948 | 900, 16384 1189 | 1239;
-// 4096: 12288 1396 | 1516, of which qkv 441 | 550); between: 1280 12288 tokens 342 | 307, 2048 628 | 608, 2560 1040 | 967.
+// Not at 512 features, where short K leaves the wider codes nothing to win (12288 tokens 113 | 125, 24576 191 | 194), nor past 3072, where
+// the int8 kernel's 256 x 256 tiles make up for it (4096, ffn 8192: 8192 tokens 956 | 1037, 16384 1833 | 1877, 24576 2730 | 2746).  Between:
+// 1280 12288 tokens 342 | 307, 2048 636 | 616, 2560 696 | 658, 3072 (ffn 6144) 8192 642 | 650, 12288 950 | 893, 16384 1182 | 1169, 24576 1797 | 1719.
 extern "C" int w4a4_encoder_layer_prefers_fp6(int M, int hidden, int ffn) {
-    if (!shape_ok(M, hidden, ffn) || hidden < 768 || M < (hidden >= 1024 ? 8192 : 12288)) return 0;
-    if (hidden > (M <= 12288 ? 3072 : 2560)) return 0;
+    if (!shape_ok(M, hidden, ffn) || hidden < 768 || hidden > 3072 || M < (hidden >= 1024 ? 8192 : 12288)) return 0;
     int lpr = 0, opl = 0;
     for (int k : {hidden, ffn})
         if (k % 128 || k < 512 || !fp6_plan(k, &lpr, &opl)) return 0;
