@@ -543,19 +543,20 @@ extern "C" int w4a4_gemm_i32(const w4a4_act *A, const w4a4_weight *W, int32_t *a
     return run_gemm(g, A->mode, grouped, OUT_I32, schedule, as_stream(stream));
 }
 
-// Everything that linear_impl can refuse of a requantizing layer behind check_layer.  Nothing is launched.
-static int check_requant(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, int ng, int fused) {
+// Everything that linear_impl can refuse of a requantizing layer behind check_layer, and the schedule of its GEMM.  Nothing is launched.
+static int check_requant(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep, int ng, int fused, int *schedule) {
     GemmArgs g;
     fill_args(g, A, W, ng);
+    g.act = ep->act;
     if (fused) {
-        int schedule = fused_schedule(fused, ep);
-        return resolve_schedule(g, false, fused_out_kind(fused, ep), &schedule);
+        *schedule = fused_schedule(fused, ep);
+        return resolve_schedule(g, false, fused_out_kind(fused, ep), schedule);
     }
     // FP6 codes exist only fused, and the row quantizer makes one odd-position sum per row
     if (ep->requant_layout == W4A4_LAYOUT_FP6) return W4A4_ERR_UNSUPPORTED_SHAPE;
     if (ep->requant_layout == W4A4_LAYOUT_MFMA && ep->requant_group != 0 && ep->requant_group != W->N) return W4A4_ERR_UNSUPPORTED_SHAPE;
-    int schedule = ep->schedule;
-    return resolve_schedule(g, A->mode == W4A4_ASYM || ng > 1, OUT_F32, &schedule);
+    *schedule = ep->schedule;
+    return resolve_schedule(g, A->mode == W4A4_ASYM || ng > 1, OUT_F32, schedule);
 }
 
 // w4a4_linear behind its argument checks.  `exchange` is the area the fused requantize exchanges row maxima
@@ -576,7 +577,8 @@ static int linear_impl(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilo
     }
     if (ep->requant_layout == W4A4_LAYOUT_MFMA && !out_gsum) return W4A4_ERR_INVALID_ARG;   // receives the odd-position code sums
     // everything that can refuse the launches is checked before the outputs are touched
-    if (const int rc = check_requant(A, W, ep, ng, fused)) return rc;
+    int schedule = 0;
+    if (const int rc = check_requant(A, W, ep, ng, fused, &schedule)) return rc;
     if (fused) {
         // One kernel: the column tiles of a row panel exchange their row maxima through the exchange area and
         // pack the codes from registers.
@@ -599,13 +601,13 @@ static int linear_impl(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilo
         if (!cleared)
             hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + n2 + 255) / 256)), dim3(256), 0, st, exchange, words,
                                reinterpret_cast<uint32_t *>(out_gsum), (int)n2);
-        return run_gemm(g, A->mode, false, fused_out_kind(fused, ep), fused_schedule(fused, ep), st);
+        return run_gemm(g, A->mode, false, fused_out_kind(fused, ep), schedule, st);
     }
     // Requantize: the per-token range needs the whole output row, which no single tile
     // sees.  The GEMM leaves the fp32 rows in the workspace and the row quantizer turns
     // them into packed codes.
     g.out = rows_f32;
-    const int rc = run_gemm(g, A->mode, grouped, OUT_F32, ep->schedule, st);
+    const int rc = run_gemm(g, A->mode, grouped, OUT_F32, schedule, st);
     if (rc) return rc;
     return quantize_rows_f32(static_cast<const float *>(rows_f32), A->M, W->N, W->N, ep->requant_mode,
                              ep->requant_group, static_cast<uint8_t *>(out), out_scale, out_zero, out_gsum, st,
@@ -759,8 +761,9 @@ extern "C" size_t w4a4_linear_chain_workspace_bytes(const w4a4_act *A, const w4a
         size_t cleared = 0, total = 0;
         if (!A || A->M <= 0 || plan_chain(A, steps, n, nullptr, nullptr, nullptr, nullptr, plan, &cleared, &total)) return 0;
         for (int i = 0; i < n; ++i) {
+            int schedule = 0;
             const int G = steps[i].W.group ? steps[i].W.group : steps[i].W.K;
-            if (G < 0 || steps[i].W.K % G || check_requant(&plan[i].A, &steps[i].W, &plan[i].ep, steps[i].W.K / G, plan[i].fused)) return 0;
+            if (G < 0 || steps[i].W.K % G || check_requant(&plan[i].A, &steps[i].W, &plan[i].ep, steps[i].W.K / G, plan[i].fused, &schedule)) return 0;
         }
         return total;
     } catch (...) {
@@ -779,11 +782,11 @@ extern "C" int w4a4_linear_chain(const w4a4_act *A, const w4a4_chain_step *steps
         if (M > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255))) return W4A4_ERR_WORKSPACE;
         for (int i = 0; i < n; ++i) {                           // everything is checked before the first launch
             ChainStep &s = plan[i];
-            int rng = 0;
+            int rng = 0, schedule = 0;
             rc = check_layer(&s.A, &steps[i].W, &s.ep, s.q, s.scale, nullptr, &s.ng, &rng);
             if (rc) return rc;
             if (s.ep.requant_layout == W4A4_LAYOUT_MFMA && M > 0 && !s.osum) return W4A4_ERR_INVALID_ARG;
-            if (M > 0 && (rc = check_requant(&s.A, &steps[i].W, &s.ep, s.ng, s.fused))) return rc;
+            if (M > 0 && (rc = check_requant(&s.A, &steps[i].W, &s.ep, s.ng, s.fused, &schedule))) return rc;
         }
         if (M == 0) return W4A4_OK;
         if (workspace_bytes < total) return W4A4_ERR_WORKSPACE;
