@@ -42,6 +42,7 @@ struct SmallArgs {
     const __half *bias; int act;
     __half *out;                     // [M, N]
     int M, N, K, tiles_n;
+    uint32_t wcpr_inv;               // 2^32 / (16-byte chunks of a row of weights), rounded up: p * wcpr_inv >> 32 is the row of chunk p < 2^16
     // LayerNorm form: the activations are LN(X + R) gamma + beta in fp16, which also go to Y
     const __half *R, *gamma, *beta;  // [M, K] dense, [K], [K]
     float eps;
@@ -76,6 +77,16 @@ __device__ __forceinline__ void codes8(const u32x4 &x, float inv, uint32_t &even
         even = __builtin_amdgcn_perm(u[2], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[6], u[4], 0x04000c0cu);
         odd = __builtin_amdgcn_perm(u[3], u[1], 0x0c0c0400u) | __builtin_amdgcn_perm(u[7], u[5], 0x04000c0cu);
     }
+}
+
+// maximum of non-negative numbers over the LPR (8, 16, 32 or 64) consecutive lanes of a token, in all of them
+template <int LPR>
+__device__ __forceinline__ float token_max(float v) {
+    auto larger = [](float p, float q) { return fmaxf(p, q); };
+    if constexpr (LPR >= 16) return lanes_reduce<LPR>(v, larger);
+    v = larger(v, dpp_fetch<0xB1>(v));
+    v = larger(v, dpp_fetch<0x4E>(v));
+    return larger(v, dpp_fetch<0x141>(v));
 }
 
 // The LayerNorm form.  X + R, normalised, scaled and shifted: bit for bit what layernorm_quantize_kernel makes of a row of K = 512,
@@ -147,8 +158,8 @@ __device__ __forceinline__ void layernorm_row(u32x4 (&x)[XCH], const u32x4 (&r)[
         }
 }
 
-// NW waves, FN column fragments of 32 channels, TM = 32 or 16 tokens per workgroup (with 16 the upper
-// half of the MFMA rows repeats the lower one and is not stored), WLDS: the weight tile is staged in LDS.
+// NW waves, FN column fragments of 32 channels, TM = 32, 16 or 8 tokens per workgroup (with fewer than 32 the upper
+// MFMA rows repeat the lower ones and are not stored), WLDS: the weight tile is staged in LDS.
 // PACKED: the activations arrive already quantized (packed codes + token scales, the output of
 // w4a4_quantize_act or of a producer kernel): pass 1 only parks their tile in LDS, and both operands are
 // widened to 16 * code on their way into the MFMA (the sums hold 256 * P).
@@ -156,24 +167,34 @@ __device__ __forceinline__ void layernorm_row(u32x4 (&x)[XCH], const u32x4 (&r)[
 // byte when PACKED), the weights are one int8 code per byte, and both go into the MFMA as they are (the
 // sums hold P).
 // ASYM (packed codes only): unsigned codes, one weight group; the sums hold P and the epilogue adds the zero-point terms.
-// LNK: 0, or K (512, 768 or 1024): the activations are the LayerNorm of X + R, which every workgroup forms for its tokens; the
-// first column tile stores them.
-template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false, int LNK = 0>
+// KC: 0, or K.  What bounds these kernels is the instructions a wave issues one behind the other (a dependent one every 8 cycles; a launch
+// by itself takes 1.5 us of such a stream, a request answered from L2 0.1), and a third of them worked out addresses: with K a
+// constant, offsets, trip counts and places in LDS are, too.  Back to back, us, before | K a run-time value, tile rows by a product instead of a
+// division and carries | K a constant, which also unrolls pass 2: fp16 activations 32 x 2304 x 768 4.31 | - | 2.95, 128 x 2304 x 768 6.04 | - | 4.17,
+// 32 x 768 x 3072 6.14 | - | 4.08; packed 32 x 2304 x 768 3.37 | 3.24 | 2.44, 128 x 768 x 3072 4.18 | 4.14 | 3.50.  One layer of 768 features, 1 x 32
+// tokens, 26.6 -> 22.2, 1 x 128 31.7 -> 26.3.
+// LN (with KC): the activations are the LayerNorm of X + R, which every workgroup forms for its tokens; the first column tile
+// stores them.
+template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false, int KC = 0, bool LN = false>
 __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     constexpr int NT = NW * 64, LPR = NT / TM;                  // LPR consecutive lanes share a token in pass 1
     constexpr int RV = TM / 2;                                  // accumulator registers per fragment that hold real rows
     constexpr int R = RV * FN;                                  // ... of the tile
-    constexpr int RPW = (R + NW - 1) / NW;                      // ... finished by one wave
-    constexpr int WCH = WLDS ? small_wchunks(NW) : 1;
-    constexpr int XCH = PACKED ? 1 : LNK ? LNK / 8 / LPR : small_xchunks(TM);
-    constexpr bool LN = LNK != 0;
-    static_assert(!LN || (!PACKED && !W8 && NW == 8), "fp16 activations of up to 1024 features");
-    constexpr int ACH = PACKED ? (W8 ? 8 : 4) : 1;              // 16-byte chunks of the packed activation tile per lane
+    constexpr int RPW = (RV + NW - 1) / NW;                     // rows' registers finished by one wave, for all column fragments
+    // Column fragments: a wave takes one of them and a larger share of K (half of the sums to add up in LDS: 128 x 2304 x 768 4.5 us ->
+    // 4.2), or all of them where K is no constant or the weights come from memory, which shares the other operand.
+    constexpr int FPW = KC && WLDS ? 1 : FN, KW = NW * FPW / FN;   // fragments of a wave, waves that share out K
+    const int K = KC ? KC : a.K;
+    constexpr int WCH = !WLDS ? 1 : KC ? (32 * FN * (W8 ? KC / 16 : KC / 32) + NT - 1) / NT : small_wchunks(NW);
+    constexpr int XCH = PACKED ? 1 : KC ? KC / 8 / LPR : small_xchunks(TM);
+    static_assert(!LN || (KC && !PACKED && !W8 && NW == 8), "fp16 activations of up to 1024 features");
+    static_assert(KC == 0 || PACKED || KC % (8 * LPR) == 0, "whole chunks for each lane of a row");
+    constexpr int ACH = !PACKED ? 1 : KC ? (TM * (W8 ? KC / 16 : KC / 32) + NT - 1) / NT : W8 ? 8 : 4;   // 16-byte chunks of the packed activation tile per lane
     constexpr bool NIBBLES = PACKED && !W8;                     // activation codes arrive two per byte
     static_assert(!ASYM || NIBBLES, "unsigned codes arrive packed");
     static_assert(LPR <= 64 && (LPR & (LPR - 1)) == 0, "a token's lanes sit in one wave");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const int wpitch = (W8 ? a.K : a.K / 2) + 16, pitch = NIBBLES ? a.K / 2 + 16 : a.K + 16;
+    const int wpitch = (W8 ? K : K / 2) + 16, pitch = NIBBLES ? K / 2 + 16 : K + 16;
     uint8_t *codes = smem;                                      // [TM][pitch] int8 activation codes (packed codes if PACKED)
     uint8_t *wt = codes + TM * pitch;                           // [32 FN][wpitch] packed weight codes (WLDS)
     int *s_sum = reinterpret_cast<int *>(wt + (WLDS ? 32 * FN * wpitch : 0));   // [R][64]
@@ -181,30 +202,29 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m0 = (blockIdx.x / a.tiles_n) * TM, n0 = (blockIdx.x % a.tiles_n) * (32 * FN);
-    const __amdgpu_buffer_rsrc_t x_rsrc = PACKED ? make_rsrc(a.Aq, (uint32_t)((long)(a.M - 1) * a.lda + (W8 ? a.K : a.K / 2)))
-                                                 : make_rsrc(a.X, (uint32_t)(((long)(a.M - 1) * a.ldx + a.K) * 2));
+    const __amdgpu_buffer_rsrc_t x_rsrc = PACKED ? make_rsrc(a.Aq, (uint32_t)((long)(a.M - 1) * a.lda + (W8 ? K : K / 2)))
+                                                 : make_rsrc(a.X, (uint32_t)(((long)(a.M - 1) * a.ldx + K) * 2));
     const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(a.Wq, (uint32_t)((long)a.N * a.ldw));
     const int r = lane & 31, h = lane >> 5;                     // pass 2: token / channel r, K half h
-    const int nb = a.K / 64;
+    const int nb = K / 64;
 
     // ---- requests, in the order they are needed: activation rows, weights, channel constants ----------------
     const int row = tid / LPR, c0 = tid % LPR;
-    const int nchunks = LN ? LNK / 8 : a.K / 8;                 // 16-byte chunks of an activation row
-    const int wcpr = W8 ? a.K / 16 : a.K / 32;                  // 16-byte chunks of a row of weight codes
+    const int nchunks = K / 8;                                  // 16-byte chunks of an activation row
+    const int wcpr = W8 ? K / 16 : K / 32;                      // 16-byte chunks of a row of weight codes
     u32x4 x[XCH];
     [[maybe_unused]] u32x4 rx[LN ? XCH : 1], gx[LN ? XCH : 1], bx[LN ? XCH : 1];
     u32x4 ast[ACH];
-    int arow_i[ACH];
-    uint32_t adst_i[ACH];
+    auto row_of = [&](int p) { return KC ? p / wcpr : (int)__umulhi((uint32_t)p, a.wcpr_inv); };   // row of chunk p of a tile of codes
     if constexpr (!PACKED) {
         const uint32_t base = (uint32_t)min(m0 + row, a.M - 1) * (uint32_t)a.ldx * 2u;
 #pragma unroll
         for (int i = 0; i < XCH; ++i)               // (chunks past the row are requested but never used)
             if (i * LPR < nchunks) x[i] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, base + (uint32_t)(c0 + i * LPR) * 16, 0, 0);
         if constexpr (LN) {
-            const __amdgpu_buffer_rsrc_t r_rsrc = make_rsrc(a.R, (uint32_t)((long)a.M * a.K * 2));
-            const __amdgpu_buffer_rsrc_t g_rsrc = make_rsrc(a.gamma, (uint32_t)a.K * 2u), be_rsrc = make_rsrc(a.beta, (uint32_t)a.K * 2u);
-            const uint32_t rbase = (uint32_t)min(m0 + row, a.M - 1) * (uint32_t)a.K * 2u;
+            const __amdgpu_buffer_rsrc_t r_rsrc = make_rsrc(a.R, (uint32_t)((long)a.M * K * 2));
+            const __amdgpu_buffer_rsrc_t g_rsrc = make_rsrc(a.gamma, (uint32_t)K * 2u), be_rsrc = make_rsrc(a.beta, (uint32_t)K * 2u);
+            const uint32_t rbase = (uint32_t)min(m0 + row, a.M - 1) * (uint32_t)K * 2u;
 #pragma unroll
             for (int i = 0; i < XCH; ++i)
                 if (i * LPR < nchunks) rx[i] = __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, rbase + (uint32_t)(c0 + i * LPR) * 16, 0, 0);
@@ -216,80 +236,90 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
                 }
         }
     } else {
-        // the packed tile, coalesced like the weight tile below (rows past M fall outside the descriptor: zeros)
-        const int stepq = NT / wcpr, stepr = NT % wcpr;
-        int rw = tid / wcpr, cl = tid % wcpr;
-        uint32_t src = (uint32_t)(m0 + rw) * (uint32_t)a.lda + (uint32_t)cl * 16, dst = (uint32_t)(rw * pitch + cl * 16);
-        const uint32_t src_q = (uint32_t)stepq * (uint32_t)a.lda + (uint32_t)stepr * 16, dst_q = (uint32_t)(stepq * pitch + stepr * 16);
-        const uint32_t src_c = (uint32_t)a.lda - (uint32_t)wcpr * 16, dst_c = (uint32_t)(pitch - wcpr * 16);
+        // the packed tile (rows past M fall outside the descriptor: zeros): chunk p is chunk p % wcpr of row p / wcpr
 #pragma unroll
-        for (int i = 0; i < ACH; ++i) {
-            arow_i[i] = rw; adst_i[i] = dst;
-            if (i * NT < TM * wcpr) ast[i] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, src, 0, 0);
-            rw += stepq; cl += stepr; src += src_q; dst += dst_q;
-            if (cl >= wcpr) { cl -= wcpr; ++rw; src += src_c; dst += dst_c; }
+        for (int i = 0; i < ACH; ++i) {                         // (chunks past the tile: turned away, cheaper than a branch around each)
+            const int p = tid + i * NT, rw = row_of(p);
+            const uint32_t off = (uint32_t)(m0 + rw) * (uint32_t)a.lda + (uint32_t)(p - rw * wcpr) * 16;
+            ast[i] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, p < TM * wcpr ? off : kPoison, 0, 0);
         }
     }
-    // weights: the whole tile, coalesced (consecutive lanes walk a channel's row), on its way to LDS; when
-    // it does not fit there, pass 2 fetches its operands itself (lane (c, h): 16 bytes of channel c)
+    // (packed form) constants of the tile's tokens, for wave 0 to pass on; in front of the weights, which nobody has to wait for here
+    float sa_m = 0.0f, za_m = 0.0f;
+    int ra_m = 0;
+    if (PACKED && wave == 0) {
+        const int m = min(m0 + lane % TM, a.M - 1);
+        sa_m = a.sa[m];
+        if constexpr (ASYM) { za_m = a.za[m]; ra_m = a.RA[m]; }
+    }
+    // weights: the whole tile, on its way to LDS; when it does not fit there, pass 2 fetches its operands itself (lane (c, h): 16
+    // bytes of channel c).  Rows of weights are dense, so the tile is one piece of memory and chunk p of it 16 p bytes from its start:
+    // which row that is matters only for the place in LDS, worked out while the requests are under way.
     u32x4 wst[WCH];
-    // chunk tid + i NT of the tile sits in row wrow_i, column wcol_i: one division, then carries
-    int wrow_i[WCH];                                            // its row, or 32 FN and more past the tile
-    uint32_t wdst_i[WCH];                                       // its byte offset in the LDS tile
     if constexpr (WLDS) {
-        const int stepq = NT / wcpr, stepr = NT % wcpr;
-        int rw = tid / wcpr, cl = tid % wcpr;
-        uint32_t src = (uint32_t)(n0 + rw) * (uint32_t)a.ldw + (uint32_t)cl * 16, dst = (uint32_t)(rw * wpitch + cl * 16);
-        const uint32_t src_q = (uint32_t)stepq * (uint32_t)a.ldw + (uint32_t)stepr * 16, dst_q = (uint32_t)(stepq * wpitch + stepr * 16);
-        const uint32_t src_c = (uint32_t)a.ldw - (uint32_t)wcpr * 16, dst_c = (uint32_t)(wpitch - wcpr * 16);   // carry into the next row
+        const uint32_t src = (uint32_t)n0 * (uint32_t)a.ldw + (uint32_t)tid * 16;
 #pragma unroll
-        for (int i = 0; i < WCH; ++i) {
-            wrow_i[i] = rw; wdst_i[i] = dst;
-            if (i * NT < 32 * FN * wcpr) wst[i] = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, src, 0, 0);
-            rw += stepq; cl += stepr; src += src_q; dst += dst_q;
-            if (cl >= wcpr) { cl -= wcpr; ++rw; src += src_c; dst += dst_c; }
-        }
+        for (int i = 0; i < WCH; ++i)
+            wst[i] = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, tid + i * NT < 32 * FN * wcpr ? src + (uint32_t)(i * NT) * 16 : kPoison, 0, 0);
     }
-    // channel constants of the accumulator registers this wave finishes (register qq of the tile belongs to
-    // wave qq % NW), as raw bits: nothing here waits for a load
+    // pass 2: wave kw of the KW that share out K for column fragments j0 ..  Lane r of fragment j holds channel FN r + j of the tile, so
+    // that a lane ends up with FN adjacent channels; with weights from memory 32 j + r, since the rows that a request reads
+    // had better be neighbours (every second row of 2 KB: 300 x 1024 x 4096 7.4 us -> 8.7)
+    constexpr bool ADJ = WLDS || FN == 1;
+    auto channel = [&](int j) { return n0 + (ADJ ? FN * r + j : 32 * j + r); };
+    const int j0 = FPW == FN ? 0 : wave % FN, kw = wave * FPW / FN;
+    constexpr int NBW = KC ? (KC / 64 + KW - 1) / KW : 1;       // blocks of 64 codes per wave
+    // Weights from memory: all of them requested here, where quantizing the tokens takes its time (300 x 1024 x 4096 11.2 us -> 10.7);
+    // behind packed activations they would only stand in each other's way (7.0 us -> 8.4)
+    constexpr bool WPRE = !WLDS && KC && !W8 && !PACKED;
+    u32x4 wpre[WPRE ? NBW : 1][FPW];
+    auto request_w = [&](int j, int b) {
+        return __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, (uint32_t)channel(j) * (uint32_t)a.ldw + (uint32_t)(b * 32 + h * 16), 0, 0);
+    };
+    if constexpr (WPRE) {
+#pragma unroll
+        for (int i = 0; i < NBW; ++i)
+            if (kw + i * KW < nb) {
+#pragma unroll
+                for (int j = 0; j < FPW; ++j) wpre[i][j] = request_w(j0 + j, kw + i * KW);
+            }
+    }
+    // constants of this lane's channels, as raw bits: nothing here waits for a load
     const __amdgpu_buffer_rsrc_t sw_rsrc = make_rsrc(a.sw, (uint32_t)a.N * 4u);
     const __amdgpu_buffer_rsrc_t b_rsrc = make_rsrc(a.bias, a.bias ? (uint32_t)a.N * 2u : 0u);   // no bias: reads zero
     const __amdgpu_buffer_rsrc_t zw_rsrc = make_rsrc(a.zw, ASYM ? (uint32_t)a.N * 4u : 0u);
     const __amdgpu_buffer_rsrc_t c_rsrc = make_rsrc(a.c, ASYM ? (uint32_t)a.N * 4u : 0u);
-    uint32_t sw_raw[RPW], zw_raw[ASYM ? RPW : 1], c_raw[ASYM ? RPW : 1];
-    unsigned short b_raw[RPW];
+    uint32_t sw_raw[FN], zw_raw[ASYM ? FN : 1], c_raw[ASYM ? FN : 1];
+    unsigned short b_raw[FN];
 #pragma unroll
-    for (int k = 0; k < RPW; ++k) {
-        const int qq = wave + k * NW, n = n0 + 32 * (qq / RV) + r;
-        sw_raw[k] = __builtin_amdgcn_raw_buffer_load_b32(sw_rsrc, (uint32_t)n * 4u, 0, 0);
-        b_raw[k] = __builtin_amdgcn_raw_buffer_load_b16(b_rsrc, (uint32_t)n * 2u, 0, 0);
+    for (int j = 0; j < FN; ++j) {
+        sw_raw[j] = __builtin_amdgcn_raw_buffer_load_b32(sw_rsrc, (uint32_t)channel(j) * 4u, 0, 0);
+        b_raw[j] = __builtin_amdgcn_raw_buffer_load_b16(b_rsrc, (uint32_t)channel(j) * 2u, 0, 0);
         if constexpr (ASYM) {
-            zw_raw[k] = __builtin_amdgcn_raw_buffer_load_b32(zw_rsrc, (uint32_t)n * 4u, 0, 0);
-            c_raw[k] = __builtin_amdgcn_raw_buffer_load_b32(c_rsrc, (uint32_t)n * 4u, 0, 0);
+            zw_raw[j] = __builtin_amdgcn_raw_buffer_load_b32(zw_rsrc, (uint32_t)channel(j) * 4u, 0, 0);
+            c_raw[j] = __builtin_amdgcn_raw_buffer_load_b32(c_rsrc, (uint32_t)channel(j) * 4u, 0, 0);
         }
     }
     for (int e = tid; e < R * 64; e += NT) s_sum[e] = 0;
 
     // ---- pass 1: ranges, codes into LDS ----------------------------------------------------------------------
     if constexpr (PACKED) {
-        if (tid < TM) {
-            const int m = min(m0 + tid, a.M - 1);
-            s_S[tid] = a.sa[m];
-            if constexpr (ASYM) {
-                s_S[TM + tid] = a.za[m];
-                s_S[2 * TM + tid] = (float)a.RA[m];
-            }
-        }
 #pragma unroll
-        for (int i = 0; i < ACH; ++i)
-            if (i * NT < TM * wcpr && arow_i[i] < TM) *reinterpret_cast<u32x4 *>(codes + adst_i[i]) = ast[i];
+        for (int i = 0; i < ACH; ++i) {
+            const int p = tid + i * NT;
+            if (p < TM * wcpr) *reinterpret_cast<u32x4 *>(codes + (p + row_of(p)) * 16) = ast[i];
+        }
+        if (tid < TM) {
+            s_S[tid] = sa_m;
+            if constexpr (ASYM) { s_S[TM + tid] = za_m; s_S[2 * TM + tid] = (float)ra_m; }
+        }
     } else {
         if constexpr (LN) {
-            layernorm_row<LPR, XCH, LNK>(x, rx, gx, bx, a.eps);
+            layernorm_row<LPR, XCH, KC>(x, rx, gx, bx, a.eps);
             if (n0 == 0 && m0 + row < a.M) {
 #pragma unroll
                 for (int i = 0; i < XCH; ++i)
-                    if (i * LPR < nchunks) *reinterpret_cast<u32x4 *>(a.Y + (long)(m0 + row) * a.K + (c0 + i * LPR) * 8) = x[i];
+                    if (i * LPR < nchunks) *reinterpret_cast<u32x4 *>(a.Y + (long)(m0 + row) * K + (c0 + i * LPR) * 8) = x[i];
             }
         }
         typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -306,8 +336,7 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
             }
         }
         float amax = fmaxf((float)mx[0], (float)mx[1]);
-#pragma unroll
-        for (int o = LPR / 2; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, kWave));
+        amax = token_max<LPR>(amax);
         Range rg = range_sym(amax);
         if (W8) {                                                // Sec. 3.1 with b = 8: 127 levels per side
             if (amax == 0.0f) { rg.inv = 0.0f; rg.S = 1.0f; }
@@ -328,22 +357,25 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
     if constexpr (WLDS) {
 #pragma unroll
         for (int i = 0; i < WCH; ++i) {
-            if (i * NT < 32 * FN * wcpr && wrow_i[i] < 32 * FN) *reinterpret_cast<u32x4 *>(wt + wdst_i[i]) = wst[i];
+            const int p = tid + i * NT;
+            if (p < 32 * FN * wcpr) {
+                const int rw = row_of(p), st = FN == 2 ? (rw & 1) * 32 + rw / 2 : rw;   // channel of the tile, its storage row
+                *reinterpret_cast<u32x4 *>(wt + (p + (st - rw) * wcpr + st) * 16) = wst[i];
+            }
         }
     }
     __syncthreads();
 
-    // ---- pass 2: this wave's share of K (a rolled loop: the accumulators stay in place) ----------------------
-    v16i acc[FN];
+    // ---- pass 2: this wave's share of K ----------------------------------------------------------------------
+    v16i acc[FPW];
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+    for (int j = 0; j < FPW; ++j)
 #pragma unroll
         for (int q = 0; q < 16; ++q) acc[j][q] = 0;
     const uint8_t *arow = codes + (r % TM) * pitch + h * (NIBBLES ? 16 : 32);
-    const uint8_t *wrow = wt + r * wpitch + h * (W8 ? 32 : 16);
-#pragma unroll 1
-    for (int b = wave; b < nb; b += NW) {
-        v4i alo, ahi;
+    const uint8_t *wrow = wt + (32 * j0 + r) * wpitch + h * (W8 ? 32 : 16);
+    auto block = [&](int b, const u32x4 (&requested)[FPW]) {
+        v4i alo, ahi, wlo[FPW], whi[FPW];
         if constexpr (NIBBLES) {
             const u32x4 ap = *reinterpret_cast<const u32x4 *>(arow + b * 32);
             alo = widen2<!ASYM>(ap[0], ap[1]);
@@ -352,50 +384,45 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
             alo = *reinterpret_cast<const v4i *>(arow + b * 64);
             ahi = *reinterpret_cast<const v4i *>(arow + b * 64 + 16);
         }
-        if constexpr (W8) {
-            // one-byte codes: lane (r, h) takes 32 bytes of channel r, two MFMA operands as they are
-            v4i w0[FN], w1[FN];
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
+        for (int j = 0; j < FPW; ++j) {
+            const uint8_t *wp = wrow + 32 * j * wpitch;
+            if constexpr (W8) {                                 // one-byte codes: 32 bytes of a channel, two MFMA operands as they are
                 if constexpr (WLDS) {
-                    w0[j] = *reinterpret_cast<const v4i *>(wrow + 32 * j * wpitch + b * 64);
-                    w1[j] = *reinterpret_cast<const v4i *>(wrow + 32 * j * wpitch + b * 64 + 16);
+                    wlo[j] = *reinterpret_cast<const v4i *>(wp + b * 64);
+                    whi[j] = *reinterpret_cast<const v4i *>(wp + b * 64 + 16);
                 } else {
-                    const uint32_t off = (uint32_t)(n0 + 32 * j + r) * (uint32_t)a.ldw + (uint32_t)(b * 64 + h * 32);
-                    const u32x4 t0 = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off, 0, 0);
-                    const u32x4 t1 = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off + 16, 0, 0);
-                    w0[j] = v4i{(int)t0[0], (int)t0[1], (int)t0[2], (int)t0[3]};
-                    w1[j] = v4i{(int)t1[0], (int)t1[1], (int)t1[2], (int)t1[3]};
+                    const uint32_t off = (uint32_t)channel(j0 + j) * (uint32_t)a.ldw + (uint32_t)(b * 64 + h * 32);
+                    wlo[j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off, 0, 0));
+                    whi[j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off + 16, 0, 0));
                 }
+            } else {
+                const u32x4 wv = WPRE ? requested[j] : WLDS ? *reinterpret_cast<const u32x4 *>(wp + b * 32) : request_w(j0 + j, b);
+                wlo[j] = widen2<!ASYM>(wv[0], wv[1]);
+                whi[j] = widen2<!ASYM>(wv[2], wv[3]);
             }
-#pragma unroll
-            for (int j = 0; j < FN; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(alo, w0[j], acc[j], 0, 0, 0);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ahi, w1[j], acc[j], 0, 0, 0);
-        } else {
-        u32x4 wv[FN];
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            if constexpr (WLDS) wv[j] = *reinterpret_cast<const u32x4 *>(wrow + 32 * j * wpitch + b * 32);
-            else wv[j] = __builtin_amdgcn_raw_buffer_load_b128(
-                     w_rsrc, (uint32_t)(n0 + 32 * j + r) * (uint32_t)a.ldw + (uint32_t)(b * 32 + h * 16), 0, 0);
         }
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
-            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(alo, widen2<!ASYM>(wv[j][0], wv[j][1]), acc[j], 0, 0, 0);
+        for (int j = 0; j < FPW; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(alo, wlo[j], acc[j], 0, 0, 0);
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
-            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ahi, widen2<!ASYM>(wv[j][2], wv[j][3]), acc[j], 0, 0, 0);
-        }
+        for (int j = 0; j < FPW; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ahi, whi[j], acc[j], 0, 0, 0);
+    };
+    if constexpr (KC && (WLDS || WPRE)) {
+#pragma unroll
+        for (int i = 0; i < NBW; ++i)
+            if (kw + i * KW < nb) block(kw + i * KW, wpre[WPRE ? i : 0]);
+    } else {
+#pragma unroll 1
+        for (int b = kw; b < nb; b += KW) block(b, wpre[0]);
     }
 
     // ---- add the partial sums of the waves in LDS (exact, so the order is free).  Accumulator register q of
-    //      lane (c, h) is row 8 (q / 4) + 4 h + q % 4: with TM = 16 only registers 0 .. 7 hold real rows ----------
-    if (wave < nb) {
+    //      lane (c, h) is row 8 (q / 4) + 4 h + q % 4: with TM = 16 only registers 0 .. 7 hold real rows, with 8 only 0 .. 3 ----------
+    if (kw < nb) {
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
+        for (int j = 0; j < FPW; ++j)
 #pragma unroll
-            for (int q = 0; q < RV; ++q) atomicAdd(&s_sum[(j * RV + q) * 64 + lane], acc[j][q]);
+            for (int q = 0; q < RV; ++q) atomicAdd(&s_sum[((j0 + j) * RV + q) * 64 + lane], acc[j][q]);
     }
     __syncthreads();
     const bool ints = PACKED && a.acc_out != nullptr;
@@ -403,49 +430,88 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
                                                : make_rsrc(a.out, (uint32_t)((long)a.M * a.N * 2));
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
-        const int qq = wave + k * NW;
-        if (qq >= R) break;
-        const int j = qq / RV, q = qq % RV;
-        const int n = n0 + 32 * j + r;
-        const bool n_ok = n < a.N;
+        const int q = wave + k * NW;
+        if (q >= RV) break;
         const int trow = frag_row(0, q, lane);
+        // output of channel j (rows >= M fall off the end; N is a multiple of 8: all of a lane's adjacent channels or none)
+        auto at = [&](int j, uint32_t size) { return channel(j) < a.N ? ((uint32_t)(m0 + trow) * (uint32_t)a.N + (uint32_t)channel(j)) * size : kPoison; };
         if (ints) {                                              // parity export: P itself
-            const uint32_t ioff = n_ok ? ((uint32_t)(m0 + trow) * (uint32_t)a.N + (uint32_t)n) * 4u : kPoison;
-            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(W8 || ASYM ? s_sum[qq * 64 + lane] : s_sum[qq * 64 + lane] >> 8), o_rsrc, ioff, 0, 0);
+            uint32_t P[FN];
+#pragma unroll
+            for (int j = 0; j < FN; ++j) P[j] = (uint32_t)(W8 || ASYM ? s_sum[(j * RV + q) * 64 + lane] : s_sum[(j * RV + q) * 64 + lane] >> 8);
+            if constexpr (ADJ) {
+                store_words<FN>(o_rsrc, at(0, 4), P);
+            } else {
+#pragma unroll
+                for (int j = 0; j < FN; ++j) __builtin_amdgcn_raw_buffer_store_b32(P[j], o_rsrc, at(j, 4), 0, 0);
+            }
             continue;
         }
         // the sums hold 16 * P (256 * P if PACKED, P itself for the INT8 sibling); a power of two, so the rescaled
         // weight scale is exact
-        const float swn = __uint_as_float(sw_raw[k]) * (W8 || ASYM ? 1.0f : PACKED ? 0.00390625f : 0.0625f);
-        float y;
-        if constexpr (ASYM) {                                    // the operation order of tile_epilogue (one weight group)
-            const float t1 = swn * (float)s_sum[qq * 64 + lane], t2 = __uint_as_float(zw_raw[k]) * s_S[2 * TM + trow];
-            y = s_S[trow] * t1;
-            const float u = s_S[trow] * t2, z = s_S[TM + trow] * __uint_as_float(c_raw[k]);
-            y = y + u;
-            y = y + z;
-        } else {
-            y = ((float)s_sum[qq * 64 + lane] * s_S[trow]) * swn;
+        float y[FN];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const float swn = __uint_as_float(sw_raw[j]) * (W8 || ASYM ? 1.0f : PACKED ? 0.00390625f : 0.0625f);
+            const float P = (float)s_sum[(j * RV + q) * 64 + lane];
+            if constexpr (ASYM) {                                // the operation order of tile_epilogue (one weight group)
+                const float t1 = swn * P, t2 = __uint_as_float(zw_raw[j]) * s_S[2 * TM + trow];
+                y[j] = s_S[trow] * t1;
+                const float u = s_S[trow] * t2, z = s_S[TM + trow] * __uint_as_float(c_raw[j]);
+                y[j] = y[j] + u;
+                y[j] = y[j] + z;
+            } else {
+                y[j] = (P * s_S[trow]) * swn;
+            }
+            if (a.bias) y[j] = y[j] + __half2float(__ushort_as_half(b_raw[j]));
         }
-        if (a.bias) y = y + __half2float(__ushort_as_half(b_raw[k]));
-        const uint32_t off = n_ok ? ((uint32_t)(m0 + trow) * (uint32_t)a.N + (uint32_t)n) * 2u : kPoison;   // rows >= M fall off the end
-        if (a.act == W4A4_ACT_GELU) __builtin_amdgcn_raw_buffer_store_b16(gelu_erf_half(y), o_rsrc, off, 0, 0);
-        else __builtin_amdgcn_raw_buffer_store_b16(__half_as_ushort(__float2half_rn(y)), o_rsrc, off, 0, 0);
+        if constexpr (ADJ) {
+            if (a.act == W4A4_ACT_GELU) store_gelu_halves<FN>(o_rsrc, at(0, 2), y);
+            else store_halves<FN>(o_rsrc, at(0, 2), y);
+        } else {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const float one[1] = {y[j]};
+                if (a.act == W4A4_ACT_GELU) store_gelu_halves<1>(o_rsrc, at(j, 2), one);
+                else store_halves<1>(o_rsrc, at(j, 2), one);
+            }
+        }
     }
 }
 
-template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false, int LNK = 0>
+template <int NW, int FN, int TM, bool WLDS, bool PACKED, bool W8 = false, bool ASYM = false, int KC = 0, bool LN = false>
 static int launch_small(SmallArgs &a, hipStream_t st) {
     a.tiles_n = (a.N + 32 * FN - 1) / (32 * FN);
+    const uint32_t wcpr = (uint32_t)(W8 ? a.K / 16 : a.K / 32);
+    a.wcpr_inv = (uint32_t)(((1ull << 32) + wcpr - 1) / wcpr);
     const long tiles = (long)((a.M + TM - 1) / TM) * a.tiles_n;
     if (tiles > 0x7fffffffL) return W4A4_ERR_UNSUPPORTED_SHAPE;
     const size_t lds = TM * (size_t)((PACKED && !W8 ? a.K / 2 : a.K) + 16) + (WLDS ? 32 * FN * (size_t)((W8 ? a.K : a.K / 2) + 16) : 0) +
                        (size_t)(TM / 2) * FN * 64 * 4 + TM * (ASYM ? 12 : 4);
-    auto kern = linear_f16act_kernel<NW, FN, TM, WLDS, PACKED, W8, ASYM, LNK>;
+    auto kern = linear_f16act_kernel<NW, FN, TM, WLDS, PACKED, W8, ASYM, KC, LN>;
     static KernelState ks;
     if (prepare_kernel(reinterpret_cast<const void *>(kern), lds, ks) < 0) return W4A4_ERR_HIP;
     launch_gemm(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, st, a);
     return launch_status();
+}
+
+// Whether a tile of tm tokens and ch channels has its weights in LDS: they fit beside the codes and the sums within a CU's 160 KB, and
+// the chunks that a lane holds on their way there into its registers.
+constexpr bool small_wlds(int tm, int ch, int code_row, int w_row, int nw, int most) {
+    return (size_t)tm * (code_row + 16) + (size_t)ch * (w_row + 16) <= 144 * 1024 && (ch * (w_row / 16) + nw * 64 - 1) / (nw * 64) <= most;
+}
+// K as a constant of the kernel: rows that give each of a token's lanes the same number of 16-byte chunks (two, three, four or six for thirty-two
+// lanes, four, six or eight for sixty-four)
+template <int NW, bool PACKED, bool W8, bool ASYM, int K>
+static int launch_const(SmallArgs &a, bool wide, bool low, hipStream_t st) {
+    constexpr int code_row = PACKED && !W8 ? K / 2 : K, w_row = W8 ? K : K / 2;
+    if (wide) return launch_small<NW, 2, 32, small_wlds(32, 64, code_row, w_row, NW, 8), PACKED, W8, ASYM, K>(a, st);
+    // Long fp16 rows: quantizing them is most of the work, so eight tokens and half the waves per workgroup while each has a CU for
+    // itself: 32 x 768 x 3072 4.90 us -> 4.08, 64 x 1024 x 4096 5.83 -> 4.86
+    if constexpr (!PACKED && NW == 16)
+        if ((long)((a.M + 7) / 8) * ((a.N + 31) / 32) <= device_cus()) return launch_small<8, 1, 8, small_wlds(8, 32, code_row, w_row, 8, 8), PACKED, W8, ASYM, K>(a, st);
+    if (low) return launch_small<NW, 1, 16, small_wlds(16, 32, code_row, w_row, NW, 8), PACKED, W8, ASYM, K>(a, st);
+    return launch_small<NW, 1, 32, small_wlds(32, 32, code_row, w_row, NW, 8), PACKED, W8, ASYM, K>(a, st);
 }
 
 // Shape policy.  Waves: enough that none walks more than four blocks of K nor holds more than 16 chunks of
@@ -458,10 +524,19 @@ static int small_dispatch(SmallArgs &a, hipStream_t st) {
     const int M = a.M, N = a.N, K = a.K;
     const long t32 = (long)((M + 31) / 32) * ((N + 31) / 32);
     const bool wide = t32 > 256, low = t32 <= 128;
-    const size_t code_b = (size_t)(low ? 16 : 32) * ((PACKED && !W8 ? K / 2 : K) + 16), wt_b = (size_t)(wide ? 64 : 32) * ((W8 ? K : K / 2) + 16);
+    if constexpr (PACKED || !W8) {
+        switch (K) {
+            case 512: return launch_const<8, PACKED, W8, ASYM, 512>(a, wide, low, st);
+            case 768: return launch_const<8, PACKED, W8, ASYM, 768>(a, wide, low, st);
+            case 1024: return launch_const<8, PACKED, W8, ASYM, 1024>(a, wide, low, st);
+            case 1536: return launch_const<8, PACKED, W8, ASYM, 1536>(a, wide, low, st);
+            case 2048: return launch_const<16, PACKED, W8, ASYM, 2048>(a, wide, low, st);
+            case 3072: return launch_const<16, PACKED, W8, ASYM, 3072>(a, wide, low, st);
+            case 4096: return launch_const<16, PACKED, W8, ASYM, 4096>(a, wide, low, st);
+        }
+    }
     const int nw = K > 1536 ? 16 : K > 384 ? 8 : 4;
-    const long wchunks = ((long)(wide ? 64 : 32) * (K / (W8 ? 16 : 32)) + nw * 64 - 1) / (nw * 64);   // per lane
-    const bool wlds = code_b + wt_b <= 144 * 1024 && wchunks <= small_wchunks(nw);   // beside the sums, within a CU's 160 KB
+    const bool wlds = small_wlds(low ? 16 : 32, wide ? 64 : 32, PACKED && !W8 ? K / 2 : K, W8 ? K : K / 2, nw, small_wchunks(nw));
 #define W4A4_SMALL(NW)                                                                                  \
     do {                                                                                                \
         if (wide) return wlds ? launch_small<NW, 2, 32, true, PACKED, W8, ASYM>(a, st) : launch_small<NW, 2, 32, false, PACKED, W8, ASYM>(a, st); \
@@ -653,9 +728,9 @@ int launch_small_grouped(int mode, GemmArgs &g, hipStream_t st) {
 template <int K>
 static int launch_layernorm(SmallArgs &a, hipStream_t st) {
     const long t32 = (long)((a.M + 31) / 32) * ((a.N + 31) / 32);
-    if (t32 > 256) return launch_small<8, 2, 32, true, false, false, false, K>(a, st);
-    if (t32 <= 128) return launch_small<8, 1, 16, true, false, false, false, K>(a, st);
-    return launch_small<8, 1, 32, true, false, false, false, K>(a, st);
+    if (t32 > 256) return launch_small<8, 2, 32, true, false, false, false, K, true>(a, st);
+    if (t32 <= 128) return launch_small<8, 1, 16, true, false, false, false, K, true>(a, st);
+    return launch_small<8, 1, 32, true, false, false, false, K, true>(a, st);
 }
 int linear_layernorm_f16act(const LnArgs &ln, const w4a4_weight &W, const w4a4_epilogue &ep, void *out, hipStream_t st) {
     SmallArgs a{};

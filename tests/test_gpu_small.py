@@ -85,6 +85,34 @@ def test_fused_non_finite_inputs_do_not_fault(B):
     assert np.isfinite(got[rows]).all()                             # the other tokens are unaffected
 
 
+# rows of every K that is a constant of the kernel, on its tiles of 8 (long rows, up to 256 of them), 16, 32 and 32 x 64, with remainders in
+# tokens and channels; and K = 640 / 2560, which are not
+@pytest.mark.parametrize("M,N", [(1, 8), (9, 40), (17, 1032), (200, 264), (137, 2056)])
+@pytest.mark.parametrize("K", [512, 640, 768, 1024, 1536, 2048, 2560, 3072, 4096])
+def test_every_tile_of_constant_rows(B, M, N, K):
+    """fp16 and packed activations, both mappings, and the INT8 sibling: exact integer sums, and the bits of the general kernel."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    X = torch.randn((M, K), device="cuda", generator=g).half()
+    X[:, ::7] *= 8
+    W = (torch.randn((N, K), device="cuda", generator=g) * 0.02).half()
+    bias = (torch.randn(N, device="cuda", generator=g) * 0.01).half()
+    general, small = B.schedule_number("generic_64x64"), B.schedule_number("small_splitk")
+    for mode in (0, 1):
+        A, Q = B.quantize_act(X, mode), B.quantize_weight(W, mode)
+        assert torch.equal(B.gemm_i32(A, Q, schedule=small), B.gemm_i32(A, Q, schedule=general))
+        want = B.linear(A, Q, bias, 1, schedule=general)
+        got = torch.full((M + 2, N), 7.0, dtype=torch.float16, device="cuda")
+        B.linear(A, Q, bias, 1, schedule=small, out=(got[:M], None, None, None))
+        assert torch.equal(got[:M].view(torch.int16), want.view(torch.int16)) and (got[M:] == 7.0).all()
+        if mode == 0:
+            fused = torch.full((M + 2, N), 7.0, dtype=torch.float16, device="cuda")
+            B.linear_f16act(X, Q, bias, 1, out=fused[:M])
+            assert torch.equal(fused.view(torch.int16), got.view(torch.int16))
+    (q, s), (w8, s8) = B.quantize_rows8(X), B.quantize_rows8(W)
+    P = B.gemm8_i32(q, s, w8, s8)                                   # up to 512 tiles of 32 x 32: this kernel
+    assert torch.equal(P.cpu(), (q.cpu().double() @ w8.cpu().double().T).int())
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("M,N,K,group,act,with_bias", [
     (1, 8, 256, 128, 0, True), (17, 40, 1024, 128, 1, True), (33, 264, 768, 128, 0, False), (32, 32, 1024, 512, 0, True),
