@@ -228,7 +228,7 @@ static int launch_variant(int variant, GemmArgs &g, hipStream_t st) {
     }
 }
 
-// Layers with one weight group on 64 x 64 tiles: shares of K for the kernel of gemm_mid.hip, 0 = the kernel above.  us,
+// Layers with one weight group on 64 x 64 tiles that tile64_ok leaves, those whose K is no multiple of 256 above all: shares of K for the kernel of gemm_mid.hip, 0 = the kernel above.  us,
 // two shares | four | none, at 768 and 1024 tokens and features where nothing else is said:
 //   symmetric    K = 768: 5.0 | 5.3 | 4.9; K = 1024: 5.3 | 5.3 | 5.6; K = 3072: 8.4 | 7.8 | 10.6; K = 4096: 10.0 | 9.0 | 13.4; more tiles
 //                than CUs (1500 tokens, 288): K = 3072 11.3 | 13.6 | 12.6, (465 tokens, 384 tiles) K = 1024 6.8 | 8.6 | 6.4
@@ -243,9 +243,13 @@ static int k_shares(const GemmArgs &g, bool asym) {
 
 bool small_grouped_ok(const GemmArgs &g, int mode, int out_kind);   // gemm_small.hip: a wave per weight group
 int launch_small_grouped(int mode, GemmArgs &g, hipStream_t st);
+bool tile64_ok(const GemmArgs &g, int mode);                         // gemm_tile64.hip: K in chunks that LDS holds
+int launch_tile64(int mode, int out_kind, GemmArgs &g, hipStream_t st);
+
 
 int launch_generic(int variant, int mode, bool grouped, int out_kind, GemmArgs &g, hipStream_t st) {
     if (variant == 1) {
+        if (tile64_ok(g, mode)) return launch_tile64(mode, out_kind, g, st);
         if (grouped && small_grouped_ok(g, mode, out_kind)) return launch_small_grouped(mode, g, st);
         if (const int shares = k_shares(g, mode == W4A4_ASYM)) return launch_mid(shares, mode, out_kind, g, st);
     }

@@ -75,16 +75,22 @@ bool part_ok(const w4a4_part *p) {
     return p && p->w4.N > 0 && p->w4.K > 0 && p->w4.K % 32 == 0 && (p->act == W4A4_ACT_NONE || p->act == W4A4_ACT_GELU);
 }
 
-// One launch for small token counts: up to 512 tiles of 32 x 32, which quantize their tokens' whole rows.  INT4 with long rows
-// only up to 128, where the kernel still takes 16-token tiles: 465 x 768 x 3072 10.4 us in one launch, 9.7 in two; 256 tokens
-// 8.7 | 7.7, 160 tokens 6.5 | 7.0; 465 tokens of K = 768 6.1 | 7.3.  INT8: 465 x 768 x 3072 12.8 | 14.5.
+// One launch for small token counts, whose workgroups quantize their tokens' whole rows.  INT4: up to 960 tiles of 32 x 32 (us, one launch |
+// two: 300 x 3072 x 768 (960) 6.0 | 6.3, 465 x 2304 x 768 (1080) 7.9 | 7.6, 300 x 3072 x 1024 (960) 6.95 | 6.85, 224 x 4096 x 1024 (896) 6.9 | 6.9, 384 x 3072 x 1024
+// (1152) 9.2 | 8.3), 512 of K > 1024; with long rows only up to 128, where the kernel still takes tiles of 8 or 16 tokens: 160 x 768 x 3072 (120) 5.3 | 6.2,
+// 224 x 768 x 3072 (168) 7.2 | 6.6.  INT8: 512; 465 x 768 x 3072 12.8 | 14.5.
 bool one_kernel_tiles(int M, int N, int K, bool int4) {
     const long tiles = (long)((M + 31) / 32) * ((N + 31) / 32);
-    return K % 64 == 0 && K <= 4096 && tiles <= (int4 && K > 2048 ? 128 : 512);
+    return K % 64 == 0 && K <= 4096 && tiles <= (!int4 ? 512 : K > 2048 ? 128 : K > 1024 ? 512 : 960);
 }
 // ... symmetric per-channel weights in the canonical layout
 bool one_kernel_shape(int M, const w4a4_weight &w) {
     return w.layout == W4A4_LAYOUT_CANONICAL && w.mode == W4A4_SYM && groups_of(w) == 1 && one_kernel_tiles(M, w.N, w.K, true);
+}
+// FFN1 of a layer: there the alternative is not a launch more, since LayerNorm's kernel writes the codes, and the one launch forms
+// LayerNorm for every column tile: up to 512 tiles (layer of 768 at 1 x 128 tokens, 384 tiles, 27.8 us in one | 28.4; 2 x 128, 768 tiles, 37.5 | 33.2).
+bool one_kernel_ffn1(int M, const w4a4_weight &w) {
+    return one_kernel_shape(M, w) && (long)((M + 31) / 32) * ((w.N + 31) / 32) <= 512;
 }
 
 int run_part(const void *X, int M, int ldx, const w4a4_part &p, bool int4, void *out, void *ws, void *stream) {
@@ -520,7 +526,7 @@ extern "C" int w4a4_encoder_layer(const void *X_f16, int batch, int seq, const w
     // result (fused_ln), or of x1 itself, what w4a4_quantize_act would make of it.  It also clears what FFN1's
     // requantizing epilogue counts in.  (16384 tokens of 768, layer: 247 us with the separate quantize and fill launches
     // and LayerNorm 2 writing codes that nothing reads, 233 us so; 465 tokens: 49.6 and 44.3 us.)
-    const bool from_codes = fused_ln || (i2 && (fused_ffn || !one_kernel_shape(M, w1)));
+    const bool from_codes = fused_ln || (i2 && (fused_ffn || !one_kernel_ffn1(M, w1)));
     const w4a4_act a1 = view_act4(p.ln, M, h, w1);
     Carver c(p.rest);
     ActBuffers hb = {};

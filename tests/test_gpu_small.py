@@ -134,3 +134,32 @@ def test_several_weight_groups_of_a_few_tokens(mode, M, N, K, group, act, with_b
     B.linear(A, Q, bias, act, out=(got[:M], None, None, None))
     assert torch.equal(got[:M].view(torch.int16), want.view(torch.int16))
     assert (got[M:] == 7.0).all()                                  # nothing behind the last row
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("K", [256, 512, 768, 1024, 1280, 1536, 2304, 4096])      # all of K at once, chunks of 256 and of 512
+@pytest.mark.parametrize("M,N", [(1, 1096), (65, 264), (200, 1032)])
+def test_tiles_of_64_by_64(B, mode, K, M, N):
+    """One weight group on 64 x 64 tiles, remainders in tokens and channels: sums, fp16 rows (GELU), a column slice of wider packed rows
+    and the fp32 rows behind a requantize, bit for bit those of the general kernel's 64 x 128 tiles."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K + mode)
+    X = torch.randn((M, K), device="cuda", generator=g).half()
+    X[:, ::7] *= 8
+    W = (torch.randn((N, K), device="cuda", generator=g) * 0.02).half()
+    bias = (torch.randn(N, device="cuda", generator=g) * 0.01).half()
+    A, Q = B.quantize_act(X, mode), B.quantize_weight(W, mode)
+    wide = torch.randint(0, 256, (M, K // 2 + 64), dtype=torch.uint8, device="cuda", generator=g)
+    wide[:, 32:32 + K // 2] = A.q
+    S = B.QAct(wide, A.scale, A.zero, A.gsum, M, K, K // 2 + 64, 0, mode, q_offset_bytes=32)
+    tile, general = B.schedule_number("generic_64x64"), B.schedule_number("generic_64x128")
+    want = B.linear(A, Q, bias, 1, schedule=general)
+    for act in (A, S):
+        assert torch.equal(B.gemm_i32(act, Q, schedule=tile), B.gemm_i32(A, Q, schedule=general))
+        got = torch.full((M + 2, N), 7.0, dtype=torch.float16, device="cuda")
+        B.linear(act, Q, bias, 1, schedule=tile, out=(got[:M], None, None, None))
+        assert torch.equal(got[:M].view(torch.int16), want.view(torch.int16)) and (got[M:] == 7.0).all()
+    if N % 32 == 0 or N == 1032:
+        N = N // 32 * 32
+        Q = B.quantize_weight(W[:N].contiguous(), mode)
+        r = [B.linear(A, Q, bias[:N].contiguous(), 0, requant=True, requant_mode=1, schedule=s) for s in (tile, general)]
+        assert torch.equal(r[0].q, r[1].q) and torch.equal(r[0].scale, r[1].scale) and torch.equal(r[0].zero, r[1].zero)
