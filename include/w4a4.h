@@ -535,6 +535,23 @@ int w4a4_dequant_epilogue(const int32_t *acc, const w4a4_act *A, const w4a4_weig
                           const w4a4_epilogue *ep, void *out, float *out_scale, float *out_zero,
                           int32_t *out_gsum, void *stream);
 
+/* A call of one of the entry points with its arguments laid out once, for callers to whom passing a dozen of them costs as
+ * much as the launch (through Python's ctypes 1.5 us and more, of this 0.3).  p, i, f and n hold the entry point's pointers,
+ * ints, float and size in the order of its parameters, the stream excepted; structs that a pointer names must still be there when
+ * the call is made.  Returns what the entry point returns, W4A4_ERR_INVALID_ARG for another `entry`. */
+typedef enum {
+    W4A4_CALL_QUANTIZE_ACT = 0, W4A4_CALL_LINEAR = 1, W4A4_CALL_LINEAR_F16ACT = 2, W4A4_CALL_LAYERNORM_QUANTIZE = 3,
+    W4A4_CALL_QUANTIZE_ROWS8 = 4, W4A4_CALL_LINEAR8 = 5        /* w8a8_quantize_rows, w8a8_linear */
+} w4a4_call_entry;
+typedef struct {
+    void *p[10];
+    size_t n;
+    int i[6];
+    float f;
+    int entry;
+} w4a4_call;
+int w4a4_run_call(const w4a4_call *call, void *stream);
+
 #ifdef __cplusplus
 }
 #endif

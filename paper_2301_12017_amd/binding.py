@@ -71,6 +71,10 @@ class _StrategyCosts(ctypes.Structure):
     _fields_ = [("part_us", (ctypes.c_float * 2) * 4), ("ffn_fused_us", ctypes.c_float)]
 
 
+class _Call(ctypes.Structure):
+    _fields_ = [("p", ctypes.c_void_p * 10), ("n", ctypes.c_size_t), ("i", ctypes.c_int * 6), ("f", ctypes.c_float), ("entry", ctypes.c_int)]
+
+
 class _LayerWeights(ctypes.Structure):
     _fields_ = [("hidden", ctypes.c_int), ("heads", ctypes.c_int), ("ffn", ctypes.c_int),
                 ("qkv", _Part), ("attn_out", _Part), ("ffn1", _Part), ("ffn2", _Part),
@@ -124,6 +128,7 @@ _SIGNATURES = {
     "w4a4_probe_stream": (_i, [_vp, _vp, _sz, _vp, _vp]),
     "w4a4_pick_schedule": (_i, [ctypes.POINTER(_Act), ctypes.POINTER(_Weight), ctypes.POINTER(_Epilogue)]),
     "w4a4_gemm_i32": (_i, [ctypes.POINTER(_Act), ctypes.POINTER(_Weight), _vp, _i, _vp]),
+    "w4a4_run_call": (_i, [ctypes.POINTER(_Call), _vp]),
     "w4a4_dequant_epilogue": (_i, [_vp, ctypes.POINTER(_Act), ctypes.POINTER(_Weight),
                                    ctypes.POINTER(_Epilogue), _vp, _vp, _vp, _vp, _vp]),
 }
@@ -411,21 +416,37 @@ def layernorm_quantize(X: torch.Tensor, R: Optional[torch.Tensor], gamma: torch.
     return out, y
 
 
-class PreparedLayerNormQuantize:
-    """A w4a4_layernorm_quantize call with its arguments marshalled once (see PreparedLinear)."""
+def _address(x):
+    """Of a tensor's first element, a ctypes struct, or None."""
+    return None if x is None else x.data_ptr() if isinstance(x, torch.Tensor) else ctypes.addressof(x)
+
+
+class _Prepared:
+    """A call of an entry point with its arguments laid out once (w4a4_call in include/w4a4.h): calling the object only makes the C
+    call on the current stream.  Handing the dozen arguments to the entry point itself took 1.5 us of the 3.8 that such a call
+    cost on the host, more than the kernels of few tokens leave to hide it behind."""
+    ENTRIES = ("w4a4_quantize_act", "w4a4_linear", "w4a4_linear_f16act", "w4a4_layernorm_quantize", "w8a8_quantize_rows", "w8a8_linear")
+
+    def _lay_out(self, name, pointers, ints=(), f=0.0, n=0):
+        self.name = name
+        self.call = _Call((ctypes.c_void_p * 10)(*map(_address, pointers)), n, (ctypes.c_int * 6)(*ints), f, self.ENTRIES.index(name))
+        self.call_ref = ctypes.byref(self.call)
+        self.fn = lib().w4a4_run_call
+
+    def __call__(self, stream=None):
+        rc = self.fn(self.call_ref, _stream() if stream is None else stream)
+        if rc:
+            raise W4A4Error(rc, self.name)
+
+
+class PreparedLayerNormQuantize(_Prepared):
+    """A w4a4_layernorm_quantize call with its arguments marshalled once."""
 
     def __init__(self, X, R, gamma, beta, eps, out: QAct, y=None):
         M, K = X.shape
         self.keep = (X, R, gamma, beta, out, y)
-        self.args = (_ptr(X), _ptr(R), M, K, X.stride(0), _ptr(gamma), _ptr(beta), float(eps), _ptr(y), out.mode,
-                     out.group, _ptr(out.q), _ptr(out.scale), _ptr(out.zero), _ptr(out.gsum), out.layout,
-                     _ptr(out.osum))
-        self.fn = lib().w4a4_layernorm_quantize
-
-    def __call__(self, stream=None):
-        rc = self.fn(*self.args, _stream() if stream is None else stream)
-        if rc:
-            raise W4A4Error(rc, "w4a4_layernorm_quantize")
+        self._lay_out("w4a4_layernorm_quantize", (X, R, gamma, beta, y, out.q, out.scale, out.zero, out.gsum, out.osum),
+                      (M, K, X.stride(0), out.mode, out.group, out.layout), f=float(eps))
 
 
 def workspace_bytes(M, N, K, requant=False) -> int:
@@ -525,7 +546,7 @@ def linear_static(A: QAct, W: QWeight, bias: Optional[torch.Tensor] = None, act=
     return QAct(o, os_, oz, og, A.M, W.N, W.N // 2, requant_group, requant_mode)
 
 
-class PreparedLinear:
+class PreparedLinear(_Prepared):
     """A w4a4_linear call with every argument marshalled once: calling the object only makes the
     C call on the current stream.  For loops that must not be slowed down by Python (benchmarks,
     graph capture).  The tensors it was built from are kept alive."""
@@ -543,14 +564,7 @@ class PreparedLinear:
         if need and workspace is None:
             workspace = torch.empty((need,), dtype=torch.uint8, device=A.q.device)
         self.workspace = workspace
-        self.args = (ctypes.byref(self.a), ctypes.byref(self.w), ctypes.byref(self.ep), _ptr(out[0]), _ptr(out[1]),
-                     _ptr(out[2]), _ptr(out[3]), _ptr(workspace), 0 if workspace is None else workspace.numel())
-        self.fn = lib().w4a4_linear
-
-    def __call__(self, stream=None):
-        rc = self.fn(*self.args, _stream() if stream is None else stream)
-        if rc:
-            raise W4A4Error(rc, "w4a4_linear")
+        self._lay_out("w4a4_linear", (self.a, self.w, self.ep, out[0], out[1], out[2], out[3], workspace), n=0 if workspace is None else workspace.numel())
 
 
 def linear_f16act(X: torch.Tensor, W: QWeight, bias: Optional[torch.Tensor] = None, act=ACT_NONE,
@@ -610,8 +624,8 @@ def gemm8_i32(Aq, sa, Wq, sw):
     return acc
 
 
-class PreparedLinear8:
-    """A w8a8_linear call with its arguments marshalled once (see PreparedLinear)."""
+class PreparedLinear8(_Prepared):
+    """A w8a8_linear call with its arguments marshalled once."""
 
     def __init__(self, Aq, sa, Wq, sw, bias=None, act=ACT_NONE, out=None):
         M, K = Aq.shape
@@ -619,26 +633,14 @@ class PreparedLinear8:
         self.out = torch.empty((M, N), dtype=torch.float16, device=Aq.device) if out is None else out
         self.keep = (Aq, sa, Wq, sw, bias)
         self.ep = _epilogue(bias, act, False, SYM, 0, 0, LAYOUT_CANONICAL)
-        self.args = (_ptr(Aq), Aq.stride(0), _ptr(sa), M, _ptr(Wq), _ptr(sw), N, K, ctypes.byref(self.ep), _ptr(self.out))
-        self.fn = lib().w8a8_linear
-
-    def __call__(self, stream=None):
-        rc = self.fn(*self.args, _stream() if stream is None else stream)
-        if rc:
-            raise W4A4Error(rc, "w8a8_linear")
+        self._lay_out("w8a8_linear", (Aq, sa, Wq, sw, self.ep, self.out), (Aq.stride(0), M, N, K))
 
 
-class PreparedQuantizeRows8:
+class PreparedQuantizeRows8(_Prepared):
     def __init__(self, X, q, scale):
         M, K = X.shape
         self.keep = (X, q, scale)
-        self.args = (_ptr(X), M, K, X.stride(0), _ptr(q), _ptr(scale))
-        self.fn = lib().w8a8_quantize_rows
-
-    def __call__(self, stream=None):
-        rc = self.fn(*self.args, _stream() if stream is None else stream)
-        if rc:
-            raise W4A4Error(rc, "w8a8_quantize_rows")
+        self._lay_out("w8a8_quantize_rows", (X, q, scale), (M, K, X.stride(0)))
 
 
 # ---- per-part strategy -------------------------------------------------------------------------------
@@ -765,8 +767,8 @@ class EncoderLayer:
         return out
 
 
-class PreparedLinearF16Act:
-    """A w4a4_linear_f16act call with its arguments marshalled once (see PreparedLinear)."""
+class PreparedLinearF16Act(_Prepared):
+    """A w4a4_linear_f16act call with its arguments marshalled once."""
 
     def __init__(self, X: torch.Tensor, W: QWeight, bias=None, act=ACT_NONE, out=None):
         assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2 and X.stride(1) == 1
@@ -776,30 +778,18 @@ class PreparedLinearF16Act:
         self.out = out
         self.keep = (X, W, bias, out)
         self.ep, self.w = _epilogue(bias, act, False, SYM, 0, 0, LAYOUT_CANONICAL), W.c()
-        self.args = (_ptr(X), M, K, X.stride(0), ctypes.byref(self.w), ctypes.byref(self.ep), _ptr(out))
-        self.fn = lib().w4a4_linear_f16act
-
-    def __call__(self, stream=None):
-        rc = self.fn(*self.args, _stream() if stream is None else stream)
-        if rc:
-            raise W4A4Error(rc, "w4a4_linear_f16act")
+        self._lay_out("w4a4_linear_f16act", (X, self.w, self.ep, out), (M, K, X.stride(0)))
 
 
-class PreparedQuantizeAct:
-    """A w4a4_quantize_act call with its arguments marshalled once (see PreparedLinear)."""
+class PreparedQuantizeAct(_Prepared):
+    """A w4a4_quantize_act call with its arguments marshalled once."""
 
     def __init__(self, X: torch.Tensor, out: QAct):
         assert X.is_cuda and X.dtype == torch.float16 and X.stride(1) == 1
         self.keep = (X, out)
         M, K = X.shape
-        self.args = (_ptr(X), M, K, X.stride(0), out.mode, out.group, _ptr(out.q), _ptr(out.scale), _ptr(out.zero),
-                     _ptr(out.gsum), out.layout, _ptr(out.osum))
-        self.fn = lib().w4a4_quantize_act
-
-    def __call__(self, stream=None):
-        rc = self.fn(*self.args, _stream() if stream is None else stream)
-        if rc:
-            raise W4A4Error(rc, "w4a4_quantize_act")
+        self._lay_out("w4a4_quantize_act", (X, out.q, out.scale, out.zero, out.gsum, out.osum),
+                      (M, K, X.stride(0), out.mode, out.group, out.layout))
 
 
 def gemm_i32(A: QAct, W: QWeight, schedule=0) -> torch.Tensor:

@@ -233,3 +233,34 @@ def test_current_stream_without_the_undocumented_handle(b, monkeypatch):
     assert b._stream() == 0x1003
     monkeypatch.setattr(b, "_raw_stream", None)
     assert b._stream() == 0x7f0012345678
+
+
+def test_calls_laid_out_once_reach_their_entry_point(b):
+    """Every entry of w4a4_run_call refuses and accepts (nothing to do) what its entry point does, with the arguments in their places."""
+    L = b.lib()
+    ep, w, a = b._Epilogue(None, 0, 0, 0, 0, 0, 0), _wt(b, K=128), _act(b, M=0, K=128)
+    at = ctypes.addressof
+    P = 0x1000
+
+    def run(entry, pointers, ints=(), f=0.0, n=0):
+        c = b._Call((ctypes.c_void_p * 10)(*pointers), n, (ctypes.c_int * 6)(*ints), f, entry)
+        return L.w4a4_run_call(ctypes.byref(c), None)
+
+    assert L.w4a4_run_call(None, None) == -1 and run(6, ()) == -1 and run(-1, ()) == -1
+    q = (P, P, P, None, None, None)
+    assert run(0, q, (0, 64, 64, 0, 0, 0)) == 0
+    assert run(0, q, (4, 64, 32, 0, 0, 0)) == -1 and run(0, q, (4, 64, 64, 0, 24, 0)) == -2 and run(0, q, (4, 64, 64, 0, 0, 1)) == -1
+    assert run(0, (P, P, P, None, None, P), (4, 64, 64, 0, 0, 5)) == -1
+    assert run(1, (at(a), at(w), at(ep), P)) == 0
+    a.M, w12 = 4, _wt(b, N=12, K=128)
+    assert run(1, (at(a), at(w), at(ep), None)) == -1 and run(1, (at(a), at(w12), at(ep), P)) == -2
+    rq, w32 = b._Epilogue(None, 0, 1, 0, 0, 0, 0), _wt(b, N=32, K=128)
+    assert run(1, (at(a), at(w32), at(rq), P, None)) == -1 and run(1, (at(a), at(w32), at(rq), P, P), n=0) == -3
+    assert run(1, (at(a), at(w32), at(rq), P, P, None, None, P), n=16) == -3
+    assert run(2, (P, at(w), at(ep), P), (0, 128, 128)) == 0 and run(2, (P, at(w), at(ep), P), (4, 128, 64)) == -1
+    ln = (P, None, P, P, None, P, P)
+    assert run(3, ln, (0, 64, 64, 0, 0, 0), 1e-5) == 0 and run(3, ln, (4, 64, 64, 0, 0, 0), -1.0) == -1
+    assert run(3, ln, (4, 64, 64, 0, 24, 0), 1e-5) == -2 and run(3, ln, (4, 64, 64, 0, 0, 1), 1e-5) == -1
+    assert run(4, (P, P, P), (0, 64, 64)) == 0 and run(4, (P, P, P), (4, 64, 32)) == -1
+    l8 = (P, P, P, P, at(ep), P)
+    assert run(5, l8, (128, 0, 8, 128)) == 0 and run(5, l8, (64, 4, 8, 128)) == -1 and run(5, l8, (128, 4, 12, 128)) == -2
