@@ -338,7 +338,7 @@ static int launch_rows(const T *X, long ldx, int rows, int K, int G, uint8_t *q,
 // quantize_stream_kernel spends most of its instructions on what a row costs once (two wave-wide reductions
 // through the LDS crossbar, the division, addressing), and at K = 1024 a lane holds only sixteen elements: a
 // 12288 x 1024 matrix took 6 us of vector-ALU issue per SIMD against 5 us of memory time.  Here a row is owned by
-// LPR = 16, 32 or 64 lanes (the smallest that keeps <= 8 chunks of eight elements per lane), so a wave quantizes
+// LPR = 16, 32 or 64 lanes (few tokens of a long row: the 256 of a workgroup; launch_tok_rows), so a wave quantizes
 // 64 / LPR tokens with one instruction stream; reductions inside 16 lanes use the cross-lane operand modes (quad
 // permutes, half-row and row mirror) instead of the LDS; and a code costs four instructions: conversion fused
 // with the first arithmetic step, the second step, the rounding add, and one shift-add that appends it to the
@@ -353,14 +353,24 @@ static int launch_rows(const T *X, long ldx, int rows, int K, int G, uint8_t *q,
 // Same arithmetic, same codes as the kernels above.
 template <int CTRL>
 __device__ __forceinline__ int dpp_move(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
+template <typename T, typename Op>
+__device__ __forceinline__ T swap_rows(T v, Op op) {                // op of the lanes l and l ^ 16
+    const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    return op(__builtin_bit_cast(T, (unsigned)sw[0]), __builtin_bit_cast(T, (unsigned)sw[1]));
+}
+template <typename T, typename Op>
+__device__ __forceinline__ T swap_halves(T v, Op op) {              // ... l and l ^ 32
+    const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    return op(__builtin_bit_cast(T, (unsigned)sw[0]), __builtin_bit_cast(T, (unsigned)sw[1]));
+}
 template <int LPR>
 __device__ __forceinline__ float sub_max(float v) {                 // maximum over the LPR lanes that own a row
     v = fmaxf(v, __int_as_float(dpp_move<0xB1>(__float_as_int(v))));     // quad_perm [1,0,3,2]
     v = fmaxf(v, __int_as_float(dpp_move<0x4E>(__float_as_int(v))));     // quad_perm [2,3,0,1]
     v = fmaxf(v, __int_as_float(dpp_move<0x141>(__float_as_int(v))));    // half-row mirror
     if (LPR >= 16) v = fmaxf(v, __int_as_float(dpp_move<0x140>(__float_as_int(v))));   // row mirror
-    if (LPR >= 32) v = fmaxf(v, __shfl_xor(v, 16, kWave));
-    if (LPR >= 64) v = fmaxf(v, __shfl_xor(v, 32, kWave));
+    if (LPR >= 32) v = swap_rows(v, [](float a, float b) { return fmaxf(a, b); });
+    if (LPR >= 64) v = swap_halves(v, [](float a, float b) { return fmaxf(a, b); });
     return v;
 }
 __device__ __forceinline__ int row16_sum(int v) {                   // sum over the sixteen lanes of a DPP row
@@ -373,21 +383,48 @@ __device__ __forceinline__ int row16_sum(int v) {                   // sum over 
 template <int LPR>
 __device__ __forceinline__ int sub_sum(int v) {
     v = row16_sum(v);
-    if (LPR >= 32) v += __shfl_xor(v, 16, kWave);
-    if (LPR >= 64) v += __shfl_xor(v, 32, kWave);
+    if (LPR >= 32) v = swap_rows(v, [](int a, int b) { return a + b; });
+    if (LPR >= 64) v = swap_halves(v, [](int a, int b) { return a + b; });
     return v;
 }
 
+// LPR == 256: a row per workgroup, whose four waves meet in LDS.
 // EXACT: K / 8 == LPR * CPL, no chunk of a lane lies past K.  ng: K-groups of the asymmetric psum (1 or K / 128).
 template <int MODE, int LPR, int CPL, int LAYOUT, bool EXACT>
 __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel(
     const __half *__restrict__ X, long ldx, int rows, int K, uint8_t *__restrict__ q, float *__restrict__ s,
     float *__restrict__ z, int32_t *__restrict__ gsum, int32_t *__restrict__ psum, int ng) {
-    constexpr int RPW = kWave / LPR;                            // tokens per wave
+    constexpr bool BLOCK = LPR == kRowsPerBlock * kWave;
+    constexpr int LPW = BLOCK ? kWave : LPR, RPW = kWave / LPW; // a row's lanes in a wave, tokens per wave
     constexpr bool ASYM = MODE == W4A4_ASYM;
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    const int lane = threadIdx.x % kWave, l = lane % LPR;
-    const long row = ((long)blockIdx.x * kRowsPerBlock + threadIdx.x / kWave) * RPW + lane / LPR;
+    __shared__ float s_max[BLOCK ? 2 * kRowsPerBlock : 1];
+    __shared__ int s_sum[BLOCK ? kRowsPerBlock : 1];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, l = threadIdx.x % LPR;
+    const long row = BLOCK ? (long)blockIdx.x : ((long)blockIdx.x * kRowsPerBlock + wave) * RPW + lane / LPW;
+    // maxima over a row's lanes, one or two of them
+    auto row_max = [&](float &a, float *b) {
+        a = sub_max<LPW>(a);
+        if (b) *b = sub_max<LPW>(*b);
+        if constexpr (BLOCK) {
+            if (lane == 0) {
+                s_max[wave] = a;
+                if (b) s_max[kRowsPerBlock + wave] = *b;
+            }
+            __syncthreads();
+            a = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+            if (b) *b = fmaxf(fmaxf(s_max[4], s_max[5]), fmaxf(s_max[6], s_max[7]));
+        }
+    };
+    auto row_sum = [&](int v) {
+        v = sub_sum<LPW>(v);
+        if constexpr (BLOCK) {
+            if (lane == 0) s_sum[wave] = v;
+            __syncthreads();
+            v = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+        }
+        return v;
+    };
     const int nchunks = K / 8;
     const bool live = row < rows;
     const u4 *src = reinterpret_cast<const u4 *>(X + (live ? row : (long)rows - 1) * ldx);
@@ -415,7 +452,9 @@ __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel
                 hi2 = __builtin_elementwise_max(hi2, *reinterpret_cast<const us2 *>(&d));
             }
         const unsigned short hmax = hi2[0] > hi2[1] ? hi2[0] : hi2[1];
-        r = range_sym(sub_max<LPR>(__half2float(__ushort_as_half(hmax))));
+        float amax = __half2float(__ushort_as_half(hmax));
+        row_max(amax, nullptr);
+        r = range_sym(amax);
         if (l == 0 && live) s[row] = r.S;
     } else {
         // ---- minimum and maximum on packed fp16 (exact: the extremes of fp16 values are fp16 values)
@@ -431,9 +470,9 @@ __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel
                 hi2 = __builtin_elementwise_max(hi2, d);
                 lo2 = __builtin_elementwise_min(lo2, d);
             }
-        const float hi = sub_max<LPR>(fmaxf((float)hi2[0], (float)hi2[1]));
-        const float lo = -sub_max<LPR>(-fminf((float)lo2[0], (float)lo2[1]));
-        r = range_asym(lo, hi);
+        float hi = fmaxf((float)hi2[0], (float)hi2[1]), nlo = -fminf((float)lo2[0], (float)lo2[1]);
+        row_max(hi, &nlo);
+        r = range_asym(-nlo, hi);
         if (l == 0 && live) {
             s[row] = r.S;
             z[row] = r.lo;
@@ -493,13 +532,17 @@ __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel
             }
         }
     }
-    if (ASYM && ng == 1 && gsum) {
-        total = sub_sum<LPR>(total);
-        if (l == 0 && live) gsum[row] = total;
-    }
-    if (LAYOUT != 0 && (!ASYM || ng == 1)) {
-        part = sub_sum<LPR>(part);
-        if (l == 0 && live) psum[row] = ASYM ? 128 * part : part;
+    if constexpr (ASYM) {                                       // both sums in one register again: a row's are below 15 K < 2^16 (K <= 4096)
+        if (ng == 1 && (gsum || LAYOUT != 0)) {
+            const uint32_t both = (uint32_t)row_sum((total << 16) | part);
+            if (l == 0 && live) {
+                if (gsum) gsum[row] = (int)(both >> 16);
+                if (LAYOUT != 0) psum[row] = 128 * (int)(both & 0xFFFFu);
+            }
+        }
+    } else if constexpr (LAYOUT != 0) {
+        part = row_sum(part);
+        if (l == 0 && live) psum[row] = part;
     }
 }
 
@@ -509,9 +552,14 @@ static int launch_tok_rows(const __half *X, long ldx, int rows, int K, uint8_t *
     if (rows == 0) return W4A4_OK;
     const int nchunks = K / 8;
     if (nchunks > 8 * kWave) return -100;
-    const int lpr = nchunks <= 8 * 16 ? 16 : nchunks <= 8 * 32 ? 32 : 64;
+    // A lane's chunks are worked through one after the other, so few of them per lane as long as the lanes of a row are full (us, lanes |
+    // us; back to back over rotating inputs; sym = symmetric, asym = unsigned in groups of 128): 2000 x 768 sym 16 2.58 | 32 2.36 | 64 2.56,
+    // asym 3.51 | 2.91 | 3.24; 16384 x 768 6.64 | 6.64 | 7.24, 8.23 | 8.27 | 9.91; 2000 x 1024 2.88 | 2.62 | 2.51, 3.98 | 3.25 | 3.01; 16384 x 1024 9.60 |
+    // 9.32 | 9.62, 11.8 | 11.4 | 11.1; 4096 x 2048 - | 5.16 | 5.04, - | 6.78 | 6.38.  With the lanes of four waves, 64 | 256: 32 x 4096 2.58 | 2.14, 3.68 | 2.56;
+    // 300 x 3072 2.50 | 2.32, 3.42 | 2.81; 1000 x 3072 2.74 | 2.87, 3.61 | 3.69.
+    const int lpr = nchunks > 128 && rows <= 512 ? 256 : nchunks > 128 || (nchunks == 128 && rows <= 2048) ? 64 : nchunks > 32 ? 32 : 16;
     const int cpl = (nchunks + lpr - 1) / lpr;
-    const long per_block = (long)kRowsPerBlock * (kWave / lpr);
+    const long per_block = lpr > kWave ? 1 : (long)kRowsPerBlock * (kWave / lpr);
     dim3 grid((unsigned)((rows + per_block - 1) / per_block)), block(kRowsPerBlock * kWave);
 #define W4A4_QF(L, C)                                                                                       \
     do {                                                                                                    \
@@ -523,13 +571,15 @@ static int launch_tok_rows(const __half *X, long ldx, int rows, int K, uint8_t *
 #define W4A4_QFL(L)                                                                                         \
     do {                                                                                                    \
         if (cpl <= 2) W4A4_QF(L, 2);                                                                        \
-        else if (cpl <= 4) W4A4_QF(L, 4);                                                                   \
-        else if (cpl <= 6) W4A4_QF(L, 6);                                                                   \
-        else W4A4_QF(L, 8);                                                                                 \
+        else if (cpl <= 3) W4A4_QF(L, 3);                                                                   \
+        else W4A4_QF(L, 4);                                                                                 \
     } while (0)
-    if (lpr == 16) W4A4_QFL(16);
+    if (lpr == 16) W4A4_QF(16, 2);
     else if (lpr == 32) W4A4_QFL(32);
-    else W4A4_QFL(64);
+    else if (lpr == 256) W4A4_QF(256, 2);
+    else if (cpl <= 4) W4A4_QFL(64);
+    else if (cpl <= 6) W4A4_QF(64, 6);
+    else W4A4_QF(64, 8);
 #undef W4A4_QFL
 #undef W4A4_QF
     return launch_status();

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kQ8RowsPerBlock *kWave) void quantize_rows8_kernel(
             const uint32_t d = raw[it][i] & 0x7FFF7FFFu;
             mx = __builtin_elementwise_max(mx, *reinterpret_cast<const h2 *>(&d));
         }
-    const float amax = wave_max(fmaxf((float)mx[0], (float)mx[1]));
+    const float amax = lanes_reduce<kWave>(fmaxf((float)mx[0], (float)mx[1]), [](float a, float b) { return fmaxf(a, b); });
     float inv, S;
     if (amax == 0.0f) { inv = 0.0f; S = 1.0f; }
     else { inv = 127.0f / amax; S = amax / 127.0f; }
@@ -47,8 +47,10 @@ __global__ __launch_bounds__(kQ8RowsPerBlock *kWave) void quantize_rows8_kernel(
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t d = raw[it][i];
-            const float2 f = __half22float2(*reinterpret_cast<const __half2 *>(&d));
-            const float t0 = f.x * inv, t1 = f.y * inv;
+            // t = (float)x * inv, rounded once: the mixed-precision multiply-add reads the fp16 half itself
+            float t0, t1;
+            asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(t0) : "v"(d), "v"(inv));
+            asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(t1) : "v"(d), "v"(inv));
             u[2 * i] = __float_as_uint(t0 + 12582912.0f);           // the code is the low byte of the sum
             u[2 * i + 1] = __float_as_uint(t1 + 12582912.0f);
         }

@@ -454,3 +454,31 @@ def test_one_weight_group_small_and_mid_sized(B, orc, mode, M, N, K):
         out = B.linear(A, Q, dev(b), 0, requant=True, requant_mode=ASYM)
         want = orc.linear(oa, ow, mode, 0, b, 0, requant=True, requant_mode=ASYM)
         assert np.array_equal(host(out.q)[rows], want["q"])
+
+
+@pytest.mark.parametrize("K", [256, 288, 512, 1024, 1056, 2048, 3072, 4096])
+@pytest.mark.parametrize("M", [1, 5, 512])
+def test_quantize_act_few_tokens_as_among_many(K, M):
+    """How many lanes share a row depends on its length and on the number of rows (16, 32, 64, or a workgroup of 256): a few rows by
+    themselves give what they give among 2100, in every mapping and layout, INT8 too."""
+    from paper_2301_12017_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    X = torch.randn((2100, K), device="cuda", generator=g).half()
+    X[0] = 3.0
+    X[:, ::11] *= 9
+    few = X[:M].contiguous()
+    cases = [(mode, group, layout) for mode in (0, 1) for group in (0, 128) for layout in (0, 1)
+             if not (group and (mode == 0 or K % 128)) and not (layout and (K % 128 or K < 256))]
+    for mode, group, layout in cases:
+        a, b = B.quantize_act(few, mode, group, layout=layout), B.quantize_act(X, mode, group, layout=layout)
+        assert torch.equal(a.q, b.q[:M]) and torch.equal(a.scale, b.scale[:M]), (mode, group, layout)
+        if mode:
+            assert torch.equal(a.zero, b.zero[:M]) and torch.equal(a.gsum, b.gsum[:M]), (group, layout)
+            low, high = a.q & 15, a.q >> 4
+            if not layout:                                          # the sums against the codes themselves
+                per = (low.int() + high.int()).view(M, -1, (group or K) // 2).sum(2)
+                assert torch.equal(per.int(), a.gsum), group
+        if layout:
+            assert torch.equal(a.osum, b.osum[..., :M] if mode else b.osum[:M]), (mode, group)
+    (q, s), (qb, sb) = B.quantize_rows8(few), B.quantize_rows8(X)
+    assert torch.equal(q, qb[:M]) and torch.equal(s, sb[:M])
