@@ -29,6 +29,10 @@
 //     walk K in steps of 256 codes, whole lines, with two stages: 128 x 128 (pairs of workgroups per CU) and 256 x 256
 //     (one workgroup of eight waves: 2/3 of the operand bytes per product of 128 x 256).  16384 x 1024 x 4096 52 -> 48 us, 16384 x 4096 x 1024
 //     + GELU 76.6 -> 68.1, 12288 x 768 x 3072 28.9 -> 27.4.
+//   * A 128 x 128 tile with a CU to itself leaves one wave to a SIMD, and what that wave waits for (a barrier, LDS, the issue of its
+//     DMA) nobody else fills: a step of 128 codes takes 0.43 us where its MFMAs take 0.22 and its 16 KB 0.19.  With long K two groups of
+//     four waves therefore share a tile, each with half of the codes of every step (KG = 2: integer sums, so their order is free), and
+//     hand each other half of the rows through LDS at the end: 3339 x 1024 x 4096 17.7 -> 15.3 us, 3000 x 768 x 3072 13.9 -> 12.0.
 #include "gemm_common.hpp"
 
 namespace w4a4 {
@@ -83,8 +87,8 @@ struct ChanParams {
 //     (its product with the scale is formed once per tile).  The outer one rounds once, to fp16 (fma_half2; in front of
 //     GELU to fp32), whatever the tile.  The real number rounded differs from the definition's by a few units in
 //     fp32's last place, the fp16 result by at most one step and only on near-ties of the fp16 grid.
-template <int FM, int FN, int OUT, bool BIAS, bool GELU>
-__device__ __forceinline__ void olay_epilogue(const GemmArgs &g, v16i (&acc)[FM][FN], const ChanParams<FN> &cp,
+template <int FM, int FN, int OUT, bool BIAS, bool GELU, int AM>
+__device__ __forceinline__ void olay_epilogue(const GemmArgs &g, v16i (&acc)[AM][FN], const ChanParams<FN> &cp,
                                               uint32_t col_off, int m0, int row_w, int lane,
                                               const float *sa_lds) {
     constexpr int ESZ = OUT == OUT_F16 ? 2 : 4;
@@ -272,13 +276,14 @@ __device__ __forceinline__ void olay_epilogue_requant(const GemmArgs &g, v16i (&
 }
 
 // WPS: waves per SIMD (all workgroups of a CU together).  ROWB: bytes (two codes each) of a row per K step.  NS: LDS stages.
-template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int OUT>
-__global__ __attribute__((amdgpu_flat_work_group_size(WM *WN * 64, WM *WN * 64), amdgpu_waves_per_eu(WPS, WPS)))
+// KG: groups of WM * WN waves that share the codes of a step; with two of them a workgroup has one tile.
+template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int KG, int OUT>
+__global__ __attribute__((amdgpu_flat_work_group_size(WM *WN *KG * 64, WM *WN *KG * 64), amdgpu_waves_per_eu(WPS, WPS)))
 void gemm_olay_kernel(GemmArgs g) {
-    constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
+    constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN * KG;
     constexpr int STAGE = (BM + BN) * ROWB;
     constexpr int CPR = ROWB / 16, RPB = 1024 / ROWB;           // 16-byte chunks of a row, rows of a 1 KB DMA block
-    constexpr int KS = ROWB / 32;                               // pairs of sub-steps: 64 codes, low and high halves of 32 bytes
+    constexpr int KS = ROWB / 32 / KG;                          // pairs of sub-steps of a wave: 64 codes, low and high halves of 32 bytes
     constexpr int SWZ = CPR == 8 ? 1 : 2;                       // rows that share a swizzle, log2: 256 bytes of LDS
     constexpr int BLOCKS = (BM + BN) / RPB;                     // 1 KB DMA blocks per stage
     constexpr int LD = BLOCKS / NW;                             // tile DMA instructions per wave per K step
@@ -296,7 +301,7 @@ void gemm_olay_kernel(GemmArgs g) {
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
+    const int kg = KG == 1 ? 0 : wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
     const int total = g.tiles_m * g.tiles_n, stride = gridDim.x;
     const int KT = g.K / (2 * ROWB);
 
@@ -321,13 +326,14 @@ void gemm_olay_kernel(GemmArgs g) {
         }
     }
     // Descriptors of a tile: base at the tile origin, size = its valid rows.
-    auto a_desc = [&](int m0) {
+    // (exists == false: no bytes at all, so that the prefetch of a tile that does not exist touches no memory)
+    auto a_desc = [&](int m0, bool exists = true) {
         const int rows = min(BM, g.M - m0);
-        return make_rsrc(g.Aq + (long)m0 * g.lda, (uint32_t)((long)(rows - 1) * g.lda + g.K / 2));
+        return make_rsrc(g.Aq + (long)m0 * g.lda, KG == 1 || exists ? (uint32_t)((long)(rows - 1) * g.lda + g.K / 2) : 0u);
     };
-    auto b_desc = [&](int n0) {
+    auto b_desc = [&](int n0, bool exists = true) {
         const int rows = min(BN, g.N - n0);
-        return make_rsrc(g.Wq + (long)n0 * g.ldw, (uint32_t)((long)rows * g.ldw));
+        return make_rsrc(g.Wq + (long)n0 * g.ldw, KG == 1 || exists ? (uint32_t)((long)rows * g.ldw) : 0u);
     };
     auto dma_one = [&](int i, int stage, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, int so) {
         uint8_t *dst = smem + stage * STAGE + (wave + i * NW) * 1024;
@@ -363,9 +369,9 @@ void gemm_olay_kernel(GemmArgs g) {
     };
 
     // ---- operand fragments -----------------------------------------------------------------------
-    // lane (r = lane&31, h = lane>>5) reads logical chunk ks*2 + h of its row
+    // lane (r = lane&31, h = lane>>5) reads logical chunk (kg*KS + ks)*2 + h of its row
     const int swz = ((lane & 31) >> SWZ) & (CPR - 1);
-    const int rd0 = (lane & 31) * ROWB + (((lane >> 5) ^ swz) << 4);   // ks = 0;  ks is rd0 ^ (32 * ks)
+    const int rd0 = (lane & 31) * ROWB + ((((lane >> 5) | (kg * KS * 2)) ^ swz) << 4);   // ks = 0;  ks is rd0 ^ (32 * ks)
     int frag_off[NF];
 #pragma unroll
     for (int f = 0; f < FM; ++f) frag_off[f] = (wm * FM * 32 + f * 32) * ROWB + rd0;
@@ -402,12 +408,14 @@ void gemm_olay_kernel(GemmArgs g) {
     if (!tile_of(vb, tile)) return;                             // (uniform) nothing to do for this workgroup
     int m0 = (tile / g.tiles_n) * BM, n0 = (tile % g.tiles_n) * BN;
     __amdgpu_buffer_rsrc_t a_cur = a_desc(m0), b_cur = b_desc(n0);
+    if constexpr (KG > 1) dma_params(m0, 0);
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
 #pragma unroll
         for (int i = 0; i < LD; ++i) dma_one(i, s, a_cur, b_cur, s * ROWB);
-    dma_params(m0, 0);
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+    if constexpr (KG == 1) dma_params(m0, 0);
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(KG > 1 ? (NS - 2) * LD : 0));   // with one tile to a workgroup the first K step alone: the others
+                                                                // are waited for where they are read
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     u32x4 P0[NF], P1[NF];
@@ -416,23 +424,24 @@ void gemm_olay_kernel(GemmArgs g) {
     int cur = 0;                                                // LDS stage of the current K step
     int parity = 0;
     for (;;) {
-        // first fragments of the tile (its first NS-1 K steps are in LDS and published)
+        // first fragments of the tile (its first K step is in LDS and published; the NS-2 requested behind it are waited for at the barrier in front of each)
 #pragma unroll
         for (int f = 0; f < NF; ++f) P0[f] = read_frag(f, cur, 0);
         // ---- tile start: C operand of the first MFMAs, channel constants, origin of the next tile -----
         // acc[i][0] = -128 * osum of the rows of fragment row i (accumulator layout: register 4q+rr of
         // lane (c, h) is row 8q + 4h + rr).  The token parameters of this tile were fetched one tile ago.
         {
+            const int osum_by = KG == 1 || kg == 0 ? -128 : 0;  // counted once
             const int *os_lds = reinterpret_cast<const int *>(par + parity * (2 * BM * 4) + BM * 4) + wm * FM * 32 + 4 * (lane >> 5);
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int4 o = *reinterpret_cast<const int4 *>(os_lds + i * 32 + 8 * q);
-                    acc[i][0][4 * q + 0] = __mul24(o.x, -128);
-                    acc[i][0][4 * q + 1] = __mul24(o.y, -128);
-                    acc[i][0][4 * q + 2] = __mul24(o.z, -128);
-                    acc[i][0][4 * q + 3] = __mul24(o.w, -128);
+                    acc[i][0][4 * q + 0] = __mul24(o.x, osum_by);
+                    acc[i][0][4 * q + 1] = __mul24(o.y, osum_by);
+                    acc[i][0][4 * q + 2] = __mul24(o.z, osum_by);
+                    acc[i][0][4 * q + 3] = __mul24(o.w, osum_by);
                 }
         }
         // channel constants of this lane's FN adjacent channels: raw loads now (channels past N read
@@ -457,7 +466,7 @@ void gemm_olay_kernel(GemmArgs g) {
         const bool has_next = tile_of(vb_next, tile_next);
         if (!has_next) tile_next = tile;
         const int m0n = (tile_next / g.tiles_n) * BM, n0n = (tile_next % g.tiles_n) * BN;
-        const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n), b_nxt = b_desc(n0n);
+        const __amdgpu_buffer_rsrc_t a_nxt = a_desc(m0n, has_next), b_nxt = b_desc(n0n, has_next);
 #pragma unroll
         for (int f = 0; f < NF; ++f) U0[f] = widen_lo(f, P0[f]);
 
@@ -483,7 +492,7 @@ void gemm_olay_kernel(GemmArgs g) {
             const int nxt = cur == NS - 1 ? 0 : cur + 1;       // stage of stream step +1
             const int free = cur == 0 ? NS - 1 : cur - 1;      // stage of stream step +NS-1 (= step -1)
             // stream step +NS-1 is K step kt+NS-1 of this tile, or K step kt+NS-1-KT of the next one (when there
-            // is none: a harmless in-bounds re-read, so that the load counting stays uniform)
+            // is none: a harmless in-bounds re-read, or requests that the descriptor turns away, so that the load counting stays uniform)
             const bool own = !LAST && kt + NS - 1 < KT;
             const __amdgpu_buffer_rsrc_t ra = own ? a_cur : a_nxt, rb = own ? b_cur : b_nxt;
             const int so = (own ? kt + NS - 1 : kt + NS - 1 - KT) * ROWB;
@@ -534,6 +543,37 @@ void gemm_olay_kernel(GemmArgs g) {
 #undef W4A4_SLOT_BEGIN
 #undef W4A4_SLOT_BEGIN_FIRST
 
+        // ---- the K groups of a tile: each wave of a pair hands over half of its rows and adds up the others -------------
+        // (every wave has passed the last barrier: nobody reads the stages any more, and no request is under way)
+        if constexpr (KG == 2) {
+            static_assert(FM % 2 == 0 && NW * (FM / 2) * FN * 4096 <= NS * STAGE, "the accumulators go through the stages");
+            constexpr int HM = FM / 2, REG = HM * FN * 4;       // 16-byte registers of half the rows
+            v4i *to = reinterpret_cast<v4i *>(smem) + wave * REG * 64 + lane;
+            const v4i *from = reinterpret_cast<const v4i *>(smem) + (wave ^ (WM * WN)) * REG * 64 + lane;
+            auto give = [&](int first) {
+#pragma unroll
+                for (int x = 0; x < REG; ++x) {
+                    const v16i &a = acc[first + x / 4 / FN][x / 4 % FN];
+                    to[x * 64] = v4i{a[x % 4 * 4], a[x % 4 * 4 + 1], a[x % 4 * 4 + 2], a[x % 4 * 4 + 3]};
+                }
+            };
+            if (kg == 0) {
+                give(HM);
+            } else {
+                give(0);
+#pragma unroll
+                for (int i = 0; i < HM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) acc[i][j] = acc[HM + i][j];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int x = 0; x < REG; ++x) {
+                const v4i v = from[x * 64];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[x / 4 / FN][x / 4 % FN][x % 4 * 4 + r] += v[r];
+            }
+        }
         // ---- epilogue of this tile ------------------------------------------------------------------
         {
             constexpr int ESZ = OUT == OUT_F16 ? 2 : 4;
@@ -547,7 +587,7 @@ void gemm_olay_kernel(GemmArgs g) {
                 cp.bias[j] = __half2float(__ushort_as_half((unsigned short)((j & 1) ? b2 >> 16 : b2 & 0xFFFFu)));
             }
             const float *sa_lds = reinterpret_cast<const float *>(par + parity * (2 * BM * 4));
-            const int row_w = wm * FM * 32;
+            const int row_w = (wm * FM + kg * (FM / KG)) * 32;
             const bool bias = g.bias != nullptr, gelu = g.act == W4A4_ACT_GELU;
             if constexpr (OUT == OUT_Q4 || OUT == OUT_Q4M) {
                 if constexpr (FM == 2 && FN == 4) {
@@ -557,10 +597,10 @@ void gemm_olay_kernel(GemmArgs g) {
                                                                   sa_lds, reinterpret_cast<float *>(par + 2 * 2 * BM * 4));
                 }
             } else
-            if (OUT == OUT_I32 || (!bias && !gelu)) olay_epilogue<FM, FN, OUT, false, false>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
-            else if (bias && !gelu) olay_epilogue<FM, FN, OUT, true, false>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
-            else if (!bias && gelu) olay_epilogue<FM, FN, OUT, false, true>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
-            else olay_epilogue<FM, FN, OUT, true, true>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
+            if (OUT == OUT_I32 || (!bias && !gelu)) olay_epilogue<FM / KG, FN, OUT, false, false>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
+            else if (bias && !gelu) olay_epilogue<FM / KG, FN, OUT, true, false>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
+            else if (!bias && gelu) olay_epilogue<FM / KG, FN, OUT, false, true>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
+            else olay_epilogue<FM / KG, FN, OUT, true, true>(g, acc, cp, col_off, m0, row_w, lane, sa_lds);
         }
         if (!has_next) break;
         vb = vb_next; tile = tile_next; m0 = m0n; n0 = n0n; a_cur = a_nxt; b_cur = b_nxt; parity ^= 1;
@@ -572,13 +612,13 @@ void gemm_olay_kernel(GemmArgs g) {
 // of a row panel wait for each other, so every workgroup of their grid must be resident: the grid is sized from
 // what the runtime reports for this kernel (hipOccupancyMaxActiveBlocksPerMultiprocessor), capped by the
 // occupancy the kernel was compiled for, and a panel's tiles_n tiles must fit into one XCD's share of it.
-template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int OUT>
+template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int KG, int OUT>
 struct OlayLaunch {
-    static constexpr int BM = WM * FM * 32, BN = WN * FN * 32, PER_CU = WPS * 4 / (WM * WN);
+    static constexpr int BM = WM * FM * 32, BN = WN * FN * 32, PER_CU = WPS * 4 / (WM * WN * KG);
     static constexpr size_t lds = NS * (size_t)(BM + BN) * ROWB + 2 * 2 * BM * 4 + (OUT == OUT_Q4 || OUT == OUT_Q4M ? WM * WN * 256 : 0);
     static_assert(lds * PER_CU <= 160 * 1024, "the workgroups of a CU share 160 KB of LDS");
     static KernelState &state() { static KernelState ks; return ks; }
-    static auto kernel() { return gemm_olay_kernel<FM, FN, WM, WN, WPS, ROWB, NS, OUT>; }
+    static auto kernel() { return gemm_olay_kernel<FM, FN, WM, WN, WPS, ROWB, NS, KG, OUT>; }
     // resident workgroups on the current device (-1: HIP error)
     static int slots() {
         const int cus = prepare_kernel(reinterpret_cast<const void *>(kernel()), lds, state());
@@ -590,9 +630,9 @@ struct OlayLaunch {
     }
 };
 
-template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int OUT>
+template <int FM, int FN, int WM, int WN, int WPS, int ROWB, int NS, int KG, int OUT>
 static int launch_one(GemmArgs &g, hipStream_t st) {
-    using L = OlayLaunch<FM, FN, WM, WN, WPS, ROWB, NS, OUT>;
+    using L = OlayLaunch<FM, FN, WM, WN, WPS, ROWB, NS, KG, OUT>;
     g.tiles_m = (g.M + L::BM - 1) / L::BM;
     g.tiles_n = (g.N + L::BN - 1) / L::BN;
     const int slots = L::slots();
@@ -608,8 +648,8 @@ static int launch_one(GemmArgs &g, hipStream_t st) {
         if (g.tiles_n > (int)(grid / kXcd)) return W4A4_ERR_UNSUPPORTED_SHAPE;
         if (g.wait_for == 0) g.wait_for = g.tiles_n;
     }
-    if (grid == 0) return W4A4_ERR_UNSUPPORTED_SHAPE;
-    launch_gemm(L::kernel(), dim3(grid), dim3(WM * WN * 64), L::lds, st, g);
+    if (grid == 0 || (KG > 1 && grid < tiles)) return W4A4_ERR_UNSUPPORTED_SHAPE;
+    launch_gemm(L::kernel(), dim3(grid), dim3(WM * WN * KG * 64), L::lds, st, g);
     return launch_status();
 }
 
@@ -617,11 +657,11 @@ static int launch_one(GemmArgs &g, hipStream_t st) {
 bool olay_whole_lines(int K) { return K % 256 == 0 && K >= 512; }
 
 template <int OUT>
-using Olay128x256 = OlayLaunch<2, 4, 2, 2, 2, 64, 3, OUT>;
+using Olay128x256 = OlayLaunch<2, 4, 2, 2, 2, 64, 3, 1, OUT>;
 template <int OUT>
-static int launch_128x256(GemmArgs &g, hipStream_t st) { return launch_one<2, 4, 2, 2, 2, 64, 3, OUT>(g, st); }
+static int launch_128x256(GemmArgs &g, hipStream_t st) { return launch_one<2, 4, 2, 2, 2, 64, 3, 1, OUT>(g, st); }
 template <int OUT>
-static int launch_256x256_lines(GemmArgs &g, hipStream_t st) { return launch_one<2, 4, 4, 2, 2, 128, 2, OUT>(g, st); }
+static int launch_256x256_lines(GemmArgs &g, hipStream_t st) { return launch_one<2, 4, 4, 2, 2, 128, 2, 1, OUT>(g, st); }
 
 // Column tiles of a row panel that the fused requantize of the persistent kernel can keep co-resident on the
 // current device (0 = the kernel does not fit, -1 = HIP error): the limit on ceil(N / 256).
@@ -635,20 +675,25 @@ static int launch_variant(int variant, GemmArgs &g, hipStream_t st) {
     const bool lines = olay_whole_lines(g.K);
     switch (variant) {
         case 0: return launch_128x256<OUT>(g, st);                  // two workgroups per CU
-        case 1: return launch_one<3, 2, 2, 2, 2, 64, 3, OUT>(g, st);   // 192 x 128, two workgroups per CU
-        case 2:                                                     // 128 x 128, two or three workgroups per CU
+        case 1: return launch_one<3, 2, 2, 2, 2, 64, 3, 1, OUT>(g, st);   // 192 x 128, two workgroups per CU
+        case 2: {                                                   // 128 x 128, two or three workgroups per CU
             // whole lines leave two stages, i.e. one step of prefetch, too little for a tile that is alone on its CU
             // (4096 x 1024 x 4096 with its quantizer 25.7 us against 24.9, 3000 x 1024 x 1024 14.0 | 11.8)
-            return lines && (long)((g.M + 127) / 128) * ((g.N + 127) / 128) > device_cus()
-                       ? launch_one<2, 2, 2, 2, 2, 128, 2, OUT>(g, st) : launch_one<2, 2, 2, 2, 3, 64, 3, OUT>(g, st);
+            const bool alone = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) <= device_cus();
+            // Alone on its CU it has room for eight waves, half of K each.  What that saves, 0.2 us per 256 codes, has to pay for
+            // the longer way to the first operands and for the sums handed over (half lines | this: 3339 x 1024 x 768 6.5 | 6.8 us, x 1024
+            // 7.35 | 7.48, x 1280 8.31 | 8.24, x 1536 9.13 | 9.00, x 2048 10.85 | 10.25, x 4096 17.7 | 15.3; 2048 x 1024 x 4096 16.6 | 14.1).
+            if (lines && alone && g.K >= 1280) return launch_one<2, 2, 2, 2, 2, 128, 3, 2, OUT>(g, st);
+            return lines && !alone ? launch_one<2, 2, 2, 2, 2, 128, 2, 1, OUT>(g, st) : launch_one<2, 2, 2, 2, 3, 64, 3, 1, OUT>(g, st);
+        }
         case 3:                                                     // 256 x 256, one workgroup of eight waves per CU
-            return lines ? launch_256x256_lines<OUT>(g, st) : launch_one<2, 4, 4, 2, 2, 64, 3, OUT>(g, st);
+            return lines ? launch_256x256_lines<OUT>(g, st) : launch_one<2, 4, 4, 2, 2, 64, 3, 1, OUT>(g, st);
         default: return W4A4_ERR_INVALID_ARG;
     }
 }
 
 static int requant_slots_256x256(int out_kind) {
-    return out_kind == OUT_Q4M ? OlayLaunch<2, 4, 4, 2, 2, 128, 2, OUT_Q4M>::slots() : OlayLaunch<2, 4, 4, 2, 2, 128, 2, OUT_Q4>::slots();
+    return out_kind == OUT_Q4M ? OlayLaunch<2, 4, 4, 2, 2, 128, 2, 1, OUT_Q4M>::slots() : OlayLaunch<2, 4, 4, 2, 2, 128, 2, 1, OUT_Q4>::slots();
 }
 // Whether a requantizing output can take the 256 x 256 tile at all.
 bool olay_requant_256x256_ok(int N, int K, int out_kind) {

@@ -163,3 +163,23 @@ def test_tiles_of_64_by_64(B, mode, K, M, N):
         Q = B.quantize_weight(W[:N].contiguous(), mode)
         r = [B.linear(A, Q, bias[:N].contiguous(), 0, requant=True, requant_mode=1, schedule=s) for s in (tile, general)]
         assert torch.equal(r[0].q, r[1].q) and torch.equal(r[0].scale, r[1].scale) and torch.equal(r[0].zero, r[1].zero)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 8, 1280), (129, 136, 1536), (300, 1032, 1280), (257, 264, 4096), (2048, 2048, 2048)])
+def test_operand_layout_tile_shared_by_two_groups_of_waves(B, M, N, K):
+    """128 x 128 tiles of the operand layout with a CU each and long K, where two groups of waves share the codes of a step: sums and
+    fp16 rows (without and with GELU) bit for bit those of 128 x 256 tiles, at the largest sums too; nothing behind the last row."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    X = torch.randn((M, K), device="cuda", generator=g).half()
+    W = (torch.randn((N, K), device="cuda", generator=g) * 0.02).half()
+    X[M // 2] = 3.0                                                # a row and a channel of nothing but the largest code
+    W[N // 2] = -0.5
+    bias = (torch.randn(N, device="cuda", generator=g) * 0.01).half()
+    A, Q = B.quantize_act(X, 0, layout=1), B.quantize_weight(W, 0, layout=1)
+    tile, other = B.schedule_number("olay_128x128"), B.schedule_number("olay_128x256")
+    assert torch.equal(B.gemm_i32(A, Q, schedule=tile), B.gemm_i32(A, Q, schedule=other))
+    for b, act in ((None, 0), (bias, 1)):
+        want = B.linear(A, Q, b, act, schedule=other)
+        got = torch.full((M + 2, N), 7.0, dtype=torch.float16, device="cuda")
+        B.linear(A, Q, b, act, schedule=tile, out=(got[:M], None, None, None))
+        assert torch.equal(got[:M].view(torch.int16), want.view(torch.int16)) and (got[M:] == 7.0).all()
