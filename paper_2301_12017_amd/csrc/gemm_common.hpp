@@ -460,6 +460,7 @@ int launch_pipe(int variant, int out_kind, GemmArgs &g, hipStream_t st);
 int launch_olay(int variant, int out_kind, GemmArgs &g, hipStream_t st);
 int launch_fp6(int variant, int out_kind, GemmArgs &g, hipStream_t st);
 int launch_group(int mode, int out_kind, GemmArgs &g, hipStream_t st);
+int launch_group_olay(int out_kind, GemmArgs &g, hipStream_t st);
 int launch_small_packed(int mode, int out_kind, GemmArgs &g, hipStream_t st);
 int launch_mid(int variant, int mode, int out_kind, GemmArgs &g, hipStream_t st);
 int device_cus();                                               // gemm.hip
@@ -476,7 +477,8 @@ inline size_t group_lds(int ng, bool tables, bool olay, bool lines) {
 }
 // Operand layout, groups of several K steps: K and the groups in pairs of K steps
 inline bool group_lines_ok(int K, int ng) { return K / ng % 256 == 0; }
-// ... groups of one K step: the tables may be read from memory, eight groups a turn.  As LDS holds those of 28 groups, that is K = 4096
+// ... groups of one K step: more groups than the 28 whose tables LDS holds, K = 4096 (gemm_group_olay.hip reads them from memory;
+// 16384 x 1024 x 4096 229 us on the general kernel, the only other one that takes so many, 89 with the tables read in the epilogue)
 inline bool group_memtab_ok(int K, int ng) { return K / ng == 128 && ng % 8 == 0 && K <= 4096; }
 
 constexpr int kFp6FewTokens = 4;                                 // gemm_fp6.hip: the variant whose waves split K

@@ -27,15 +27,15 @@
 // Symmetric grouped layers run here too (signed codes are widened to 16*code, so the sums carry
 // a factor 256 that the group scale absorbs exactly).
 //
-// OLAY = true is the same kernel on unsigned codes kept in the MFMA operand layout (see w4a4_layout), built to
-// take vector-ALU work out of it:
+// OLAY = true is the same kernel on unsigned codes kept in the MFMA operand layout (see w4a4_layout; five groups of one K step and
+// more run in gemm_group_olay.hip), built to take vector-ALU work out of it:
 //   * one v_and per operand register instead of a shift and a mask (activations: low nibble u, high nibble
 //     u - 8; weights: nibbles swapped).  A group's accumulator then holds 16*(P_g - 8*AE[m,g] - 8*WO[n,g]) with AE
 //     the token's even-position code sum and WO the channel's odd-position code sum of the group.  The token term
 //     costs nothing: 128*AE[m,g] arrives with the group's K step in LDS (one 4-byte DMA per row, the array is kept
 //     group-major for that) and is the C operand of the group's first MFMAs, shared by the column fragments.  The
 //     channel term is a constant per channel over all groups, 8 * sum_g sw[n,g]*WO[n,g], precomputed with the
-//     weights; the fp32 accumulators start from it (with the tables in memory, 32 groups, it comes last).
+//     weights; the fp32 accumulators start from it.
 //   * the fold is a conversion and ONE fused multiply-add per accumulator and group,
 //     t1 = fma(sw[n,g]/16, (float)acc, t1), and the zero-point sum, the token scale, the zero-point product and
 //     the bias are fused multiply-adds as well:  y = fma(sa, fma-chain(zw[n,g], RA[m,g], t1), fma(za, c[n], b[n])).
@@ -52,16 +52,15 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 // s_waitcnt immediate for "vmcnt <= n", lgkmcnt and expcnt unconstrained (gfx9 encoding)
 static constexpr int vmcnt_only(int n) { return (n & 0xF) | (0x7 << 4) | (0xF << 8) | (((n >> 4) & 0x3) << 14); }
 
-// LINES (OLAY): rows of 128 bytes, whole cache lines, i.e. two K steps per LDS stage and DMA; two stages.  MEMTAB (OLAY): the
-// zero-point tables are read from memory in the epilogue.
-template <int MODE, int OUT, bool OLAY, bool SPG1, bool LINES, bool MEMTAB>
+// LINES (OLAY): rows of 128 bytes, whole cache lines, i.e. two K steps per LDS stage and DMA; two stages.
+template <int MODE, int OUT, bool OLAY, bool SPG1, bool LINES>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void gemm_group_kernel(GemmArgs g) {
     static_assert(!OLAY || MODE == W4A4_ASYM, "the symmetric operand layout has its own kernel");
     constexpr bool SGN = MODE == W4A4_SYM;
     constexpr int FM = 2, FN = 2, WM = 2, WN = 2;
     constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
-    static_assert(OLAY || (!LINES && !MEMTAB), "canonical codes take half lines and LDS tables");
+    static_assert(OLAY || !LINES, "canonical codes take half lines");
     static_assert(!SPG1 || !LINES, "groups of one K step take half lines");
     constexpr int STEPB = kBK / 2;                              // 64 bytes of codes per row per K step
     constexpr int SPS = LINES ? 2 : 1, ROWB = SPS * STEPB;      // K steps per stage
@@ -161,7 +160,7 @@ void gemm_group_kernel(GemmArgs g) {
     // tile's 128 rows of [.., ng] are one contiguous piece of memory and are copied as they lie (group by group, a
     // DMA instruction's 64 lanes touched 64 cache lines); else piece grp is group grp.
     auto dma_table = [&](int m0, int n0, int grp) {
-        if constexpr (MODE == W4A4_ASYM && !MEMTAB) {
+        if constexpr (MODE == W4A4_ASYM) {
             const int half = wave & 1;
             const int row0 = wave < 2 ? n0 : m0;
             const int src = OLAY ? row0 * g.ng + grp * 128 + half * 64 + lane : (row0 + half * 64 + lane) * g.ng + grp;
@@ -264,7 +263,7 @@ void gemm_group_kernel(GemmArgs g) {
             for (int j = 0; j < FN; ++j)
                 kw_raw[j] = __builtin_amdgcn_raw_buffer_load_b32(wo_rsrc, ((n_lane + j) * (g.ng + 1) + g.ng) * 4, 0, 0);
         };
-        if constexpr (OLAY && !MEMTAB) request_kw();
+        if constexpr (OLAY) request_kw();
         const int vb_next = vb + stride;
         const bool has_next = vb_next < total;
         const int tile_next = xcd_tile(has_next ? vb_next : vb, total);
@@ -277,7 +276,7 @@ void gemm_group_kernel(GemmArgs g) {
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) facc[i][j][r] = OLAY && !MEMTAB ? __uint_as_float(kw_raw[j]) : 0.0f;
+                for (int r = 0; r < 16; ++r) facc[i][j][r] = OLAY ? __uint_as_float(kw_raw[j]) : 0.0f;
 
         // ---- main loop ---------------------------------------------------------------------------------
 #define W4A4_SLOT_BEGIN(Ucur, k)                                                                          \
@@ -335,7 +334,7 @@ void gemm_group_kernel(GemmArgs g) {
             constexpr int Q = decltype(q_tag)::value;
             constexpr bool ODD = LINES && decltype(odd_tag)::value, EVEN = LINES && !ODD;
             constexpr int KS0 = ODD ? 2 : 0;                    // first 64 codes of the step in its stage
-            constexpr int BEHIND = (MODE == W4A4_ASYM && !MEMTAB ? 1 : 0) + (OUT == OUT_I32 || Q > 0 || Q == kFinal ? 0 : FN);   // requests behind the tile DMAs of a group's first step
+            constexpr int BEHIND = (MODE == W4A4_ASYM ? 1 : 0) + (OUT == OUT_I32 || Q > 0 || Q == kFinal ? 0 : FN);   // requests behind the tile DMAs of a group's first step
             constexpr bool FOG = decltype(fog_tag)::value;     // first K step of a weight group
             constexpr bool LAST = decltype(last_tag)::value;   // last K step of the tile
             const int nxt = cur == NS - 1 ? 0 : cur + 1;       // stage of stream step +1
@@ -531,38 +530,7 @@ void gemm_group_kernel(GemmArgs g) {
             const float cv[FN] = {__uint_as_float(c_raw[0]), __uint_as_float(c_raw[1])};
             const float bv[FN] = {__half2float(__ushort_as_half((unsigned short)(bias_raw & 0xFFFFu))),
                                   __half2float(__ushort_as_half((unsigned short)(bias_raw >> 16)))};
-            if constexpr (MEMTAB) {
-                // as below, from memory: a lane takes four consecutive groups per request (lanes 0-31 groups 8t .. 8t+3, lanes
-                // 32-63 8t+4 .. 8t+7: ng is a multiple of 8).  With so many groups the order of the sum decides its rounding noise:
-                // the groups' sums (half of t1), the zero-point sum (minus t1, nearly) and what the layout's offsets add (the other
-                // half) in this order keep the partial sums at half of t1, where starting from the offsets takes them up to t1.
-                // Error against float64, K = 4096 in 32 groups: canonical kernel 4.11e-4, from the offsets 4.51e-4, so 2.92e-4; times unchanged
-                // (16384 x 1024 x 4096 86 | 86 us, 2048 x 1024 x 4096 27 | 27).
-                request_kw();
-                const uint32_t g0 = (uint32_t)(lane >> 5) * 16u;
-                for (int t = 0; t * 8 < g.ng; ++t) {
-                    u32x4 ra4[FM], zw4[FN];
-#pragma unroll
-                    for (int i = 0; i < FM; ++i)
-                        ra4[i] = __builtin_amdgcn_raw_buffer_load_b128(ra_rsrc, (uint32_t)(m0 + row_w + i * 32 + (lane & 31)) * (uint32_t)g.ng * 4u + g0, t * 32, 0);
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-                        zw4[j] = __builtin_amdgcn_raw_buffer_load_b128(zw_rsrc, (uint32_t)(n_lane + j) * (uint32_t)g.ng * 4u + g0, t * 32, 0);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int i = 0; i < FM; ++i)
-#pragma unroll
-                            for (int j = 0; j < FN; ++j)
-                                facc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32((float)(int)ra4[i][u], __uint_as_float(zw4[j][u]), facc[i][j], 0, 0, 0);
-                }
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) facc[i][j][r] = facc[i][j][r] + __uint_as_float(kw_raw[j]);
-            } else if constexpr (OLAY) {
+            if constexpr (OLAY) {
                 // sum_g zw[n,g] * RA[m,g]: a rank-ng product of the tile's two group tables, continued into the fp32
                 // accumulators by the fp32 MFMA, two groups per instruction (lanes 0-31 carry group gp, lanes 32-63
                 // group gp + 1; a missing last group contributes zeros)
@@ -666,20 +634,20 @@ void gemm_group_kernel(GemmArgs g) {
                 }
         }
         if (!has_next) break;
-        if constexpr (MODE == W4A4_ASYM && !MEMTAB) __syncthreads();   // the group tables are single: every wave is done reading them
+        if constexpr (MODE == W4A4_ASYM) __syncthreads();   // the group tables are single: every wave is done reading them
         vb = vb_next; tile = tile_next; m0 = m0n; n0 = n0n; a_cur = a_nxt; b_cur = b_nxt; parity ^= 1;
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_only(0));                  // no DMA may outlive the workgroup's LDS
 }
 
-template <int MODE, int OUT, bool OLAY, bool SPG1, bool LINES, bool MEMTAB>
+template <int MODE, int OUT, bool OLAY, bool SPG1, bool LINES>
 static int launch_kernel(GemmArgs &g, hipStream_t st) {
     constexpr int BM = 128, BN = 128;
-    const size_t lds = group_lds(g.ng, MODE == W4A4_ASYM && !MEMTAB, OLAY, LINES);
+    const size_t lds = group_lds(g.ng, MODE == W4A4_ASYM, OLAY, LINES);
     if (lds > kGroupLds) return W4A4_ERR_UNSUPPORTED_SHAPE;       // the group tables do not fit beside two workgroups' stages
     g.tiles_m = (g.M + BM - 1) / BM;
     g.tiles_n = (g.N + BN - 1) / BN;
-    auto kern = gemm_group_kernel<MODE, OUT, OLAY, SPG1, LINES, MEMTAB>;
+    auto kern = gemm_group_kernel<MODE, OUT, OLAY, SPG1, LINES>;
     static KernelState ks;
     const int cus = prepare_kernel(reinterpret_cast<const void *>(kern), lds, ks);
     if (cus < 0) return W4A4_ERR_HIP;
@@ -695,18 +663,13 @@ static int launch_kernel(GemmArgs &g, hipStream_t st) {
 // K steps and the tables fit beside them: asymmetric per-channel, 16384 x 4096 x 1024 + GELU 94.7 -> 91.6 us, 16384 x 1024 x
 // 4096 61.9 -> 57.9, 16384 x 768 x 3072 36.8 -> 34.5; the four linears at 2048 tokens of 1024 70.2 -> 67.1.  Groups of one K
 // step do not (16384 x 3072 x 768 + GELU 82.0 | 87.3 with whole lines, K = 3072 the same: the fold leaves no registers for the
-// second half's addresses, and it has the time to wait for half lines).  Their tables stay in LDS where they fit; more than
-// 28 groups (K = 4096 in groups of 128) read them from memory in the epilogue: 16384 x 1024 x 4096 229 us on the general
-// kernel, the only other one that takes so many groups, 89 here; 2048 x 1024 x 4096 39 | 30.
+// second half's addresses, and it has the time to wait for half lines); five of them and more have a kernel of their own.
 template <int MODE, int OUT, bool OLAY, bool SPG1>
 static int launch_spg(GemmArgs &g, hipStream_t st) {
     if constexpr (OLAY && !SPG1) {
-        if (group_lines_ok(g.K, g.ng) && group_lds(g.ng, true, true, true) <= kGroupLds) return launch_kernel<MODE, OUT, true, false, true, false>(g, st);
+        if (group_lines_ok(g.K, g.ng) && group_lds(g.ng, true, true, true) <= kGroupLds) return launch_kernel<MODE, OUT, true, false, true>(g, st);
     }
-    if constexpr (OLAY && SPG1) {
-        if (group_lds(g.ng, true, true, false) > kGroupLds && group_memtab_ok(g.K, g.ng)) return launch_kernel<MODE, OUT, true, true, false, true>(g, st);
-    }
-    return launch_kernel<MODE, OUT, OLAY, SPG1, false, false>(g, st);
+    return launch_kernel<MODE, OUT, OLAY, SPG1, false>(g, st);
 }
 
 template <int MODE, int OUT, bool OLAY>
@@ -728,6 +691,8 @@ int launch_group(int mode, int out_kind, GemmArgs &g, hipStream_t st) {
             default: return W4A4_ERR_INVALID_ARG;
         }
     }
+    // five groups of one K step and more: times of both at the kernel
+    if (olay && g.steps_per_group == 1 && g.K >= 640) return launch_group_olay(out_kind, g, st);
     if (olay) {
         switch (out_kind) {
             case OUT_F16: return launch_one<W4A4_ASYM, OUT_F16, true>(g, st);

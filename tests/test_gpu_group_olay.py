@@ -195,3 +195,31 @@ def test_many_groups_lose_no_precision(B, orc, seed):
     e_gpu, e_orc = (np.sqrt(np.mean((v.astype(np.float64) - truth) ** 2))
                     for v in (host(B.linear(A, Q, dev(b), 0)), orc.linear(a, w, ASYM, group, b, 0)["out"]))
     assert e_gpu <= e_orc, (e_gpu, e_orc)
+
+
+@pytest.mark.parametrize("ng", [4, 5, 6, 7, 8, 9, 12, 13, 28, 32])   # a kernel for up to four groups and one for more, whose loop takes four
+@pytest.mark.parametrize("M,N", [(1, 8), (130, 264)])
+def test_groups_of_128(B, orc, ng, M, N):
+    """Every remainder of the groups that are left behind a quad: planes exact, fp16 outputs no further from the float64 evaluation
+    than the oracle's fp32 order, fp32 outputs (the ranges of a requantized row) the same to a step of fp16."""
+    K = 128 * ng
+    rng = np.random.default_rng(ng + M)
+    A, Q, a, w = _layer(B, orc, rng, M, N, K, 128)
+    assert B.pick_schedule(A, Q) == "group_128x128"
+    assert np.array_equal(host(B.gemm_i32(A, Q)), orc.gemm_i32(a["q"], w["q"], ASYM, 128))
+    b = (rng.standard_normal(N) * 0.01).astype(np.float16)
+    for act in (0, 1):
+        want = orc.linear(a, w, ASYM, 128, b, act)["out"]
+        got = host(B.linear(A, Q, dev(b), act))
+        ok, ratio = f16_close_budget(got, want, asym_budget(orc, a, w, 128))
+        assert ok, ratio
+        truth = orc.truth64(a, w, ASYM, b, act)
+        rms = [np.sqrt(np.mean((x.astype(np.float64) - truth) ** 2)) for x in (got, want)]
+        assert rms[0] <= 1.5 * rms[1] + 1e-7, rms
+    if N % 32 == 0 or N == 264:
+        n = N // 32 * 32
+        Qn = B.quantize_weight(dev(_w(np.random.default_rng(3), n, K)), ASYM, 128, layout=MFMA)
+        y = host(B.linear(A, Qn, None, 0)).astype(np.float64)
+        r = B.linear(A, Qn, None, 0, requant=True, requant_mode=ASYM)
+        span = (y.max(axis=1) - y.min(axis=1)) / 15.0
+        assert np.allclose(host(r.scale), span, rtol=4e-3)
