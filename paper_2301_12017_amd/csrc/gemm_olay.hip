@@ -301,7 +301,7 @@ void gemm_olay_kernel(GemmArgs g) {
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = KG == 1 ? 0 : wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+    const int kg = KG == 1 ? 0 : wave / (WM * WN), wm = KG == 1 ? wave / WN : wave % (WM * WN) / WN, wn = wave % WN;
     const int total = g.tiles_m * g.tiles_n, stride = gridDim.x;
     const int KT = g.K / (2 * ROWB);
 
