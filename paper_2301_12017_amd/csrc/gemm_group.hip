@@ -19,7 +19,7 @@
 //     requests decide as much as the vector ALU: one whose 64 lanes touch 32 or 64 cache lines occupies the memory
 //     path of the CU for as many cycles, and one issued in front of a K step's tile DMAs is waited for at its barrier.
 //     Tables as they lie in memory, spread over the K steps, and scales behind the DMAs, four groups per request, one
-//     launch behind the other: 16384 x 768 x 3072 (24 groups) 62 -> 53 us, 2048 x 768 x 3072 27 -> 23, 16384 x 768 x 768
+//     launch behind the other (operand layout, when this kernel ran all its groups of 128): 16384 x 768 x 3072 (24 groups) 62 -> 53 us, 2048 x 768 x 3072 27 -> 23, 16384 x 768 x 768
 //     (6 groups) 19 -> 18, 16384 x 3072 x 768 + GELU 73.5 -> 72; canonical codes, 16384 x 768 x 3072: 81 -> 79 asymmetric,
 //     55 -> 49 symmetric (83 and 54 with one group per request, which takes 40 registers less);
 //   * 128 x 128 tiles, four waves of 64 x 64 (64 integer + 64 fp32 accumulators per lane), two
