@@ -475,11 +475,6 @@ constexpr size_t kGroupLds = 80 * 1024;
 inline size_t group_lds(int ng, bool tables, bool olay, bool lines) {
     return (lines ? 4 : 3) * (size_t)(256 * 64) + (olay ? (lines ? 2 : 3) * 512 : 0) + 2048 + (tables ? (size_t)ng * 256 * 4 : 0);
 }
-// Rows of ng group constants are fetched `width` groups to a request.  First group of the request that brings group grp0 and those
-// behind it: with fewer than `width` left, the row's last ones, because a request past the end of the last row is one past the end of the array:
-// the range check is for the vector offset, and the group stands in the scalar one.  width <= ng.
-__host__ __device__ constexpr int request_first(int grp0, int ng, int width) { return grp0 + width <= ng ? grp0 : ng - width; }
-
 // Operand layout, groups of several K steps: K and the groups in pairs of K steps
 inline bool group_lines_ok(int K, int ng) { return K / ng % 256 == 0; }
 // ... groups of one K step: more groups than the 28 whose tables LDS holds, K = 4096 (gemm_group_olay.hip reads them from memory;

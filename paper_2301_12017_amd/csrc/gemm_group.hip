@@ -303,8 +303,8 @@ void gemm_group_kernel(GemmArgs g) {
     __builtin_amdgcn_sched_barrier(0);
         constexpr int kBarSlot = NM - NF;
         // Weight scales of this lane's channels: the current group's (swg) and those requested ahead, four groups at a time
-        // in layers of five groups and more (one request costs the same 32 cache lines as for one group; behind the last whole
-        // quad the row's last four), else one.  They are requested BEHIND a K step's tile DMAs and needed one K step later at the earliest: in front of
+        // while a whole quad of groups lies ahead (one request costs the same 32 cache lines as for one group), else
+        // one.  They are requested BEHIND a K step's tile DMAs and needed one K step later at the earliest: in front of
         // them, the barrier of that K step, which waits for everything older than its own DMAs, exposed their latency.
         float swg[FN], swn[FN];
         u32x4 quad[FN], quad_n[FN];
@@ -313,19 +313,13 @@ void gemm_group_kernel(GemmArgs g) {
             for (int j = 0; j < FN; ++j) one[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sw_rsrc, (n_lane + j) * g.ng * 4, grp0 * 4, 0));
         };
         auto request_quad = [&](int grp0, u32x4 (&four)[FN]) {
-            const int first = request_first(grp0, g.ng, 4);
 #pragma unroll
-            for (int j = 0; j < FN; ++j) four[j] = __builtin_amdgcn_raw_buffer_load_b128(sw_rsrc, (n_lane + j) * g.ng * 4, first * 4, 0);
-        };
-        auto request_first_scales = [&]() {                     // of up to four groups, which are fetched one by one
-#pragma unroll
-            for (int j = 0; j < FN; ++j) quad[j] = u32x4{__builtin_amdgcn_raw_buffer_load_b32(sw_rsrc, (n_lane + j) * g.ng * 4, 0, 0), 0u, 0u, 0u};
+            for (int j = 0; j < FN; ++j) four[j] = __builtin_amdgcn_raw_buffer_load_b128(sw_rsrc, (n_lane + j) * g.ng * 4, grp0 * 4, 0);
         };
         constexpr bool QUADS = SPG1 && OUT != OUT_I32;
         constexpr int kFinal = -2;
-        if constexpr (!QUADS) request_scales(0, swn);
-        else if (KT > 4) request_quad(0, quad);
-        else request_first_scales();
+        if constexpr (QUADS) request_quad(0, quad);
+        else request_scales(0, swn);
         int wog[FN] = {0, 0};                                   // OLAY, int32 export: its odd-position code sums
         int grp = 0;                                            // index of the current weight group
         // LINES: ODD steps read the second half of their stage and request nothing; an even step requests the next stage (whose group
@@ -481,9 +475,8 @@ void gemm_group_kernel(GemmArgs g) {
 #pragma unroll
                         for (int j = 0; j < FN; ++j) quad[j] = quad_n[j];
                     }
-                    const int at = KT > 4 ? kt - request_first(kt, g.ng, 4) : 0;   // place of the next group's
 #pragma unroll
-                    for (int j = 0; j < FN; ++j) swn[j] = __uint_as_float(at == 0 ? quad[j][0] : at == 1 ? quad[j][1] : at == 2 ? quad[j][2] : quad[j][3]);
+                    for (int j = 0; j < FN; ++j) swn[j] = __uint_as_float(quad[j][0]);
                 }
                 while (kt < KT - 1) step_and_fold(single);
                 k_step(yes, yes, final_group, kt, no);

@@ -195,24 +195,16 @@ void gemm_group_olay_kernel(GemmArgs g) {
         u32x4 quad[FN];
         float held[FN][2];
         u32x2 zw2[FN], ra2[FM];
-        auto request_quad = [&](int grp0) __attribute__((always_inline)) {     // (fewer than four left: the row's last four)
-            const int first = request_first(grp0, g.ng, 4);
+        auto request_quad = [&](int grp0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j) quad[j] = __builtin_amdgcn_raw_buffer_load_b128(sw_rsrc, (n_lane + j) * g.ng * 4, first * 4, 0);
+            for (int j = 0; j < FN; ++j) quad[j] = __builtin_amdgcn_raw_buffer_load_b128(sw_rsrc, (n_lane + j) * g.ng * 4, grp0 * 4, 0);
         };
-        auto request_zero_points = [&](int grp0) __attribute__((always_inline)) {     // four groups that are there
+        auto request_zero_points = [&](int grp0) __attribute__((always_inline)) {
             const int two = (lane >> 5) * 8;
 #pragma unroll
             for (int j = 0; j < FN; ++j) zw2[j] = __builtin_amdgcn_raw_buffer_load_b64(zw_rsrc, (n_lane + j) * g.ng * 4 + two, grp0 * 4, 0);
 #pragma unroll
             for (int i = 0; i < FM; ++i) ra2[i] = __builtin_amdgcn_raw_buffer_load_b64(ra_rsrc, (m0 + wm * FM * 32 + i * 32 + (lane & 31)) * g.ng * 4 + two, grp0 * 4, 0);
-        };
-        auto request_zero_points_left = [&](int grp0) __attribute__((always_inline)) {     // one to four: a lane whose two are not there reads the row's last two
-            const int first = request_first(grp0 + (lane >> 5) * 2, g.ng, 2);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) zw2[j] = __builtin_amdgcn_raw_buffer_load_b64(zw_rsrc, ((n_lane + j) * g.ng + first) * 4, 0, 0);
-#pragma unroll
-            for (int i = 0; i < FM; ++i) ra2[i] = __builtin_amdgcn_raw_buffer_load_b64(ra_rsrc, ((m0 + wm * FM * 32 + i * 32 + (lane & 31)) * g.ng + first) * 4, 0, 0);
         };
         auto add_zero_points = [&](int k, int u) __attribute__((always_inline)) {
             facc[k / FN][k % FN] = __builtin_amdgcn_mfma_f32_32x32x2f32((float)(int)ra2[k / FN][u], __uint_as_float(zw2[k % FN][u]), facc[k / FN][k % FN], 0, 0, 0);
@@ -314,16 +306,9 @@ void gemm_group_olay_kernel(GemmArgs g) {
                 k_step(std::integral_constant<int, 3>{}, kt + 3);
                 kt += 4;
             } while (kt + 4 <= KT);
-            // of the one to four groups that are left
-            const int shift = kt - 1 - request_first(kt - 1, g.ng, 4);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                if (shift & 1) quad[j] = u32x4{quad[j][1], quad[j][2], quad[j][3], 0u};
-                if (shift & 2) quad[j] = u32x4{quad[j][2], quad[j][3], 0u, 0u};
-            }
-            request_zero_points_left(kt - 1);
+            request_zero_points(kt - 1);                        // of the one to four groups that are left
         }
-        [[maybe_unused]] const int left0 = kt - 1;              // the first of them
+        const int rest = KT - (kt - 1);
         for (; kt < KT; ++kt) {
             k_step(std::integral_constant<int, kTail>{}, kt);
             if constexpr (OUT == OUT_I32) export_group(kt);
@@ -352,14 +337,15 @@ void gemm_group_olay_kernel(GemmArgs g) {
             const float cv[FN] = {__uint_as_float(c_raw[0]), __uint_as_float(c_raw[1])};
             const float bv[FN] = {__half2float(__ushort_as_half((unsigned short)(bias_raw & 0xFFFFu))),
                                   __half2float(__ushort_as_half((unsigned short)(bias_raw >> 16)))};
-            // the zero points of the groups behind the last quad, this lane's two in their places, zeros for those that are not there
-            const int mine = left0 + (lane >> 5) * 2, skip = mine - request_first(mine, g.ng, 2);
-            const uint32_t as_is = skip == 0 ? ~0u : 0u, second = skip == 1 ? ~0u : 0u;      // (no branch)
-            auto place = [&](u32x2 &v) { v = u32x2{(v[0] & as_is) | (v[1] & second), v[1] & as_is}; };
+            // the zero points of the groups behind the last quad; what lies past the last group belongs to another row
 #pragma unroll
-            for (int i = 0; i < FM; ++i) place(ra2[i]);
+            for (int u = 0; u < 2; ++u) {
+                const bool live = (lane >> 5) * 2 + u < rest;
 #pragma unroll
-            for (int j = 0; j < FN; ++j) place(zw2[j]);
+                for (int i = 0; i < FM; ++i) ra2[i][u] = live ? ra2[i][u] : 0u;
+#pragma unroll
+                for (int j = 0; j < FN; ++j) zw2[j][u] = live ? zw2[j][u] : 0u;
+            }
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll

@@ -155,31 +155,3 @@ def test_the_search_for_early_reads_finds_them():
                    "v_mov_b32_dpp v1, v82 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"):
         assert _early_reads([*asm, "\ts_nop 0", "\t" + reader]) and not _early_reads([*asm, "\ts_nop 1", "\t" + reader])
     assert not _early_reads([*asm, "\tv_mul_f32_e32 v1, v82, v82"])
-
-
-def test_requests_for_group_constants_stay_in_their_row(tmp_path):
-    """The group kernels fetch a row's constants two and four groups to a request, the group's place in the scalar offset, which is
-    excluded from the range check: whatever the number of groups, no request may reach past the row, and each group is in the one
-    that is made for it."""
-    src = tmp_path / "requests.hip"
-    src.write_text("""#include "gemm_common.hpp"
-constexpr bool in_row(int ng, int grp0, int width) {
-    const int first = w4a4::request_first(grp0, ng, width);
-    if (first < 0 || first + width > ng) return false;
-    for (int g = grp0; g < grp0 + width && g < ng; ++g)
-        if (g < first || g >= first + width) return false;
-    return grp0 + width > ng || first == grp0;
-}
-constexpr bool all_in_row() {
-    for (int ng = 5; ng <= 64; ++ng)
-        for (int grp0 = 0; grp0 < ng; grp0 += 4)                // scales of four; zero points of two by each half of the lanes
-            if (!in_row(ng, grp0, 4) || !in_row(ng, grp0, 2) || !in_row(ng, grp0 + 2, 2)) return false;
-    return true;
-}
-static_assert(all_in_row(), "a request reaches past its row");
-""")
-    subprocess.run([build.HIPCC, *build.FLAGS, "-I", build.CSRC, "--cuda-host-only", "-fsyntax-only", str(src)], check=True)
-    for name in ("gemm_group.hip", "gemm_group_olay.hip"):          # ... and every such request goes by it
-        with open(os.path.join(build.CSRC, name)) as f:
-            loads = [line for line in f if re.search(r"raw_buffer_load_b(64|128)\((sw|zw|ra|wo)_rsrc", line)]
-        assert loads and all("first" in line or "two, grp0" in line for line in loads), loads
