@@ -373,18 +373,19 @@ __device__ __forceinline__ float sub_max(float v) {                 // maximum o
     if (LPR >= 64) v = swap_halves(v, [](float a, float b) { return fmaxf(a, b); });
     return v;
 }
-__device__ __forceinline__ int row16_sum(int v) {                   // sum over the sixteen lanes of a DPP row
-    v += dpp_move<0xB1>(v);
-    v += dpp_move<0x4E>(v);
-    v += dpp_move<0x141>(v);
-    v += dpp_move<0x140>(v);
+template <typename T>
+__device__ __forceinline__ T row16_sum(T v) {                       // sum over the sixteen lanes of a DPP row
+    v += dpp_fetch<0xB1>(v);
+    v += dpp_fetch<0x4E>(v);
+    v += dpp_fetch<0x141>(v);
+    v += dpp_fetch<0x140>(v);
     return v;
 }
-template <int LPR>
-__device__ __forceinline__ int sub_sum(int v) {
+template <int LPR, typename T>
+__device__ __forceinline__ T sub_sum(T v) {
     v = row16_sum(v);
-    if (LPR >= 32) v = swap_rows(v, [](int a, int b) { return a + b; });
-    if (LPR >= 64) v = swap_halves(v, [](int a, int b) { return a + b; });
+    if (LPR >= 32) v = swap_rows(v, [](T a, T b) { return a + b; });
+    if (LPR >= 64) v = swap_halves(v, [](T a, T b) { return a + b; });
     return v;
 }
 
@@ -398,8 +399,9 @@ __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel
     constexpr int LPW = BLOCK ? kWave : LPR, RPW = kWave / LPW; // a row's lanes in a wave, tokens per wave
     constexpr bool ASYM = MODE == W4A4_ASYM;
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    typedef typename std::conditional<ASYM, uint32_t, int>::type Sum;   // (unsigned codes: two sums to a word, which fill it)
     __shared__ float s_max[BLOCK ? 2 * kRowsPerBlock : 1];
-    __shared__ int s_sum[BLOCK ? kRowsPerBlock : 1];
+    __shared__ Sum s_sum[BLOCK ? kRowsPerBlock : 1];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, l = threadIdx.x % LPR;
     const long row = BLOCK ? (long)blockIdx.x : ((long)blockIdx.x * kRowsPerBlock + wave) * RPW + lane / LPW;
     // maxima over a row's lanes, one or two of them
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel
             if (b) *b = fmaxf(fmaxf(s_max[4], s_max[5]), fmaxf(s_max[6], s_max[7]));
         }
     };
-    auto row_sum = [&](int v) {
+    auto row_sum = [&](Sum v) {
         v = sub_sum<LPW>(v);
         if constexpr (BLOCK) {
             if (lane == 0) s_sum[wave] = v;
@@ -486,7 +488,8 @@ __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel
     constexpr uint32_t kFlip = LAYOUT != 0 ? 0x80808080u : ASYM ? 0u : 0x88888888u;
     const float neg_lo = -r.lo;
     uint32_t *qr = reinterpret_cast<uint32_t *>(q + row * (long)(K / 2));
-    int part = 0, total = 0;
+    Sum part = 0;
+    [[maybe_unused]] uint32_t total = 0;
 #pragma unroll
     for (int it = 0; it < CPL; ++it) {
         const int c = l + it * LPR;
@@ -519,22 +522,22 @@ __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel
             // (a K-group of 128 holds at most 64 * 15 there)
             const uint32_t ev = __builtin_amdgcn_sad_u8(packed & 0x0F0F0F0Fu, 0u, 0u);
             const uint32_t all = __builtin_amdgcn_sad_u8((packed >> 4) & 0x0F0F0F0Fu, 0u, ev);
-            const int both = in ? (int)((all << 16) | ev) : 0;
+            const uint32_t both = in ? (all << 16) | ev : 0u;
             if (ng == 1) {
-                part += both & 0xFFFF;
+                part += both & 0xFFFFu;
                 total += both >> 16;
             } else if (LAYOUT != 0 || gsum) {                   // chunks 16 j .. 16 j + 15 are K-group j
-                const int gs = row16_sum(both);
+                const uint32_t gs = row16_sum(both);
                 if ((l & 15) == 0 && live && in) {
-                    if (LAYOUT != 0) psum[(long)(c >> 4) * rows + row] = 128 * (gs & 0xFFFF);
-                    if (gsum) gsum[row * (long)ng + (c >> 4)] = gs >> 16;
+                    if (LAYOUT != 0) psum[(long)(c >> 4) * rows + row] = 128 * (int)(gs & 0xFFFFu);
+                    if (gsum) gsum[row * (long)ng + (c >> 4)] = (int)(gs >> 16);
                 }
             }
         }
     }
     if constexpr (ASYM) {                                       // both sums in one register again: a row's are below 15 K < 2^16 (K <= 4096)
         if (ng == 1 && (gsum || LAYOUT != 0)) {
-            const uint32_t both = (uint32_t)row_sum((total << 16) | part);
+            const uint32_t both = row_sum((total << 16) | part);
             if (l == 0 && live) {
                 if (gsum) gsum[row] = (int)(both >> 16);
                 if (LAYOUT != 0) psum[row] = 128 * (int)(both & 0xFFFFu);

@@ -155,3 +155,21 @@ def test_the_search_for_early_reads_finds_them():
                    "v_mov_b32_dpp v1, v82 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"):
         assert _early_reads([*asm, "\ts_nop 0", "\t" + reader]) and not _early_reads([*asm, "\ts_nop 1", "\t" + reader])
     assert not _early_reads([*asm, "\tv_mul_f32_e32 v1, v82, v82"])
+
+
+def test_packed_code_sums_are_unsigned(tmp_path):
+    """A row's two code sums ride in one word, the sum of all codes above bit 16: with 4096 codes it passes 2^15, and the word would
+    overflow as a signed one.  No addition of lanes' values in those kernels may promise the compiler that it does not (nsw)."""
+    ir = tmp_path / "quantize.ll"
+    subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S", "-emit-llvm", os.path.join(build.CSRC, "quantize.hip"), "-o", str(ir)],
+                   check=True, stderr=subprocess.DEVNULL)
+    kernels = re.findall(r"^define [^\n]*quantize_tok_rows_kernelILi1E[^\n]*\{\n(.*?)^\}", ir.read_text(), re.S | re.M)
+    assert len(kernels) >= 20
+    added = 0
+    for body in kernels:
+        moved = set(re.findall(r"(%\S+) = (?:tail )?call [^\n]*@llvm\.amdgcn\.update\.dpp\.i32", body))
+        adds = re.findall(r"= add (nuw |nsw |nuw nsw )?i32 (%[^,\s]+), (%[^,\s]+)", body)
+        crossed = [flags for flags, a, b in adds if a in moved or b in moved]
+        assert not any("nsw" in f for f in crossed), crossed
+        added += len(crossed)
+    assert added >= 4 * len(kernels)

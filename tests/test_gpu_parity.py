@@ -433,6 +433,24 @@ def test_quantize_act_many_rows_asymmetric(B, orc, layout, M, K, ldx, group):
         assert np.array_equal(host(A.osum).astype(np.int64), 128 * even.T)
 
 
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("K,M", [(4096, 3), (4096, 600), (3072, 512), (4064, 3)])     # a workgroup to a row, a wave, chunks that do not fill it
+def test_quantize_act_largest_code_sums(B, orc, layout, K, M):
+    """One group of unsigned codes that are nearly all the largest: a row's sum passes 2^15 and comes up to 15 (K - 1), which shares a
+    word with the even positions' sum."""
+    if layout == 1 and K % 128:
+        pytest.skip("the operand layout of unsigned codes takes K in multiples of 128")
+    rng = np.random.default_rng(M + K)
+    X = (8.0 - 0.2 * rng.random((M, K))).astype(np.float16)
+    X[:, K // 2] = -1.0
+    X[1] = np.linspace(0.0, 15.0, K).astype(np.float16)       # half of that: 2^15 is passed by the lanes' sums alone
+    A, want = B.quantize_act(dev(X), ASYM, 0, layout=layout), orc.quantize_act(X, ASYM, 0)
+    assert want["gsum"].max() == 15 * (K - 1) > 1 << 15 and np.array_equal(host(A.gsum), want["gsum"])
+    if layout == 1:
+        even = orc.unpack(want["q"], ASYM).astype(np.int64)[:, 0::2].sum(axis=1)
+        assert np.array_equal(host(A.osum).astype(np.int64).reshape(-1), 128 * even)
+
+
 @pytest.mark.parametrize("mode", [SYM, ASYM])
 @pytest.mark.parametrize("M,N,K", [
     (1, 8, 64), (17, 40, 192), (33, 520, 4096), (512, 1024, 128),             # the kernel whose waves split K
