@@ -519,6 +519,9 @@ static int launch_const(SmallArgs &a, bool wide, bool low, hipStream_t st) {
 // redundant work, but a tile is one CU's job: 32 x 32 while that gives at most one workgroup per CU, 32 x 64
 // beyond, and 16-token tiles when 32-token tiles would leave more than half of the CUs idle.  The weight
 // tile is staged in LDS (coalesced loads) whenever it fits beside the activation codes.
+// Lengths of a row that the kernel has as a constant.
+bool small_constant_k(int K) { return K == 512 || K == 768 || K == 1024 || K == 1536 || K == 2048 || K == 3072 || K == 4096; }
+
 template <bool PACKED, bool W8 = false, bool ASYM = false>
 static int small_dispatch(SmallArgs &a, hipStream_t st) {
     const int M = a.M, N = a.N, K = a.K;

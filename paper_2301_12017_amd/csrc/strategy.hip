@@ -78,10 +78,12 @@ bool part_ok(const w4a4_part *p) {
 // One launch for small token counts, whose workgroups quantize their tokens' whole rows.  INT4: up to 960 tiles of 32 x 32 (us, one launch |
 // two: 300 x 3072 x 768 (960) 6.0 | 6.3, 465 x 2304 x 768 (1080) 7.9 | 7.6, 300 x 3072 x 1024 (960) 6.95 | 6.85, 224 x 4096 x 1024 (896) 6.9 | 6.9, 384 x 3072 x 1024
 // (1152) 9.2 | 8.3), 512 of K > 1024; with long rows only up to 128, where the kernel still takes tiles of 8 or 16 tokens: 160 x 768 x 3072 (120) 5.3 | 6.2,
-// 224 x 768 x 3072 (168) 7.2 | 6.6.  INT8: 512; 465 x 768 x 3072 12.8 | 14.5.
+// 224 x 768 x 3072 (168) 7.2 | 6.6.  Where the kernel has K at run time, which costs it some 30 %, more than 512 tiles take one launch up to 600 tokens:
+// 507 x 1920 x 640 (960) 6.9 | 7.2, 411 x 2304 x 576 (936) 6.9 | 7.1, 923 x 640 x 640 (580) 7.1 | 7.15, 1179 x 640 x 640 (740) 8.1 | 7.3, 1691 x 576 x 576 (954) 8.5 | 7.2,
+// 603 x 960 x 960 (570) 8.9 | 8.8, 1019 x 960 x 960 (960) 9.3 | 8.9.  INT8: 512; 465 x 768 x 3072 12.8 | 14.5.
 bool one_kernel_tiles(int M, int N, int K, bool int4) {
     const long tiles = (long)((M + 31) / 32) * ((N + 31) / 32);
-    return K % 64 == 0 && K <= 4096 && tiles <= (!int4 ? 512 : K > 2048 ? 128 : K > 1024 ? 512 : 960);
+    return K % 64 == 0 && K <= 4096 && tiles <= (!int4 ? 512 : K > 2048 ? 128 : K > 1024 || (!small_constant_k(K) && M > 600) ? 512 : 960);
 }
 // ... symmetric per-channel weights in the canonical layout
 bool one_kernel_shape(int M, const w4a4_weight &w) {

@@ -47,6 +47,21 @@ def test_part_linear_int4(B, orc, M, N, K, act):
         assert ok, ratio
 
 
+@pytest.mark.parametrize("K,M,N,one", [(768, 500, 1152, True), (768, 640, 1600, False), (512, 800, 1152, True), (640, 600, 1600, True),
+                                       (640, 601, 1600, False), (576, 960, 544, True), (576, 960, 576, False), (960, 640, 832, False), (1152, 512, 1024, True), (1152, 512, 1056, False)])
+def test_part_linear_in_one_launch_or_two(B, K, M, N, one):
+    """Few tokens take one launch, which needs no workspace: up to 960 tiles of 32 x 32, 512 of more than 600 tokens where
+    the kernel has K at run time."""
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    X = torch.randn((M, K), device="cuda", generator=g).half()
+    P = B.Part((torch.randn((N, K), device="cuda", generator=g) * 0.02).half(), M, layout=0)
+    ws = torch.full((M * K + (1 << 16),), 0xAB, dtype=torch.uint8, device="cuda")
+    out = B.part_linear(X, P, True, workspace=ws)
+    assert bool((ws == 0xAB).all()) == one
+    A = B.quantize_act(X, 0)
+    assert torch.equal(out.view(torch.int16), B.linear(A, P.w4).view(torch.int16))
+
+
 @pytest.mark.parametrize("M,N,K", [(48, 96, 128), (1100, 768, 256), (40, 64, 4096)])
 @pytest.mark.parametrize("act", [0, 1])
 def test_part_linear_int8(B, orc, M, N, K, act):
