@@ -270,9 +270,14 @@ int launch_out(int out_kind, GemmArgs &g, hipStream_t st) {
 // workgroups of four waves to a CU, does without the sums in LDS (us, that kernel | this one: 600 x 3072 x 768, 480 tiles, 5.9 | 5.6, 1024 x 2304 x 768 (576)
 // 6.9 | 6.8, 1400 x 3072 x 768 (1056) 9.6 | 10.1, 800 x 3072 x 1024 (624) 8.3 | 8.5; 1024 x 1024 x 256 (256) 3.47 | 3.41, 1400 x 1024 x 256
 // (352) 3.9 | 4.2; 2000 x 1536 x 1536 (768) 11.3 | 10.8; asymmetric, against gemm_mid.hip, 1400 x 3072 x 768 14.7 | 11.8, 2000 x 1024 x 256 5.6 | 4.8).
+// Chunks of 256 codes leave one such chunk ahead, where gemm_mid.hip has three steps ahead in each of four shares of K: K past 4096 in them goes there
+// while there are too many tiles for one L2 to keep their operands and a CU for each (us, asymmetric, gemm_mid.hip | here, over rotating operands [over the same ones,
+// which that L2 keeps]: 250 x 1600 x 4352 (100 tiles) 10.5 | 10.8 [8.6 | 8.0], x 5376 11.7 | 12.4 [9.6 | 9.0]; 1000 x 512 x 5376 (128) 11.2 | 12.4 [9.8 | 9.1]; 857 x 480 x 7936
+// (112) 13.7 | 16.6 [12.3 | 11.8]; 506 x 240 x 6912 (32) 11.0 | 10.6; 780 x 1504 x 6400 (312) 18.1 | 16.1; in chunks of 512, 126 x 3832 x 4608 (120) 10.4 | 9.0).
 bool tile64_ok(const GemmArgs &g, int mode) {
     if (g.ng != 1 || g.K % 256 || g.lda >= (1 << 24) || g.ldw >= (1 << 24)) return false;
     const long tiles = (long)((g.M + kTile - 1) / kTile) * ((g.N + kTile - 1) / kTile);
+    if (g.K % 512 && g.K > 4096 && tiles > 32 && tiles <= 256) return false;
     return mode == W4A4_ASYM || g.K >= 1536 || tiles <= (g.K >= 512 ? 512 : 256);
 }
 int launch_tile64(int mode, int out_kind, GemmArgs &g, hipStream_t st) {
