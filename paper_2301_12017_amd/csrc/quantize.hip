@@ -560,7 +560,13 @@ static int launch_tok_rows(const __half *X, long ldx, int rows, int K, uint8_t *
     // asym 3.51 | 2.91 | 3.24; 16384 x 768 6.64 | 6.64 | 7.24, 8.23 | 8.27 | 9.91; 2000 x 1024 2.88 | 2.62 | 2.51, 3.98 | 3.25 | 3.01; 16384 x 1024 9.60 |
     // 9.32 | 9.62, 11.8 | 11.4 | 11.1; 4096 x 2048 - | 5.16 | 5.04, - | 6.78 | 6.38.  With the lanes of four waves, 64 | 256: 32 x 4096 2.58 | 2.14, 3.68 | 2.56;
     // 300 x 3072 2.50 | 2.32, 3.42 | 2.81; 1000 x 3072 2.74 | 2.87, 3.61 | 3.69.
-    const int lpr = nchunks > 128 && rows <= 512 ? 256 : nchunks > 128 || (nchunks == 128 && rows <= 2048) ? 64 : nchunks > 32 ? 32 : 16;
+    // Many tokens of a row that would leave a third of those lanes without a last chunk: half the lanes, full, on three chunks or five (16 | 32: 12576 x 288
+    // sym 3.03 | 3.27, unsigned in one group 3.98 | 4.71; x 384 sym 3.14 | 3.57, asym 4.07 | 5.18; 3000 x 384 2.09 | 2.16, 2.59 | 2.71; on four, 12576 x 416 sym 3.99 | 3.73,
+    // unsigned in one group 5.05 | 5.16.  32 | 64: 4096 x 1088 sym 3.13 | 3.39, unsigned in one group 4.09 | 4.59; x 1280 sym 3.37 | 3.72, asym 4.31 | 5.15; 12576 x 1280
+    // 8.00 | 7.90, 10.15 | 10.37; on six, 12576 x 1408 8.68 | 8.25, 11.4 | 10.6).
+    const bool many = rows > 2048;
+    const int lpr = many && nchunks > 32 && nchunks <= 48 ? 16 : many && nchunks > 128 && nchunks <= 160 ? 32
+                  : nchunks > 128 && rows <= 512 ? 256 : nchunks > 128 || (nchunks == 128 && rows <= 2048) ? 64 : nchunks > 32 ? 32 : 16;
     const int cpl = (nchunks + lpr - 1) / lpr;
     const long per_block = lpr > kWave ? 1 : (long)kRowsPerBlock * (kWave / lpr);
     dim3 grid((unsigned)((rows + per_block - 1) / per_block)), block(kRowsPerBlock * kWave);
@@ -577,7 +583,9 @@ static int launch_tok_rows(const __half *X, long ldx, int rows, int K, uint8_t *
         else if (cpl <= 3) W4A4_QF(L, 3);                                                                   \
         else W4A4_QF(L, 4);                                                                                 \
     } while (0)
-    if (lpr == 16) W4A4_QF(16, 2);
+    if (lpr == 16 && cpl <= 2) W4A4_QF(16, 2);
+    else if (lpr == 16) W4A4_QF(16, 3);
+    else if (lpr == 32 && cpl == 5) W4A4_QF(32, 5);
     else if (lpr == 32) W4A4_QFL(32);
     else if (lpr == 256) W4A4_QF(256, 2);
     else if (cpl <= 4) W4A4_QFL(64);

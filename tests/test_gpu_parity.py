@@ -475,7 +475,7 @@ def test_one_weight_group_small_and_mid_sized(B, orc, mode, M, N, K):
         assert np.array_equal(host(out.q)[rows], want["q"])
 
 
-@pytest.mark.parametrize("K", [256, 288, 512, 1024, 1056, 2048, 3072, 4096])
+@pytest.mark.parametrize("K", [256, 288, 384, 512, 1024, 1056, 1152, 1280, 2048, 3072, 4096])
 @pytest.mark.parametrize("M", [1, 5, 512])
 def test_quantize_act_few_tokens_as_among_many(K, M):
     """How many lanes share a row depends on its length and on the number of rows (16, 32, 64, or a workgroup of 256): a few rows by
