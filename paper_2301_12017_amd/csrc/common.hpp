@@ -95,15 +95,15 @@ __device__ __forceinline__ void reduce_scatter16(T (&v)[16], int lane, Op op) {
     reduce_scatter_bit<2, 1, 6, 0x4E>(v, lane, op);               // quad permute [2,3,0,1]
 }
 
-// op over the LPR (16, 32 or 64) consecutive lanes that own a row, in all of them: quad permutes, half-row and row mirror
+// op over the LPR (8, 16, 32 or 64) consecutive lanes that own a row, in all of them: quad permutes, half-row and row mirror
 // inside sixteen lanes, then the row and half-wave exchanges.
 template <int LPR, typename T, typename Op>
 __device__ __forceinline__ T lanes_reduce(T v, Op op) {
-    static_assert(sizeof(T) == 4 && (LPR == 16 || LPR == 32 || LPR == 64), "one register, a DPP row at least");
+    static_assert(sizeof(T) == 4 && (LPR == 8 || LPR == 16 || LPR == 32 || LPR == 64), "one register, half a DPP row at least");
     v = op(v, dpp_fetch<0xB1>(v));
     v = op(v, dpp_fetch<0x4E>(v));
     v = op(v, dpp_fetch<0x141>(v));
-    v = op(v, dpp_fetch<0x140>(v));
+    if (LPR >= 16) v = op(v, dpp_fetch<0x140>(v));
     if (LPR >= 32) {
         const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
         v = op(__builtin_bit_cast(T, (unsigned)sw[0]), __builtin_bit_cast(T, (unsigned)sw[1]));

@@ -79,16 +79,6 @@ __device__ __forceinline__ void codes8(const u32x4 &x, float inv, uint32_t &even
     }
 }
 
-// maximum of non-negative numbers over the LPR (8, 16, 32 or 64) consecutive lanes of a token, in all of them
-template <int LPR>
-__device__ __forceinline__ float token_max(float v) {
-    auto larger = [](float p, float q) { return fmaxf(p, q); };
-    if constexpr (LPR >= 16) return lanes_reduce<LPR>(v, larger);
-    v = larger(v, dpp_fetch<0xB1>(v));
-    v = larger(v, dpp_fetch<0x4E>(v));
-    return larger(v, dpp_fetch<0x141>(v));
-}
-
 // The LayerNorm form.  X + R, normalised, scaled and shifted: bit for bit what layernorm_quantize_kernel makes of a row of K = 512,
 // 768 or 1024, whose thirty-two lanes hold chunks l + 32 it.  Here LPR = 32 lanes hold the same chunks, or sixteen hold
 // l + 16 i, of which the even i are lane l's there and the odd i lane l + 16's: the sums are formed apart and joined last.
@@ -336,7 +326,7 @@ __global__ __launch_bounds__(NW * 64) void linear_f16act_kernel(SmallArgs a) {
             }
         }
         float amax = fmaxf((float)mx[0], (float)mx[1]);
-        amax = token_max<LPR>(amax);
+        amax = lanes_reduce<LPR>(amax, [](float p, float q) { return fmaxf(p, q); });
         Range rg = range_sym(amax);
         if (W8) {                                                // Sec. 3.1 with b = 8: 127 levels per side
             if (amax == 0.0f) { rg.inv = 0.0f; rg.S = 1.0f; }

@@ -351,43 +351,10 @@ static int launch_rows(const T *X, long ldx, int rows, int K, int G, uint8_t *q,
 // codes), for groups of 128 elements (the sixteen chunks of a group are the sixteen lanes of a DPP row in one
 // register slot) or one group per row.
 // Same arithmetic, same codes as the kernels above.
-template <int CTRL>
-__device__ __forceinline__ int dpp_move(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
-template <typename T, typename Op>
-__device__ __forceinline__ T swap_rows(T v, Op op) {                // op of the lanes l and l ^ 16
-    const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
-    return op(__builtin_bit_cast(T, (unsigned)sw[0]), __builtin_bit_cast(T, (unsigned)sw[1]));
-}
-template <typename T, typename Op>
-__device__ __forceinline__ T swap_halves(T v, Op op) {              // ... l and l ^ 32
-    const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
-    return op(__builtin_bit_cast(T, (unsigned)sw[0]), __builtin_bit_cast(T, (unsigned)sw[1]));
-}
 template <int LPR>
-__device__ __forceinline__ float sub_max(float v) {                 // maximum over the LPR lanes that own a row
-    v = fmaxf(v, __int_as_float(dpp_move<0xB1>(__float_as_int(v))));     // quad_perm [1,0,3,2]
-    v = fmaxf(v, __int_as_float(dpp_move<0x4E>(__float_as_int(v))));     // quad_perm [2,3,0,1]
-    v = fmaxf(v, __int_as_float(dpp_move<0x141>(__float_as_int(v))));    // half-row mirror
-    if (LPR >= 16) v = fmaxf(v, __int_as_float(dpp_move<0x140>(__float_as_int(v))));   // row mirror
-    if (LPR >= 32) v = swap_rows(v, [](float a, float b) { return fmaxf(a, b); });
-    if (LPR >= 64) v = swap_halves(v, [](float a, float b) { return fmaxf(a, b); });
-    return v;
-}
-template <typename T>
-__device__ __forceinline__ T row16_sum(T v) {                       // sum over the sixteen lanes of a DPP row
-    v += dpp_fetch<0xB1>(v);
-    v += dpp_fetch<0x4E>(v);
-    v += dpp_fetch<0x141>(v);
-    v += dpp_fetch<0x140>(v);
-    return v;
-}
+__device__ __forceinline__ float sub_max(float v) { return lanes_reduce<LPR>(v, [](float a, float b) { return fmaxf(a, b); }); }
 template <int LPR, typename T>
-__device__ __forceinline__ T sub_sum(T v) {
-    v = row16_sum(v);
-    if (LPR >= 32) v = swap_rows(v, [](T a, T b) { return a + b; });
-    if (LPR >= 64) v = swap_halves(v, [](T a, T b) { return a + b; });
-    return v;
-}
+__device__ __forceinline__ T sub_sum(T v) { return lanes_reduce<LPR>(v, [](T a, T b) { return a + b; }); }
 
 // LPR == 256: a row per workgroup, whose four waves meet in LDS.
 // EXACT: K / 8 == LPR * CPL, no chunk of a lane lies past K.  ng: K-groups of the asymmetric psum (1 or K / 128).
@@ -527,7 +494,7 @@ __global__ __launch_bounds__(kRowsPerBlock *kWave) void quantize_tok_rows_kernel
                 part += both & 0xFFFFu;
                 total += both >> 16;
             } else if (LAYOUT != 0 || gsum) {                   // chunks 16 j .. 16 j + 15 are K-group j
-                const uint32_t gs = row16_sum(both);
+                const uint32_t gs = sub_sum<16>(both);
                 if ((l & 15) == 0 && live && in) {
                     if (LAYOUT != 0) psum[(long)(c >> 4) * rows + row] = 128 * (int)(gs & 0xFFFFu);
                     if (gsum) gsum[row * (long)ng + (c >> 4)] = (int)(gs >> 16);
