@@ -77,8 +77,7 @@ typedef enum { W4A4_SYM = 0, W4A4_ASYM = 1 } w4a4_mode;
  *              their terms again; int32 results (w4a4_gemm_i32) are exact in both layouts.
  * The MFMA layout needs K % 128 == 0 and, for symmetric codes, per-channel weight scales
  * (group == 0); for unsigned codes, weight groups that are multiples of 128 (or one group), up to 28
- * of them, whose tables the kernel keeps on chip, or 32 of 128 (K == 4096), which it reads from memory;
- * other numbers are UNSUPPORTED_SHAPE.  w4a4_preferred_layout tells whether w4a4_linear is faster in it
+ * of them, or 32 of 128 (K == 4096); other numbers are UNSUPPORTED_SHAPE.  w4a4_preferred_layout tells whether w4a4_linear is faster in it
  * for a shape.
  *   FP6        not a nibble encoding: every symmetric code c in [-7, 7] (the range the quantizers
  *              produce; -8 does not exist here) is stored as the 6-bit FP6 E2M3 number of the same
@@ -362,6 +361,8 @@ int w4a4_probe_stream(const void *src, void *dst, size_t bytes, uint32_t *sink, 
 
 /* The schedule number (1-based, see w4a4_schedule_name) that w4a4_linear would run this layer on with
  * ep->schedule as given (0 = the built-in shape table), or a w4a4_status < 0 if it would refuse the layer.
+ * A schedule is a family of kernels and a tile; which kernel of the family runs may depend on the layer as well
+ * (generic_64x64: four of them, by weight groups and K; group_128x128: two, by the groups).
  * Host arithmetic only; pointers inside A and W are not read. */
 int w4a4_pick_schedule(const w4a4_act *A, const w4a4_weight *W, const w4a4_epilogue *ep);
 

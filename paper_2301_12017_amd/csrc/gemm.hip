@@ -61,14 +61,16 @@ static bool small_ok(const GemmArgs &g, int out_kind) {
            (long)g.M * g.lda < 0x7fffffffL && (long)g.N * g.ldw < 0x7fffffffL && ((long)g.M + 32) * g.N * 4 < 0x7fffffffL;
 }
 
-// Whether the group kernel takes ng weight groups: their tables fit its LDS, or (operand layout) it reads them from memory.
-static bool group_tables_fit(int K, int ng, bool olay) {
-    return group_lds(ng, true, olay, false) <= kGroupLds || (olay && group_memtab_ok(K, ng));
+// Numbers of weight groups that the group kernels take: those whose tables fit the LDS of gemm_group.hip (30, 28 in the operand layout), and
+// in the operand layout 32 of 128.  gemm_group_olay.hip keeps no tables and would run any number of groups of 128; 29 to 31 and more than
+// 32 are not offered it, a limit of this interface.
+static bool group_count_ok(int K, int ng, bool olay) {
+    return group_lds(ng, true, olay, false) <= kGroupLds || (olay && ng == 32 && K == 4096);
 }
 static bool group_ok(const GemmArgs &g, bool grouped) {
     return grouped && g.K % kBK == 0 && g.K >= 2 * kBK && (long)g.M * g.lda < 0x7fffffffL &&
            (long)g.N * g.ldw < 0x7fffffffL && (long)g.N * (g.ng + 1) * 4 < 0x7fffffffL && (long)g.M * g.ng * 4 < 0x7fffffffL &&
-           group_tables_fit(g.K, g.ng, g.osum != nullptr);
+           group_count_ok(g.K, g.ng, g.osum != nullptr);
 }
 
 // Built-in shape table of the canonical layout: large problems take the pipelined tiles (192 x 128 when the
@@ -76,8 +78,9 @@ static bool group_ok(const GemmArgs &g, bool grouped) {
 // workgroups per CU; 128 x 256 otherwise) or the group kernel, a few hundred 32 x 32 tiles the kernel whose waves
 // split K, everything between them 64 x 64 tiles (kernel per shape: launch_generic).
 static int pick_schedule(const GemmArgs &g, bool grouped, int out_kind) {
-    // a few hundred 32 x 32 tiles at most: latency decides, the waves of a workgroup split K (us at 301 tokens, against
-    // 64 x 64 tiles: 768 x 768 symmetric 3.8 | 4.7, 768 x 3072 4.6 | 7.1; above, at 540 tiles: 6.0 | 4.9)
+    // a few hundred 32 x 32 tiles at most: latency decides, the waves of a workgroup split K (us, against 64 x 64 tiles: 301 x 768 x 768
+    // symmetric 2.8 | 3.6, x 3072 4.0 | 6.1; 465 x 1024 x 768 (480) 3.4 | 3.6, x 3072 5.9 | 7.1; above, 700 x 768 x 768 (528) 4.3 | 3.7, x 3072 10.2 | 6.6;
+    // K = 512 to 4096, either mapping, 320 to 512 tiles 0.82 - 0.96 of the time, 528 and more 1.05 - 1.69)
     if ((long)((g.M + 31) / 32) * ((g.N + 31) / 32) <= 512 && small_ok(g, out_kind)) return S_SMALL;
     const long big = (long)((g.M + 127) / 128) * ((g.N + 255) / 256);
     if (big >= 256) {
@@ -88,7 +91,7 @@ static int pick_schedule(const GemmArgs &g, bool grouped, int out_kind) {
     // 64 x 128 tiles pay from five rounds of 64 x 64 ones over the CUs (us, 64 x 64 | 64 x 128: 1024 x 3072 x 1024, 768 tiles,
     // 8.2 | 9.6; 1500 x 3072 x 768, 1152 tiles, 10.1 | 10.9; 1500 x 4096 x 1024, 1536 tiles, 16.1 | 13.3; in groups of 128
     // 15.7 | 18.6, 21.0 | 22.7, 26.9 | 25.3), never for asymmetric layers with one group, which have their own 64 x 64
-    // kernel.  32 x 32 tiles (12.4 | 12.4 at 64 tokens, slower above) are left with the group tables too large for 64 x 64.
+    // kernels.  32 x 32 tiles (12.4 | 12.4 at 64 tokens, slower above) are left with the group tables too large for 64 x 64.
     const long small = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
     if (small >= 1280 && !(grouped && g.ng == 1)) return S_GEN_64x128;
     return grouped && g.ng > 160 ? S_GEN_32x32 : S_GEN_64x64;
@@ -295,7 +298,7 @@ static int check_operands(const w4a4_act *A, const w4a4_weight *W, int *ng_out) 
             if (W->group != 0 && W->group != W->K) return W4A4_ERR_UNSUPPORTED_SHAPE;
         } else {                                                // unsigned codes: whole K steps per weight group
             const int G = W->group == 0 ? W->K : W->group;
-            if (G % kBK || W->K % G || !group_tables_fit(W->K, W->K / G, true)) return W4A4_ERR_UNSUPPORTED_SHAPE;
+            if (G % kBK || W->K % G || !group_count_ok(W->K, W->K / G, true)) return W4A4_ERR_UNSUPPORTED_SHAPE;
         }
     }
     const int K = A->K;
@@ -377,16 +380,19 @@ extern "C" int w4a4_schedule_count(void) { return kTileSchedules; }
 extern "C" int w4a4_preferred_layout(int M, int N, int K, int mode, int group) {
     (void)N;
     // the operand layout exists for symmetric per-channel layers whose K the persistent kernel accepts, and for
-    // unsigned codes with weight groups of whole K steps whose tables fit the group kernel's LDS;
+    // unsigned codes with weight groups of whole K steps, as many as the group kernels take;
     // small token counts (latency-bound, a handful of 128-row tiles) stay on the canonical kernels
     if (K % kBK || K < 2 * kBK || K <= 0) return W4A4_LAYOUT_CANONICAL;
     if (mode == W4A4_SYM) {
         if (group != 0 && group != K) return W4A4_LAYOUT_CANONICAL;
     } else {
         const int G = group == 0 ? K : group;
-        if (G <= 0 || G % kBK || K % G || !group_tables_fit(K, K / G, true)) return W4A4_LAYOUT_CANONICAL;
+        if (G <= 0 || G % kBK || K % G || !group_count_ok(K, K / G, true)) return W4A4_LAYOUT_CANONICAL;
     }
-    return M >= 1536 ? W4A4_LAYOUT_MFMA : W4A4_LAYOUT_CANONICAL;   // (measured crossover between 1024 and 1536 tokens)
+    // One line for all: where symmetric layers cross (four linears with their quantizers, us, canonical | operand layout: 768 features 1280 tokens 39 | 49, 1536
+    // 45 | 43; 1024 features 1280 53 | 58, 1536 57 | 52).  One asymmetric group crosses at 1536 to 2048 (768 features 2048 56.7 | 57.1; 1024 features 1536 65 | 64),
+    // groups of 128 at 512 (768 features 512 63 | 57, 1024 86 | 60).
+    return M >= 1536 ? W4A4_LAYOUT_MFMA : W4A4_LAYOUT_CANONICAL;
 }
 
 extern "C" const char *w4a4_schedule_name(int schedule) {

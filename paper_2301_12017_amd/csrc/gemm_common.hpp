@@ -477,9 +477,6 @@ inline size_t group_lds(int ng, bool tables, bool olay, bool lines) {
 }
 // Operand layout, groups of several K steps: K and the groups in pairs of K steps
 inline bool group_lines_ok(int K, int ng) { return K / ng % 256 == 0; }
-// ... groups of one K step: more groups than the 28 whose tables LDS holds, K = 4096 (gemm_group_olay.hip reads them from memory;
-// 16384 x 1024 x 4096 229 us on the general kernel, the only other one that takes so many, 89 with the tables read in the epilogue)
-inline bool group_memtab_ok(int K, int ng) { return K / ng == 128 && ng % 8 == 0 && K <= 4096; }
 
 constexpr int kFp6FewTokens = 4;                                 // gemm_fp6.hip: the variant whose waves split K
 int fp6_requant_max_tiles_n();

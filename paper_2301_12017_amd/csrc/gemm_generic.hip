@@ -228,12 +228,13 @@ static int launch_variant(int variant, GemmArgs &g, hipStream_t st) {
     }
 }
 
-// Layers with one weight group on 64 x 64 tiles that tile64_ok leaves, those whose K is no multiple of 256 above all: shares of K for the kernel of gemm_mid.hip, 0 = the kernel above.  us,
-// two shares | four | none, at 768 and 1024 tokens and features where nothing else is said:
-//   symmetric    K = 768: 5.0 | 5.3 | 4.9; K = 1024: 5.3 | 5.3 | 5.6; K = 3072: 8.4 | 7.8 | 10.6; K = 4096: 10.0 | 9.0 | 13.4; more tiles
-//                than CUs (1500 tokens, 288): K = 3072 11.3 | 13.6 | 12.6, (465 tokens, 384 tiles) K = 1024 6.8 | 8.6 | 6.4
-//   asymmetric   K = 768: 5.3 | 5.3 | 8.1; K = 3072: 8.6 | 8.0 | 16.6; 465 x 2304 x 768 (288 tiles) 6.5 | 8.8 | 8.5,
-//                1500 x 4096 x 1024 (1536) 18.2 | 25.8 | 20.8
+// Layers with one weight group on 64 x 64 tiles that tile64_ok leaves, those whose K is no multiple of 256 above all: shares of K for the
+// kernel of gemm_mid.hip, 0 = the kernel above.  us, two shares | four | none, at 768 tokens and features where nothing else is said:
+//   symmetric    K = 640: 4.6 | 4.7 | 4.2; 896: 5.0 | 4.7 | 4.9; 1152: 5.3 | 5.3 | 5.6; 2176: 6.8 | 6.6 | 8.2; 4224: 10.5 | 10.2 | 18.6; more tiles than
+//                CUs (1500 tokens, 288): 1152 6.9 | 9.5 | 6.5, 1920 8.5 | 10.9 | 8.9, 2176 9.2 | 11.9 | 9.8, 4224 14.1 | 18.0 | 18.7; 1024 x 3072 (768): 2176 17.1 |
+//                21.0 | 15.1, 4224 26.1 | 31.0 | 25.8
+//   asymmetric   K = 640: 4.7 | 4.9 | 7.3; 1152: 5.5 | 5.5 | 9.2; 4224: 10.6 | 10.4 | 24.0; 465 x 2304 x 640 (288) 6.1 | 8.5 | 7.8, 1024 x 3072 x 1152 (768) 12.6 |
+//                16.5 | 13.4
 static int k_shares(const GemmArgs &g, bool asym) {
     const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
     if (g.ng != 1 || g.lda >= (1 << 24) || g.ldw >= (1 << 24)) return 0;
@@ -245,7 +246,6 @@ bool small_grouped_ok(const GemmArgs &g, int mode, int out_kind);   // gemm_smal
 int launch_small_grouped(int mode, GemmArgs &g, hipStream_t st);
 bool tile64_ok(const GemmArgs &g, int mode);                         // gemm_tile64.hip: K in chunks that LDS holds
 int launch_tile64(int mode, int out_kind, GemmArgs &g, hipStream_t st);
-
 
 int launch_generic(int variant, int mode, bool grouped, int out_kind, GemmArgs &g, hipStream_t st) {
     if (variant == 1) {

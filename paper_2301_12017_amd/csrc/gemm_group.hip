@@ -90,8 +90,7 @@ void gemm_group_kernel(GemmArgs g) {
     // ---- global -> LDS plan (fixed for the whole kernel) -------------------------------------------
     // DMA instruction i of this wave fills block wave + i*NW of a stage, rows RPB (wave + i*NW) ..: what i adds is the same for
     // all lanes (and leaves the swizzle alone).  LINES: one address register serves the activations and one the weights, and
-    // dma_voff() adds it where it is needed, to the vector offset, which is what the range check of a row past the last one
-    // looks at; half lines have registers for all of them (groups of 128, 16384 x 768: 1 % less).  LDS row p of the weight tile
+    // dma_voff() adds it where it is needed, to the vector offset (the scalar one carries K); half lines have registers for all of them (groups of 128, 16384 x 768: 1 % less).  LDS row p of the weight tile
     // holds output channel nl: MFMA column cc of fragment f is channel cc*FN + f of the wave's span, so a lane ends up with
     // FN adjacent channels.
     constexpr int STRIDE = NW * RPB;                            // rows from one instruction to the next: 32 or 64
@@ -303,8 +302,9 @@ void gemm_group_kernel(GemmArgs g) {
     __builtin_amdgcn_sched_barrier(0);
         constexpr int kBarSlot = NM - NF;
         // Weight scales of this lane's channels: the current group's (swg) and those requested ahead, four groups at a time
-        // while a whole quad of groups lies ahead (one request costs the same 32 cache lines as for one group), else
-        // one.  They are requested BEHIND a K step's tile DMAs and needed one K step later at the earliest: in front of
+        // while a whole quad of groups lies ahead (one request costs the same 32 cache lines as for one group; what it brings of
+        // the next row is not used, and past the end of the array it is zeros: the range check takes the sum of both offsets, dword by
+        // dword), else one.  They are requested BEHIND a K step's tile DMAs and needed one K step later at the earliest: in front of
         // them, the barrier of that K step, which waits for everything older than its own DMAs, exposed their latency.
         float swg[FN], swn[FN];
         u32x4 quad[FN], quad_n[FN];

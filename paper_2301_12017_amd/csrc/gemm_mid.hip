@@ -11,8 +11,8 @@
 //     workgroup at KS = 4; unpadded rows with the XOR swizzle of gemm_olay.hip;
 //   * the epilogue is dealt to all waves: a pair finishes 32 / KS rows of each of the tile's halves.
 // What is left is the vector ALU of the widening (72 instructions per wave and step beside eight MFMAs): without the
-// DMA a step takes 5 % less, without the MFMAs 20 %.  1024 x 768 x 3072 10.6 -> 7.8 us against the generic kernel,
-// asymmetric 16.6 -> 8.0; 301 x 2304 x 768 asymmetric 8.0 -> 5.2 (the choice per shape: launch_generic).
+// DMA a step takes 5 % less, without the MFMAs 20 %.  768 x 768 x 2176 8.2 -> 6.6 us against the generic kernel, asymmetric 12.9 -> 6.7; x 4224
+// 18.6 -> 10.2 and 24.0 -> 10.4.  What is left to it is K in no whole chunks of 256 codes, and some long K (tile64_ok; the shares per shape: k_shares).
 #include "gemm_common.hpp"
 
 namespace w4a4 {

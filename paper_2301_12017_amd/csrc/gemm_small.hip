@@ -504,14 +504,14 @@ static int launch_const(SmallArgs &a, bool wide, bool low, hipStream_t st) {
     return launch_small<NW, 1, 32, small_wlds(32, 32, code_row, w_row, NW, 8), PACKED, W8, ASYM, K>(a, st);
 }
 
+// Lengths of a row that the kernel has as a constant: those of the switch below.
+bool small_constant_k(int K) { return K == 512 || K == 768 || K == 1024 || K == 1536 || K == 2048 || K == 3072 || K == 4096; }
+
 // Shape policy.  Waves: enough that none walks more than four blocks of K nor holds more than 16 chunks of
 // a row.  Tile: every column tile re-quantizes (or re-reads) its token rows, so fewer, wider tiles do less
 // redundant work, but a tile is one CU's job: 32 x 32 while that gives at most one workgroup per CU, 32 x 64
 // beyond, and 16-token tiles when 32-token tiles would leave more than half of the CUs idle.  The weight
 // tile is staged in LDS (coalesced loads) whenever it fits beside the activation codes.
-// Lengths of a row that the kernel has as a constant.
-bool small_constant_k(int K) { return K == 512 || K == 768 || K == 1024 || K == 1536 || K == 2048 || K == 3072 || K == 4096; }
-
 template <bool PACKED, bool W8 = false, bool ASYM = false>
 static int small_dispatch(SmallArgs &a, hipStream_t st) {
     const int M = a.M, N = a.N, K = a.K;

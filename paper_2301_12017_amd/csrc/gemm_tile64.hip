@@ -38,9 +38,7 @@ __device__ __forceinline__ int swizzle(int row) {
 // first, since it cannot tell which bytes a DMA writes); they are waited for in the same block.
 template <int N>
 __device__ __forceinline__ void lds_read(const uint32_t (&at)[N], v4f (&v)[N]) {
-    static_assert(N == 2 || N == 4 || N == 6 || N == 8 || N == 3, "batches that are used");
-    if constexpr (N == 2)
-        asm volatile("ds_read_b128 %0, %2\nds_read_b128 %1, %3\ns_waitcnt lgkmcnt(0)" : "=&v"(v[0]), "=&v"(v[1]) : "v"(at[0]), "v"(at[1]));
+    static_assert(N == 3 || N == 4 || N == 6 || N == 8, "batches that are used");
     if constexpr (N == 3)
         asm volatile("ds_read_b128 %0, %3\nds_read_b128 %1, %4\nds_read_b128 %2, %5\ns_waitcnt lgkmcnt(0)"
                      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]) : "v"(at[0]), "v"(at[1]), "v"(at[2]));

@@ -201,7 +201,8 @@ def test_many_groups_lose_no_precision(B, orc, seed):
 @pytest.mark.parametrize("M,N", [(1, 8), (130, 264)])
 def test_groups_of_128(B, orc, ng, M, N):
     """Every remainder of the groups that are left behind a quad: planes exact, fp16 outputs no further from the float64 evaluation
-    than the oracle's fp32 order, fp32 outputs (the ranges of a requantized row) the same to a step of fp16."""
+    than the oracle's fp32 order (0.5 to 0.999 of its rms error; of eight outputs, which one rounding of fp16 can tip, half as far again),
+    fp32 outputs (the ranges of a requantized row) the same to a step of fp16."""
     K = 128 * ng
     rng = np.random.default_rng(ng + M)
     A, Q, a, w = _layer(B, orc, rng, M, N, K, 128)
@@ -215,7 +216,7 @@ def test_groups_of_128(B, orc, ng, M, N):
         assert ok, ratio
         truth = orc.truth64(a, w, ASYM, b, act)
         rms = [np.sqrt(np.mean((x.astype(np.float64) - truth) ** 2)) for x in (got, want)]
-        assert rms[0] <= 1.5 * rms[1] + 1e-7, rms
+        assert rms[0] <= (1.0 if M * N > 1000 else 1.5) * rms[1] + (0 if M * N > 1000 else 1e-7), rms
     if N % 32 == 0 or N == 264:
         n = N // 32 * 32
         Qn = B.quantize_weight(dev(_w(np.random.default_rng(3), n, K)), ASYM, 128, layout=MFMA)

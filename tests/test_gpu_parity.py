@@ -453,10 +453,11 @@ def test_quantize_act_largest_code_sums(B, orc, layout, K, M):
 
 @pytest.mark.parametrize("mode", [SYM, ASYM])
 @pytest.mark.parametrize("M,N,K", [
-    (1, 8, 64), (17, 40, 192), (33, 520, 4096), (512, 1024, 128),             # the kernel whose waves split K
-    (513, 520, 1056), (65, 4104, 768), (1000, 1024, 1024), (640, 1640, 1024),  # 64 x 64 tiles: a tail of K, one round, more
-    (577, 1024, 4160), (1100, 1096, 2080), (1024, 1032, 3072),                 # ... K in four shares and in two
-    (300, 520, 4864), (33, 520, 4864)])                                        # long K in chunks of 256: 45 tiles, 9
+    (1, 8, 64), (17, 40, 192), (33, 520, 4096), (512, 1024, 128), (65, 4104, 768),   # the kernel whose waves split K
+    (513, 520, 1056), (577, 1024, 4160), (1100, 1096, 2080),                      # 64 x 64 tiles: a tail of K, K in four shares and in two
+    (1000, 1024, 1024), (640, 1640, 1024), (1024, 1032, 3072),                 # chunks of 256 codes and more: one round, more, long K
+    (300, 520, 4864), (33, 520, 4864),                                         # K in chunks of 256 alone: four shares with 45 tiles, not with 9
+    (1024, 2048, 768), (1024, 2056, 768), (1000, 1024, 256), (1025, 1024, 256)])   # 512 tiles and 528, 256 and 272: the symmetric limits of chunks
 def test_one_weight_group_small_and_mid_sized(B, orc, mode, M, N, K):
     """Layers with one weight group between one token and a few rounds of 64 x 64 tiles, ragged in M, N and K: int32 sums
     and fp16 outputs (with a bias; GELU behind it on sampled rows) equal the oracle's bits."""
